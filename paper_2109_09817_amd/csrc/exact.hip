@@ -125,64 +125,153 @@ __device__ __forceinline__ void diag_inverse(const double (*Ls)[kEb + 1], double
   __syncthreads();
 }
 
-// Unblocked Cholesky of the diagonal block A[j0.., j0..] (jb <= 64 rows) in
-// LDS, the block outside jb padded with the identity; writes L (lower, zero
-// above the diagonal) and, when Dinv is given, L^{-1} (64 x 64 row-major).  A
-// pivot that is not positive records its global index + 1 in *info (the first
-// one only) and continues with 1, so that every later step stays finite and
-// bounded.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// v of lane `lane` (a constant), as a wave-uniform value.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+constexpr int kDb = 16;         // sub-block edge of the diagonal factorisation
+constexpr int kDbLd = kEb + 2;  // LDS pitch: the MFMA's 16-row operand reads hit distinct banks
+
+// Cholesky of a 16 x 16 block and the inverse of its factor, by one wave in
+// registers: lane l holds row l % 16 in a (lower part; the upper part is
+// ignored on entry and zero on return) and column l % 16 of the inverse in x.
+// Entries of other lanes are read as scalars.  base: global index of row 0.
+__device__ __forceinline__ void chol_inverse_16(double (&a)[kDb], double (&x)[kDb], int lr, int base, int& bad) {
+#pragma unroll
+  for (int k = 0; k < kDb; ++k) {
+    double p = lane_value(a[k], k);
+    if (!(p > 0.0) || !isfinite(p)) {
+      if (bad == 0) bad = base + k + 1;
+      p = 1.0;
+    }
+    const double piv = sqrt(p);
+    const double l = a[k] / piv;
+    a[k] = lr == k ? piv : (lr > k ? l : 0.0);
+#pragma unroll
+    for (int c = k + 1; c < kDb; ++c) a[c] = fma(-a[k], lane_value(a[k], c), a[c]);
+  }
+#pragma unroll
+  for (int r = 0; r < kDb; ++r) x[r] = r == lr ? 1.0 : 0.0;
+#pragma unroll
+  for (int r = 0; r < kDb; ++r) {
+    x[r] /= lane_value(a[r], r);
+#pragma unroll
+    for (int q = r + 1; q < kDb; ++q) x[q] = fma(-lane_value(a[r], q), x[r], x[q]);
+  }
+}
+
+// Cholesky of the diagonal block A[j0.., j0..] (jb <= 64 rows) in LDS, the
+// block outside jb padded with the identity; writes L (lower, zero above the
+// diagonal) and, when Dinv is given, L^{-1} (64 x 64 row-major).  A pivot that
+// is not positive records its global index + 1 in *info (the first one only)
+// and continues with 1, so that every later step stays finite and bounded.
+//
+// One workgroup on the factorisation's critical path: the time is the length
+// of its serial chain.  Four 16-column steps: wave 0 factors and inverts the
+// 16 x 16 diagonal block in registers, the waves multiply the rows below by
+// that inverse and update the trailing 16 x 16 tiles on the FP64 matrix cores
+// (lane l supplies P(l % 16, l / 16) and Q(l / 16, l % 16), and receives rows
+// l / 16 + 4 i); 3 barriers a step.  The inverse's blocks below the diagonal
+// follow block diagonal by block diagonal, X_ij = -X_ii sum_k L_ik X_kj.
+// Column by column over all 64 (128 barriers, then 64 dependent rows of the
+// inverse) it took 74 us; this form: 29 us (n = 7,503: 118 of them, 30.1 -> 24.8 ms).
 __global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A, int64_t n, int64_t j0, int jb,
                                                          int* __restrict__ info, double* __restrict__ Dinv) {
-  __shared__ double Ls[kEb][kEb + 1];
-  __shared__ double Xs[kEb][kEb + 1];
+  __shared__ double Ls[kEb * kDbLd];
+  __shared__ double Xs[kEb * kDbLd];
+  constexpr int kPer = kEb * kEb / 256;
+  const int tid = threadIdx.x;
   {
-    constexpr int kPer = kEb * kEb / 256;
     double v[kPer];  // every load in flight before the first LDS write
 #pragma unroll
     for (int it = 0; it < kPer; ++it) {
-      const int e = (int)threadIdx.x + 256 * it, r = e / kEb, c = e % kEb;
+      const int e = tid + 256 * it, r = e / kEb, c = e % kEb;
       v[it] = (r < jb && c < jb) ? A[(j0 + r) * n + j0 + c] : (r == c ? 1.0 : 0.0);
     }
 #pragma unroll
     for (int it = 0; it < kPer; ++it) {
-      const int e = (int)threadIdx.x + 256 * it;
-      Ls[e / kEb][e % kEb] = v[it];
+      const int e = tid + 256 * it;
+      Ls[e / kEb * kDbLd + e % kEb] = v[it];
+      Xs[e / kEb * kDbLd + e % kEb] = 0.0;
     }
   }
-  int bad = 0;  // thread 0 only
-  for (int k = 0; k < kEb; ++k) {
-    __syncthreads();
-    double p = Ls[k][k];
-    if (!(p > 0.0) || !isfinite(p)) {
-      if (threadIdx.x == 0 && bad == 0) bad = (int)(j0 + k + 1);
-      p = 1.0;
-    }
-    const double piv = sqrt(p);
-    if ((int)threadIdx.x > k && (int)threadIdx.x < kEb) Ls[threadIdx.x][k] /= piv;
-    __syncthreads();
-    if (threadIdx.x == 0) Ls[k][k] = piv;
-    // thread (wave w, lane c) updates entry c of the rows w + 4 it; every read
-    // is issued unconditionally so that they overlap, the write is guarded
-    const int c = threadIdx.x & (kEb - 1), w = threadIdx.x >> 6;
-    const double lck = Ls[c][k];
+  const int lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  constexpr int kNb = kEb / kDb;
+  int bad = 0;  // wave 0 only
+  __syncthreads();
+  for (int b = 0; b < kNb; ++b) {
+    const int c0 = kDb * b;
+    if (wave == 0) {
+      double a[kDb], x[kDb];
 #pragma unroll
-    for (int it = 0; it < kEb / 4; ++it) {
-      const int r = w + 4 * it;
-      const double v = Ls[r][c] - Ls[r][k] * lck;
-      if (c > k && c <= r) Ls[r][c] = v;
+      for (int j = 0; j < kDb; ++j) a[j] = Ls[(c0 + lr) * kDbLd + c0 + j];
+      chol_inverse_16(a, x, lr, (int)j0 + c0, bad);
+      if (lk == 0) {
+#pragma unroll
+        for (int j = 0; j < kDb; ++j) {
+          Ls[(c0 + lr) * kDbLd + c0 + j] = a[j];
+          Xs[(c0 + j) * kDbLd + c0 + lr] = x[j];
+        }
+      }
     }
+    __syncthreads();
+    const int below = kNb - 1 - b;
+    if (wave < below) {  // row block b + 1 + wave: L = A X_bb^T
+      const int r0 = c0 + kDb * (1 + wave);
+      f64x4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(Ls[(r0 + lr) * kDbLd + c0 + 4 * s + lk],
+                                                 Xs[(c0 + lr) * kDbLd + c0 + 4 * s + lk], d, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) Ls[(r0 + lk + 4 * i) * kDbLd + c0 + lr] = d[i];
+    }
+    __syncthreads();
+    for (int q = wave; q < below * (below + 1) / 2; q += 4) {  // trailing tiles (ri, cj), cj <= ri
+      const int ri = q >= 3 ? 2 : (q >= 1 ? 1 : 0), cj = q - ri * (ri + 1) / 2;
+      const int r0 = c0 + kDb * (1 + ri), q0 = c0 + kDb * (1 + cj);
+      f64x4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(Ls[(r0 + lr) * kDbLd + c0 + 4 * s + lk],
+                                                 Ls[(q0 + lr) * kDbLd + c0 + 4 * s + lk], d, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) Ls[(r0 + lk + 4 * i) * kDbLd + q0 + lr] -= d[i];
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < kEb * kEb; e += 256) {
+  for (int e = tid; e < kEb * kEb; e += 256) {
     const int r = e / kEb, c = e % kEb;
-    if (c > r) Ls[r][c] = 0.0;
-    if (r < jb && c < jb) A[(j0 + r) * n + j0 + c] = c <= r ? Ls[r][c] : 0.0;
+    if (r < jb && c < jb) A[(j0 + r) * n + j0 + c] = c <= r ? Ls[r * kDbLd + c] : 0.0;
   }
-  if (threadIdx.x == 0 && bad != 0 && *info == 0) *info = bad;
+  if (tid == 0 && bad != 0 && *info == 0) *info = bad;
   if (!Dinv) return;
-  __syncthreads();
-  diag_inverse(Ls, Xs);
-  for (int e = threadIdx.x; e < kEb * kEb; e += 256) Dinv[e] = Xs[e / kEb][e % kEb];
+  for (int dist = 1; dist < kNb; ++dist) {
+    if (wave < kNb - dist) {
+      const int j = wave, i = wave + dist;
+      f64x4 t = {0.0, 0.0, 0.0, 0.0};
+      for (int k = j; k < i; ++k)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          t = __builtin_amdgcn_mfma_f64_16x16x4f64(Ls[(kDb * i + lr) * kDbLd + kDb * k + 4 * s + lk],
+                                                   Xs[(kDb * k + 4 * s + lk) * kDbLd + kDb * j + lr], t, 0, 0, 0);
+      f64x4 d = {0.0, 0.0, 0.0, 0.0};  // register s of t holds its rows 4 s + l / 16
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(Xs[(kDb * i + lr) * kDbLd + kDb * i + 4 * s + lk], t[s], d, 0, 0, 0);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) Xs[(kDb * i + lk + 4 * s) * kDbLd + kDb * j + lr] = -d[s];
+    }
+    __syncthreads();
+  }
+  for (int e = tid; e < kEb * kEb; e += 256) Dinv[e] = Xs[e / kEb * kDbLd + e % kEb];
 }
 
 // Dinv + 64 * 64 * bi = L_ii^{-1} for every diagonal block bi (one workgroup each).
@@ -217,7 +306,6 @@ __global__ __launch_bounds__(256) void trtri_blocks_kernel(const double* __restr
 // contiguous: k-major [k][x] (pitch 80 doubles) when the source runs along x,
 // x-major [x][k] (pitch 66) when it runs along k.  Both pitches put the 32
 // lanes of a half-wave on distinct banks for the operand reads.
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kKMajorLd = kEb + 16;
 constexpr int kXMajorLd = kEb + 2;
 
