@@ -465,8 +465,8 @@ int run_bcg(const gp_kernel* kern, int precision, const double* X, int64_t n, co
 // L_M^{-1} K_MX K_XM L_M^{-T}.  The jitter bounds cond(K_MM + delta I) by
 // about 1 / kNysCholJitter (nearly repeated landmark rows make K_MM singular)
 // and keeps P an under-approximation of K_hat.  The O(n r^2) products (F, the
-// Gram matrix, E) run on the FP64 matrix cores (dense_gemm), the two
-// factorisations and triangular inverses on blocked FP64 tile kernels.
+// Gram matrix, E) run on the FP64 matrix cores (dense_lower_times, dense_gram),
+// the two factorisations and triangular inverses on blocked FP64 tile kernels.
 //
 // The solver with this preconditioner is block preconditioned CG (O'Leary) on
 // K_hat W = B with P^{-1}: its iterates are those of block CG on the
@@ -502,7 +502,7 @@ size_t nystrom_chol_ws_bytes(int d, int64_t n, int r) {
   b += align256((size_t)r * d * 8);                 // landmark rows
   b += 2 * align256((size_t)r * r * 8);             // K_MM -> L_M -> G -> L_G; L^{-1}
   b += align256(dense_dinv_doubles(r) * 8);         // diagonal-block inverses
-  b += align256((size_t)n * r * 8);                 // K_XM, later E^T
+  b += align256((size_t)n * r * 8);                 // F^T
   b += align256(sizeof(int) * 2);                   // Cholesky status
   return b + 4096;
 }
@@ -539,7 +539,7 @@ int run_nystrom_chol(const gp_kernel* kern, const double* X, int64_t n, const in
     else
       kernel_cols_kernel<GP_RBF><<<grid, 256, 0, st>>>(P, np, d, scd, idx, r, kern->outputscale, out);
   };
-  kcols(X, n, Mdev, T);
+  kcols(X, n, Mdev, E);
   kcols(XM, r, iota, A);
   GPK_HIP(hipGetLastError());
   // L_M L_M^T = K_MM + delta I (lower triangle), L_M^{-1}
@@ -547,17 +547,16 @@ int run_nystrom_chol(const gp_kernel* kern, const double* X, int64_t n, const in
   GPK_HIP(hipGetLastError());
   GPK_HIP(dense_cholesky(A, r, info, Dinv, st));
   GPK_HIP(dense_lower_inverse(A, Linv, Dinv, r, st));
-  // F^T = L_M^{-1} K_MX (r x n row-major, i.e. F column-major), into E
-  GPK_HIP(dense_gemm(false, false, false, r, n, r, Linv, r, T, n, E, n, st));
+  // F^T = L_M^{-1} K_MX (r x n row-major, i.e. F column-major)
+  GPK_HIP(dense_lower_times(r, n, Linv, r, E, n, T, n, st));
   // G = F^T F + sigma^2 I (lower tiles), L_G, L_G^{-1}
-  GPK_HIP(dense_gemm(false, true, true, r, r, n, E, n, E, n, A, r, st));
+  GPK_HIP(dense_gram(r, n, T, n, A, r, st));
   add_diag_kernel<<<(unsigned)((r + thr - 1) / thr), thr, 0, st>>>(A, r, kern->noise);
   GPK_HIP(hipGetLastError());
   GPK_HIP(dense_cholesky(A, r, info + 1, Dinv, st));
   GPK_HIP(dense_lower_inverse(A, Linv, Dinv, r, st));
   // E^T = L_G^{-1} F^T (r x n row-major = E column-major)
-  GPK_HIP(dense_gemm(false, false, false, r, n, r, Linv, r, E, n, T, n, st));
-  GPK_HIP(hipMemcpyAsync(E, T, sizeof(double) * n * r, hipMemcpyDeviceToDevice, st));
+  GPK_HIP(dense_lower_times(r, n, Linv, r, T, n, E, n, st));
   int h_info[2] = {0, 0};
   GPK_HIP(hipMemcpyAsync(h_info, info, sizeof(h_info), hipMemcpyDeviceToHost, st));
   GPK_HIP(hipStreamSynchronize(st));

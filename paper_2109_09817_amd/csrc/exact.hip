@@ -431,12 +431,13 @@ static hipError_t tile_update(const double* Pm, int64_t ldp, int64_t pfix, int64
 // cores, 64 x 64 output tiles, k in chunks of 64 staged in LDS as in the tile
 // kernel above:  A(i, k) = TA ? A[k lda + i] : A[i lda + k],
 //                B(k, j) = TB ? B[j ldb + k] : B[k ldb + j].
-// LOWER computes only the tiles with tj <= ti (m = nn).  Rows, columns and k
+// LOWER computes only the tiles with tj <= ti (m = nn).  tri: A is lower
+// triangular, so row tile ti takes k < 64 (ti + 1) only.  Rows, columns and k
 // beyond the matrices read as zero; nothing outside C's m x nn block is written.
 template <bool TA, bool TB, bool LOWER>
 __global__ __launch_bounds__(256) void gemm_f64_kernel(const double* A, int64_t lda, const double* B, int64_t ldb,
-                                                       double* C, int64_t ldc, int64_t m, int64_t nn, int64_t kk,
-                                                       int nrt, int nct) {
+                                                       double* C, int64_t ldc, int64_t m, int64_t nn, int64_t kk_all,
+                                                       int nrt, int nct, int tri) {
   __shared__ double As[kEb * kKMajorLd];  // A(r, k) at lds_at<TA>(k, r)
   __shared__ double Bs[kEb * kKMajorLd];  // B(k, c) at lds_at<!TB>(k, c)
   const int64_t T = LOWER ? (int64_t)nrt * (nrt + 1) / 2 : (int64_t)nrt * nct;
@@ -453,6 +454,7 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(const double* A, int64_t 
     tj = b - ti * nct;
   }
   const int64_t R = kEb * ti, Cc = kEb * tj;
+  const int64_t kk = tri && R + kEb < kk_all ? R + kEb : kk_all;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r0 = 32 * (wave >> 1), c0 = 32 * (wave & 1);
   const int lr = lane & 15, lk = lane >> 4;
@@ -516,10 +518,199 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(const double* A, int64_t 
       }
 }
 
+// The same products in 128 x 128 output tiles, k in chunks of 16 in two LDS
+// buffers: C = A B, or (SUB) C -= A B, A and B as above.  LOWER computes only
+// the tiles with tj <= ti.  tri: A is lower triangular (zero above the
+// diagonal), so row tile ti takes k < 128 (ti + 1) only.
+//
+// Bound by the FP64 matrix cores (64 cycles per v_mfma_f64_16x16x4 and SIMD,
+// 74 TF/s measured on a large library product).  A wave owns a 64 x 64
+// quadrant, 16 MFMAs for every 8 operand reads, against 4 for 4 in the 64-wide
+// tiles, and a tile reads half the bytes per flop; two workgroups per CU
+// (74 KB of LDS each), so one multiplies while the other waits at its barrier.
+// Each operand keeps its source orientation in LDS: k-major [k][x], pitch 144
+// doubles, or x-major [x][k], pitch 18, both with 16-byte rows and distinct
+// banks for the 32 lanes of a half-wave.  Interior chunks load 16 bytes per
+// lane (rows need 8-byte alignment only), edges element by element.
+// n = 32,768, r = 4,096: L F takes 9.4 ms (59 TF/s of useful flops) against 24 ms
+// in 64-wide tiles over the full square; trailing updates of the exact GP (k = 256)
+// reach 39 TF/s against 28.
+constexpr int kGt = 128;       // tile edge
+constexpr int kGk = 16;        // k per chunk
+constexpr int kGKLd = kGt + 16;
+constexpr int kGXLd = kGk + 2;
+constexpr int kGBuf = kGt * kGXLd > kGk * kGKLd ? kGt * kGXLd : kGk * kGKLd;
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
+
+template <bool KMAJOR>
+__device__ __forceinline__ int gemm_at(int k, int x) {
+  return KMAJOR ? k * kGKLd + x : x * kGXLd + k;
+}
+
+// This thread's four 16-byte pieces of a 128 x 16 operand chunk at (x0, k0).
+// KMAJOR: element (x, k) at P[k ld + x], otherwise P[x ld + k]; x >= xn reads
+// some valid row (its outputs are not stored), k >= kn reads as zero.
+template <bool KMAJOR>
+__device__ __forceinline__ void gemm_load(const double* __restrict__ P, int64_t ld, int64_t x0, int64_t xn, int64_t k0,
+                                          int64_t kn, f64x2 (&v)[4]) {
+  const int tid = threadIdx.x;
+  if constexpr (KMAJOR) {
+    const int x = 2 * (tid & 63), k = tid >> 6;
+    if (x0 + kGt <= xn && k0 + kGk <= kn) {
+      const double* src = P + (k0 + k) * ld + x0 + x;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = *(const f64x2u*)(src + 4 * u * ld);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int64_t xx = x0 + x + e < xn ? x0 + x + e : xn - 1;
+          const int64_t kk = k0 + k + 4 * u;
+          v[u][e] = kk < kn ? P[kk * ld + xx] : 0.0;
+        }
+    }
+  } else {
+    const int x = tid >> 3, k = 2 * (tid & 7);
+    const bool inner = k0 + kGk <= kn;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t xx = x0 + x + 32 * u < xn ? x0 + x + 32 * u : xn - 1;
+      const double* src = P + xx * ld + k0 + k;
+      if (inner) {
+        v[u] = *(const f64x2u*)src;
+      } else {
+        v[u][0] = k0 + k < kn ? src[0] : 0.0;
+        v[u][1] = k0 + k + 1 < kn ? src[1] : 0.0;
+      }
+    }
+  }
+}
+
+template <bool KMAJOR>
+__device__ __forceinline__ void gemm_store(double* buf, const f64x2 (&v)[4]) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int at = KMAJOR ? gemm_at<true>((tid >> 6) + 4 * u, 2 * (tid & 63))
+                          : gemm_at<false>(2 * (tid & 7), (tid >> 3) + 32 * u);
+    *(f64x2*)(buf + at) = v[u];
+  }
+}
+
+template <bool TA, bool TB, bool LOWER, bool SUB>
+__global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(const double* __restrict__ A, int64_t lda,
+                                                             const double* __restrict__ B, int64_t ldb, double* C,
+                                                             int64_t ldc, int64_t m, int64_t nn, int64_t kk, int nrt,
+                                                             int nct, int tri) {
+  __shared__ __attribute__((aligned(16))) double As[2][kGBuf], Bs[2][kGBuf];
+  // Workgroup h runs on XCD h % 8: each XCD takes a contiguous run of the tile
+  // order.  Rectangles go through groups of 8 tile columns, row by row within
+  // a group, so the ~64 tiles an XCD works on at once share 8 + 8 panels in
+  // its L2; under tri the long rows of each group come first.
+  const int64_t T = LOWER ? (int64_t)nrt * (nrt + 1) / 2 : (int64_t)nrt * nct;
+  const int64_t h = blockIdx.x, xcd = h & 7, q8 = T >> 3, rem8 = T & 7;
+  const int64_t b = xcd * q8 + (xcd < rem8 ? xcd : rem8) + (h >> 3);
+  int64_t ti, tj;
+  if (LOWER) {
+    ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+    while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
+    while (ti * (ti + 1) / 2 > b) --ti;
+    tj = b - ti * (ti + 1) / 2;
+  } else {
+    const int64_t grp = b / (8 * (int64_t)nrt), rest = b - grp * 8 * nrt;
+    const int64_t width = nct - 8 * grp < 8 ? nct - 8 * grp : 8;
+    ti = rest / width;
+    tj = 8 * grp + rest - ti * width;
+    if (tri) ti = nrt - 1 - ti;
+  }
+  const int64_t R = kGt * ti, Cc = kGt * tj;
+  const int64_t kn = tri && R + kGt < kk ? R + kGt : kk;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r0 = 64 * (wave >> 1), c0 = 64 * (wave & 1);
+  const int lr = lane & 15, lk = lane >> 4;
+  f64x4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  f64x2 av[4], bv[4];
+  gemm_load<TA>(A, lda, R, m, 0, kn, av);
+  gemm_load<!TB>(B, ldb, Cc, nn, 0, kn, bv);
+  gemm_store<TA>(As[0], av);
+  gemm_store<!TB>(Bs[0], bv);
+  __syncthreads();
+  int cur = 0;
+  for (int64_t kc = 0; kc < kn; kc += kGk, cur ^= 1) {
+    const bool more = kc + kGk < kn;
+    if (more) {
+      gemm_load<TA>(A, lda, R, m, kc + kGk, kn, av);
+      gemm_load<!TB>(B, ldb, Cc, nn, kc + kGk, kn, bv);
+    }
+#pragma unroll
+    for (int k = 0; k < kGk; k += 4) {
+      double a[4], q[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        a[i] = As[cur][gemm_at<TA>(k + lk, r0 + 16 * i + lr)];
+        q[i] = Bs[cur][gemm_at<!TB>(k + lk, c0 + 16 * i + lr)];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], q[j], acc[i][j], 0, 0, 0);
+    }
+    if (more) {  // the other buffer's readers passed the previous barrier
+      gemm_store<TA>(As[cur ^ 1], av);
+      gemm_store<!TB>(Bs[cur ^ 1], bv);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb) {
+    double old[4][4];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int64_t row = R + r0 + 16 * rb + lk + 4 * i, col = Cc + c0 + 16 * cb + lr;
+        old[cb][i] = (SUB && row < m && col < nn) ? C[row * ldc + col] : 0.0;
+      }
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int64_t row = R + r0 + 16 * rb + lk + 4 * i, col = Cc + c0 + 16 * cb + lr;
+        if (row < m && col < nn) C[row * ldc + col] = SUB ? old[cb][i] - acc[rb][cb][i] : acc[rb][cb][i];
+      }
+  }
+}
+
+static int64_t gemm128_tiles(bool lower, int64_t m, int64_t nn) {
+  const int64_t nrt = (m + kGt - 1) / kGt, nct = (nn + kGt - 1) / kGt;
+  return lower ? nrt * (nrt + 1) / 2 : nrt * nct;
+}
+
+// The 128-wide tiles fill the chip from about this many on; below it the
+// 64-wide tiles, four times as many, use more of the 256 CUs.
+constexpr int64_t kGemm128MinTiles = 256;
+
+template <bool TA, bool TB, bool LOWER, bool SUB>
+static hipError_t gemm128(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, int64_t m,
+                          int64_t nn, int64_t kk, bool tri, hipStream_t st) {
+  const int64_t tiles = gemm128_tiles(LOWER, m, nn);
+  if (tiles <= 0) return hipSuccess;
+  if (tiles > 0x7fffffff || kk < 1) return hipErrorInvalidValue;
+  gemm128_f64_kernel<TA, TB, LOWER, SUB><<<(unsigned)tiles, 256, 0, st>>>(
+      A, lda, B, ldb, C, ldc, m, nn, kk, (int)((m + kGt - 1) / kGt), (int)((nn + kGt - 1) / kGt), tri ? 1 : 0);
+  return hipGetLastError();
+}
+
 static int ntiles(int64_t len) { return (int)((len + kEb - 1) / kEb); }
 
 // A = L L^T in place (lower triangle; the diagonal blocks' upper parts are
-// zeroed, the rest of the upper triangle is left as it was).  Two levels of
+// zeroed, the rest of the upper triangle holds no result).  Two levels of
 // blocking: 64-wide panels inside 256-wide super-panels.  A panel updates only
 // the columns of its own super-panel; the trailing matrix beyond it takes the
 // whole super-panel at once (k = 256), so that it is read and written once per
@@ -556,8 +747,13 @@ static hipError_t cholesky(double* A, int64_t n, int* info, double* Dinv, hipStr
     }
     // A22 -= L21 L21^T over the lower tiles beyond the super-panel, k = Jend - J0
     if (n > Jend) {
-      e = tile_update<false, true, true, false>(A, n, -1, J0, A, n, -1, J0, A, n, (int)(Jend - J0), Jend, Jend,
-                                                ntiles(n - Jend), 0, st);
+      const int64_t rest = n - Jend;
+      if (gemm128_tiles(true, rest, rest) >= kGemm128MinTiles)
+        e = gemm128<false, true, true, true>(A + Jend * n + J0, n, A + Jend * n + J0, n, A + Jend * n + Jend, n, rest,
+                                             rest, Jend - J0, false, st);
+      else
+        e = tile_update<false, true, true, false>(A, n, -1, J0, A, n, -1, J0, A, n, (int)(Jend - J0), Jend, Jend,
+                                                  ntiles(rest), 0, st);
       if (e != hipSuccess) return e;
     }
   }
@@ -602,8 +798,12 @@ static hipError_t lower_inverse_forward(const double* L, double* B, double* Dinv
       }
     }
     if (n > Iend) {
-      e = tile_update<false, false, false, false>(L, n, -1, I0, B, n, -1, I0, B, n, (int)(Iend - I0), Iend, 0,
-                                                  ntiles(n - Iend), ntiles(Iend), st);
+      if (gemm128_tiles(false, n - Iend, Iend) >= kGemm128MinTiles)
+        e = gemm128<false, false, false, true>(L + Iend * n + I0, n, B + I0 * n, n, B + Iend * n, n, n - Iend, Iend,
+                                               Iend - I0, false, st);
+      else
+        e = tile_update<false, false, false, false>(L, n, -1, I0, B, n, -1, I0, B, n, (int)(Iend - I0), Iend, 0,
+                                                    ntiles(n - Iend), ntiles(Iend), st);
       if (e != hipSuccess) return e;
     }
   }
@@ -647,8 +847,13 @@ static hipError_t inverse_from_cholesky(const double* L, double* B, double* Dinv
       }
     }
     if (I0 > 0) {
-      e = tile_update<true, false, true, false>(L, n, -1, I0, B, n, -1, I0, B, n, (int)(Iend - I0), 0, 0,
-                                                ntiles(I0), 0, st);
+      // (a 128-wide diagonal tile also writes above the 64-wide block diagonal,
+      // which nothing reads before the mirror overwrites it)
+      if (gemm128_tiles(true, I0, I0) >= kGemm128MinTiles)
+        e = gemm128<true, false, true, true>(L + I0 * n, n, B + I0 * n, n, B, n, I0, I0, Iend - I0, false, st);
+      else
+        e = tile_update<true, false, true, false>(L, n, -1, I0, B, n, -1, I0, B, n, (int)(Iend - I0), 0, 0,
+                                                  ntiles(I0), 0, st);
       if (e != hipSuccess) return e;
     }
   }
@@ -894,23 +1099,24 @@ int run_exact(const gp_kernel* kern, const double* X, const double* y, int64_t n
 
 // ---------------------------------------------------------------- exported dense pieces
 
-hipError_t dense_gemm(bool ta, bool tb, bool lower, int64_t m, int64_t nn, int64_t kk, const double* A, int64_t lda,
-                      const double* B, int64_t ldb, double* C, int64_t ldc, hipStream_t st) {
+hipError_t dense_lower_times(int64_t m, int64_t nn, const double* L, int64_t ldl, const double* B, int64_t ldb,
+                             double* C, int64_t ldc, hipStream_t st) {
   if (m <= 0 || nn <= 0) return hipSuccess;
-  if (lower && m != nn) return hipErrorInvalidValue;
+  if (gemm128_tiles(false, m, nn) >= kGemm128MinTiles)
+    return gemm128<false, false, false, false>(L, ldl, B, ldb, C, ldc, m, nn, m, /*tri=*/true, st);
   const int nrt = ntiles(m), nct = ntiles(nn);
-  const int64_t tiles = lower ? (int64_t)nrt * (nrt + 1) / 2 : (int64_t)nrt * nct;
-  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  const unsigned g = (unsigned)tiles;
-#define GPK_GEMM(TA, TB, LO) gemm_f64_kernel<TA, TB, LO><<<g, 256, 0, st>>>(A, lda, B, ldb, C, ldc, m, nn, kk, nrt, nct)
-  if (lower) {
-    if (ta && tb) GPK_GEMM(true, true, true); else if (ta) GPK_GEMM(true, false, true);
-    else if (tb) GPK_GEMM(false, true, true); else GPK_GEMM(false, false, true);
-  } else {
-    if (ta && tb) GPK_GEMM(true, true, false); else if (ta) GPK_GEMM(true, false, false);
-    else if (tb) GPK_GEMM(false, true, false); else GPK_GEMM(false, false, false);
-  }
-#undef GPK_GEMM
+  gemm_f64_kernel<false, false, false><<<(unsigned)(nrt * nct), 256, 0, st>>>(L, ldl, B, ldb, C, ldc, m, nn, m, nrt,
+                                                                              nct, 1);
+  return hipGetLastError();
+}
+
+hipError_t dense_gram(int64_t m, int64_t kk, const double* A, int64_t lda, double* C, int64_t ldc, hipStream_t st) {
+  if (m <= 0) return hipSuccess;
+  if (gemm128_tiles(true, m, m) >= kGemm128MinTiles)
+    return gemm128<false, true, true, false>(A, lda, A, lda, C, ldc, m, m, kk, false, st);
+  const int nrt = ntiles(m);
+  gemm_f64_kernel<false, true, true><<<(unsigned)(nrt * (nrt + 1) / 2), 256, 0, st>>>(A, lda, A, lda, C, ldc, m, m,
+                                                                                     kk, nrt, nrt, 0);
   return hipGetLastError();
 }
 

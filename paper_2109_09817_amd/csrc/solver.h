@@ -92,11 +92,11 @@ hipError_t pivchol_launch_column(const double* X, int64_t n, const gp_kernel* ke
                                  const PivState& ps, int m, hipStream_t st);
 
 // Dense FP64 pieces on the matrix cores (exact.hip).  Row-major matrices.
-// C (m x nn, ldc) = A B with A(i, k) = ta ? A[k lda + i] : A[i lda + k] and
-// B(k, j) = tb ? B[j ldb + k] : B[k ldb + j]; lower: only the tiles on and
-// below the diagonal (m = nn).
-hipError_t dense_gemm(bool ta, bool tb, bool lower, int64_t m, int64_t nn, int64_t kk, const double* A, int64_t lda,
-                      const double* B, int64_t ldb, double* C, int64_t ldc, hipStream_t st);
+// C (m x nn) = L B, L m x m lower triangular (zero above the diagonal).
+hipError_t dense_lower_times(int64_t m, int64_t nn, const double* L, int64_t ldl, const double* B, int64_t ldb,
+                             double* C, int64_t ldc, hipStream_t st);
+// C (m x m) = A A^T for A m x kk: the tiles on and below the diagonal.
+hipError_t dense_gram(int64_t m, int64_t kk, const double* A, int64_t lda, double* C, int64_t ldc, hipStream_t st);
 // Doubles of the diagonal-block scratch of the two routines below.
 size_t dense_dinv_doubles(int64_t n);
 // In-place lower Cholesky factor of the symmetric n x n A (lower triangle read);

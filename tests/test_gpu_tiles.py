@@ -28,3 +28,37 @@ def test_exact_gp_at_the_edges_of_the_16_wide_diagonal_steps(n):
     assert abs(r.mll - o["mll"]) <= 1e-10 * (abs(o["quad"]) + abs(o["logdet"]) + n)
     assert np.linalg.norm(host(r.omega) - o["omega"]) <= 1e-10 * np.linalg.norm(o["omega"])
     assert np.max(np.abs(r.grad - g)) <= 1e-10 * np.max(np.abs(g)) * n
+
+
+def test_exact_gp_with_128_wide_tiles_and_a_ragged_edge():
+    """From 23 tile rows on the trailing updates take 128-wide tiles; n = 3,301 leaves a ragged last tile.  Bars as
+    for the dense parity cases (1e-14 kappa with kappa below 1e4 here)."""
+    from paper_2109_09817_amd import gp
+    n = 3301
+    rng = np.random.default_rng(5)
+    X, y = rng.standard_normal((n, 3)), rng.standard_normal(n)
+    th = ok.Theta(rng.uniform(0.3, 0.6, 3), 1.3, 1e-1, ok.MATERN52)
+    r = gp.exact_mll_and_grad(_gk(th), dev(X), dev(y), with_grad=True, with_omega=True)
+    o = exact.cholesky_gp(X, y, th)
+    g = exact.mll_grad(X, y, th)
+    assert abs(r.mll - o["mll"]) <= 1e-10 * (abs(o["quad"]) + abs(o["logdet"]) + n)
+    assert np.linalg.norm(host(r.omega) - o["omega"]) <= 1e-10 * np.linalg.norm(o["omega"])
+    assert np.max(np.abs(r.grad - g)) <= 1e-9 * np.max(np.abs(g))
+
+
+@pytest.mark.parametrize("n,r", [(11009, 333), (700, 129)])
+def test_large_rank_factor_on_both_tile_sizes(n, r):
+    """E^T = L_G^{-1} L_M^{-1} K_MX against numpy: 128-wide tiles (n = 11,009, ragged both ways) and 64-wide ones.
+    Rounding is amplified by cond(K_MM + delta I), below 1e4 on this data: bar 1e-11."""
+    import scipy.linalg as sl
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, 6))
+    th = ok.Theta(rng.uniform(0.5, 1.0, 6), 1.0, 1e-2, ok.MATERN52)
+    M = np.sort(rng.choice(n, r, replace=False))
+    E = host(gp.nystrom_chol_precond(_gk(th), dev(X), M).E)
+    KMX = ok.kernel(X[M], X, th)
+    Lm = np.linalg.cholesky(KMX[:, M] + 1e-10 * r * np.eye(r))
+    F = sl.solve_triangular(Lm, KMX, lower=True)
+    ref = sl.solve_triangular(np.linalg.cholesky(F @ F.T + 1e-2 * np.eye(r)), F, lower=True)
+    assert np.linalg.norm(E - ref) <= 1e-11 * np.linalg.norm(ref)
