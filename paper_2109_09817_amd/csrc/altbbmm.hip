@@ -500,7 +500,7 @@ size_t nystrom_chol_ws_bytes(int d, int64_t n, int r) {
   b += 2 * align256((size_t)r * 8);                 // landmark indices, iota
   b += align256((size_t)d * 8);                     // feature scales
   b += align256((size_t)r * d * 8);                 // landmark rows
-  b += 2 * align256((size_t)r * r * 8);             // K_MM -> L_M -> G -> L_G; L^{-1}
+  b += 2 * align256((size_t)r * r * 8);             // K_MM -> L_M -> L_M^{-1}; G -> L_G -> L_G^{-1}
   b += align256(dense_dinv_doubles(r) * 8);         // diagonal-block inverses
   b += align256((size_t)n * r * 8);                 // F^T
   b += align256(sizeof(int) * 2);                   // Cholesky status
@@ -516,7 +516,7 @@ int run_nystrom_chol(const gp_kernel* kern, const double* X, int64_t n, const in
   double* scd = cv.take<double>(d);
   double* XM = cv.take<double>((size_t)r * d);
   double* A = cv.take<double>((size_t)r * r);
-  double* Linv = cv.take<double>((size_t)r * r);
+  double* G = cv.take<double>((size_t)r * r);
   double* Dinv = cv.take<double>(dense_dinv_doubles(r));
   double* T = cv.take<double>((size_t)n * r);
   int* info = cv.take<int>(2);
@@ -546,17 +546,17 @@ int run_nystrom_chol(const gp_kernel* kern, const double* X, int64_t n, const in
   add_diag_kernel<<<(unsigned)((r + thr - 1) / thr), thr, 0, st>>>(A, r, kNysCholJitter * r * kern->outputscale);
   GPK_HIP(hipGetLastError());
   GPK_HIP(dense_cholesky(A, r, info, Dinv, st));
-  GPK_HIP(dense_lower_inverse(A, Linv, Dinv, r, st));
+  GPK_HIP(dense_lower_inverse(A, G, Dinv, r, st));
   // F^T = L_M^{-1} K_MX (r x n row-major, i.e. F column-major)
-  GPK_HIP(dense_lower_times(r, n, Linv, r, E, n, T, n, st));
+  GPK_HIP(dense_lower_times(r, n, A, r, E, n, T, n, st));
   // G = F^T F + sigma^2 I (lower tiles), L_G, L_G^{-1}
-  GPK_HIP(dense_gram(r, n, T, n, A, r, st));
-  add_diag_kernel<<<(unsigned)((r + thr - 1) / thr), thr, 0, st>>>(A, r, kern->noise);
+  GPK_HIP(dense_gram(r, n, T, n, G, r, st));
+  add_diag_kernel<<<(unsigned)((r + thr - 1) / thr), thr, 0, st>>>(G, r, kern->noise);
   GPK_HIP(hipGetLastError());
-  GPK_HIP(dense_cholesky(A, r, info + 1, Dinv, st));
-  GPK_HIP(dense_lower_inverse(A, Linv, Dinv, r, st));
+  GPK_HIP(dense_cholesky(G, r, info + 1, Dinv, st));
+  GPK_HIP(dense_lower_inverse(G, A, Dinv, r, st));
   // E^T = L_G^{-1} F^T (r x n row-major = E column-major)
-  GPK_HIP(dense_lower_times(r, n, Linv, r, T, n, E, n, st));
+  GPK_HIP(dense_lower_times(r, n, G, r, T, n, E, n, st));
   int h_info[2] = {0, 0};
   GPK_HIP(hipMemcpyAsync(h_info, info, sizeof(h_info), hipMemcpyDeviceToHost, st));
   GPK_HIP(hipStreamSynchronize(st));

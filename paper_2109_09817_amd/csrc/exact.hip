@@ -3,8 +3,8 @@
 // training molecules).  Dense FP64 throughout:
 //
 //   K_hat = L L^T (blocked right-looking Cholesky, 64-wide panels)
-//   K_hat^{-1} = L^{-T} L^{-1}   (two blocked triangular solves against I,
-//                                 each restricted to the lower triangle)
+//   X = L^{-1}                   (by doubling the inverted diagonal blocks)
+//   K_hat^{-1} = X^T X           (lower tiles)
 //   omega = K_hat^{-1} y
 //   L(theta) = -1/2 y^T omega - sum_a log L_aa - n/2 log 2 pi       (Eq. 2)
 //   dL/dlog theta = 1/2 sum_ab (omega omega^T - K_hat^{-1})_ab dK_hat_ab/dlog theta
@@ -81,50 +81,6 @@ __global__ __launch_bounds__(256) void form_khat_kernel(const double* __restrict
 
 // ---------------------------------------------------------------- Cholesky
 
-// Load the factored diagonal block L[i0.., i0..] (ib rows) into LDS, identity-padded.
-__device__ __forceinline__ void load_diag_block(const double* __restrict__ L, int64_t n, int64_t i0, int ib,
-                                                double (*Ls)[kEb + 1]) {
-  constexpr int kPer = kEb * kEb / 256;  // 256 threads
-  double v[kPer];  // every load in flight before the first LDS write
-#pragma unroll
-  for (int it = 0; it < kPer; ++it) {
-    const int e = (int)threadIdx.x + 256 * it, r = e / kEb, c = e % kEb;
-    v[it] = (r < ib && c < ib) ? (c <= r ? L[(i0 + r) * n + i0 + c] : 0.0) : (r == c ? 1.0 : 0.0);
-  }
-#pragma unroll
-  for (int it = 0; it < kPer; ++it) {
-    const int e = (int)threadIdx.x + 256 * it;
-    Ls[e / kEb][e % kEb] = v[it];
-  }
-}
-
-// Xs = Ls^{-1} for a lower-triangular 64 x 64 Ls in LDS (zero above the
-// diagonal), 256 threads: lanes 4j..4j+3 form column j by forward
-// substitution against e_j, lane s keeping in registers the entries
-// X[4q + s][j] of its residue class and summing their terms.  Entries not yet
-// formed (and those above the diagonal) are zero, so every row takes the same
-// 16 terms per lane and no index test; the four partial sums meet by shuffles.
-// Ends with a barrier; Xs is complete (zero above the diagonal).
-__device__ __forceinline__ void diag_inverse(const double (*Ls)[kEb + 1], double (*Xs)[kEb + 1]) {
-  const int j = threadIdx.x >> 2, sub = threadIdx.x & 3;
-  double x[kEb / 4];
-#pragma unroll
-  for (int q = 0; q < kEb / 4; ++q) x[q] = 0.0;
-#pragma unroll
-  for (int r = 0; r < kEb; ++r) {
-    double part = 0.0;
-#pragma unroll
-    for (int q = 0; q < kEb / 4; ++q) part = fma(Ls[r][4 * q + sub], x[q], part);
-    part += __shfl_xor(part, 1);
-    part += __shfl_xor(part, 2);
-    const double xr = ((r == j ? 1.0 : 0.0) - part) / Ls[r][r];
-    if ((r & 3) == sub) x[r >> 2] = xr;
-  }
-#pragma unroll
-  for (int q = 0; q < kEb / 4; ++q) Xs[4 * q + sub][j] = x[q];
-  __syncthreads();
-}
-
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // v of lane `lane` (a constant), as a wave-uniform value.
@@ -168,8 +124,8 @@ __device__ __forceinline__ void chol_inverse_16(double (&a)[kDb], double (&x)[kD
 
 // Cholesky of the diagonal block A[j0.., j0..] (jb <= 64 rows) in LDS, the
 // block outside jb padded with the identity; writes L (lower, zero above the
-// diagonal) and, when Dinv is given, L^{-1} (64 x 64 row-major).  A pivot that
-// is not positive records its global index + 1 in *info (the first one only)
+// diagonal) and L^{-1} (64 x 64 row-major, into Dinv).  A pivot that is not
+// positive records its global index + 1 in *info (the first one only)
 // and continues with 1, so that every later step stays finite and bounded.
 //
 // One workgroup on the factorisation's critical path: the time is the length
@@ -252,7 +208,6 @@ __global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A,
     if (r < jb && c < jb) A[(j0 + r) * n + j0 + c] = c <= r ? Ls[r * kDbLd + c] : 0.0;
   }
   if (tid == 0 && bad != 0 && *info == 0) *info = bad;
-  if (!Dinv) return;
   for (int dist = 1; dist < kNb; ++dist) {
     if (wave < kNb - dist) {
       const int j = wave, i = wave + dist;
@@ -272,19 +227,6 @@ __global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A,
     __syncthreads();
   }
   for (int e = tid; e < kEb * kEb; e += 256) Dinv[e] = Xs[e / kEb * kDbLd + e % kEb];
-}
-
-// Dinv + 64 * 64 * bi = L_ii^{-1} for every diagonal block bi (one workgroup each).
-__global__ __launch_bounds__(256) void trtri_blocks_kernel(const double* __restrict__ L, int64_t n,
-                                                           double* __restrict__ Dinv) {
-  __shared__ double Ls[kEb][kEb + 1];
-  __shared__ double Xs[kEb][kEb + 1];
-  const int64_t i0 = (int64_t)blockIdx.x * kEb;
-  load_diag_block(L, n, i0, (int)(n - i0 < kEb ? n - i0 : kEb), Ls);
-  __syncthreads();
-  diag_inverse(Ls, Xs);
-  double* D = Dinv + (int64_t)blockIdx.x * kEb * kEb;
-  for (int e = threadIdx.x; e < kEb * kEb; e += 256) D[e] = Xs[e / kEb][e % kEb];
 }
 
 // ---------------------------------------------------------------- tile updates
@@ -427,34 +369,93 @@ static hipError_t tile_update(const double* Pm, int64_t ldp, int64_t pfix, int64
   return hipGetLastError();
 }
 
-// General FP64 product C = A B (m x nn, row-major with ldc) on the matrix
-// cores, 64 x 64 output tiles, k in chunks of 64 staged in LDS as in the tile
-// kernel above:  A(i, k) = TA ? A[k lda + i] : A[i lda + k],
-//                B(k, j) = TB ? B[j ldb + k] : B[k ldb + j].
-// LOWER computes only the tiles with tj <= ti (m = nn).  tri: A is lower
-// triangular, so row tile ti takes k < 64 (ti + 1) only.  Rows, columns and k
-// beyond the matrices read as zero; nothing outside C's m x nn block is written.
-template <bool TA, bool TB, bool LOWER>
-__global__ __launch_bounds__(256) void gemm_f64_kernel(const double* A, int64_t lda, const double* B, int64_t ldb,
-                                                       double* C, int64_t ldc, int64_t m, int64_t nn, int64_t kk_all,
-                                                       int nrt, int nct, int tri) {
-  __shared__ double As[kEb * kKMajorLd];  // A(r, k) at lds_at<TA>(k, r)
-  __shared__ double Bs[kEb * kKMajorLd];  // B(k, c) at lds_at<!TB>(k, c)
-  const int64_t T = LOWER ? (int64_t)nrt * (nrt + 1) / 2 : (int64_t)nrt * nct;
+// General FP64 products on the matrix cores.  C (m x nn, row-major with ldc)
+// = A B, = -A B or -= A B:
+//   A(i, k) = TA ? A[k lda + i] : A[i lda + k], B(k, j) = TB ? B[j ldb + k] : B[k ldb + j].
+// LOWER computes only the tiles with tj <= ti (m = nn).  Rows and columns
+// beyond the matrices read as zero or as some valid row; nothing outside C's
+// m x nn block is written.  tri skips the k range where an operand is zero:
+//   kTriA: A is lower triangular, row tile R takes k < R + edge;
+//   kTriAt: A is the transpose of a lower triangle, row tile R takes k >= R;
+//   kTriB: B is lower triangular, column tile Cc takes k >= Cc
+// (each operand zero above the diagonal inside its diagonal tiles).
+// Batches (blockIdx.y = p) shift the three matrices by p times their strides;
+// with mstep > 0 the batch's rows end at m - p mstep (the ragged last block of
+// a block-diagonal sweep), and under kTriA so does its k.
+enum Tri { kTriNone = 0, kTriA, kTriAt, kTriB };
+enum GemmMode { kAssign = 0, kSubtract, kNegate };
+
+// The order of k puts the large entries near a triangle's diagonal last, so
+// that the many small ones are summed before they meet a large partial sum: in
+// X^T X, taken from the diagonal outwards, positive terms below half a unit of
+// the running sum were lost one by one (the log s_f derivative, a trace, was
+// off by 2e-13 at n = 7,503 instead of 4e-16).
+__device__ __forceinline__ bool gemm_descends(int tri) { return tri == kTriAt || tri == kTriB; }
+
+struct GemmArgs {
+  const double* A;
+  int64_t lda, sA;
+  const double* B;
+  int64_t ldb, sB;
+  double* C;
+  int64_t ldc, sC;
+  int64_t m, nn, kk;
+  int64_t mmax, mstep;  // batches: rows of batch p = min(mmax, m - p mstep)
+  int nrt, nct, tri;
+};
+
+// Tile (ti, tj) and k range of this workgroup; false when it has no rows.
+// Workgroup h runs on XCD h % 8.  Each XCD takes a contiguous run of the tile
+// order, so that its tiles share panels in its L2: rectangles go through
+// groups of 8 tile columns, row by row (under kTriA the long rows first); under
+// kTriB, whose columns differ in length, through groups of 8 tile rows, so that
+// every XCD gets all lengths.  Lower triangles run along tile rows; under
+// kTriAt, whose rows differ in length, they are dealt out round-robin.
+template <bool LOWER, int EDGE>
+__device__ __forceinline__ bool gemm_tile(const GemmArgs& g, int64_t m, int64_t kk_all, int64_t& R, int64_t& Cc,
+                                          int64_t& k0, int64_t& kn) {
+  const int64_t T = LOWER ? (int64_t)g.nrt * (g.nrt + 1) / 2 : (int64_t)g.nrt * g.nct;
   const int64_t h = blockIdx.x, xcd = h & 7, q8 = T >> 3, rem8 = T & 7;
-  const int64_t b = xcd * q8 + (xcd < rem8 ? xcd : rem8) + (h >> 3);
+  const int64_t b = LOWER && g.tri == kTriAt ? h : xcd * q8 + (xcd < rem8 ? xcd : rem8) + (h >> 3);
   int64_t ti, tj;
   if (LOWER) {
     ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
     while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
     while (ti * (ti + 1) / 2 > b) --ti;
     tj = b - ti * (ti + 1) / 2;
+  } else if (g.tri == kTriB) {
+    const int64_t grp = b / (8 * (int64_t)g.nct), rest = b - grp * 8 * g.nct;
+    const int64_t width = g.nrt - 8 * grp < 8 ? g.nrt - 8 * grp : 8;
+    tj = rest / width;
+    ti = 8 * grp + rest - tj * width;
   } else {
-    ti = b / nct;
-    tj = b - ti * nct;
+    const int64_t grp = b / (8 * (int64_t)g.nrt), rest = b - grp * 8 * g.nrt;
+    const int64_t width = g.nct - 8 * grp < 8 ? g.nct - 8 * grp : 8;
+    ti = rest / width;
+    tj = 8 * grp + rest - ti * width;
+    if (g.tri == kTriA) ti = g.nrt - 1 - ti;
   }
-  const int64_t R = kEb * ti, Cc = kEb * tj;
-  const int64_t kk = tri && R + kEb < kk_all ? R + kEb : kk_all;
+  R = EDGE * ti;
+  Cc = EDGE * tj;
+  k0 = g.tri == kTriAt ? R : (g.tri == kTriB ? Cc : 0);
+  kn = g.tri == kTriA && R + EDGE < kk_all ? R + EDGE : kk_all;
+  return R < m;
+}
+
+// 64 x 64 output tiles, k in chunks of 64 staged in LDS as in the tile kernel above.
+template <bool TA, bool TB, bool LOWER, int MODE>
+__global__ __launch_bounds__(256) void gemm64_f64_kernel(GemmArgs g) {
+  __shared__ double As[kEb * kKMajorLd];  // A(r, k) at lds_at<TA>(k, r)
+  __shared__ double Bs[kEb * kKMajorLd];  // B(k, c) at lds_at<!TB>(k, c)
+  const int64_t p = blockIdx.y;
+  const double* A = g.A + p * g.sA;
+  const double* B = g.B + p * g.sB;
+  double* C = g.C + p * g.sC;
+  const int64_t m = g.mstep > 0 ? (g.m - p * g.mstep < g.mmax ? g.m - p * g.mstep : g.mmax) : g.m;
+  const int64_t kall = g.mstep > 0 && g.tri == kTriA ? m : g.kk;
+  const int64_t lda = g.lda, ldb = g.ldb, ldc = g.ldc, nn = g.nn;
+  int64_t R, Cc, kbeg, kk;
+  if (!gemm_tile<LOWER, kEb>(g, m, kall, R, Cc, kbeg, kk)) return;  // whole workgroup
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r0 = 32 * (wave >> 1), c0 = 32 * (wave & 1);
   const int lr = lane & 15, lk = lane >> 4;
@@ -491,12 +492,15 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(const double* A, int64_t 
       Bs[TB ? lds_at<false>(y, x) : lds_at<true>(x, y)] = bv[it];
     }
   };
-  load(0);
-  for (int64_t kc = 0; kc < kk; kc += kEb) {
-    if (kc > 0) __syncthreads();  // every wave is done with the previous chunk
+  const int64_t nch = (kk - kbeg + kEb - 1) / kEb;
+  const int64_t kfirst = gemm_descends(g.tri) ? kbeg + (nch - 1) * kEb : kbeg;
+  const int64_t kstep = gemm_descends(g.tri) ? -kEb : kEb;
+  load(kfirst);
+  for (int64_t c = 0, kc = kfirst; c < nch; ++c, kc += kstep) {
+    if (c > 0) __syncthreads();  // every wave is done with the previous chunk
     store();
     __syncthreads();
-    if (kc + kEb < kk) load(kc + kEb);
+    if (c + 1 < nch) load(kc + kstep);
 #pragma unroll 4
     for (int k = 0; k < kEb; k += 4) {
       const double a0 = As[lds_at<TA>(k + lk, r0 + lr)], a1 = As[lds_at<TA>(k + lk, r0 + 16 + lr)];
@@ -514,14 +518,12 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(const double* A, int64_t 
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int64_t row = R + r0 + 16 * rb + lk + 4 * i, col = Cc + c0 + 16 * cb + lr;
-        if (row < m && col < nn) C[row * ldc + col] = acc[rb][cb][i];
+        if (row < m && col < nn) C[row * ldc + col] = MODE == kNegate ? -acc[rb][cb][i] : acc[rb][cb][i];
       }
 }
 
 // The same products in 128 x 128 output tiles, k in chunks of 16 in two LDS
-// buffers: C = A B, or (SUB) C -= A B, A and B as above.  LOWER computes only
-// the tiles with tj <= ti.  tri: A is lower triangular (zero above the
-// diagonal), so row tile ti takes k < 128 (ti + 1) only.
+// buffers.
 //
 // Bound by the FP64 matrix cores (64 cycles per v_mfma_f64_16x16x4 and SIMD,
 // 74 TF/s measured on a large library product).  A wave owns a 64 x 64
@@ -599,34 +601,18 @@ __device__ __forceinline__ void gemm_store(double* buf, const f64x2 (&v)[4]) {
   }
 }
 
-template <bool TA, bool TB, bool LOWER, bool SUB>
-__global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(const double* __restrict__ A, int64_t lda,
-                                                             const double* __restrict__ B, int64_t ldb, double* C,
-                                                             int64_t ldc, int64_t m, int64_t nn, int64_t kk, int nrt,
-                                                             int nct, int tri) {
+template <bool TA, bool TB, bool LOWER, int MODE>
+__global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) double As[2][kGBuf], Bs[2][kGBuf];
-  // Workgroup h runs on XCD h % 8: each XCD takes a contiguous run of the tile
-  // order.  Rectangles go through groups of 8 tile columns, row by row within
-  // a group, so the ~64 tiles an XCD works on at once share 8 + 8 panels in
-  // its L2; under tri the long rows of each group come first.
-  const int64_t T = LOWER ? (int64_t)nrt * (nrt + 1) / 2 : (int64_t)nrt * nct;
-  const int64_t h = blockIdx.x, xcd = h & 7, q8 = T >> 3, rem8 = T & 7;
-  const int64_t b = xcd * q8 + (xcd < rem8 ? xcd : rem8) + (h >> 3);
-  int64_t ti, tj;
-  if (LOWER) {
-    ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
-    while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
-    while (ti * (ti + 1) / 2 > b) --ti;
-    tj = b - ti * (ti + 1) / 2;
-  } else {
-    const int64_t grp = b / (8 * (int64_t)nrt), rest = b - grp * 8 * nrt;
-    const int64_t width = nct - 8 * grp < 8 ? nct - 8 * grp : 8;
-    ti = rest / width;
-    tj = 8 * grp + rest - ti * width;
-    if (tri) ti = nrt - 1 - ti;
-  }
-  const int64_t R = kGt * ti, Cc = kGt * tj;
-  const int64_t kn = tri && R + kGt < kk ? R + kGt : kk;
+  const int64_t p = blockIdx.y;
+  const double* __restrict__ A = g.A + p * g.sA;
+  const double* __restrict__ B = g.B + p * g.sB;
+  double* C = g.C + p * g.sC;
+  const int64_t m = g.mstep > 0 ? (g.m - p * g.mstep < g.mmax ? g.m - p * g.mstep : g.mmax) : g.m;
+  const int64_t kall = g.mstep > 0 && g.tri == kTriA ? m : g.kk;
+  const int64_t lda = g.lda, ldb = g.ldb, ldc = g.ldc, nn = g.nn;
+  int64_t R, Cc, kbeg, kn;
+  if (!gemm_tile<LOWER, kGt>(g, m, kall, R, Cc, kbeg, kn)) return;  // whole workgroup
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r0 = 64 * (wave >> 1), c0 = 64 * (wave & 1);
   const int lr = lane & 15, lk = lane >> 4;
@@ -636,17 +622,20 @@ __global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(const double* __res
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
   f64x2 av[4], bv[4];
-  gemm_load<TA>(A, lda, R, m, 0, kn, av);
-  gemm_load<!TB>(B, ldb, Cc, nn, 0, kn, bv);
+  const int64_t nch = (kn - kbeg + kGk - 1) / kGk;
+  const int64_t kfirst = gemm_descends(g.tri) ? kbeg + (nch - 1) * kGk : kbeg;
+  const int64_t kstep = gemm_descends(g.tri) ? -kGk : kGk;
+  gemm_load<TA>(A, lda, R, m, kfirst, kn, av);
+  gemm_load<!TB>(B, ldb, Cc, nn, kfirst, kn, bv);
   gemm_store<TA>(As[0], av);
   gemm_store<!TB>(Bs[0], bv);
   __syncthreads();
   int cur = 0;
-  for (int64_t kc = 0; kc < kn; kc += kGk, cur ^= 1) {
-    const bool more = kc + kGk < kn;
+  for (int64_t c = 0, kc = kfirst; c < nch; ++c, kc += kstep, cur ^= 1) {
+    const bool more = c + 1 < nch;
     if (more) {
-      gemm_load<TA>(A, lda, R, m, kc + kGk, kn, av);
-      gemm_load<!TB>(B, ldb, Cc, nn, kc + kGk, kn, bv);
+      gemm_load<TA>(A, lda, R, m, kc + kstep, kn, av);
+      gemm_load<!TB>(B, ldb, Cc, nn, kc + kstep, kn, bv);
     }
 #pragma unroll
     for (int k = 0; k < kGk; k += 4) {
@@ -675,20 +664,22 @@ __global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(const double* __res
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int64_t row = R + r0 + 16 * rb + lk + 4 * i, col = Cc + c0 + 16 * cb + lr;
-        old[cb][i] = (SUB && row < m && col < nn) ? C[row * ldc + col] : 0.0;
+        old[cb][i] = (MODE == kSubtract && row < m && col < nn) ? C[row * ldc + col] : 0.0;
       }
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int64_t row = R + r0 + 16 * rb + lk + 4 * i, col = Cc + c0 + 16 * cb + lr;
-        if (row < m && col < nn) C[row * ldc + col] = SUB ? old[cb][i] - acc[rb][cb][i] : acc[rb][cb][i];
+        if (row < m && col < nn)
+          C[row * ldc + col] = MODE == kSubtract ? old[cb][i] - acc[rb][cb][i]
+                                                 : (MODE == kNegate ? -acc[rb][cb][i] : acc[rb][cb][i]);
       }
   }
 }
 
-static int64_t gemm128_tiles(bool lower, int64_t m, int64_t nn) {
-  const int64_t nrt = (m + kGt - 1) / kGt, nct = (nn + kGt - 1) / kGt;
+static int64_t tile_count(bool lower, int64_t m, int64_t nn, int64_t edge) {
+  const int64_t nrt = (m + edge - 1) / edge, nct = (nn + edge - 1) / edge;
   return lower ? nrt * (nrt + 1) / 2 : nrt * nct;
 }
 
@@ -696,21 +687,31 @@ static int64_t gemm128_tiles(bool lower, int64_t m, int64_t nn) {
 // 64-wide tiles, four times as many, use more of the 256 CUs.
 constexpr int64_t kGemm128MinTiles = 256;
 
-template <bool TA, bool TB, bool LOWER, bool SUB>
-static hipError_t gemm128(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, int64_t m,
-                          int64_t nn, int64_t kk, bool tri, hipStream_t st) {
-  const int64_t tiles = gemm128_tiles(LOWER, m, nn);
-  if (tiles <= 0) return hipSuccess;
-  if (tiles > 0x7fffffff || kk < 1) return hipErrorInvalidValue;
-  gemm128_f64_kernel<TA, TB, LOWER, SUB><<<(unsigned)tiles, 256, 0, st>>>(
-      A, lda, B, ldb, C, ldc, m, nn, kk, (int)((m + kGt - 1) / kGt), (int)((nn + kGt - 1) / kGt), tri ? 1 : 0);
+static bool use_gemm128(bool lower, int64_t m, int64_t nn) { return tile_count(lower, m, nn, kGt) >= kGemm128MinTiles; }
+
+// `batch` products (blockIdx.y); g.nrt and g.nct are filled in here.  g.mmax rows per batch when batched.
+template <bool TA, bool TB, bool LOWER, int MODE, bool WIDE>
+static hipError_t gemm_launch(GemmArgs g, int64_t batch, hipStream_t st) {
+  constexpr int64_t edge = WIDE ? kGt : kEb;
+  const int64_t rows = g.mstep > 0 ? g.mmax : g.m;
+  const int64_t tiles = tile_count(LOWER, rows, g.nn, edge);
+  if (tiles <= 0 || batch <= 0) return hipSuccess;
+  if (tiles > 0x7fffffff || batch > 65535 || g.kk < 1) return hipErrorInvalidValue;
+  g.nrt = (int)((rows + edge - 1) / edge);
+  g.nct = (int)((g.nn + edge - 1) / edge);
+  const dim3 grid((unsigned)tiles, (unsigned)batch);
+  if constexpr (WIDE)
+    gemm128_f64_kernel<TA, TB, LOWER, MODE><<<grid, 256, 0, st>>>(g);
+  else
+    gemm64_f64_kernel<TA, TB, LOWER, MODE><<<grid, 256, 0, st>>>(g);
   return hipGetLastError();
 }
 
 static int ntiles(int64_t len) { return (int)((len + kEb - 1) / kEb); }
 
 // A = L L^T in place (lower triangle; the diagonal blocks' upper parts are
-// zeroed, the rest of the upper triangle holds no result).  Two levels of
+// zeroed, the rest of the upper triangle holds no result); the inverses of the
+// diagonal blocks stay in Dinv (block bi at 64 * 64 * bi).  Two levels of
 // blocking: 64-wide panels inside 256-wide super-panels.  A panel updates only
 // the columns of its own super-panel; the trailing matrix beyond it takes the
 // whole super-panel at once (k = 256), so that it is read and written once per
@@ -724,11 +725,12 @@ static hipError_t cholesky(double* A, int64_t n, int* info, double* Dinv, hipStr
     for (int64_t j0 = J0; j0 < Jend; j0 += kEb) {
       const int jb = (int)std::min<int64_t>(kEb, n - j0);
       const int64_t rest = n - j0 - jb;
-      potrf_diag_kernel<<<1, 256, 0, st>>>(A, n, j0, jb, info, rest > 0 ? Dinv : nullptr);
+      double* Di = Dinv + j0 / kEb * kEb * kEb;
+      potrf_diag_kernel<<<1, 256, 0, st>>>(A, n, j0, jb, info, Di);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       if (rest <= 0) return hipSuccess;
-      // L21 = A21 L11^{-T} = A21 Dinv^T for every row below (jb = 64 here)
-      e = tile_update<false, true, false, true>(A, n, -1, j0, Dinv, kEb, 0, 0, A, n, jb, j0 + jb, j0, ntiles(rest),
+      // L21 = A21 L11^{-T} for every row below (jb = 64 here)
+      e = tile_update<false, true, false, true>(A, n, -1, j0, Di, kEb, 0, 0, A, n, jb, j0 + jb, j0, ntiles(rest),
                                                 1, st);
       if (e != hipSuccess) return e;
       // the rest of this super-panel's columns, [j0 + 64, Jend): the lower
@@ -748,9 +750,10 @@ static hipError_t cholesky(double* A, int64_t n, int* info, double* Dinv, hipStr
     // A22 -= L21 L21^T over the lower tiles beyond the super-panel, k = Jend - J0
     if (n > Jend) {
       const int64_t rest = n - Jend;
-      if (gemm128_tiles(true, rest, rest) >= kGemm128MinTiles)
-        e = gemm128<false, true, true, true>(A + Jend * n + J0, n, A + Jend * n + J0, n, A + Jend * n + Jend, n, rest,
-                                             rest, Jend - J0, false, st);
+      const double* P = A + Jend * n + J0;
+      if (use_gemm128(true, rest, rest))
+        e = gemm_launch<false, true, true, kSubtract, true>(
+            GemmArgs{P, n, 0, P, n, 0, A + Jend * n + Jend, n, 0, rest, rest, Jend - J0, 0, 0, 0, 0, kTriNone}, 1, st);
       else
         e = tile_update<false, true, true, false>(A, n, -1, J0, A, n, -1, J0, A, n, (int)(Jend - J0), Jend, Jend,
                                                   ntiles(rest), 0, st);
@@ -762,102 +765,58 @@ static hipError_t cholesky(double* A, int64_t n, int* info, double* Dinv, hipStr
 
 // ---------------------------------------------------------------- K_hat^{-1}
 
-__global__ void identity_kernel(double* __restrict__ B, int64_t n) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n * n) return;
-  B[e] = (e / n == e % n) ? 1.0 : 0.0;
-}
-
-// B <- K_hat^{-1} from the Cholesky factor in L: first L^{-1} (lower
-// triangular, so block row i needs columns [0, i0 + 64) only), then
-// L^{-T} L^{-1} on the lower triangle, then mirrored.  Both passes are blocked
-// like the factorisation: 64-row blocks update the rest of their 256-row
-// super-block, and the rows beyond it take the whole super-block at once.
-// B <- L^{-1} B for B = I on entry (the diagonal blocks' inverses in Dinv):
-// block row i needs columns [0, i0 + 64) only.
-static hipError_t lower_inverse_forward(const double* L, double* B, double* Dinv, int64_t n, hipStream_t st) {
-  hipError_t e = hipSuccess;
-  // forward: X_i = L_ii^{-1} B_i on columns [0, i0 + ib); then B_r -= L_ri X_i
-  // on the same columns for the rows r of the super-block below block i; after
-  // the super-block, the rows below it at once (k = its height, columns
-  // [0, Iend), where X is zero beyond each block's own columns)
-  for (int64_t I0 = 0; I0 < n; I0 += kSp) {
-    const int64_t Iend = std::min<int64_t>(n, I0 + kSp);
-    for (int64_t i0 = I0; i0 < Iend; i0 += kEb) {
-      const int64_t bi = i0 / kEb;
-      const int ib = (int)std::min<int64_t>(kEb, n - i0);
-      const int64_t ncols = i0 + ib;
-      e = tile_update<false, false, false, true>(Dinv + bi * kEb * kEb, kEb, 0, 0, B, n, -1, i0, B, n, ib, i0, 0, 1,
-                                                 ntiles(ncols), st);
-      if (e != hipSuccess) return e;
-      const int64_t below = Iend - i0 - ib;
-      if (below > 0) {
-        e = tile_update<false, false, false, false>(L, n, -1, i0, B, n, -1, i0, B, n, ib, i0 + ib, 0, ntiles(below),
-                                                    ntiles(ncols), st);
-        if (e != hipSuccess) return e;
-      }
-    }
-    if (n > Iend) {
-      if (gemm128_tiles(false, n - Iend, Iend) >= kGemm128MinTiles)
-        e = gemm128<false, false, false, true>(L + Iend * n + I0, n, B + I0 * n, n, B + Iend * n, n, n - Iend, Iend,
-                                               Iend - I0, false, st);
-      else
-        e = tile_update<false, false, false, false>(L, n, -1, I0, B, n, -1, I0, B, n, (int)(Iend - I0), Iend, 0,
-                                                    ntiles(n - Iend), ntiles(Iend), st);
-      if (e != hipSuccess) return e;
-    }
+// The diagonal blocks of the factor replaced by their inverses, the upper half
+// of every 128-wide diagonal tile zeroed; dL (nullable) receives the factor's
+// diagonal.  One workgroup per 64-row block.
+__global__ __launch_bounds__(256) void seed_inverse_kernel(double* __restrict__ A, int64_t n,
+                                                           const double* __restrict__ Dinv, double* __restrict__ dL) {
+  const int64_t bi = blockIdx.x, i0 = bi * kEb;
+  if (dL && threadIdx.x < kEb && i0 + threadIdx.x < n)
+    dL[i0 + threadIdx.x] = A[(i0 + threadIdx.x) * n + i0 + threadIdx.x];
+  __syncthreads();
+  for (int e = threadIdx.x; e < kEb * kEb; e += 256) {
+    const int64_t r = i0 + e / kEb, c = i0 + e % kEb;
+    if (r < n && c < n) A[r * n + c] = Dinv[bi * kEb * kEb + e];
+    if ((bi & 1) == 0 && r < n && c + kEb < n) A[r * n + c + kEb] = 0.0;
   }
-  return hipSuccess;
 }
 
-static hipError_t inverse_from_cholesky(const double* L, double* B, double* Dinv, int64_t n, hipStream_t st) {
-  identity_kernel<<<(unsigned)((n * n + 255) / 256), 256, 0, st>>>(B, n);
+// A <- L^{-1} in place (lower triangle; zero above the diagonal inside the
+// 128-wide diagonal tiles, nothing beyond them) from the factor L in A and its
+// diagonal blocks' inverses; W is scratch of the same size.  Doubling: with the
+// inverses X of the size-s diagonal blocks in place, each pair of neighbours
+// takes X21 = -X22 (L21 X11), all pairs of a size in two launches, so the work
+// is ~log2(n / 64) large triangular products instead of a sweep of 64-row
+// steps that rewrites the trailing rows for each.
+static hipError_t lower_inverse(double* A, double* W, const double* Dinv, double* dL, int64_t n, hipStream_t st) {
+  seed_inverse_kernel<<<(unsigned)((n + kEb - 1) / kEb), 256, 0, st>>>(A, n, Dinv, dL);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // The diagonal blocks' inverses, kept for both passes: block bi at Dinv + 64 * 64 * bi.
-  const int64_t nb = (n + kEb - 1) / kEb;
-  trtri_blocks_kernel<<<(unsigned)nb, 256, 0, st>>>(L, n, Dinv);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = lower_inverse_forward(L, B, Dinv, n, st)) != hipSuccess) return e;
-  // backward, from the last block: Z_i = L_ii^{-T} C_i on columns
-  // [0, i0 + ib); then C[R][Cc] -= L[i-block][R]^T Z[i-block][Cc] on the lower
-  // tiles of the super-block's rows above block i (their triangle, then the
-  // columns left of the super-block); after the super-block, the lower tiles
-  // of every row above it at once
-  const int64_t nsb = (n + kSp - 1) / kSp;
-  for (int64_t sb = nsb - 1; sb >= 0; --sb) {
-    const int64_t I0 = sb * kSp;
-    const int64_t Iend = std::min<int64_t>(n, I0 + kSp);
-    for (int64_t bi = (Iend - 1) / kEb; bi >= I0 / kEb; --bi) {
-      const int64_t i0 = bi * kEb;
-      const int ib = (int)std::min<int64_t>(kEb, n - i0);
-      const int64_t ncols = i0 + ib;
-      e = tile_update<true, false, false, true>(Dinv + bi * kEb * kEb, kEb, 0, 0, B, n, -1, i0, B, n, ib, i0, 0, 1,
-                                                ntiles(ncols), st);
-      if (e != hipSuccess) return e;
-      if (i0 > I0) {
-        e = tile_update<true, false, true, false>(L, n, -1, i0, B, n, -1, i0, B, n, ib, I0, I0, ntiles(i0 - I0), 0,
-                                                  st);
-        if (e != hipSuccess) return e;
-        if (I0 > 0) {
-          e = tile_update<true, false, false, false>(L, n, -1, i0, B, n, -1, i0, B, n, ib, I0, 0, ntiles(i0 - I0),
-                                                     ntiles(I0), st);
-          if (e != hipSuccess) return e;
-        }
-      }
-    }
-    if (I0 > 0) {
-      // (a 128-wide diagonal tile also writes above the 64-wide block diagonal,
-      // which nothing reads before the mirror overwrites it)
-      if (gemm128_tiles(true, I0, I0) >= kGemm128MinTiles)
-        e = gemm128<true, false, true, true>(L + I0 * n, n, B + I0 * n, n, B, n, I0, I0, Iend - I0, false, st);
-      else
-        e = tile_update<true, false, true, false>(L, n, -1, I0, B, n, -1, I0, B, n, (int)(Iend - I0), 0, 0,
-                                                  ntiles(I0), 0, st);
-      if (e != hipSuccess) return e;
+  for (int64_t s = kEb; s < n && e == hipSuccess; s *= 2) {
+    const int64_t pairs = (n - s + 2 * s - 1) / (2 * s);  // blocks p with a row beyond (2 p + 1) s
+    const int64_t step = 2 * s * (n + 1);
+    double* L21 = A + s * n;
+    // W21 = L21 X11, then A21 = -X22 W21
+    const GemmArgs t{L21, n, step, A, n, step, W + s * n, n, step, n - s, s, s, s, 2 * s, 0, 0, kTriB};
+    const GemmArgs x{A + s * (n + 1), n, step, W + s * n, n, step, L21, n, step, n - s, s, s, s, 2 * s, 0, 0, kTriA};
+    if (tile_count(false, s, s, kGt) * pairs >= kGemm128MinTiles) {
+      e = gemm_launch<false, false, false, kAssign, true>(t, pairs, st);
+      if (e == hipSuccess) e = gemm_launch<false, false, false, kNegate, true>(x, pairs, st);
+    } else {
+      e = gemm_launch<false, false, false, kAssign, false>(t, pairs, st);
+      if (e == hipSuccess) e = gemm_launch<false, false, false, kNegate, false>(x, pairs, st);
     }
   }
-  return hipSuccess;
+  return e;
+}
+
+// The lower tiles of B = K_hat^{-1} = X^T X, X = L^{-1} left in A.
+static hipError_t inverse_from_cholesky(double* A, double* B, const double* Dinv, double* dL, int64_t n,
+                                        hipStream_t st) {
+  hipError_t e = lower_inverse(A, B, Dinv, dL, n, st);
+  if (e != hipSuccess) return e;
+  const GemmArgs g{A, n, 0, A, n, 0, B, n, 0, n, n, n, 0, 0, 0, 0, kTriAt};
+  return use_gemm128(true, n, n) ? gemm_launch<true, false, true, kAssign, true>(g, 1, st)
+                                 : gemm_launch<true, false, true, kAssign, false>(g, 1, st);
 }
 
 // B[r][c] = B[c][r] for c > r (the upper triangle from the lower one).
@@ -880,12 +839,9 @@ __global__ __launch_bounds__(256) void gemv_rows_kernel(const double* __restrict
   if (lane == 0) out[a] = s;
 }
 
-__global__ void diag_kernel(const double* __restrict__ A, const double* __restrict__ B, int64_t n,
-                            double* __restrict__ dA, double* __restrict__ dB) {
+__global__ void diag_kernel(const double* __restrict__ B, int64_t n, double* __restrict__ dB) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  dA[i] = A[i * n + i];
-  dB[i] = B[i * n + i];
+  if (i < n) dB[i] = B[i * n + i];
 }
 
 // ---------------------------------------------------------------- gradient
@@ -1007,7 +963,7 @@ static int64_t lower_tiles(int64_t n) {
 
 size_t exact_ws_bytes(int d, int64_t n) {
   if (n < 1 || n > kExactMaxN || d < 1 || d > kExactMaxD) return 0;
-  size_t b = 2 * align256((size_t)n * n * 8);                            // K_hat -> L; I -> K_hat^{-1}
+  size_t b = 2 * align256((size_t)n * n * 8);                            // K_hat -> L -> L^{-1}; scratch -> K_hat^{-1}
   b += 3 * align256((size_t)n * 8);                                      // omega, diag L, diag K_hat^{-1}
   b += 2 * align256((size_t)GP_MAX_D * 8);                               // feature scales
   b += align256((size_t)lower_tiles(n) * (exact_dp(d) + 1) * 8);         // gradient partials
@@ -1050,12 +1006,12 @@ int run_exact(const gp_kernel* kern, const double* X, const double* y, int64_t n
     form_khat_kernel<GP_RBF><<<g2, 256, 0, st>>>(X, n, d, sc, kern->outputscale, kern->noise, A);
   GPK_HIP(hipGetLastError());
   GPK_HIP(cholesky(A, n, info, Dinv, st));
-  GPK_HIP(inverse_from_cholesky(A, B, Dinv, n, st));
+  GPK_HIP(inverse_from_cholesky(A, B, Dinv, dA, n, st));
   mirror_kernel<<<(unsigned)((n * n + 255) / 256), 256, 0, st>>>(B, n);
   GPK_HIP(hipGetLastError());
   gemv_rows_kernel<<<(unsigned)((n + 3) / 4), 256, 0, st>>>(B, y, n, om);
   GPK_HIP(hipGetLastError());
-  diag_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(A, B, n, dA, dB);
+  diag_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(B, n, dB);
   GPK_HIP(hipGetLastError());
   if (grad) {
     if (kern->kind == GP_MATERN52)
@@ -1101,23 +1057,15 @@ int run_exact(const gp_kernel* kern, const double* X, const double* y, int64_t n
 
 hipError_t dense_lower_times(int64_t m, int64_t nn, const double* L, int64_t ldl, const double* B, int64_t ldb,
                              double* C, int64_t ldc, hipStream_t st) {
-  if (m <= 0 || nn <= 0) return hipSuccess;
-  if (gemm128_tiles(false, m, nn) >= kGemm128MinTiles)
-    return gemm128<false, false, false, false>(L, ldl, B, ldb, C, ldc, m, nn, m, /*tri=*/true, st);
-  const int nrt = ntiles(m), nct = ntiles(nn);
-  gemm_f64_kernel<false, false, false><<<(unsigned)(nrt * nct), 256, 0, st>>>(L, ldl, B, ldb, C, ldc, m, nn, m, nrt,
-                                                                              nct, 1);
-  return hipGetLastError();
+  const GemmArgs g{L, ldl, 0, B, ldb, 0, C, ldc, 0, m, nn, m, 0, 0, 0, 0, kTriA};
+  return use_gemm128(false, m, nn) ? gemm_launch<false, false, false, kAssign, true>(g, 1, st)
+                                   : gemm_launch<false, false, false, kAssign, false>(g, 1, st);
 }
 
 hipError_t dense_gram(int64_t m, int64_t kk, const double* A, int64_t lda, double* C, int64_t ldc, hipStream_t st) {
-  if (m <= 0) return hipSuccess;
-  if (gemm128_tiles(true, m, m) >= kGemm128MinTiles)
-    return gemm128<false, true, true, false>(A, lda, A, lda, C, ldc, m, m, kk, false, st);
-  const int nrt = ntiles(m);
-  gemm_f64_kernel<false, true, true><<<(unsigned)(nrt * (nrt + 1) / 2), 256, 0, st>>>(A, lda, A, lda, C, ldc, m, m,
-                                                                                     kk, nrt, nrt, 0);
-  return hipGetLastError();
+  const GemmArgs g{A, lda, 0, A, lda, 0, C, ldc, 0, m, m, kk, 0, 0, 0, 0, kTriNone};
+  return use_gemm128(true, m, m) ? gemm_launch<false, true, true, kAssign, true>(g, 1, st)
+                                 : gemm_launch<false, true, true, kAssign, false>(g, 1, st);
 }
 
 size_t dense_dinv_doubles(int64_t n) { return (size_t)((n + kEb - 1) / kEb) * kEb * kEb; }
@@ -1126,16 +1074,8 @@ hipError_t dense_cholesky(double* A, int64_t n, int* info, double* Dinv, hipStre
   return cholesky(A, n, info, Dinv, st);
 }
 
-// B = L^{-1} (lower triangular, zero above the diagonal) for the lower factor L
-// (row-major n x n, ld n): the forward pass of inverse_from_cholesky.
-hipError_t dense_lower_inverse(const double* L, double* B, double* Dinv, int64_t n, hipStream_t st) {
-  identity_kernel<<<(unsigned)((n * n + 255) / 256), 256, 0, st>>>(B, n);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t nb = (n + kEb - 1) / kEb;
-  trtri_blocks_kernel<<<(unsigned)nb, 256, 0, st>>>(L, n, Dinv);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  return lower_inverse_forward(L, B, Dinv, n, st);
+hipError_t dense_lower_inverse(double* L, double* W, const double* Dinv, int64_t n, hipStream_t st) {
+  return lower_inverse(L, W, Dinv, nullptr, n, st);
 }
 
 }  // namespace gpk

@@ -92,7 +92,7 @@ hipError_t pivchol_launch_column(const double* X, int64_t n, const gp_kernel* ke
                                  const PivState& ps, int m, hipStream_t st);
 
 // Dense FP64 pieces on the matrix cores (exact.hip).  Row-major matrices.
-// C (m x nn) = L B, L m x m lower triangular (zero above the diagonal).
+// C (m x nn) = L B, L m x m lower triangular as dense_lower_inverse leaves it.
 hipError_t dense_lower_times(int64_t m, int64_t nn, const double* L, int64_t ldl, const double* B, int64_t ldb,
                              double* C, int64_t ldc, hipStream_t st);
 // C (m x m) = A A^T for A m x kk: the tiles on and below the diagonal.
@@ -100,10 +100,12 @@ hipError_t dense_gram(int64_t m, int64_t kk, const double* A, int64_t lda, doubl
 // Doubles of the diagonal-block scratch of the two routines below.
 size_t dense_dinv_doubles(int64_t n);
 // In-place lower Cholesky factor of the symmetric n x n A (lower triangle read);
-// *info (device, zeroed by the caller) receives 1 + the first non-positive pivot.
+// the inverses of its 64 x 64 diagonal blocks into Dinv; *info (device, zeroed by
+// the caller) receives 1 + the first non-positive pivot.
 hipError_t dense_cholesky(double* A, int64_t n, int* info, double* Dinv, hipStream_t st);
-// B = L^{-1} for a lower Cholesky factor L (zero above the diagonal).
-hipError_t dense_lower_inverse(const double* L, double* B, double* Dinv, int64_t n, hipStream_t st);
+// L <- L^{-1} in place for a lower Cholesky factor and its Dinv; W: n x n scratch.
+// Zero above the diagonal inside the 128 x 128 diagonal tiles, unset beyond them.
+hipError_t dense_lower_inverse(double* L, double* W, const double* Dinv, int64_t n, hipStream_t st);
 
 // Host: e_1^T log(T) e_1 for the Lanczos tridiagonal of CG coefficients
 // (alpha[j*stride], beta[j*stride], j < J).  Returns false if T is not

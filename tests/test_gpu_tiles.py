@@ -14,10 +14,10 @@ def _gk(th):
     return gp.Kernel(th.ell, th.sf, th.noise, "matern52" if th.kind == ok.MATERN52 else "rbf")
 
 
-@pytest.mark.parametrize("n", [15, 16, 17, 33, 47, 49, 81])
-def test_exact_gp_at_the_edges_of_the_16_wide_diagonal_steps(n):
-    """Diagonal blocks are factored in 16-column steps; the bars are those of the dense parity cases
-    (1e-10, well above 1e-14 kappa here)."""
+@pytest.mark.parametrize("n", [15, 16, 17, 33, 47, 49, 81, 193, 449])
+def test_exact_gp_at_the_edges_of_the_diagonal_steps(n):
+    """Diagonal blocks are factored in 16-column steps and inverted pairwise (64, 128, 256 ... rows); the bars are
+    those of the dense parity cases (1e-10, well above 1e-14 kappa here)."""
     from paper_2109_09817_amd import gp
     rng = np.random.default_rng(n)
     X, y = rng.standard_normal((n, 4)), rng.standard_normal(n)
