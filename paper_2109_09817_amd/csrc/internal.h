@@ -16,6 +16,14 @@ struct Scale {
   double s[GP_MAX_D];
 };
 
+// Split of an FP64 product: cps chunks of the b range per split, partial sums
+// [split][column][row] of slab rows and cpass columns at a time (bytes; none when nsplit = 1).
+struct F64Split {
+  int64_t cps = 0, nsplit = 1, slab = 0;
+  int cpass = 0;
+  size_t bytes = 0;
+};
+
 // Geometry of one prepared kernel-matrix product (square K_hat V or cross K(Z, X) V).
 //
 // Operand streams (all in caller workspace):
@@ -59,7 +67,7 @@ struct KmmPlan {
   const double* z64 = nullptr;  // output rows, m x d
   double* sc64 = nullptr;       // d feature scales
   double* nb64 = nullptr;       // n squared norms of the scaled b points
-  double* na64 = nullptr;       // m squared norms of the scaled output rows
+  F64Split f64;                 // how the sweep is split; its partial sums are in part
 };
 
 // Number of 32-wide K steps (BF16X3) or 16-wide groups (FP32) for d features.
@@ -115,6 +123,11 @@ bool kmm_plan_model(KmmPlan& p, const gp_kernel* kern, int precision, int64_t n,
 // so that each output row's arithmetic does not depend on m.
 hipError_t kmm_apply(const KmmPlan& p, const double* V, int64_t ldv, int t, double* out,
                      int64_t ldo, hipStream_t st, bool row_independent = false);
+
+// The FP64 form (kmm_fp64.hip).
+F64Split f64_split(int64_t n, int64_t m, bool square, int t);
+hipError_t fp64_prepare(KmmPlan& p, const gp_kernel* kern, const double* X, const double* Z, hipStream_t st);
+hipError_t fp64_sweep(const KmmPlan& p, const double* V, int64_t ldv, int t, double* out, int64_t ldo, hipStream_t st);
 
 // Sweep timing (see gp_profile_enable / gp_profile_read).
 void profile_enable(bool on);

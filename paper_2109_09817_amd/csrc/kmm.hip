@@ -35,9 +35,9 @@
 //   FP32:   v_mfma_f32_16x16x4_f32 for both products; the squared norms
 //           initialise the distance accumulator.
 // Row-independent BF16X3 cross products with many columns (prediction) use a
-// variant that evaluates each entry once for all columns (the wide sweep), and
-// the FP64 form (low-noise regime) runs both contractions on
-// v_mfma_f64_16x16x4; both are described where they are defined.
+// variant that evaluates each entry once for all columns (the wide sweep),
+// described where it is defined; the FP64 form (low-noise regime) is in
+// kmm_fp64.hip.
 #include "internal.h"
 #include "mfma_bf16.h"
 
@@ -50,9 +50,6 @@ namespace gpk {
 
 constexpr int kFlush = 32;  // 32-point chunks accumulated in FP32 before the FP64 flush
 constexpr int kF64MaxD = 64;   // FP64 form: features held in registers
-constexpr int kF64Chunk = 32;  // FP64 form: points per LDS chunk
-constexpr int kF64Cols = 64;   // FP64 form: V columns per pass
-constexpr int kF64Rows = 64;   // FP64 form: output rows per workgroup
 
 // The profile m(r) from S = r^2 scaled as above.  ACCURATE replaces the raw
 // v_sqrt_f32 by v_rsq_f32 plus one Newton step on the residual S - u^2.  The raw
@@ -1088,7 +1085,8 @@ size_t kmm_plan_bytes(int precision, int d, int64_t n, int64_t m, bool square, i
   const int ks = kmm_ksteps(precision, d);
   if (ks < 0) return 0;
   if (precision == GP_PREC_FP64)
-    return align256((size_t)d * 8) + align256((size_t)n * 8) + (square ? 0 : align256((size_t)m * 8)) + 256;
+    return align256((size_t)d * 8) + align256((size_t)n * 8) + align256(f64_split(n, square ? n : m, square, tmax).bytes) +
+           256;
   const int64_t npad = round_up(n, 32);
   const int64_t mrows = square ? n : m;
   const int64_t mpad = round_up(mrows, 256);
@@ -1129,7 +1127,8 @@ bool kmm_plan_init(KmmPlan& p, const gp_kernel* kern, int precision, int64_t n, 
     char* c = (char*)ws;
     p.sc64 = (double*)c;  c += align256((size_t)p.d * 8);
     p.nb64 = (double*)c;  c += align256((size_t)n * 8);
-    p.na64 = square ? p.nb64 : (double*)c;
+    p.part = (double*)c;
+    p.f64 = f64_split(n, p.m, square, tmax);
     return true;
   }
   const int64_t bpad = std::max(p.npad, p.mpad);
@@ -1211,210 +1210,6 @@ bool kmm_plan_model(KmmPlan& p, const gp_kernel* kern, int precision, int64_t n,
   return true;
 }
 
-// ------------------------------------------------------------------ FP64 form
-//
-// The low-noise regime (sigma^2 down to 1e-8, Sec. 3.2 and Sec. 4) needs K_hat V
-// to FP64 accuracy.  Both contractions run on the FP64 matrix cores
-// (v_mfma_f64_16x16x4: lane l supplies A(l % 16, k = l / 16) and B(k = l / 16,
-// l % 16), and holds D(l / 16 + 4 i, l % 16)).  A workgroup owns 64 output rows
-// and up to 64 columns; wave w owns rows 16 w .. 16 w + 15, their scaled
-// features held in registers as the B operand.  Per 32-point chunk of the b
-// stream (scaled points, norms and V values staged in LDS), for each 16-point
-// half: the MFMA gives x_b . x_a with the point along D's rows, so after the
-// profile (r^2 = n_a + n_b - 2 x_a.x_b, then m(r) in FP64) register i of every
-// lane holds the entries of points 4 i .. 4 i + 3 of that half, exactly the A
-// operand of the M V step that contracts over them.  Each entry is evaluated
-// once and never leaves registers; the output tile goes through LDS so that
-// the stores are coalesced.  The diagonal entry is exactly s_f (m(0) = 1) and
-// sigma^2 V is added exactly.  Every row's sums run in the same order whatever
-// the other rows are.
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-// sc64[f] = feature scale (thread f < d); nrm[p] = |x_p (.) sc|^2 for p < rows.
-__global__ void prep_fp64_kernel(const double* __restrict__ X, int64_t rows, int d, Scale sc,
-                                 double* __restrict__ sc64, double* __restrict__ nrm) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (sc64 && p < d) sc64[p] = sc.s[p];
-  if (p >= rows) return;
-  double s = 0.0;
-  for (int f = 0; f < d; ++f) {
-    const double v = X[p * d + f] * sc.s[f];
-    s = fma(v, v, s);
-  }
-  nrm[p] = s;
-}
-
-template <int DP, int KIND>
-__global__ __launch_bounds__(256) void sweep_fp64_kernel(const double* __restrict__ Xb, const double* __restrict__ nb,
-                                                         int64_t n, const double* __restrict__ Xa,
-                                                         const double* __restrict__ na, int64_t m, int d,
-                                                         const double* __restrict__ sc64, const double* __restrict__ V,
-                                                         int64_t ldv, int t, double sf, double noise, int square,
-                                                         double* __restrict__ out, int64_t ldo) {
-  constexpr int kBLd = DP + 2;           // point rows: the MFMA's 16-lane reads hit distinct banks
-  constexpr int kVLd = kF64Chunk + 2;    // V columns, likewise
-  constexpr int kOLd = kF64Rows + 1;     // output tile columns
-  constexpr int kKs = DP / 4;            // K steps of the distance MFMA
-  constexpr int kStage = kF64Chunk * kBLd + kF64Cols * kVLd;
-  constexpr int kBuf = kStage > kF64Cols * kOLd ? kStage : kF64Cols * kOLd;
-  __shared__ double buf[kBuf];  // the chunk's points [j][f] and V [c][j]; at the end the output tile [c][row]
-  __shared__ double Ns[kF64Chunk];
-  double* const Bs = buf;
-  double* const Vs = buf + kF64Chunk * kBLd;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int lr = lane & 15, lk = lane >> 4;
-  const int64_t a0 = (int64_t)blockIdx.x * kF64Rows;
-  const int c0 = blockIdx.y * kF64Cols;
-  const int tc = t - c0 < kF64Cols ? t - c0 : kF64Cols;  // columns of this pass
-  const int ncb = (tc + 15) / 16;                        // 16-column blocks
-  const int64_t arow = a0 + 16 * wave + lr;              // this lane's row in the products
-  double xa[kKs];
-#pragma unroll
-  for (int s = 0; s < kKs; ++s) {
-    const int f = 4 * s + lk;
-    xa[s] = (arow < m && f < d) ? Xa[arow * d + f] * sc64[f] : 0.0;
-  }
-  const double naa = arow < m ? na[arow] : 0.0;
-  // the staging threads' feature scales (the same features in every chunk)
-  static_assert(kF64Chunk * DP % 256 == 0 && kF64Chunk * kF64Cols % 256 == 0, "256 threads");
-  double bs[kF64Chunk * DP / 256];
-#pragma unroll
-  for (int it = 0; it < kF64Chunk * DP / 256; ++it) {
-    const int f = (tid + 256 * it) % DP;
-    bs[it] = f < d ? sc64[f] : 0.0;
-  }
-  f64x4 acc[4];
-#pragma unroll
-  for (int cb = 0; cb < 4; ++cb) acc[cb] = f64x4{0.0, 0.0, 0.0, 0.0};
-  // staging: the next chunk's points, V and norms are loaded into registers
-  // while the current chunk is computed from LDS
-  constexpr int kBPer = kF64Chunk * DP / 256, kVPer = kF64Chunk * kF64Cols / 256;
-  double bv[kBPer], vv[kVPer], nv;
-  auto load = [&](int64_t c0b) {
-#pragma unroll
-    for (int it = 0; it < kBPer; ++it) {
-      const int e = tid + 256 * it, j = e / DP, f = e - j * DP;
-      const int64_t b = c0b + j;
-      bv[it] = (b < n && f < d) ? Xb[b * d + f] : 0.0;
-    }
-#pragma unroll
-    for (int it = 0; it < kVPer; ++it) {
-      const int e = tid + 256 * it, c = e / kF64Chunk, j = e - c * kF64Chunk;
-      const int64_t b = c0b + j;
-      vv[it] = (b < n && c < tc) ? V[(int64_t)(c0 + c) * ldv + b] : 0.0;
-    }
-    nv = (tid < kF64Chunk && c0b + tid < n) ? nb[c0b + tid] : 0.0;
-  };
-  load(0);
-  for (int64_t b0 = 0; b0 < n; b0 += kF64Chunk) {
-    __syncthreads();  // the previous chunk's readers are done
-#pragma unroll
-    for (int it = 0; it < kBPer; ++it) {
-      const int e = tid + 256 * it, j = e / DP, f = e - j * DP;
-      Bs[j * kBLd + f] = bv[it] * bs[it];
-    }
-#pragma unroll
-    for (int it = 0; it < kVPer; ++it) {
-      const int e = tid + 256 * it, c = e / kF64Chunk;
-      Vs[c * kVLd + e - c * kF64Chunk] = vv[it];
-    }
-    if (tid < kF64Chunk) Ns[tid] = nv;
-    __syncthreads();
-    if (b0 + kF64Chunk < n) load(b0 + kF64Chunk);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int pb = 0; pb < 2; ++pb) {
-      // x_b . x_a: D(point 16 pb + lk + 4 i, row arow)
-      f64x4 dt = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int s = 0; s < kKs; ++s)
-        dt = __builtin_amdgcn_mfma_f64_16x16x4f64(Bs[(16 * pb + lr) * kBLd + 4 * s + lk], xa[s], dt, 0, 0, 0);
-      double mt[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int j = 16 * pb + lk + 4 * i;
-        const int64_t b = b0 + j;
-        const double S = fmax(naa + Ns[j] - 2.0 * dt[i], 0.0);
-        double mv;
-        if (b >= n) {
-          mv = 0.0;
-        } else if (square && b == arow) {
-          mv = 1.0;
-        } else if constexpr (KIND == GP_MATERN52) {
-          const double u = sqrt(S);
-          mv = fma(u, fma(u, 1.0 / 3.0, 1.0), 1.0) * exp(-u);
-        } else {
-          mv = exp(-0.5 * S);
-        }
-        mt[i] = mv;
-      }
-      // acc(row, column) += sum over the half's points of M(row, point) V(point, column)
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        if (cb < ncb) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                mt[i], Vs[(16 * cb + lr) * kVLd + 16 * pb + 4 * i + lk], acc[cb], 0, 0, 0);
-        }
-      }
-    }
-  }
-  // acc[cb][i]: row 16 wave + lk + 4 i, column 16 cb + lr -> LDS tile [column][row]
-  __syncthreads();
-  double* const Os = buf;
-#pragma unroll
-  for (int cb = 0; cb < 4; ++cb) {
-    if (cb < ncb) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) Os[(16 * cb + lr) * kOLd + 16 * wave + lk + 4 * i] = acc[cb][i];
-    }
-  }
-  __syncthreads();
-  const int64_t a = a0 + lane;
-  if (a >= m) return;
-  for (int c = wave; c < tc; c += 4) {
-    double y = sf * Os[c * kOLd + lane];
-    if (square) y = fma(noise, V[(int64_t)(c0 + c) * ldv + a], y);
-    out[(int64_t)(c0 + c) * ldo + a] = y;
-  }
-}
-
-// Feature scales of the FP64 form: Matern sqrt5 / l (so that r^2 -> u^2, u = sqrt5 r), RBF 1 / l.
-static Scale make_scale64(const gp_kernel* kern) {
-  Scale s{};
-  const double c = kern->kind == GP_MATERN52 ? std::sqrt(5.0) : 1.0;
-  for (int j = 0; j < kern->d; ++j) s.s[j] = c / kern->lengthscale[j];
-  return s;
-}
-
-template <int DP>
-static void launch_fp64(int kind, dim3 grid, const KmmPlan& p, const double* V, int64_t ldv, int t, double* out,
-                        int64_t ldo, hipStream_t st) {
-  if (kind == GP_MATERN52)
-    sweep_fp64_kernel<DP, GP_MATERN52><<<grid, 256, 0, st>>>(p.x64, p.nb64, p.n, p.z64, p.na64, p.m, p.d, p.sc64, V,
-                                                             ldv, t, p.sf, p.noise, p.square ? 1 : 0, out, ldo);
-  else
-    sweep_fp64_kernel<DP, GP_RBF><<<grid, 256, 0, st>>>(p.x64, p.nb64, p.n, p.z64, p.na64, p.m, p.d, p.sc64, V, ldv,
-                                                        t, p.sf, p.noise, p.square ? 1 : 0, out, ldo);
-}
-
-static hipError_t sweep_fp64(const KmmPlan& p, const double* V, int64_t ldv, int t, double* out, int64_t ldo,
-                             hipStream_t st) {
-  if (!p.x64 || !p.z64 || !V || !out || t < 1) return hipErrorInvalidValue;
-  dim3 grid((unsigned)((p.m + kF64Rows - 1) / kF64Rows), (unsigned)((t + kF64Cols - 1) / kF64Cols));
-  const int dp = (p.d + 15) / 16 * 16;
-  switch (dp) {
-    case 16: launch_fp64<16>(p.kind, grid, p, V, ldv, t, out, ldo, st); break;
-    case 32: launch_fp64<32>(p.kind, grid, p, V, ldv, t, out, ldo, st); break;
-    case 48: launch_fp64<48>(p.kind, grid, p, V, ldv, t, out, ldo, st); break;
-    case 64: launch_fp64<64>(p.kind, grid, p, V, ldv, t, out, ldo, st); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 double profile_coordinate_scale(int kind) {
   return kind == GP_MATERN52 ? std::sqrt(5.0) * M_LOG2E : std::sqrt(0.5 * M_LOG2E);
 }
@@ -1456,18 +1251,7 @@ static hipError_t prep_points(const KmmPlan& p, const Scale& sc, const double* P
 
 hipError_t kmm_prepare(KmmPlan& p, const gp_kernel* kern, const double* X, const double* Z,
                        hipStream_t st) {
-  if (p.precision == GP_PREC_FP64) {
-    if (!X || (!p.square && !Z) || !p.sc64) return hipErrorInvalidValue;
-    const Scale s64 = make_scale64(kern);
-    p.x64 = X;
-    p.z64 = p.square ? X : Z;
-    const int thr = 256;
-    prep_fp64_kernel<<<(unsigned)((std::max<int64_t>(p.n, p.d) + thr - 1) / thr), thr, 0, st>>>(X, p.n, p.d, s64,
-                                                                                              p.sc64, p.nb64);
-    if (!p.square)
-      prep_fp64_kernel<<<(unsigned)((p.m + thr - 1) / thr), thr, 0, st>>>(Z, p.m, p.d, s64, nullptr, p.na64);
-    return hipGetLastError();
-  }
+  if (p.precision == GP_PREC_FP64) return fp64_prepare(p, kern, X, Z, st);
   const Scale sc = make_scale(kern);
   if (p.square) {
     // one pass gives both sides; rows up to max(npad, mpad) so xc covers mpad
@@ -1701,7 +1485,7 @@ hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, 
 
 hipError_t kmm_apply(const KmmPlan& p, const double* V, int64_t ldv, int t, double* out, int64_t ldo,
                      hipStream_t st, bool row_independent) {
-  if (p.precision == GP_PREC_FP64) return sweep_fp64(p, V, ldv, t, out, ldo, st);
+  if (p.precision == GP_PREC_FP64) return fp64_sweep(p, V, ldv, t, out, ldo, st);
   hipError_t e = kmm_prepare_v(p, V, ldv, t, row_independent, st);
   if (e != hipSuccess) return e;
   return kmm_sweep(p, t, V, ldv, out, ldo, st, row_independent);

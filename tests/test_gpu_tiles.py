@@ -62,3 +62,49 @@ def test_large_rank_factor_on_both_tile_sizes(n, r):
     F = sl.solve_triangular(Lm, KMX, lower=True)
     ref = sl.solve_triangular(np.linalg.cholesky(F @ F.T + 1e-2 * np.eye(r)), F, lower=True)
     assert np.linalg.norm(E - ref) <= 1e-11 * np.linalg.norm(ref)
+
+
+def _fp64_err(th, X, V, Z=None):
+    from paper_2109_09817_amd import gp
+    got = host(gp.kmm(_gk(th), dev(X), dev(V), Z=None if Z is None else dev(Z), precision="fp64"))
+    mm = (lambda W: ok.khat_matmul(X, th, W.T).T) if Z is None else (lambda W: ok.cross_matmul(Z, X, th, W.T).T)
+    return got, float(np.max(np.abs(got - mm(V)) / mm(np.abs(V))))
+
+
+@pytest.mark.parametrize("kind", [ok.MATERN52, ok.RBF])
+@pytest.mark.parametrize("n,d,t", [(100, 5, 4), (257, 16, 5), (800, 17, 17), (513, 33, 36), (600, 48, 52),
+                                   (1000, 48, 63), (777, 64, 68), (320, 20, 515)])
+def test_fp64_product_column_remainders_and_splits(n, d, t, kind):
+    """Columns beyond a 16-wide block on the vector units (1 to 4) or in a padded block, one split and several,
+    two column passes (t = 515).  Bar as for the other FP64 products: 1e-13 of |K| |V|."""
+    rng = np.random.default_rng(n + t)
+    X, V = rng.standard_normal((n, d)), rng.standard_normal((t, n))
+    th = ok.Theta(rng.uniform(1.0, 2.0, d) * np.sqrt(d), 1.2, 1e-3, kind)
+    assert _fp64_err(th, X, V)[1] <= 1e-13
+
+
+def test_fp64_cross_product_in_row_slabs_and_row_independence():
+    """m = 8,300 rows of 200 columns exceed one slab (4,480 rows) of partial sums; a row's result is bitwise that of a
+    call with that row alone (the split of the b range depends on n only)."""
+    from paper_2109_09817_amd import gp
+    n, d, t, m = 3000, 8, 200, 8300
+    rng = np.random.default_rng(2)
+    X, V, Z = rng.standard_normal((n, d)), rng.standard_normal((t, n)), rng.standard_normal((m, d))
+    th = ok.Theta(rng.uniform(2.0, 4.0, d), 1.0, 0.0, ok.MATERN52)
+    got, err = _fp64_err(th, X, V, Z)
+    assert err <= 1e-13
+    for r in (0, 4479, 4480, 8299):
+        one = host(gp.kmm(_gk(th), dev(X), dev(V), Z=dev(Z[r:r + 1]), precision="fp64"))
+        np.testing.assert_array_equal(one[:, 0], got[:, r])
+
+
+def test_fp64_product_without_a_workspace_matches_bitwise():
+    import torch
+    from paper_2109_09817_amd import gp
+    n, d, t = 5000, 48, 16
+    rng = np.random.default_rng(4)
+    X, V = dev(rng.standard_normal((n, d))), dev(rng.standard_normal((t, n)))
+    k = gp.Kernel(rng.uniform(5.0, 9.0, d), 1.0, 1e-4)
+    out = torch.empty_like(V)
+    gp.kmm_noalloc(k, X, V, out, precision="fp64")
+    np.testing.assert_array_equal(host(out), host(gp.kmm(k, X, V, precision="fp64")))
