@@ -34,8 +34,6 @@
 namespace gpk {
 
 constexpr int kNysTile = 32;   // landmarks per workgroup of the column kernel
-constexpr int kTallK = 32;     // K rows of C staged per step of the tall product
-constexpr int kTallMaxS = 64;  // columns of the tall product
 constexpr int kNysMaxR = 1024;
 constexpr double kNysRcond = 1e-7;  // K_MM eigenvalues kept: lam > kNysRcond * lam_max
 
@@ -92,85 +90,24 @@ __global__ void gather_landmark_rows_kernel(const double* __restrict__ KXM, int6
   out[e] = KXM[j * n + M[i]];
 }
 
-// Y = alpha V + A C for A (nrows x kk, column-major, lda), C (kk x s, row-major
-// with row stride ldc), V and Y (nrows x s): column-major with ldv / ldy, or
-// (ROWMAJOR) row-major with s per row.  One thread per row; each thread reads all of its row of A before
-// writing its row of Y, so Y may alias A or V.
-template <bool ROWMAJOR>
-__global__ __launch_bounds__(256) void tall_product_kernel(const double* __restrict__ A, int64_t lda,
-                                                           int64_t nrows, int kk, const double* __restrict__ C,
-                                                           int64_t ldc, int s, double alpha, const double* V, int64_t ldv,
-                                                           double* Y, int64_t ldy) {
-  __shared__ double Cs[kTallK][kTallMaxS];
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  double acc[kTallMaxS];
-#pragma unroll
-  for (int c = 0; c < kTallMaxS; ++c) acc[c] = 0.0;
-  for (int k0 = 0; k0 < kk; k0 += kTallK) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < kTallK * kTallMaxS; e += blockDim.x) {
-      const int k = e / kTallMaxS, c = e - k * kTallMaxS;
-      Cs[k][c] = (k0 + k < kk && c < s) ? C[(int64_t)(k0 + k) * ldc + c] : 0.0;
-    }
-    __syncthreads();
-    if (p < nrows) {
-      const int kn = kk - k0 < kTallK ? kk - k0 : kTallK;
-      for (int k = 0; k < kn; ++k) {
-        const double a = A[(int64_t)(k0 + k) * lda + p];
-#pragma unroll
-        for (int c = 0; c < kTallMaxS; ++c) acc[c] = fma(a, Cs[k][c], acc[c]);
-      }
-    }
-  }
-  if (p >= nrows) return;
-#pragma unroll
-  for (int c = 0; c < kTallMaxS; ++c) {
-    if (c < s) {
-      double y = acc[c];
-      if (V) y += alpha * (ROWMAJOR ? V[p * s + c] : V[(int64_t)c * ldv + p]);
-      if (ROWMAJOR)
-        Y[p * s + c] = y;
-      else
-        Y[(int64_t)c * ldy + p] = y;
-    }
-  }
-}
-
-static hipError_t tall_product(const double* A, int64_t lda, int64_t nrows, int kk, const double* C, int64_t ldc,
-                               int s, double alpha, const double* V, int64_t ldv, double* Y, int64_t ldy,
-                               bool rowmajor, hipStream_t st) {
-  const unsigned grid = (unsigned)((nrows + 255) / 256);
-  if (rowmajor)
-    tall_product_kernel<true><<<grid, 256, 0, st>>>(A, lda, nrows, kk, C, ldc, s, alpha, V, ldv, Y, ldy);
-  else
-    tall_product_kernel<false><<<grid, 256, 0, st>>>(A, lda, nrows, kk, C, ldc, s, alpha, V, ldv, Y, ldy);
-  return hipGetLastError();
-}
-
 // Y = A C for C (kk x m row-major) with any m: column blocks of kTallMaxS.
 // A (nrows x kk) and Y (nrows x m) column-major with ld nrows.
 static hipError_t tall_product_wide(const double* A, int64_t nrows, int kk, const double* C, int m, double* Y,
                                     hipStream_t st) {
   for (int c0 = 0; c0 < m; c0 += kTallMaxS) {
     const int sc = std::min(kTallMaxS, m - c0);
-    hipError_t e = tall_product(A, nrows, nrows, kk, C + c0, m, sc, 0.0, nullptr, 0, Y + (int64_t)c0 * nrows,
-                                nrows, false, st);
+    hipError_t e = tall_product(A, nrows, nrows, kk, C + c0, m, sc, 1.0, 1.0, nullptr, 0, Y + (int64_t)c0 * nrows,
+                                nrows, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-// out[e] = a in[e] for e < count.
-__global__ void tall_scale_kernel(const double* __restrict__ in, int64_t count, double a, double* __restrict__ out) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < count) out[e] = a * in[e];
-}
-
-// out[e] = g[e / s] in[e] for e < r s (rows of an r x s row-major block).
-__global__ void scale_rows_kernel(const double* __restrict__ in, const double* __restrict__ g, int r, int s,
+// out[e] = a g[e / s] in[e] for e < r s (rows of an r x s row-major block).
+__global__ void scale_rows_kernel(const double* __restrict__ in, const double* __restrict__ g, int r, int s, double a,
                                   double* __restrict__ out) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < r * s) out[e] = g[e / s] * in[e];
+  if (e < r * s) out[e] = a * g[e / s] * in[e];
 }
 
 // A^T B with the row split sized to the output: ~2048 workgroups whatever pa, qb.
@@ -297,9 +234,10 @@ static hipError_t nystrom_apply(const double* Zt, const double* g, int64_t n, in
   hipError_t e;
   if (ldv != n) return hipErrorInvalidValue;  // gram() takes ld = n
   if ((e = gram(Zt, r, V, s, n, C1, part, st)) != hipSuccess) return e;
-  scale_rows_kernel<<<(unsigned)((r * s + 255) / 256), 256, 0, st>>>(C1, g, r, s, C2);
+  const double sigma = std::sqrt(noise);  // Y = sigma^{-1} (V + Z^T (sigma g C1))
+  scale_rows_kernel<<<(unsigned)((r * s + 255) / 256), 256, 0, st>>>(C1, g, r, s, sigma, C2);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  return tall_product(Zt, n, n, r, C2, s, s, 1.0 / std::sqrt(noise), V, ldv, Y, ldy, false, st);
+  return tall_product(Zt, n, n, r, C2, s, s, 1.0, 1.0 / sigma, V, ldv, Y, ldy, st);
 }
 
 // ---------------------------------------------------------------- block CG
@@ -394,7 +332,7 @@ int run_bcg(const gp_kernel* kern, int precision, const double* X, int64_t n, co
   GPK_HIP(kmm_prepare(plan, kern, X, nullptr, st));
   // host s x s blocks; each stays untouched until the stream synchronisation that
   // follows its upload
-  std::vector<double> RtR, RtRn, DtQ, alpha, nalpha, beta;
+  std::vector<double> RtR, RtRn, DtQ, alpha, beta;
   GPK_HIP(gram_host(R, R, RtR));
   std::vector<double> bnorm(s);
   for (int c = 0; c < s; ++c) {
@@ -412,12 +350,9 @@ int run_bcg(const gp_kernel* kern, int precision, const double* X, int64_t n, co
     GPK_HIP(gram_host(D, Q, DtQ));
     if (!host_lu_solve(DtQ, s, RtR, alpha))
       return fail(GP_ENOTPD, "gp_bcg: D^T A D singular at iteration %d (block breakdown)", it);
-    nalpha = alpha;
-    for (auto& v : nalpha) v = -v;
     GPK_HIP(hipMemcpyAsync(Ad, alpha.data(), sizeof(double) * s * s, hipMemcpyHostToDevice, st));
-    GPK_HIP(hipMemcpyAsync(Bd, nalpha.data(), sizeof(double) * s * s, hipMemcpyHostToDevice, st));
-    GPK_HIP(tall_product(D, n, n, s, Ad, s, s, 1.0, Z, n, Z, n, false, st));   // Z += D alpha
-    GPK_HIP(tall_product(Q, n, n, s, Bd, s, s, 1.0, R, n, R, n, false, st));   // R -= Q alpha
+    GPK_HIP(tall_product(D, n, n, s, Ad, s, s, 1.0, 1.0, Z, n, Z, n, st));   // Z += D alpha
+    GPK_HIP(tall_product(Q, n, n, s, Ad, s, s, -1.0, 1.0, R, n, R, n, st));   // R -= Q alpha
     GPK_HIP(gram_host(R, R, RtRn));  // also orders the uploads above before alpha is rewritten
     ++it;
     bool all = true;
@@ -434,7 +369,7 @@ int run_bcg(const gp_kernel* kern, int precision, const double* X, int64_t n, co
     if (!host_lu_solve(RtR, s, RtRn, beta))
       return fail(GP_ENOTPD, "gp_bcg: R^T R singular at iteration %d (block breakdown)", it);
     GPK_HIP(hipMemcpyAsync(Bd, beta.data(), sizeof(double) * s * s, hipMemcpyHostToDevice, st));
-    GPK_HIP(tall_product(D, n, n, s, Bd, s, s, 1.0, R, n, D, n, false, st));   // D = R + D beta
+    GPK_HIP(tall_product(D, n, n, s, Bd, s, s, 1.0, 1.0, R, n, D, n, st));   // D = R + D beta
     RtR.swap(RtRn);
     GPK_HIP(hipStreamSynchronize(st));  // beta's upload completes before the host vector is reused
   }
@@ -569,20 +504,16 @@ int run_nystrom_chol(const gp_kernel* kern, const double* X, int64_t n, const in
 
 // Y = P^{-1} V = sigma^{-2} (V - E (E^T V)) for an n x s block (ld n); Y may alias V.
 static hipError_t nystrom_chol_apply(const double* E, int64_t n, int r, double noise, const double* V, int s,
-                                     double* Y, double* C1, double* C2, double* part, hipStream_t st) {
+                                     double* Y, double* C1, double* part, hipStream_t st) {
   hipError_t e;
   if ((e = gram(E, r, V, s, n, C1, part, st)) != hipSuccess) return e;
-  const double inv = 1.0 / noise;
-  // C2 = -sigma^{-2} C1
-  tall_scale_kernel<<<(unsigned)(((int64_t)r * s + 255) / 256), 256, 0, st>>>(C1, (int64_t)r * s, -inv, C2);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  return tall_product(E, n, n, r, C2, s, s, inv, V, n, Y, n, false, st);
+  return tall_product(E, n, n, r, C1, s, s, -1.0, 1.0 / noise, V, n, Y, n, st);
 }
 
 size_t bpcg_ws_bytes(int precision, int d, int64_t n, int r, int s) {
   size_t b = kmm_plan_bytes(precision, d, n, n, true, s);
   b += 5 * align256((size_t)n * s * 8);                              // U, R, Z, D, Q
-  b += 2 * align256((size_t)std::max(r, 1) * s * 8);                 // E^T V and its scaled copy
+  b += align256((size_t)std::max(r, 1) * s * 8);                     // E^T V
   b += align256(std::max(gram_partial_doubles(n, std::max(r, 1), s), gram_partial_doubles(n, s, s)) * 8);
   b += 3 * align256((size_t)s * s * 8);                              // Gram out, alpha, beta
   return b + 4096;
@@ -603,14 +534,13 @@ int run_bpcg(const gp_kernel* kern, int precision, const double* X, int64_t n, c
   double* D = cv.take<double>(ns);
   double* Q = cv.take<double>(ns);
   double* C1 = cv.take<double>((size_t)std::max(r, 1) * s);
-  double* C2 = cv.take<double>((size_t)std::max(r, 1) * s);
   double* part = cv.take<double>(std::max(gram_partial_doubles(n, std::max(r, 1), s), gram_partial_doubles(n, s, s)));
   double* Gd = cv.take<double>((size_t)s * s);
   double* Ad = cv.take<double>((size_t)s * s);
   double* Bd = cv.take<double>((size_t)s * s);
   if (!Bd) return fail(GP_EWORKSPACE, "gp_bpcg: workspace layout failed");
   auto precond = [&](const double* in, double* out) -> hipError_t {
-    if (r > 0) return nystrom_chol_apply(E, n, r, kern->noise, in, s, out, C1, C2, part, st);
+    if (r > 0) return nystrom_chol_apply(E, n, r, kern->noise, in, s, out, C1, part, st);
     return hipMemcpyAsync(out, in, sizeof(double) * ns, hipMemcpyDeviceToDevice, st);
   };
   auto gram_host = [&](const double* A, const double* Bm, std::vector<double>& out) -> hipError_t {
@@ -628,7 +558,7 @@ int run_bpcg(const gp_kernel* kern, int precision, const double* X, int64_t n, c
   GPK_HIP(hipMemcpyAsync(D, Zb, sizeof(double) * ns, hipMemcpyDeviceToDevice, st));
   GPK_HIP(launch_fill(U, 0.0, (int64_t)ns, st));
   GPK_HIP(kmm_prepare(plan, kern, X, nullptr, st));
-  std::vector<double> RtZ, RtZn, DtQ, alpha, nalpha, beta;
+  std::vector<double> RtZ, RtZn, DtQ, alpha, beta;
   GPK_HIP(gram_host(R, Zb, RtZ));
   std::vector<double> bnorm(s);
   for (int c = 0; c < s; ++c) {
@@ -644,12 +574,9 @@ int run_bpcg(const gp_kernel* kern, int precision, const double* X, int64_t n, c
     GPK_HIP(gram_host(D, Q, DtQ));
     if (!host_lu_solve(DtQ, s, RtZ, alpha))
       return fail(GP_ENOTPD, "gp_bpcg: D^T K_hat D singular at iteration %d (block breakdown)", it);
-    nalpha = alpha;
-    for (auto& v : nalpha) v = -v;
     GPK_HIP(hipMemcpyAsync(Ad, alpha.data(), sizeof(double) * s * s, hipMemcpyHostToDevice, st));
-    GPK_HIP(hipMemcpyAsync(Bd, nalpha.data(), sizeof(double) * s * s, hipMemcpyHostToDevice, st));
-    GPK_HIP(tall_product(D, n, n, s, Ad, s, s, 1.0, U, n, U, n, false, st));   // U += D alpha
-    GPK_HIP(tall_product(Q, n, n, s, Bd, s, s, 1.0, R, n, R, n, false, st));   // R -= Q alpha
+    GPK_HIP(tall_product(D, n, n, s, Ad, s, s, 1.0, 1.0, U, n, U, n, st));   // U += D alpha
+    GPK_HIP(tall_product(Q, n, n, s, Ad, s, s, -1.0, 1.0, R, n, R, n, st));   // R -= Q alpha
     GPK_HIP(precond(R, Zb));
     GPK_HIP(gram_host(R, Zb, RtZn));  // also orders the uploads above before alpha is rewritten
     ++it;
@@ -667,7 +594,7 @@ int run_bpcg(const gp_kernel* kern, int precision, const double* X, int64_t n, c
     if (!host_lu_solve(RtZ, s, RtZn, beta))
       return fail(GP_ENOTPD, "gp_bpcg: R^T P^{-1} R singular at iteration %d (block breakdown)", it);
     GPK_HIP(hipMemcpyAsync(Bd, beta.data(), sizeof(double) * s * s, hipMemcpyHostToDevice, st));
-    GPK_HIP(tall_product(D, n, n, s, Bd, s, s, 1.0, Zb, n, D, n, false, st));   // D = Z + D beta
+    GPK_HIP(tall_product(D, n, n, s, Bd, s, s, 1.0, 1.0, Zb, n, D, n, st));   // D = Z + D beta
     RtZ.swap(RtZn);
     GPK_HIP(hipStreamSynchronize(st));  // beta's upload completes before the host vector is reused
   }

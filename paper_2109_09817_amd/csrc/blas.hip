@@ -165,78 +165,223 @@ __global__ void mbcg_init_kernel(MbcgState st) {
 
 // -------------------------------------------------------- tall-skinny products
 
+// Both products run on the FP64 matrix cores (v_mfma_f64_16x16x4: lane l supplies
+// A(l % 16, k = l / 16) and B(k = l / 16, l % 16), and holds D(l / 16 + 4 i, l % 16)),
+// straight from global memory: every element of the tall matrix is used by one
+// wave only, so LDS staging would buy nothing.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
+
 // partial[blk][p][q] of G = A^T B over this block's rows, A (n x pa), B (n x qb),
-// both column-major with ld n.  grid = (nblk, ceil(pa/64), ceil(qb/(4 MQ))),
-// 256 threads, 64-row tiles staged in LDS; each thread owns MQ outputs
-// (q = q0 + tid / 64 + 4 m, m < MQ), so a narrow B carries no idle columns.
-template <int MQ>
+// both column-major with ld n.  grid = (nblk, ceil(pa / 32), ceil(qb / (16 NQ))).
+// A workgroup takes 32 columns of A and 16 NQ of B; its four waves take a quarter
+// of the rows each, in 16-row chunks, and meet in LDS.  The contraction index is free to permute,
+// so lane (x, g) loads four consecutive rows 4 g .. 4 g + 3 of column x (32 bytes;
+// 128-byte runs per column) and MFMA i contracts rows 4 g + i.
+// Bound by HBM for narrow B (8,192 x 1,024 against 50 columns: the matrix cores,
+// 14 us).  8,192 x 1,024 against 50 columns: 21 us (57 us in 64 x 64 LDS tiles with
+// one FMA per LDS read); 65,536 x 100 against 16: 14 us (28 us).
+template <int NQ>
 __global__ void __launch_bounds__(256) atb_partial_kernel(const double* __restrict__ A, int pa,
                                                           const double* __restrict__ B, int qb, int64_t n,
                                                           int64_t rows_per_blk, double* __restrict__ partial) {
-  __shared__ double As[64][65];
-  __shared__ double Bs[4 * MQ][65];
-  const int p0 = blockIdx.y * 64, q0 = blockIdx.z * (4 * MQ);
-  const int tid = threadIdx.x;
-  const int pl = tid & 63;        // this thread's p (local)
-  const int qg = tid >> 6;        // q = q0 + qg + 4 m, m = 0..MQ-1
-  double acc[MQ];
-#pragma unroll
-  for (int m = 0; m < MQ; ++m) acc[m] = 0.0;
+  constexpr int NP = 2;
+  __shared__ double red[3][16 * NP][16 * NQ + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lx = lane & 15, lg = lane >> 4;
+  const int p0 = blockIdx.y * 16 * NP, q0 = blockIdx.z * 16 * NQ;
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_blk;
   const int64_t r1 = r0 + rows_per_blk < n ? r0 + rows_per_blk : n;
-  for (int64_t t0 = r0; t0 < r1; t0 += 64) {
-    // stage A[t0..t0+63][p0..p0+63] and B likewise (zero outside): this thread
-    // stages row t0 + tid % 64 of columns tid / 64 + 4 u, all 32 loads issued
-    // before the first store (indexes clamped into the matrices)
-    const int r = tid & 63;
-    const int64_t row = t0 + r;
-    const int64_t rowc = row < n ? row : n - 1;
-    double av[16], bv[MQ];
+  const double* Ac[NP];
+  const double* Bc[NQ];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int col = (tid >> 6) + 4 * u;
-      av[u] = A[(int64_t)(p0 + col < pa ? p0 + col : pa - 1) * n + rowc];
-      if (u < MQ) bv[u] = B[(int64_t)(q0 + col < qb ? q0 + col : qb - 1) * n + rowc];
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int col = (tid >> 6) + 4 * u;
-      As[col][r] = (row < r1 && p0 + col < pa) ? av[u] : 0.0;
-      if (u < MQ) Bs[col][r] = (row < r1 && q0 + col < qb) ? bv[u] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int r = 0; r < 64; ++r) {
-      const double av = As[pl][r];
-#pragma unroll
-      for (int m = 0; m < MQ; ++m) acc[m] += av * Bs[qg + 4 * m][r];
-    }
-    __syncthreads();
+  for (int f = 0; f < NP; ++f) {  // columns beyond the matrices repeat the last one and are not stored
+    const int c = p0 + 16 * f + lx;
+    Ac[f] = A + (int64_t)(c < pa ? c : pa - 1) * n;
   }
+#pragma unroll
+  for (int f = 0; f < NQ; ++f) {
+    const int c = q0 + 16 * f + lx;
+    Bc[f] = B + (int64_t)(c < qb ? c : qb - 1) * n;
+  }
+  f64x4 acc[NP][NQ];
+#pragma unroll
+  for (int f = 0; f < NP; ++f)
+#pragma unroll
+    for (int h = 0; h < NQ; ++h) acc[f][h] = f64x4{0.0, 0.0, 0.0, 0.0};
+  auto load = [&](const double* P, int64_t row, double (&v)[4]) {
+    if (row + 4 <= r1) {
+      const f64x2u x = *(const f64x2u*)(P + row), y = *(const f64x2u*)(P + row + 2);
+      v[0] = x[0];
+      v[1] = x[1];
+      v[2] = y[0];
+      v[3] = y[1];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = row + i < r1 ? P[row + i] : 0.0;
+    }
+  };
+  const int64_t wq = (rows_per_blk / 4 + 15) / 16 * 16;  // this wave's quarter of the block's rows
+  const int64_t w1 = r0 + (wave + 1) * wq < r1 ? r0 + (wave + 1) * wq : r1;
+  for (int64_t t0 = r0 + wave * wq; t0 < w1; t0 += 16) {
+    double av[NP][4], bv[NQ][4];
+#pragma unroll
+    for (int f = 0; f < NP; ++f) load(Ac[f], t0 + 4 * lg, av[f]);
+#pragma unroll
+    for (int h = 0; h < NQ; ++h) load(Bc[h], t0 + 4 * lg, bv[h]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int f = 0; f < NP; ++f)
+#pragma unroll
+        for (int h = 0; h < NQ; ++h)
+          acc[f][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[f][i], bv[h][i], acc[f][h], 0, 0, 0);
+  }
+  if (wave > 0) {
+#pragma unroll
+    for (int f = 0; f < NP; ++f)
+#pragma unroll
+      for (int h = 0; h < NQ; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[wave - 1][16 * f + lg + 4 * i][16 * h + lx] = acc[f][h][i];
+  }
+  __syncthreads();
+  if (wave > 0) return;
   const int64_t base = (int64_t)blockIdx.x * pa * qb;
 #pragma unroll
-  for (int m = 0; m < MQ; ++m) {
-    const int p = p0 + pl, q = q0 + qg + 4 * m;
-    if (p < pa && q < qb) partial[base + (int64_t)p * qb + q] = acc[m];
+  for (int f = 0; f < NP; ++f)
+#pragma unroll
+    for (int h = 0; h < NQ; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int pl = 16 * f + lg + 4 * i, ql = 16 * h + lx;
+        const double v = ((acc[f][h][i] + red[0][pl][ql]) + red[1][pl][ql]) + red[2][pl][ql];
+        if (p0 + pl < pa && q0 + ql < qb) partial[base + (int64_t)(p0 + pl) * qb + q0 + ql] = v;
+      }
+}
+
+// out[p*qb + q] = sum_blk partial (fixed order): 16 outputs per workgroup, thread
+// slice k of 16 adds blocks k, k + 16, ..., then the slices are added in order.
+__global__ __launch_bounds__(256) void atb_reduce_kernel(const double* __restrict__ partial, int64_t nblk, int64_t pq,
+                                                         double* __restrict__ out) {
+  __shared__ double red[16][17];
+  const int o = threadIdx.x & 15, k = threadIdx.x >> 4;
+  const int64_t e = (int64_t)blockIdx.x * 16 + o;
+  double acc = 0.0;
+  if (e < pq) {
+    int64_t b = k;
+    for (; b + 48 < nblk; b += 64) {  // four loads in flight
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = partial[(b + 16 * u) * pq + e];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc += v[u];
+    }
+    for (; b < nblk; b += 16) acc += partial[b * pq + e];
+  }
+  red[k][o] = acc;
+  __syncthreads();
+  if (k == 0 && e < pq) {
+    double s = red[0][o];
+#pragma unroll
+    for (int u = 1; u < 16; ++u) s += red[u][o];
+    out[e] = s;
   }
 }
 
-// out[p*qb + q] = sum_blk partial (fixed order).  One thread per output.
-__global__ void atb_reduce_kernel(const double* __restrict__ partial, int64_t nblk, int64_t pq,
-                                  double* __restrict__ out) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= pq) return;
-  double acc = 0.0;
-  int64_t b = 0;
-  for (; b + 8 <= nblk; b += 8) {  // eight loads in flight, added in block order
-    double v[8];
+// Y = post (V + sign A C) (V null: post sign A C) for A (nrows x kk, column-major,
+// lda), C (kk x s, row-major with row stride ldc), V and Y (nrows x s,
+// column-major with ldv / ldy), s <= 16 NCB.  A workgroup owns 16 NR rows; its
+// four waves split k into quarters, so that a block of 8,192 rows already gives
+// every SIMD two waves, and meet in LDS.  It reads all of its rows of A and V
+// before it writes Y, so Y may alias A or V.
+// Bound by HBM (A read once) for narrow C, by the matrix cores for wide ones
+// (8,192 x 1,024 times 50 columns: 14 us).  One thread per row with 64
+// accumulators, 32 workgroups at 8,192 rows, took 199 us,
+// this form 14 us on average over the block solver's products; 65,536 x 100 times
+// 16 columns (the Woodbury finish): 92 -> 15 us.
+template <int NR, int NCB>
+__global__ __launch_bounds__(256) void tall_product_kernel(const double* A, int64_t lda, int64_t nrows, int kk,
+                                                           const double* __restrict__ C, int64_t ldc, int s, double sign,
+                                                           double post, const double* V, int64_t ldv, double* Y,
+                                                           int64_t ldy) {
+  constexpr int kRows = 16 * NR, kCols = 16 * NCB;
+  __shared__ double red[4][kCols][kRows + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lx = lane & 15, lg = lane >> 4;
+  const int64_t r0 = (int64_t)blockIdx.x * kRows;
+  const int kq = (kk + 15) / 16 * 4;
+  const int kbeg = wave * kq, kend = kbeg + kq < kk ? kbeg + kq : kk;
+  const double* Ar[NR];
+  const double* Cc[NCB];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = partial[(b + u) * pq + e];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc += v[u];
+  for (int f = 0; f < NR; ++f) {  // rows and columns beyond the matrices repeat the last one and are not stored
+    const int64_t r = r0 + 16 * f + lx;
+    Ar[f] = A + (r < nrows ? r : nrows - 1);
   }
-  for (; b < nblk; ++b) acc += partial[b * pq + e];
-  out[e] = acc;
+#pragma unroll
+  for (int h = 0; h < NCB; ++h) Cc[h] = C + (16 * h + lx < s ? 16 * h + lx : s - 1);
+  f64x4 acc[NR][NCB];
+#pragma unroll
+  for (int f = 0; f < NR; ++f)
+#pragma unroll
+    for (int h = 0; h < NCB; ++h) acc[f][h] = f64x4{0.0, 0.0, 0.0, 0.0};
+  double av[4][NR], cv[4][NCB];
+  auto load = [&](int k) {  // 16 k values: MFMA u takes k + 4 u + lg; beyond kend A is zero
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int kx = k + 4 * u + lg;
+      const int64_t kc = kx < kend ? kx : kend - 1;
+#pragma unroll
+      for (int f = 0; f < NR; ++f) {
+        const double v = Ar[f][kc * lda];
+        av[u][f] = kx < kend ? v : 0.0;
+      }
+#pragma unroll
+      for (int h = 0; h < NCB; ++h) cv[u][h] = Cc[h][kc * ldc];
+    }
+  };
+  if (kbeg < kend) {
+    load(kbeg);
+    for (int k = kbeg; k < kend; k += 16) {
+      double a[4][NR], c[4][NCB];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+#pragma unroll
+        for (int f = 0; f < NR; ++f) a[u][f] = av[u][f];
+#pragma unroll
+        for (int h = 0; h < NCB; ++h) c[u][h] = cv[u][h];
+      }
+      if (k + 16 < kend) load(k + 16);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int f = 0; f < NR; ++f)
+#pragma unroll
+          for (int h = 0; h < NCB; ++h)
+            acc[f][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][f], c[u][h], acc[f][h], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int f = 0; f < NR; ++f)
+#pragma unroll
+    for (int h = 0; h < NCB; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) red[wave][16 * h + lx][16 * f + lg + 4 * i] = acc[f][h][i];
+  constexpr int kPer = kRows * kCols / 256;
+  double v[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int e = (int)threadIdx.x + 256 * u, r = e % kRows, c = e / kRows;
+    v[u] = V && c < s && r0 + r < nrows ? V[(int64_t)c * ldv + r0 + r] : 0.0;
+  }
+  __syncthreads();  // every wave has read its part of A, every thread its part of V
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int e = (int)threadIdx.x + 256 * u, r = e % kRows, c = e / kRows;
+    const double p = ((red[0][c][r] + red[1][c][r]) + red[2][c][r]) + red[3][c][r];
+    if (c < s && r0 + r < nrows) Y[(int64_t)c * ldy + r0 + r] = post * (v[u] + sign * p);
+  }
 }
 
 // Y := C^{-1} Y for the k x s right-hand sides Y (row-major k x s, entry [j*s + c]),
@@ -280,44 +425,6 @@ __global__ void chol_solve_kernel(const double* __restrict__ Lc, int k, double* 
     for (; i < k; ++i) v -= Lc[(int64_t)j * k + i] * Y[(int64_t)i * s + c];
     Y[(int64_t)j * s + c] = v / Lc[(int64_t)j * k + j];
   }
-}
-
-// Z = inv_noise * (R - L Y) for columns [c0, c0 + sc), sc <= SC, Y row-major k x s.
-// One thread per row with SC accumulators; Y staged in LDS in chunks of 64 rows.
-template <int SC>
-__global__ __launch_bounds__(256) void woodbury_finish_kernel(const double* __restrict__ L, int k,
-                                                              const double* __restrict__ Y, int s, int c0, int sc,
-                                                              const double* __restrict__ R, double* __restrict__ Z,
-                                                              int64_t n, double inv_noise) {
-  __shared__ double Ys[64 * SC];
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  double acc[SC];
-#pragma unroll
-  for (int c = 0; c < SC; ++c) acc[c] = 0.0;
-  for (int j0 = 0; j0 < k; j0 += 64) {
-    const int jn = k - j0 < 64 ? k - j0 : 64;
-    __syncthreads();
-    for (int e = threadIdx.x; e < jn * sc; e += blockDim.x) {
-      const int jj = e / sc, c = e - jj * sc;
-      Ys[jj * SC + c] = Y[(int64_t)(j0 + jj) * s + c0 + c];
-    }
-    __syncthreads();
-    if (i < n) {
-      for (int jj = 0; jj < jn; ++jj) {
-        const double l = L[(int64_t)(j0 + jj) * n + i];
-#pragma unroll
-        for (int c = 0; c < SC; ++c)
-          if (c < sc) acc[c] += l * Ys[jj * SC + c];
-      }
-    }
-  }
-  if (i >= n) return;
-#pragma unroll
-  for (int c = 0; c < SC; ++c)
-    if (c < sc) {
-      const int64_t o = (int64_t)(c0 + c) * n + i;
-      Z[o] = inv_noise * (R[o] - acc[c]);
-    }
 }
 
 __global__ void copy_kernel(const double* __restrict__ src, double* __restrict__ dst, int64_t count) {
@@ -574,15 +681,18 @@ hipError_t coldot(const double* A, const double* B, int64_t n, int s, double* ou
 
 static void launch_atb_partial(const double* A, int pa, const double* B, int qb, int64_t n, const RowSplit& rs,
                                double* partial, hipStream_t st) {
-  const unsigned gy = (unsigned)((pa + 63) / 64);
-  if (qb <= 4) {
+  const unsigned gy = (unsigned)((pa + 31) / 32);
+  if (qb <= 16)
     atb_partial_kernel<1><<<dim3((unsigned)rs.nblk, gy, 1), 256, 0, st>>>(A, pa, B, qb, n, rs.rows_per_blk, partial);
-  } else if (qb <= 16) {
-    atb_partial_kernel<4><<<dim3((unsigned)rs.nblk, gy, 1), 256, 0, st>>>(A, pa, B, qb, n, rs.rows_per_blk, partial);
-  } else {
-    atb_partial_kernel<16><<<dim3((unsigned)rs.nblk, gy, (unsigned)((qb + 63) / 64)), 256, 0, st>>>(
+  else if (qb <= 32)
+    atb_partial_kernel<2><<<dim3((unsigned)rs.nblk, gy, 1), 256, 0, st>>>(A, pa, B, qb, n, rs.rows_per_blk, partial);
+  else
+    atb_partial_kernel<4><<<dim3((unsigned)rs.nblk, gy, (unsigned)((qb + 63) / 64)), 256, 0, st>>>(
         A, pa, B, qb, n, rs.rows_per_blk, partial);
-  }
+}
+
+static void launch_atb_reduce(const double* partial, int64_t nblk, int64_t pq, double* out, hipStream_t st) {
+  atb_reduce_kernel<<<blocks_for(pq, 16), 256, 0, st>>>(partial, nblk, pq, out);
 }
 
 size_t atb_partial_doubles(int64_t n, int pa, int qb) {
@@ -595,7 +705,7 @@ hipError_t atb(const double* A, int pa, const double* B, int qb, int64_t n, doub
   const RowSplit rs = row_split(n, kAtbBlocks);
   launch_atb_partial(A, pa, B, qb, n, rs, partial, st);
   const int64_t pq = (int64_t)pa * qb;
-  atb_reduce_kernel<<<blocks_for(pq), kThreads, 0, st>>>(partial, rs.nblk, pq, out);
+  launch_atb_reduce(partial, rs.nblk, pq, out, st);
   return hipGetLastError();
 }
 
@@ -604,7 +714,7 @@ hipError_t atb_n(const double* A, int pa, const double* B, int qb, int64_t n, do
   const RowSplit rs = row_split(n, nblk);
   launch_atb_partial(A, pa, B, qb, n, rs, partial, st);
   const int64_t pq = (int64_t)pa * qb;
-  atb_reduce_kernel<<<blocks_for(pq), kThreads, 0, st>>>(partial, rs.nblk, pq, out);
+  launch_atb_reduce(partial, rs.nblk, pq, out, st);
   return hipGetLastError();
 }
 
@@ -618,16 +728,44 @@ hipError_t precond_apply(const Precond& pc, const double* R, double* Z, int64_t 
   hipError_t e = atb(pc.L, pc.rank, R, s, n, Y, partial, st);
   if (e != hipSuccess) return e;
   chol_solve_kernel<<<blocks_for(s, 64), 64, 0, st>>>(pc.Cchol, pc.rank, Y, s);
-  for (int c0 = 0; c0 < s; c0 += 64) {
-    const int sc = s - c0 < 64 ? s - c0 : 64;
-    const double inv = 1.0 / pc.noise;
-    if (sc <= 16)
-      woodbury_finish_kernel<16><<<blocks_for(n), kThreads, 0, st>>>(pc.L, pc.rank, Y, s, c0, sc, R, Z, n, inv);
-    else if (sc <= 32)
-      woodbury_finish_kernel<32><<<blocks_for(n), kThreads, 0, st>>>(pc.L, pc.rank, Y, s, c0, sc, R, Z, n, inv);
-    else
-      woodbury_finish_kernel<64><<<blocks_for(n), kThreads, 0, st>>>(pc.L, pc.rank, Y, s, c0, sc, R, Z, n, inv);
+  // Z = (R - L Y) / sigma^2
+  for (int c0 = 0; c0 < s; c0 += kTallMaxS) {
+    const int sc = s - c0 < kTallMaxS ? s - c0 : kTallMaxS;
+    e = tall_product(pc.L, n, n, pc.rank, Y + c0, s, sc, -1.0, 1.0 / pc.noise, R + (int64_t)c0 * n, n,
+                     Z + (int64_t)c0 * n, n, st);
+    if (e != hipSuccess) return e;
   }
+  return hipSuccess;
+}
+
+template <int NR>
+static void launch_tall(const double* A, int64_t lda, int64_t nrows, int kk, const double* C, int64_t ldc, int s,
+                        double sign, double post, const double* V, int64_t ldv, double* Y, int64_t ldy,
+                        hipStream_t st) {
+  const unsigned grid = blocks_for(nrows, 16 * NR);
+#define GPK_TALL(NCB) \
+  tall_product_kernel<NR, NCB><<<grid, 256, 0, st>>>(A, lda, nrows, kk, C, ldc, s, sign, post, V, ldv, Y, ldy)
+  switch ((s + 15) / 16) {
+    case 1: GPK_TALL(1); break;
+    case 2: GPK_TALL(2); break;
+    case 3: GPK_TALL(3); break;
+    default: GPK_TALL(4); break;
+  }
+#undef GPK_TALL
+}
+
+// Rows from which a workgroup takes 32 instead of 16: each row of C then serves
+// twice the rows, and there are workgroups enough (2,048) either way.
+constexpr int64_t kTallWideRows = 65536;
+
+hipError_t tall_product(const double* A, int64_t lda, int64_t nrows, int kk, const double* C, int64_t ldc, int s,
+                        double sign, double post, const double* V, int64_t ldv, double* Y, int64_t ldy,
+                        hipStream_t st) {
+  if (s < 1 || s > kTallMaxS || kk < 1) return hipErrorInvalidValue;
+  if (nrows >= kTallWideRows)
+    launch_tall<2>(A, lda, nrows, kk, C, ldc, s, sign, post, V, ldv, Y, ldy, st);
+  else
+    launch_tall<1>(A, lda, nrows, kk, C, ldc, s, sign, post, V, ldv, Y, ldy, st);
   return hipGetLastError();
 }
 

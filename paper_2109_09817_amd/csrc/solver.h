@@ -64,6 +64,13 @@ hipError_t atb(const double* A, int pa, const double* B, int qb, int64_t n, doub
 // atb with the row split into (at most) nblk blocks; partial holds nblk * pa * qb doubles.
 hipError_t atb_n(const double* A, int pa, const double* B, int qb, int64_t n, double* out, double* partial,
                  int64_t nblk, hipStream_t st);
+// Y = post (V + sign A C) for A (nrows x kk, column-major, lda), C (kk x s, row-major
+// with row stride ldc), V (null: 0) and Y (nrows x s, column-major), s <= kTallMaxS.
+// Y may alias A or V.
+constexpr int kTallMaxS = 64;
+hipError_t tall_product(const double* A, int64_t lda, int64_t nrows, int kk, const double* C, int64_t ldc, int s,
+                        double sign, double post, const double* V, int64_t ldv, double* Y, int64_t ldy,
+                        hipStream_t st);
 // Z = P^{-1} R for an n x s block.  Y: rank x s scratch; partial: atb scratch.
 hipError_t precond_apply(const Precond& pc, const double* R, double* Z, int64_t n, int s, double* Y,
                          double* partial, hipStream_t st);

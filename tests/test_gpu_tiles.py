@@ -108,3 +108,29 @@ def test_fp64_product_without_a_workspace_matches_bitwise():
     out = torch.empty_like(V)
     gp.kmm_noalloc(k, X, V, out, precision="fp64")
     np.testing.assert_array_equal(host(out), host(gp.kmm(k, X, V, precision="fp64")))
+
+
+@pytest.mark.parametrize("n,r,s", [(17, 1, 1), (33, 17, 15), (1000, 3, 16), (259, 64, 17), (4097, 65, 33),
+                                   (300, 130, 50), (515, 31, 64), (65549, 20, 50), (66001, 5, 3)])
+def test_tall_products_at_ragged_sizes(n, r, s):
+    """sigma^{-1} V + Z^T diag(g) Z V (both tall-skinny products) on random factors, ragged rows, ranks and columns,
+    16 and 32 rows per workgroup.  Bar: 1e-13 of the sums of magnitudes (two sums of at most n and r terms)."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n + r + s)
+    Z, g, V = rng.standard_normal((r, n)), rng.standard_normal(r), rng.standard_normal((s, n))
+    pc = gp.Nystrom(dev(Z), dev(g), np.arange(r), 0.25)
+    got = host(gp.nystrom_apply(pc, dev(V)))
+    ref = 2.0 * V + ((V @ Z.T) * g) @ Z
+    mag = 2.0 * np.abs(V) + ((np.abs(V) @ np.abs(Z).T) * np.abs(g)) @ np.abs(Z)
+    assert np.max(np.abs(got - ref) / mag) <= 1e-13
+
+
+def test_tall_product_in_place():
+    """Y may be V itself: bitwise the result of the call with a separate output."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(8)
+    Z, g, V = dev(rng.standard_normal((37, 70001))), dev(rng.standard_normal(37)), dev(rng.standard_normal((20, 70001)))
+    pc = gp.Nystrom(Z, g, np.arange(37), 0.25)
+    ref = host(gp.nystrom_apply(pc, V))
+    gp.nystrom_apply(pc, V, out=V)
+    np.testing.assert_array_equal(host(V), ref)
