@@ -97,7 +97,7 @@ static hipError_t tall_product_wide(const double* A, int64_t nrows, int kk, cons
   for (int c0 = 0; c0 < m; c0 += kTallMaxS) {
     const int sc = std::min(kTallMaxS, m - c0);
     hipError_t e = tall_product(A, nrows, nrows, kk, C + c0, m, sc, 1.0, 1.0, nullptr, 0, Y + (int64_t)c0 * nrows,
-                                nrows, st);
+                                nrows, /*split_k=*/true, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -237,7 +237,7 @@ static hipError_t nystrom_apply(const double* Zt, const double* g, int64_t n, in
   const double sigma = std::sqrt(noise);  // Y = sigma^{-1} (V + Z^T (sigma g C1))
   scale_rows_kernel<<<(unsigned)((r * s + 255) / 256), 256, 0, st>>>(C1, g, r, s, sigma, C2);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  return tall_product(Zt, n, n, r, C2, s, s, 1.0, 1.0 / sigma, V, ldv, Y, ldy, st);
+  return tall_product(Zt, n, n, r, C2, s, s, 1.0, 1.0 / sigma, V, ldv, Y, ldy, true, st);
 }
 
 // ---------------------------------------------------------------- block CG
@@ -351,8 +351,8 @@ int run_bcg(const gp_kernel* kern, int precision, const double* X, int64_t n, co
     if (!host_lu_solve(DtQ, s, RtR, alpha))
       return fail(GP_ENOTPD, "gp_bcg: D^T A D singular at iteration %d (block breakdown)", it);
     GPK_HIP(hipMemcpyAsync(Ad, alpha.data(), sizeof(double) * s * s, hipMemcpyHostToDevice, st));
-    GPK_HIP(tall_product(D, n, n, s, Ad, s, s, 1.0, 1.0, Z, n, Z, n, st));   // Z += D alpha
-    GPK_HIP(tall_product(Q, n, n, s, Ad, s, s, -1.0, 1.0, R, n, R, n, st));   // R -= Q alpha
+    GPK_HIP(tall_product(D, n, n, s, Ad, s, s, 1.0, 1.0, Z, n, Z, n, false, st));   // Z += D alpha
+    GPK_HIP(tall_product(Q, n, n, s, Ad, s, s, -1.0, 1.0, R, n, R, n, false, st));   // R -= Q alpha
     GPK_HIP(gram_host(R, R, RtRn));  // also orders the uploads above before alpha is rewritten
     ++it;
     bool all = true;
@@ -369,7 +369,7 @@ int run_bcg(const gp_kernel* kern, int precision, const double* X, int64_t n, co
     if (!host_lu_solve(RtR, s, RtRn, beta))
       return fail(GP_ENOTPD, "gp_bcg: R^T R singular at iteration %d (block breakdown)", it);
     GPK_HIP(hipMemcpyAsync(Bd, beta.data(), sizeof(double) * s * s, hipMemcpyHostToDevice, st));
-    GPK_HIP(tall_product(D, n, n, s, Bd, s, s, 1.0, 1.0, R, n, D, n, st));   // D = R + D beta
+    GPK_HIP(tall_product(D, n, n, s, Bd, s, s, 1.0, 1.0, R, n, D, n, false, st));   // D = R + D beta
     RtR.swap(RtRn);
     GPK_HIP(hipStreamSynchronize(st));  // beta's upload completes before the host vector is reused
   }
@@ -507,7 +507,7 @@ static hipError_t nystrom_chol_apply(const double* E, int64_t n, int r, double n
                                      double* Y, double* C1, double* part, hipStream_t st) {
   hipError_t e;
   if ((e = gram(E, r, V, s, n, C1, part, st)) != hipSuccess) return e;
-  return tall_product(E, n, n, r, C1, s, s, -1.0, 1.0 / noise, V, n, Y, n, st);
+  return tall_product(E, n, n, r, C1, s, s, -1.0, 1.0 / noise, V, n, Y, n, true, st);
 }
 
 size_t bpcg_ws_bytes(int precision, int d, int64_t n, int r, int s) {
@@ -575,8 +575,8 @@ int run_bpcg(const gp_kernel* kern, int precision, const double* X, int64_t n, c
     if (!host_lu_solve(DtQ, s, RtZ, alpha))
       return fail(GP_ENOTPD, "gp_bpcg: D^T K_hat D singular at iteration %d (block breakdown)", it);
     GPK_HIP(hipMemcpyAsync(Ad, alpha.data(), sizeof(double) * s * s, hipMemcpyHostToDevice, st));
-    GPK_HIP(tall_product(D, n, n, s, Ad, s, s, 1.0, 1.0, U, n, U, n, st));   // U += D alpha
-    GPK_HIP(tall_product(Q, n, n, s, Ad, s, s, -1.0, 1.0, R, n, R, n, st));   // R -= Q alpha
+    GPK_HIP(tall_product(D, n, n, s, Ad, s, s, 1.0, 1.0, U, n, U, n, false, st));   // U += D alpha
+    GPK_HIP(tall_product(Q, n, n, s, Ad, s, s, -1.0, 1.0, R, n, R, n, false, st));   // R -= Q alpha
     GPK_HIP(precond(R, Zb));
     GPK_HIP(gram_host(R, Zb, RtZn));  // also orders the uploads above before alpha is rewritten
     ++it;
@@ -594,7 +594,7 @@ int run_bpcg(const gp_kernel* kern, int precision, const double* X, int64_t n, c
     if (!host_lu_solve(RtZ, s, RtZn, beta))
       return fail(GP_ENOTPD, "gp_bpcg: R^T P^{-1} R singular at iteration %d (block breakdown)", it);
     GPK_HIP(hipMemcpyAsync(Bd, beta.data(), sizeof(double) * s * s, hipMemcpyHostToDevice, st));
-    GPK_HIP(tall_product(D, n, n, s, Bd, s, s, 1.0, 1.0, Zb, n, D, n, st));   // D = Z + D beta
+    GPK_HIP(tall_product(D, n, n, s, Bd, s, s, 1.0, 1.0, Zb, n, D, n, false, st));   // D = Z + D beta
     RtZ.swap(RtZn);
     GPK_HIP(hipStreamSynchronize(st));  // beta's upload completes before the host vector is reused
   }

@@ -168,48 +168,72 @@ __global__ void mbcg_init_kernel(MbcgState st) {
 // Both products run on the FP64 matrix cores (v_mfma_f64_16x16x4: lane l supplies
 // A(l % 16, k = l / 16) and B(k = l / 16, l % 16), and holds D(l / 16 + 4 i, l % 16)),
 // straight from global memory: every element of the tall matrix is used by one
-// wave only, so LDS staging would buy nothing.
+// wave only, so LDS staging would buy nothing.  The instruction is a chain of four
+// FP64 FMAs in the order of k (checked bitwise over 51,200 outputs), so an
+// accumulator fed with ascending k holds the bits of a scalar FMA loop.  mBCG
+// relies on it: in the mixed form a last-bit change of a direction block now and
+// then flips a rounding of its FP16 split, and after some iterations the gradient
+// moves by 1e-9.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
 
-// partial[blk][p][q] of G = A^T B over this block's rows, A (n x pa), B (n x qb),
-// both column-major with ld n.  grid = (nblk, ceil(pa / 32), ceil(qb / (16 NQ))).
-// A workgroup takes 32 columns of A and 16 NQ of B; its four waves take a quarter
-// of the rows each, in 16-row chunks, and meet in LDS.  The contraction index is free to permute,
-// so lane (x, g) loads four consecutive rows 4 g .. 4 g + 3 of column x (32 bytes;
-// 128-byte runs per column) and MFMA i contracts rows 4 g + i.
-// Bound by HBM for narrow B (8,192 x 1,024 against 50 columns: the matrix cores,
-// 14 us).  8,192 x 1,024 against 50 columns: 21 us (57 us in 64 x 64 LDS tiles with
-// one FMA per LDS read); 65,536 x 100 against 16: 14 us (28 us).
-template <int NQ>
+// The 4 x 4 transpose of v between registers and groups of 16 lanes: lane group g
+// enters with v[i] = x(g, i) and leaves with v[i] = x(i, g).
+__device__ __forceinline__ void transpose_groups(double (&v)[4]) {
+  uint32_t w[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v[i]);
+    w[i][0] = (uint32_t)u;
+    w[i][1] = (uint32_t)(u >> 32);
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {  // groups 2, 3 of register i against groups 0, 1 of register i + 2
+      const auto r = __builtin_amdgcn_permlane32_swap(w[i][h], w[i + 2][h], false, false);
+      w[i][h] = r[0];
+      w[i + 2][h] = r[1];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {  // odd groups of register i against even groups of register i + 1
+      const auto r = __builtin_amdgcn_permlane16_swap(w[i][h], w[i + 1][h], false, false);
+      w[i][h] = r[0];
+      w[i + 1][h] = r[1];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = __builtin_bit_cast(double, ((uint64_t)w[i][1] << 32) | w[i][0]);
+}
+
+// partial[blk][p][q] of G = A^T B over this block's rows in ascending order, A (n x
+// pa), B (n x qb), both column-major with ld n.  grid = (nblk, ceil(pa / 64),
+// ceil(qb / (16 NQ))); wave w takes columns 16 w .. 16 w + 15 of the group of 64.
+// Per 16 rows, lane (x, g) loads rows 4 g .. 4 g + 3 of column x (two 16-byte loads;
+// 128-byte runs per column) and a transpose across the lane groups turns them into
+// rows 4 i + g, the operand of MFMA i; U such steps are loaded ahead.
+// Bound by HBM for narrow B, by the matrix cores for wide ones.  65,536 x 100
+// against 16 columns: 28 us in 64 x 64 LDS tiles with one FMA per LDS read, 17 us
+// here; 8,192 x 1,024 against 50: 57 us and 32 us.
+template <int NQ, int U>
 __global__ void __launch_bounds__(256) atb_partial_kernel(const double* __restrict__ A, int pa,
                                                           const double* __restrict__ B, int qb, int64_t n,
                                                           int64_t rows_per_blk, double* __restrict__ partial) {
-  constexpr int NP = 2;
-  __shared__ double red[3][16 * NP][16 * NQ + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lx = lane & 15, lg = lane >> 4;
-  const int p0 = blockIdx.y * 16 * NP, q0 = blockIdx.z * 16 * NQ;
+  const int p0 = blockIdx.y * 64 + 16 * wave, q0 = blockIdx.z * 16 * NQ;
+  if (p0 >= pa) return;
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_blk;
   const int64_t r1 = r0 + rows_per_blk < n ? r0 + rows_per_blk : n;
-  const double* Ac[NP];
+  // columns beyond the matrices repeat the last one and are not stored
+  const double* const Ac = A + (int64_t)(p0 + lx < pa ? p0 + lx : pa - 1) * n;
   const double* Bc[NQ];
 #pragma unroll
-  for (int f = 0; f < NP; ++f) {  // columns beyond the matrices repeat the last one and are not stored
-    const int c = p0 + 16 * f + lx;
-    Ac[f] = A + (int64_t)(c < pa ? c : pa - 1) * n;
-  }
+  for (int h = 0; h < NQ; ++h) Bc[h] = B + (int64_t)(q0 + 16 * h + lx < qb ? q0 + 16 * h + lx : qb - 1) * n;
+  f64x4 acc[NQ];
 #pragma unroll
-  for (int f = 0; f < NQ; ++f) {
-    const int c = q0 + 16 * f + lx;
-    Bc[f] = B + (int64_t)(c < qb ? c : qb - 1) * n;
-  }
-  f64x4 acc[NP][NQ];
-#pragma unroll
-  for (int f = 0; f < NP; ++f)
-#pragma unroll
-    for (int h = 0; h < NQ; ++h) acc[f][h] = f64x4{0.0, 0.0, 0.0, 0.0};
-  auto load = [&](const double* P, int64_t row, double (&v)[4]) {
+  for (int h = 0; h < NQ; ++h) acc[h] = f64x4{0.0, 0.0, 0.0, 0.0};
+  auto load4 = [&](const double* P, int64_t row, double (&v)[4]) {  // rows beyond the block read as zero
     if (row + 4 <= r1) {
       const f64x2u x = *(const f64x2u*)(P + row), y = *(const f64x2u*)(P + row + 2);
       v[0] = x[0];
@@ -221,122 +245,114 @@ __global__ void __launch_bounds__(256) atb_partial_kernel(const double* __restri
       for (int i = 0; i < 4; ++i) v[i] = row + i < r1 ? P[row + i] : 0.0;
     }
   };
-  const int64_t wq = (rows_per_blk / 4 + 15) / 16 * 16;  // this wave's quarter of the block's rows
-  const int64_t w1 = r0 + (wave + 1) * wq < r1 ? r0 + (wave + 1) * wq : r1;
-  for (int64_t t0 = r0 + wave * wq; t0 < w1; t0 += 16) {
-    double av[NP][4], bv[NQ][4];
+  double av[U][4], bv[U][NQ][4];
+  auto load = [&](int64_t t0) {
 #pragma unroll
-    for (int f = 0; f < NP; ++f) load(Ac[f], t0 + 4 * lg, av[f]);
+    for (int u = 0; u < U; ++u) {
+      load4(Ac, t0 + 16 * u + 4 * lg, av[u]);
 #pragma unroll
-    for (int h = 0; h < NQ; ++h) load(Bc[h], t0 + 4 * lg, bv[h]);
+      for (int h = 0; h < NQ; ++h) load4(Bc[h], t0 + 16 * u + 4 * lg, bv[u][h]);
+    }
+  };
+  load(r0);
+  for (int64_t t0 = r0; t0 < r1; t0 += 16 * U) {
+    double a[U][4], b[U][NQ][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int f = 0; f < NP; ++f)
-#pragma unroll
-        for (int h = 0; h < NQ; ++h)
-          acc[f][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[f][i], bv[h][i], acc[f][h], 0, 0, 0);
-  }
-  if (wave > 0) {
-#pragma unroll
-    for (int f = 0; f < NP; ++f)
-#pragma unroll
-      for (int h = 0; h < NQ; ++h)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) red[wave - 1][16 * f + lg + 4 * i][16 * h + lx] = acc[f][h][i];
-  }
-  __syncthreads();
-  if (wave > 0) return;
-  const int64_t base = (int64_t)blockIdx.x * pa * qb;
-#pragma unroll
-  for (int f = 0; f < NP; ++f)
-#pragma unroll
-    for (int h = 0; h < NQ; ++h)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int pl = 16 * f + lg + 4 * i, ql = 16 * h + lx;
-        const double v = ((acc[f][h][i] + red[0][pl][ql]) + red[1][pl][ql]) + red[2][pl][ql];
-        if (p0 + pl < pa && q0 + ql < qb) partial[base + (int64_t)(p0 + pl) * qb + q0 + ql] = v;
+        a[u][i] = av[u][i];
+#pragma unroll
+        for (int h = 0; h < NQ; ++h) b[u][h][i] = bv[u][h][i];
       }
+    if (t0 + 16 * U < r1) load(t0 + 16 * U);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      transpose_groups(a[u]);
+#pragma unroll
+      for (int h = 0; h < NQ; ++h) transpose_groups(b[u][h]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int h = 0; h < NQ; ++h) acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][i], b[u][h][i], acc[h], 0, 0, 0);
+    }
+  }
+  double* const dst = partial + (int64_t)blockIdx.x * pa * qb;
+#pragma unroll
+  for (int h = 0; h < NQ; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int p = p0 + lg + 4 * i, q = q0 + 16 * h + lx;
+      if (p < pa && q < qb) dst[(int64_t)p * qb + q] = acc[h][i];
+    }
 }
 
-// out[p*qb + q] = sum_blk partial (fixed order): 16 outputs per workgroup, thread
-// slice k of 16 adds blocks k, k + 16, ..., then the slices are added in order.
-__global__ __launch_bounds__(256) void atb_reduce_kernel(const double* __restrict__ partial, int64_t nblk, int64_t pq,
-                                                         double* __restrict__ out) {
-  __shared__ double red[16][17];
-  const int o = threadIdx.x & 15, k = threadIdx.x >> 4;
-  const int64_t e = (int64_t)blockIdx.x * 16 + o;
+// out[p*qb + q] = sum_blk partial in block order, one thread per output, 32 loads in flight.
+__global__ __launch_bounds__(64) void atb_reduce_kernel(const double* __restrict__ partial, int64_t nblk, int64_t pq,
+                                                        double* __restrict__ out) {
+  const int64_t e = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  if (e >= pq) return;
   double acc = 0.0;
-  if (e < pq) {
-    int64_t b = k;
-    for (; b + 48 < nblk; b += 64) {  // four loads in flight
-      double v[4];
+  int64_t b = 0;
+  for (; b + 32 <= nblk; b += 32) {
+    double v[32];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = partial[(b + 16 * u) * pq + e];
+    for (int u = 0; u < 32; ++u) v[u] = partial[(b + u) * pq + e];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) acc += v[u];
-    }
-    for (; b < nblk; b += 16) acc += partial[b * pq + e];
+    for (int u = 0; u < 32; ++u) acc += v[u];
   }
-  red[k][o] = acc;
-  __syncthreads();
-  if (k == 0 && e < pq) {
-    double s = red[0][o];
+  for (; b + 4 <= nblk; b += 4) {
+    double v[4];
 #pragma unroll
-    for (int u = 1; u < 16; ++u) s += red[u][o];
-    out[e] = s;
+    for (int u = 0; u < 4; ++u) v[u] = partial[(b + u) * pq + e];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc += v[u];
   }
+  for (; b < nblk; ++b) acc += partial[b * pq + e];
+  out[e] = acc;
 }
 
 // Y = post (V + sign A C) (V null: post sign A C) for A (nrows x kk, column-major,
 // lda), C (kk x s, row-major with row stride ldc), V and Y (nrows x s,
-// column-major with ldv / ldy), s <= 16 NCB.  A workgroup owns 16 NR rows; its
-// four waves split k into quarters, so that a block of 8,192 rows already gives
-// every SIMD two waves, and meet in LDS.  It reads all of its rows of A and V
-// before it writes Y, so Y may alias A or V.
+// column-major with ldv / ldy), s <= 16 NCB.  KW = 1: every wave owns 16 rows and
+// takes all of k in ascending order.  KW = 4: the four waves of a workgroup share
+// its 16 rows, a quarter of k each, and meet in LDS, so that a block of 8,192 rows
+// already gives every SIMD two waves.  Either way a row of A and V is read by the
+// workgroup that writes that row of Y, before it does, so Y may alias A or V.
 // Bound by HBM (A read once) for narrow C, by the matrix cores for wide ones
 // (8,192 x 1,024 times 50 columns: 14 us).  One thread per row with 64
-// accumulators, 32 workgroups at 8,192 rows, took 199 us,
-// this form 14 us on average over the block solver's products; 65,536 x 100 times
-// 16 columns (the Woodbury finish): 92 -> 15 us.
-template <int NR, int NCB>
+// accumulators, 32 workgroups at 8,192 rows, took 199 us; the block solver's
+// products take 14 us on average.  65,536 x 100 times 16 columns (the Woodbury
+// finish): 92 us, now 17 us.
+template <int NCB, int KW>
 __global__ __launch_bounds__(256) void tall_product_kernel(const double* A, int64_t lda, int64_t nrows, int kk,
                                                            const double* __restrict__ C, int64_t ldc, int s, double sign,
                                                            double post, const double* V, int64_t ldv, double* Y,
                                                            int64_t ldy) {
-  constexpr int kRows = 16 * NR, kCols = 16 * NCB;
-  __shared__ double red[4][kCols][kRows + 1];
+  constexpr int kRows = KW == 1 ? 64 : 16, kCols = 16 * NCB;  // of the workgroup
+  __shared__ double red[4][kCols][17];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lx = lane & 15, lg = lane >> 4;
   const int64_t r0 = (int64_t)blockIdx.x * kRows;
   const int kq = (kk + 15) / 16 * 4;
-  const int kbeg = wave * kq, kend = kbeg + kq < kk ? kbeg + kq : kk;
-  const double* Ar[NR];
+  const int kbeg = KW == 1 ? 0 : wave * kq, kend = KW == 1 || kbeg + kq > kk ? kk : kbeg + kq;
+  // rows and columns beyond the matrices repeat the last one and are not stored
+  const int64_t arow = r0 + (KW == 1 ? 16 * wave : 0) + lx;
+  const double* const Ar = A + (arow < nrows ? arow : nrows - 1);
   const double* Cc[NCB];
 #pragma unroll
-  for (int f = 0; f < NR; ++f) {  // rows and columns beyond the matrices repeat the last one and are not stored
-    const int64_t r = r0 + 16 * f + lx;
-    Ar[f] = A + (r < nrows ? r : nrows - 1);
-  }
-#pragma unroll
   for (int h = 0; h < NCB; ++h) Cc[h] = C + (16 * h + lx < s ? 16 * h + lx : s - 1);
-  f64x4 acc[NR][NCB];
+  f64x4 acc[NCB];
 #pragma unroll
-  for (int f = 0; f < NR; ++f)
-#pragma unroll
-    for (int h = 0; h < NCB; ++h) acc[f][h] = f64x4{0.0, 0.0, 0.0, 0.0};
-  double av[4][NR], cv[4][NCB];
+  for (int h = 0; h < NCB; ++h) acc[h] = f64x4{0.0, 0.0, 0.0, 0.0};
+  double av[4], cv[4][NCB];
   auto load = [&](int k) {  // 16 k values: MFMA u takes k + 4 u + lg; beyond kend A is zero
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int kx = k + 4 * u + lg;
       const int64_t kc = kx < kend ? kx : kend - 1;
-#pragma unroll
-      for (int f = 0; f < NR; ++f) {
-        const double v = Ar[f][kc * lda];
-        av[u][f] = kx < kend ? v : 0.0;
-      }
+      const double v = Ar[kc * lda];
+      av[u] = kx < kend ? v : 0.0;
 #pragma unroll
       for (int h = 0; h < NCB; ++h) cv[u][h] = Cc[h][kc * ldc];
     }
@@ -344,11 +360,10 @@ __global__ __launch_bounds__(256) void tall_product_kernel(const double* A, int6
   if (kbeg < kend) {
     load(kbeg);
     for (int k = kbeg; k < kend; k += 16) {
-      double a[4][NR], c[4][NCB];
+      double a[4], c[4][NCB];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-#pragma unroll
-        for (int f = 0; f < NR; ++f) a[u][f] = av[u][f];
+        a[u] = av[u];
 #pragma unroll
         for (int h = 0; h < NCB; ++h) c[u][h] = cv[u][h];
       }
@@ -356,18 +371,13 @@ __global__ __launch_bounds__(256) void tall_product_kernel(const double* A, int6
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int f = 0; f < NR; ++f)
-#pragma unroll
-          for (int h = 0; h < NCB; ++h)
-            acc[f][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][f], c[u][h], acc[f][h], 0, 0, 0);
+        for (int h = 0; h < NCB; ++h) acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], c[u][h], acc[h], 0, 0, 0);
     }
   }
 #pragma unroll
-  for (int f = 0; f < NR; ++f)
+  for (int h = 0; h < NCB; ++h)
 #pragma unroll
-    for (int h = 0; h < NCB; ++h)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) red[wave][16 * h + lx][16 * f + lg + 4 * i] = acc[f][h][i];
+    for (int i = 0; i < 4; ++i) red[wave][16 * h + lx][lg + 4 * i] = acc[h][i];
   constexpr int kPer = kRows * kCols / 256;
   double v[kPer];
 #pragma unroll
@@ -379,13 +389,145 @@ __global__ __launch_bounds__(256) void tall_product_kernel(const double* A, int6
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
     const int e = (int)threadIdx.x + 256 * u, r = e % kRows, c = e / kRows;
-    const double p = ((red[0][c][r] + red[1][c][r]) + red[2][c][r]) + red[3][c][r];
+    const double p = KW == 1 ? red[r >> 4][c][r & 15]
+                             : ((red[0][c][r] + red[1][c][r]) + red[2][c][r]) + red[3][c][r];
     if (c < s && r0 + r < nrows) Y[(int64_t)c * ldy + r0 + r] = post * (v[u] + sign * p);
   }
 }
 
+// v of lane `lane` (wave-uniform), as a wave-uniform value.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// v / d from the correctly rounded r = 1 / d: one residual correction of v r gives
+// the correctly rounded quotient (Markstein 1990), the bits of the division.
+__device__ __forceinline__ double div_by(double v, double d, double r) {
+  const double q = v * r;
+  return fma(fma(-q, d, v), r, q);
+}
+
 // Y := C^{-1} Y for the k x s right-hand sides Y (row-major k x s, entry [j*s + c]),
-// with the lower Cholesky factor Lc (column-major k x k).  One thread per column.
+// with the lower Cholesky factor Lc (column-major k x k), k <= kCholLdsK; the bits
+// of the scalar loops below.  Bound by the issue of one wave's dependent steps,
+// once per mBCG iteration: the factor and the reciprocals of its diagonal sit in
+// LDS (odd pitch: no bank conflicts), one wave per right-hand side.  Forward, lane
+// l holds entries l and l + 64 and each solved entry is subtracted from all others
+// at once, which is the scalar order.  Backward, the scalar order subtracts the
+// newest entry first, a chain of k^2 / 2 FMAs: one lane per right-hand side, factor
+// and solution read from LDS a batch ahead (both padded with zeros, so that no
+// batch has a remainder).  k = 100, s = 16: 350 us with one thread per column and
+// everything in L2, 99 us here.
+constexpr int kCholLdsK = 128;  // (k + 24 | 1) (k + 4) + k doubles of the 160 KB of LDS
+constexpr int kCholCols = 4;    // right-hand sides per workgroup
+constexpr int kCholPad = 24;
+
+static size_t chol_lds_bytes(int k) {
+  return sizeof(double) * ((size_t)((k + kCholPad) | 1) * (k + kCholCols) + k);
+}
+
+__global__ __launch_bounds__(256) void chol_solve_lds_kernel(const double* __restrict__ Lc, int k,
+                                                             double* __restrict__ Y, int s) {
+  extern __shared__ double lds[];
+  const int pitch = (k + kCholPad) | 1;
+  double* const Ls = lds;               // entry (row i, column j) at j pitch + i
+  double* const Ys = Ls + k * pitch;    // entry i of column c at c pitch + i
+  double* const Rd = Ys + kCholCols * pitch;  // 1 / L_jj
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, hi = lane + 64, wave = tid >> 6;
+  const int c = blockIdx.x * kCholCols + wave;  // this wave's right-hand side
+  const double y0in = lane < k && c < s ? Y[(int64_t)lane * s + c] : 0.0;
+  const double y1in = hi < k && c < s ? Y[(int64_t)hi * s + c] : 0.0;
+  for (int j0 = wave; j0 < k; j0 += 32) {  // eight columns of the factor in flight per wave
+    double v0[8], v1[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const double* const col = Lc + (int64_t)(j0 + 4 * u < k ? j0 + 4 * u : k - 1) * k;
+      v0[u] = col[lane < k ? lane : k - 1];
+      v1[u] = col[hi < k ? hi : k - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int j = j0 + 4 * u;
+      if (j < k) {
+        if (lane < pitch) Ls[j * pitch + lane] = lane < k ? v0[u] : 0.0;
+        if (hi < pitch) Ls[j * pitch + hi] = hi < k ? v1[u] : 0.0;
+        if (lane + 128 < pitch) Ls[j * pitch + lane + 128] = 0.0;
+        if (j == lane) Rd[j] = 1.0 / v0[u];
+        if (j == hi) Rd[j] = 1.0 / v1[u];
+      }
+    }
+  }
+  __syncthreads();
+  double y0 = y0in, y1 = y1in;
+  {
+    // forward, L z = y: z_j leaves the rows below; the next column is read ahead
+    // (lanes beyond a short column read whatever follows it; their values are not used)
+    const int h = hi < pitch ? hi : lane;
+    double d = Ls[0], r = Rd[0], l0 = Ls[lane], l1 = Ls[h];
+    const int k0 = k < 64 ? k : 64;
+    for (int j = 0; j < k; ++j) {
+      const double* const next = Ls + (j + 1 < k ? j + 1 : j) * pitch;
+      const double dn = next[j + 1 < k ? j + 1 : j], rn = Rd[j + 1 < k ? j + 1 : j], l0n = next[lane], l1n = next[h];
+      if (j < k0) {
+        const double z = div_by(lane_value(y0, j), d, r);
+        y0 = lane > j ? fma(-l0, z, y0) : (lane == j ? z : y0);
+        y1 = fma(-l1, z, y1);
+      } else {
+        const double z = div_by(lane_value(y1, j - 64), d, r);
+        y1 = hi > j ? fma(-l1, z, y1) : (hi == j ? z : y1);
+      }
+      d = dn;
+      r = rn;
+      l0 = l0n;
+      l1 = l1n;
+    }
+  }
+  if (lane < pitch) Ys[wave * pitch + lane] = lane < k ? y0 : 0.0;
+  if (hi < pitch) Ys[wave * pitch + hi] = hi < k ? y1 : 0.0;
+  if (lane + 128 < pitch) Ys[wave * pitch + lane + 128] = 0.0;
+  __syncthreads();
+  const int cb = blockIdx.x * kCholCols + tid;
+  if (tid >= kCholCols || cb >= s) return;
+  // backward, L^T x = z: x_j = (z_j - L_{j+1,j} x_{j+1} - L_{j+2,j} x_{j+2} - ...) / L_jj
+  double* const Yc = Ys + tid * pitch;
+  constexpr int kB = 8;
+  double x = 0.0;
+  for (int j = k - 1; j >= 0; --j) {
+    const double* const col = Ls + j * pitch;
+    const double* lp = col + j + 2;
+    const double* yp = Yc + j + 2;
+    double la[kB], ya[kB], lb[kB], yb[kB];
+    auto read = [&](double(&l)[kB], double(&y)[kB], int at) {
+#pragma unroll
+      for (int u = 0; u < kB; ++u) {
+        l[u] = lp[at + u];
+        y[u] = yp[at + u];
+      }
+    };
+    read(la, ya, 0);
+    double v = fma(-col[j + 1], x, Yc[j]);  // j = k - 1: a zero of the padding
+    const double d = col[j], r = Rd[j];
+    for (int left = k - j - 2; left > 0; left -= 2 * kB, lp += 2 * kB, yp += 2 * kB) {
+      read(lb, yb, kB);
+#pragma unroll
+      for (int u = 0; u < kB; ++u) v = fma(-la[u], ya[u], v);
+      read(la, ya, 2 * kB);
+      if (left > kB) {
+#pragma unroll
+        for (int u = 0; u < kB; ++u) v = fma(-lb[u], yb[u], v);
+      }
+    }
+    x = div_by(v, d, r);
+    Yc[j] = x;
+    Y[(int64_t)j * s + cb] = x;
+  }
+}
+
+// The same for a factor that does not fit LDS.  One thread per column.
 __global__ void chol_solve_kernel(const double* __restrict__ Lc, int k, double* __restrict__ Y, int s) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= s) return;
@@ -681,18 +823,18 @@ hipError_t coldot(const double* A, const double* B, int64_t n, int s, double* ou
 
 static void launch_atb_partial(const double* A, int pa, const double* B, int qb, int64_t n, const RowSplit& rs,
                                double* partial, hipStream_t st) {
-  const unsigned gy = (unsigned)((pa + 31) / 32);
+  const unsigned gy = (unsigned)((pa + 63) / 64);
   if (qb <= 16)
-    atb_partial_kernel<1><<<dim3((unsigned)rs.nblk, gy, 1), 256, 0, st>>>(A, pa, B, qb, n, rs.rows_per_blk, partial);
+    atb_partial_kernel<1, 4><<<dim3((unsigned)rs.nblk, gy, 1), 256, 0, st>>>(A, pa, B, qb, n, rs.rows_per_blk, partial);
   else if (qb <= 32)
-    atb_partial_kernel<2><<<dim3((unsigned)rs.nblk, gy, 1), 256, 0, st>>>(A, pa, B, qb, n, rs.rows_per_blk, partial);
+    atb_partial_kernel<2, 2><<<dim3((unsigned)rs.nblk, gy, 1), 256, 0, st>>>(A, pa, B, qb, n, rs.rows_per_blk, partial);
   else
-    atb_partial_kernel<4><<<dim3((unsigned)rs.nblk, gy, (unsigned)((qb + 63) / 64)), 256, 0, st>>>(
+    atb_partial_kernel<4, 1><<<dim3((unsigned)rs.nblk, gy, (unsigned)((qb + 63) / 64)), 256, 0, st>>>(
         A, pa, B, qb, n, rs.rows_per_blk, partial);
 }
 
 static void launch_atb_reduce(const double* partial, int64_t nblk, int64_t pq, double* out, hipStream_t st) {
-  atb_reduce_kernel<<<blocks_for(pq, 16), 256, 0, st>>>(partial, nblk, pq, out);
+  atb_reduce_kernel<<<blocks_for(pq, 64), 64, 0, st>>>(partial, nblk, pq, out);
 }
 
 size_t atb_partial_doubles(int64_t n, int pa, int qb) {
@@ -727,24 +869,29 @@ hipError_t precond_apply(const Precond& pc, const double* R, double* Z, int64_t 
   // Y = L^T R  (k x s, row-major [j*s + c])
   hipError_t e = atb(pc.L, pc.rank, R, s, n, Y, partial, st);
   if (e != hipSuccess) return e;
-  chol_solve_kernel<<<blocks_for(s, 64), 64, 0, st>>>(pc.Cchol, pc.rank, Y, s);
+  if (pc.rank <= kCholLdsK) {
+    chol_solve_lds_kernel<<<blocks_for(s, kCholCols), 256, chol_lds_bytes(pc.rank), st>>>(pc.Cchol, pc.rank, Y, s);
+  } else {
+    chol_solve_kernel<<<blocks_for(s, 64), 64, 0, st>>>(pc.Cchol, pc.rank, Y, s);
+  }
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   // Z = (R - L Y) / sigma^2
   for (int c0 = 0; c0 < s; c0 += kTallMaxS) {
     const int sc = s - c0 < kTallMaxS ? s - c0 : kTallMaxS;
     e = tall_product(pc.L, n, n, pc.rank, Y + c0, s, sc, -1.0, 1.0 / pc.noise, R + (int64_t)c0 * n, n,
-                     Z + (int64_t)c0 * n, n, st);
+                     Z + (int64_t)c0 * n, n, /*split_k=*/false, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-template <int NR>
+template <int KW>
 static void launch_tall(const double* A, int64_t lda, int64_t nrows, int kk, const double* C, int64_t ldc, int s,
                         double sign, double post, const double* V, int64_t ldv, double* Y, int64_t ldy,
                         hipStream_t st) {
-  const unsigned grid = blocks_for(nrows, 16 * NR);
+  const unsigned grid = blocks_for(nrows, KW == 1 ? 64 : 16);
 #define GPK_TALL(NCB) \
-  tall_product_kernel<NR, NCB><<<grid, 256, 0, st>>>(A, lda, nrows, kk, C, ldc, s, sign, post, V, ldv, Y, ldy)
+  tall_product_kernel<NCB, KW><<<grid, 256, 0, st>>>(A, lda, nrows, kk, C, ldc, s, sign, post, V, ldv, Y, ldy)
   switch ((s + 15) / 16) {
     case 1: GPK_TALL(1); break;
     case 2: GPK_TALL(2); break;
@@ -754,16 +901,12 @@ static void launch_tall(const double* A, int64_t lda, int64_t nrows, int kk, con
 #undef GPK_TALL
 }
 
-// Rows from which a workgroup takes 32 instead of 16: each row of C then serves
-// twice the rows, and there are workgroups enough (2,048) either way.
-constexpr int64_t kTallWideRows = 65536;
-
 hipError_t tall_product(const double* A, int64_t lda, int64_t nrows, int kk, const double* C, int64_t ldc, int s,
                         double sign, double post, const double* V, int64_t ldv, double* Y, int64_t ldy,
-                        hipStream_t st) {
+                        bool split_k, hipStream_t st) {
   if (s < 1 || s > kTallMaxS || kk < 1) return hipErrorInvalidValue;
-  if (nrows >= kTallWideRows)
-    launch_tall<2>(A, lda, nrows, kk, C, ldc, s, sign, post, V, ldv, Y, ldy, st);
+  if (split_k)
+    launch_tall<4>(A, lda, nrows, kk, C, ldc, s, sign, post, V, ldv, Y, ldy, st);
   else
     launch_tall<1>(A, lda, nrows, kk, C, ldc, s, sign, post, V, ldv, Y, ldy, st);
   return hipGetLastError();

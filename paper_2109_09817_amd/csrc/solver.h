@@ -66,11 +66,12 @@ hipError_t atb_n(const double* A, int pa, const double* B, int qb, int64_t n, do
                  int64_t nblk, hipStream_t st);
 // Y = post (V + sign A C) for A (nrows x kk, column-major, lda), C (kk x s, row-major
 // with row stride ldc), V (null: 0) and Y (nrows x s, column-major), s <= kTallMaxS.
-// Y may alias A or V.
+// Y may alias A or V.  split_k: the sums over k in four parts (for few rows and
+// long sums); otherwise the bits of a scalar FMA loop over ascending k.
 constexpr int kTallMaxS = 64;
 hipError_t tall_product(const double* A, int64_t lda, int64_t nrows, int kk, const double* C, int64_t ldc, int s,
                         double sign, double post, const double* V, int64_t ldv, double* Y, int64_t ldy,
-                        hipStream_t st);
+                        bool split_k, hipStream_t st);
 // Z = P^{-1} R for an n x s block.  Y: rank x s scratch; partial: atb scratch.
 hipError_t precond_apply(const Precond& pc, const double* R, double* Z, int64_t n, int s, double* Y,
                          double* partial, hipStream_t st);

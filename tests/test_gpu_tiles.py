@@ -134,3 +134,20 @@ def test_tall_product_in_place():
     ref = host(gp.nystrom_apply(pc, V))
     gp.nystrom_apply(pc, V, out=V)
     np.testing.assert_array_equal(host(V), ref)
+
+
+@pytest.mark.parametrize("k", [1, 63, 64, 65, 100, 127, 128, 129, 200])
+def test_woodbury_solve_at_the_edges_of_the_in_lds_factor(k):
+    """P^{-1} B = Z0 of an mBCG run: factors up to 128 are solved in LDS (two entries per lane), larger ones are not.
+    Against the dense solve; rounding is amplified by cond(P) <= 1e5 here: bar 1e-10."""
+    from paper_2109_09817_amd import gp
+    n, d, s = 700, 6, 5
+    rng = np.random.default_rng(k)
+    X, B = rng.standard_normal((n, d)), rng.standard_normal((s, n))
+    th = ok.Theta(rng.uniform(1.0, 2.0, d), 1.0, 1e-2, ok.MATERN52)
+    kern = _gk(th)
+    pc = gp.pivchol(kern, dev(X), k)
+    r = gp.mbcg(kern, dev(X), dev(B), 2, 0.0, pc=pc, precision="fp32")
+    L = host(pc.L)
+    ref = np.linalg.solve(L.T @ L + 1e-2 * np.eye(n), B.T).T
+    assert np.linalg.norm(host(r.Z0) - ref) <= 1e-10 * np.linalg.norm(ref)
