@@ -241,11 +241,19 @@ __global__ __launch_bounds__(256, 2) void grad_sweep_kernel(GradArgs a) {
   }
 }
 
-__global__ void grad_final_kernel(const double* __restrict__ part, int64_t nparts, int dd, double* __restrict__ out) {
+__global__ __launch_bounds__(256) void grad_final_kernel(const double* __restrict__ part, int64_t nparts, int dd, double* __restrict__ out) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= dd) return;
   double s = 0.0;
-  for (int64_t p = 0; p < nparts; ++p) s += part[p * dd + j];
+  int64_t p = 0;
+  for (; p + 16 <= nparts; p += 16) {  // in order, 16 loads in flight
+    double v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = part[(p + u) * dd + j];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += v[u];
+  }
+  for (; p < nparts; ++p) s += part[p * dd + j];
   out[j] = s;
 }
 
@@ -384,14 +392,23 @@ __global__ __launch_bounds__(64) void grad_group_scale_kernel(const double* __re
 
 // First level of the unit reduction: block b sums units [b kRedUnits, ...) per entry.
 constexpr int kRedUnits = 512;
-__global__ void grad_reduce_units_kernel(const double* __restrict__ part, int64_t nunits, int dd,
+__global__ __launch_bounds__(128) void grad_reduce_units_kernel(const double* __restrict__ part, int64_t nunits, int dd,
                                          double* __restrict__ out) {
   const int j = threadIdx.x;
   if (j >= dd) return;
   const int64_t u0 = (int64_t)blockIdx.x * kRedUnits;
   const int64_t u1 = u0 + kRedUnits < nunits ? u0 + kRedUnits : nunits;
   double s = 0.0;
-  for (int64_t u = u0; u < u1; ++u) s += part[u * dd + j];
+  int64_t u = u0;
+  // in order, 32 loads in flight (one at a time took 127 us at n = 50,001, 10 us now)
+  for (; u + 32 <= u1; u += 32) {
+    double v[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = part[(u + i) * dd + j];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) s += v[i];
+  }
+  for (; u < u1; ++u) s += part[u * dd + j];
   out[(int64_t)blockIdx.x * dd + j] = s;
 }
 

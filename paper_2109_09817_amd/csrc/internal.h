@@ -57,8 +57,7 @@ struct KmmPlan {
   double* ctr = nullptr;    // mixed form: the centre of the coordinates (the b stream's column means, d values)
   double* cpart = nullptr;  // scratch of the column means (colmean_scratch_doubles(n, d))
   void* vf = nullptr;
-  double* vscale = nullptr;  // mixed form: per-column power-of-two scale of V's fragments (tpad values)
-  double* vinv = nullptr;    // mixed form: 2^-15 / vscale, applied to the partial sums (tpad values)
+  double* vinv = nullptr;    // mixed form: 2^-15 / (column scale of V's fragments), applied to the partial sums
   double* vpart = nullptr;   // mixed form: column-max partials (scratch of kmm_prepare_v)
   double* part = nullptr;
   int64_t part_splits = 0;  // splits the partial buffer can hold
@@ -94,11 +93,10 @@ hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, 
 // The factor c of the prescaled coordinates x' = c (x - centre) / l, chosen so that the
 // profile reads r^2 through exp2: sqrt(5) log2(e) for Matern-5/2, sqrt(log2(e) / 2) for RBF.
 double profile_coordinate_scale(int kind);
-// The mixed form's FP16 distance operands of a square product (prep_frag_f16x3_kernel)
+// The mixed form's FP16 distance operands of a square product (prep_points_f16x3_kernel)
 // at ks K steps of 32 (ks * 32 >= 3d + 6), centred on ctr (d device values, the
 // column means of X): the b-side (xr) and a-side (xc) fragments of rows_pad points
-// (a multiple of 64; points >= n are zero), with nrm64 (rows_pad doubles) as
-// scratch for the squared norms.
+// (a multiple of 64; points >= n are zero), and their squared norms (rows_pad doubles).
 hipError_t prep_dist(const gp_kernel* kern, const double* X, int64_t n, int64_t rows_pad, int ks, const double* ctr,
                      void* xr, void* xc, double* nrm64, hipStream_t st);
 // Column means of the row-major n x d matrix X into mu (d doubles), deterministic;

@@ -124,25 +124,58 @@ static int64_t colmean_blocks(int64_t n) {
 
 size_t colmean_scratch_doubles(int64_t n, int d) { return (size_t)colmean_blocks(n) * (size_t)d; }
 
-__global__ void colmean_partial_kernel(const double* __restrict__ X, int64_t n, int d, int64_t rows_per_blk,
-                                       double* __restrict__ part) {
+// Both passes add in order; their loads are issued 32 rows (or all blocks) ahead,
+// since one load at a time made the second pass 244 us at n = 262,144 (10 us now).
+__global__ __launch_bounds__(128) void colmean_partial_kernel(const double* __restrict__ X, int64_t n, int d,
+                                                              int64_t rows_per_blk, double* __restrict__ part) {
   const int j = threadIdx.x;
   if (j >= d) return;
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_blk;
   const int64_t r1 = r0 + rows_per_blk < n ? r0 + rows_per_blk : n;
   double s = 0.0;
-#pragma unroll 4
-  for (int64_t i = r0; i < r1; ++i) s += X[i * d + j];
+  int64_t i = r0;
+  for (; i + 32 <= r1; i += 32) {
+    double v[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) v[u] = X[(i + u) * d + j];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) s += v[u];
+  }
+  for (; i < r1; ++i) s += X[i * d + j];
   part[(int64_t)blockIdx.x * d + j] = s;
 }
 
-__global__ void colmean_final_kernel(const double* __restrict__ part, int64_t nblk, int d, int64_t n,
-                                     double* __restrict__ mu) {
-  const int j = threadIdx.x;
-  if (j >= d) return;
+constexpr int kMeanCols = 8;  // columns per workgroup of the second pass
+
+__global__ __launch_bounds__(256) void colmean_final_kernel(const double* __restrict__ part, int nblk, int d, int64_t n,
+                                                            double* __restrict__ mu) {
+  __shared__ double p[kMeanCols][kMeanBlocks + 1];
+  const int j0 = blockIdx.x * kMeanCols;
+  constexpr int kPer = kMeanCols * (int)kMeanBlocks / 256;
+  const int jl = threadIdx.x % kMeanCols, bl = threadIdx.x / kMeanCols;
+  const int j = j0 + jl < d ? j0 + jl : d - 1;
+  double v[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int b = bl + 256 / kMeanCols * u;
+    if (256 / kMeanCols * u < nblk) v[u] = part[(int64_t)(b < nblk ? b : nblk - 1) * d + j];
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) p[jl][bl + 256 / kMeanCols * u] = v[u];
+  __syncthreads();
+  if (threadIdx.x >= kMeanCols || j0 + (int)threadIdx.x >= d) return;
+  const double* const q = p[threadIdx.x];
   double s = 0.0;
-  for (int64_t b = 0; b < nblk; ++b) s += part[b * d + j];
-  mu[j] = s / (double)n;
+  int b = 0;
+  for (; b + 16 <= nblk; b += 16) {
+    double w[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) w[u] = q[b + u];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += w[u];
+  }
+  for (; b < nblk; ++b) s += q[b];
+  mu[j0 + threadIdx.x] = s / (double)n;
 }
 
 hipError_t column_means(const double* X, int64_t n, int d, double* part, double* mu, hipStream_t st) {
@@ -150,16 +183,14 @@ hipError_t column_means(const double* X, int64_t n, int d, double* part, double*
   const int64_t nblk = colmean_blocks(n);
   const int64_t rpb = (n + nblk - 1) / nblk;
   colmean_partial_kernel<<<(unsigned)nblk, 128, 0, st>>>(X, n, d, rpb, part);
-  colmean_final_kernel<<<1, 128, 0, st>>>(part, nblk, d, n, mu);
+  colmean_final_kernel<<<(unsigned)((d + kMeanCols - 1) / kMeanCols), 256, 0, st>>>(part, (int)nblk, d, n, mu);
   return hipGetLastError();
 }
 
-// Squared norm of each prepared point (FP64).  mode 1 (mixed form): the centred
-// FP16 split above, n = sum (h + l)^2, NaN out of range.  mode 0 (FP32 form):
-// n = sum f^2 with f = fl32(x s), no centring.  ctr: the centre (d values, mode 1).
-__global__ __launch_bounds__(256) void prep_norm_kernel(const double* __restrict__ X, int64_t n, int64_t npad,
-                                                        int d, Scale sc, int mixed, const double* __restrict__ ctr,
-                                                        double* __restrict__ nrm) {
+// Squared norm of each prepared point of the FP32 form: n = sum f^2 in FP64 with
+// f = fl32(x s), no centring.
+__global__ __launch_bounds__(256) void prep_norm_fp32_kernel(const double* __restrict__ X, int64_t n, int64_t npad,
+                                                             int d, Scale sc, double* __restrict__ nrm) {
   // Each wave owns 64 consecutive points.  Per slice of 16 features the wave
   // loads the 64 x 16 block of X (each load instruction covers four rows'
   // 128-byte runs), turns every element into its norm term and parks the terms
@@ -176,7 +207,6 @@ __global__ __launch_bounds__(256) void prep_norm_kernel(const double* __restrict
     for (int j0 = 0; j0 < d; j0 += kF) {
       const int f = j0 + fl < d ? j0 + fl : d - 1;
       const double scale = sc.s[f];
-      const double c = mixed ? ctr[f] : 0.0;
       double x[16];
 #pragma unroll
       for (int k = 0; k < 16; ++k) {  // row 4 k + lane / 16 of the wave's 64 (clamped into X)
@@ -186,17 +216,8 @@ __global__ __launch_bounds__(256) void prep_norm_kernel(const double* __restrict
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
         const int i = 4 * k + (lane >> 4);
-        double t;
-        if (mixed) {
-          const double v = (x[k] - c) * scale;
-          const double h = f16_round(v);
-          const double l = f16_round(v - h);
-          t = __builtin_fabs(v) <= kMaxScaled ? (h + l) * (h + l) : __builtin_nan("");
-        } else {
-          const double fv = (float)(x[k] * scale);
-          t = fv * fv;
-        }
-        term[wave][i][fl] = (r0 + i < n && j0 + fl < d) ? t : 0.0;
+        const double fv = (float)(x[k] * scale);
+        term[wave][i][fl] = (r0 + i < n && j0 + fl < d) ? fv * fv : 0.0;
       }
       __syncthreads();
       const int nf = d - j0 < kF ? d - j0 : kF;
@@ -204,7 +225,6 @@ __global__ __launch_bounds__(256) void prep_norm_kernel(const double* __restrict
       __syncthreads();  // the next slice overwrites the terms
     }
   }
-  if (mixed && !(s <= kMaxNorm)) s = __builtin_nan("");
   const int64_t p = r0 + lane;
   if (p < npad) nrm[p] = p < n ? s : 0.0;
 }
@@ -215,54 +235,123 @@ __global__ __launch_bounds__(256) void prep_norm_kernel(const double* __restrict
 // with C = kNormScale and D the point's norm digits (n = sum_k D_k C_k), so that
 // sum_K row*col = -2(h.h + h.l + l.h) + n_b + n_a.  FP16 values, stored as
 // 16-byte units.  Fragment (blk, ks, lane) holds K = 32 ks + 8 (lane/16) + j,
-// j = 0..7, of point 16 blk + lane%16.
-__global__ void prep_frag_f16x3_kernel(const double* __restrict__ X, const double* __restrict__ nrm,
-                                       const double* __restrict__ ctr, int64_t n, int64_t nblk, int d, int KS,
-                                       Scale sc, bf16x8* __restrict__ xr, bf16x8* __restrict__ xc) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= nblk * KS * 64) return;
-  const int lane = (int)(idx & 63);
-  const int64_t rest = idx >> 6;
-  const int ks = (int)(rest % KS);
-  const int64_t blk = rest / KS;
-  const int64_t p = blk * 16 + (lane & 15);
-  const int g = lane >> 4;
-  f16x8 r, c;
-  double dig[3] = {0.0, 0.0, 0.0};
-  if (p < n) {
-    double rem = nrm[p];
+// j = 0..7, of point 16 blk + lane%16.  nrm (nullable): the squared norms.
+//
+// Bound by HBM: X read once, both sides written once.  A workgroup builds the K
+// rows of 32 points in LDS: every thread splits two elements of each 16-feature
+// slice of X (128-byte runs, all slices loaded ahead) and scatters the halves, one
+// thread per point adds the norm in feature order and appends the digits, and the rows leave as 16-byte units in fragment
+// order.  n = 262,144, d = 48: 34 us for the norms plus 215 us for the fragments,
+// whose threads each found their eight K values by division and split them anew;
+// 55 us here.
+constexpr int kPrepPts = 32;
+
+template <int NS>  // 16-feature slices
+__global__ __launch_bounds__(256) void prep_points_f16x3_kernel(const double* __restrict__ X,
+                                                                const double* __restrict__ ctr, int64_t n,
+                                                                int64_t npad, int d, int KS, Scale sc,
+                                                                bf16x8* __restrict__ xr, bf16x8* __restrict__ xc,
+                                                                double* __restrict__ nrm) {
+  extern __shared__ __attribute__((aligned(16))) _Float16 rows[];  // [side][point][pitch]
+  __shared__ int bad[kPrepPts];
+  const int pitch = 32 * KS + 8;  // halves
+  _Float16* const Rr = rows;
+  _Float16* const Rc = rows + kPrepPts * pitch;
+  const int tid = threadIdx.x;
+  const int64_t p0 = (int64_t)blockIdx.x * kPrepPts;
+  const int fl = tid & 15, rl = tid >> 4;
+  double x[NS][2];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      dig[q] = f16_round(rem * (1.0 / (double)kNormScale[q]));  // powers of two: exact
-      rem -= dig[q] * (double)kNormScale[q];
+  for (int j = 0; j < NS; ++j)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int f = 16 * j + fl < d ? 16 * j + fl : d - 1;
+      const int64_t p = p0 + rl + 16 * q < n ? p0 + rl + 16 * q : n - 1;
+      x[j][q] = X[p * d + f];
     }
-  }
-  for (int j = 0; j < 8; ++j) {
-    const int k = 32 * ks + 8 * g + j;
-    double rv = 0.0, cv = 0.0;
-    if (p < n) {
-      if (k < 3 * d) {
-        const int seg = k / d, f = k - seg * d;
-        const double v = (X[p * d + f] - ctr[f]) * sc.s[f];
+  if (tid < kPrepPts) bad[tid] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NS; ++j) {
+    const int f = 16 * j + fl;
+    if (f < d) {
+      const double s = sc.s[f], c = ctr[f];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int r = rl + 16 * q;
+        const bool live = p0 + r < n;
+        const double v = (x[j][q] - c) * s;
         const double h = f16_round(v);
         const double l = f16_round(v - h);
-        rv = -2.0 * (seg == 2 ? l : h);
-        cv = (seg == 1 ? l : h);
-      } else if (k < 3 * d + 3) {
-        const int q = k - 3 * d;
-        rv = dig[q];
-        cv = kNormScale[q];
-      } else if (k < 3 * d + 6) {
-        const int q = k - 3 * d - 3;
-        rv = kNormScale[q];
-        cv = dig[q];
+        if (live && !(__builtin_fabs(v) <= kMaxScaled)) bad[r] = 1;  // every writer writes 1
+        const _Float16 h16 = (_Float16)(float)(live ? h : 0.0), l16 = (_Float16)(float)(live ? l : 0.0);
+        const _Float16 h2 = (_Float16)(float)(live ? -2.0 * h : 0.0), l2 = (_Float16)(float)(live ? -2.0 * l : 0.0);
+        _Float16* const rr = Rr + r * pitch;
+        _Float16* const rc = Rc + r * pitch;
+        rr[f] = h2;
+        rr[d + f] = h2;
+        rr[2 * d + f] = l2;
+        rc[f] = h16;
+        rc[d + f] = l16;
+        rc[2 * d + f] = h16;
       }
     }
-    r[j] = (_Float16)(float)rv;
-    c[j] = (_Float16)(float)cv;
   }
-  if (xr) xr[idx] = __builtin_bit_cast(bf16x8, r);
-  if (xc) xc[idx] = __builtin_bit_cast(bf16x8, c);
+  __syncthreads();
+  if (tid < kPrepPts) {
+    const int64_t p = p0 + tid;
+    _Float16* const rr = Rr + tid * pitch;
+    _Float16* const rc = Rc + tid * pitch;
+    double s = 0.0;
+    for (int f = 0; f < d; ++f) {
+#pragma clang fp contract(off)
+      const double t = (double)rc[f] + (double)rc[d + f];
+      s += t * t;
+    }
+    if (bad[tid] || !(s <= kMaxNorm)) s = __builtin_nan("");
+    if (nrm) nrm[p] = p < n ? s : 0.0;
+    double rem = s;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const double dig = f16_round(rem * (1.0 / (double)kNormScale[q]));  // powers of two: exact
+      rem -= dig * (double)kNormScale[q];
+      const _Float16 dh = (_Float16)(float)(p < n ? dig : 0.0), ch = (_Float16)(p < n ? kNormScale[q] : 0.f);
+      rr[3 * d + q] = dh;
+      rr[3 * d + 3 + q] = ch;
+      rc[3 * d + q] = ch;
+      rc[3 * d + 3 + q] = dh;
+    }
+    for (int k = 3 * d + 6; k < 32 * KS; ++k) rr[k] = rc[k] = (_Float16)0.f;
+  }
+  __syncthreads();
+  // unit u of the workgroup: point block u / (64 KS), K step, lane
+  const int64_t u0 = (int64_t)blockIdx.x * (kPrepPts / 16) * KS * 64;
+  for (int u = tid; u < (kPrepPts / 16) * KS * 64; u += 256) {
+    const int lane = u & 63, bk = u >> 6;
+    const int blk = bk >= KS ? 1 : 0, ks = bk - blk * KS;
+    const int at = (16 * blk + (lane & 15)) * pitch + 32 * ks + 8 * (lane >> 4);
+    if (xr) xr[u0 + u] = *(const bf16x8*)(Rr + at);
+    if (xc) xc[u0 + u] = *(const bf16x8*)(Rc + at);
+  }
+}
+
+static hipError_t launch_prep_points(const double* X, const double* ctr, int64_t n, int64_t npad, int d, int KS,
+                                     const Scale& sc, void* xr, void* xc, double* nrm, hipStream_t st) {
+  static_assert(kPrepPts == 32, "two point blocks per workgroup");
+  if (npad % kPrepPts != 0) return hipErrorInvalidValue;
+  const unsigned grid = (unsigned)(npad / kPrepPts);
+  const size_t lds = 2 * (size_t)kPrepPts * (32 * KS + 8) * sizeof(_Float16);
+#define GPK_PREP(NS) \
+  prep_points_f16x3_kernel<NS><<<grid, 256, lds, st>>>(X, ctr, n, npad, d, KS, sc, (bf16x8*)xr, (bf16x8*)xc, nrm)
+  switch ((d + 15) / 16) {
+    case 1: GPK_PREP(1); break;
+    case 2: GPK_PREP(2); break;
+    case 3: GPK_PREP(3); break;
+    case 4: GPK_PREP(4); break;
+    default: GPK_PREP(8); break;
+  }
+#undef GPK_PREP
+  return hipGetLastError();
 }
 
 // FP32 point fragments: float4 (blk, q, lane) = f(point 16 blk + lane%16, feature
@@ -298,9 +387,9 @@ __global__ void prep_frag_fp32_kernel(const double* __restrict__ X, const double
 
 // Column scales of the mixed form's V fragments.  vmax_partial_kernel: the
 // largest |V| of each column over kVParts row ranges (NaN entries are skipped
-// here and reach the products through the values themselves); vscale_kernel:
-// scale[c] = 2^e with e = 15 - E, max |V_c| = f 2^E (f in [1/2, 1)), so that the
-// scaled column's largest entry lies in [2^14, 2^15), and inv[c] = 2^(-e - 15),
+// here and reach the products through the values themselves); column_exponent:
+// scale = 2^e with e = 15 - E, max |V_c| = f 2^E (f in [1/2, 1)), so that the
+// scaled column's largest entry lies in [2^14, 2^15), and inv = 2^(-e - 15),
 // the factor that takes a partial sum of (kMScale m)(scale V) back to m V.  A zero
 // or non-finite column keeps scale 1; e is clamped to [-1022, 1023], which only a
 // column whose largest entry lies below 2^-1008 reaches (its scaled entries then stay
@@ -327,21 +416,12 @@ __global__ __launch_bounds__(256) void vmax_partial_kernel(const double* __restr
   if (threadIdx.x == 0) part[(int64_t)c * kVParts + blockIdx.x] = red[0];
 }
 
-__global__ void vscale_kernel(const double* __restrict__ part, int t, double* __restrict__ scale,
-                              double* __restrict__ inv) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= t) return;
-  double mx = 0.0;
-  for (int q = 0; q < kVParts; ++q) mx = fmax(mx, part[(int64_t)c * kVParts + q]);
-  int e = 0;
-  if (mx > 0.0 && mx <= 1.7976931348623157e308) {
-    int E = 0;
-    (void)frexp(mx, &E);
-    e = 15 - E;
-    e = e < -1022 ? -1022 : (e > 1023 ? 1023 : e);  // 2^e and 2^(-e - 15) stay representable
-  }
-  scale[c] = ldexp(1.0, e);
-  inv[c] = ldexp(1.0, -e - 15);
+__device__ __forceinline__ int column_exponent(double mx) {
+  if (!(mx > 0.0 && mx <= 1.7976931348623157e308)) return 0;
+  int E = 0;
+  (void)frexp(mx, &E);
+  const int e = 15 - E;
+  return e < -1022 ? -1022 : (e > 1023 ? 1023 : e);  // 2^e and 2^(-e - 15) stay representable
 }
 
 __global__ void colmax_final_kernel(const double* __restrict__ part, int t, double* __restrict__ out) {
@@ -363,30 +443,59 @@ hipError_t column_absmax(const double* V, int64_t ldv, int64_t n, int t, double*
 
 // Mixed-form V fragments: (chunk, cb, hl, lane) -> 8 FP16 of v' = scale[c] V[b][c],
 // b = 32 chunk + vperm(g, j), c = 16 cb + lane%16; hl = 0: hi = RNE16(v'),
-// hl = 1: lo = RNE16(v' - hi).  Columns c >= t are zero.
-__global__ void prep_v_f16x3_kernel(const double* __restrict__ V, int64_t ldv, const double* __restrict__ col0,
-                                    const double* __restrict__ scale, int64_t n, int t, int64_t nchunks, int ntb,
-                                    bf16x8* __restrict__ vf) {
+// hl = 1: lo = RNE16(v' - hi).  Columns c >= t are zero.  Every wave derives its
+// columns' scales from the kVParts maxima (a quarter per lane group), once for the
+// `per` chunks it converts; the first chunk's waves store inv.
+__global__ __launch_bounds__(256) void prep_v_f16x3_kernel(const double* __restrict__ V, int64_t ldv,
+                                                           const double* __restrict__ col0,
+                                                           const double* __restrict__ part, double* __restrict__ inv,
+                                                           int64_t n, int t, int64_t nchunks, int ntb, int per,
+                                                           bf16x8* __restrict__ vf) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= nchunks * ntb * 64) return;
   const int lane = (int)(idx & 63);
-  const int64_t rest = idx >> 6;
-  const int cb = (int)(rest % ntb);
-  const int64_t ch = rest / ntb;
+  const int cb = (int)((idx >> 6) % ntb);
+  const int64_t ch0 = (idx >> 6) / ntb * per;  // this wave: chunks ch0 .. ch0 + per - 1 of column block cb
+  if (ch0 >= nchunks) return;
+  const int64_t ch1 = ch0 + per < nchunks ? ch0 + per : nchunks;
   const int c = 16 * cb + (lane & 15);
   const int g = lane >> 4;
-  const double sc = c < t ? scale[c] : 0.0;
-  f16x8 hi, lo;
-  for (int j = 0; j < 8; ++j) {
-    const int64_t b = ch * 32 + vperm(g, j);
-    double v = 0.0;
-    if (b < n && c < t) v = sc * (col0 ? (c == 0 ? col0[b] : V[(int64_t)(c - 1) * ldv + b]) : V[(int64_t)c * ldv + b]);
-    const double h = f16_round(v);
-    hi[j] = (_Float16)(float)h;
-    lo[j] = (_Float16)(float)(v - h);
+  const int cc = c < t ? c : t - 1;
+  const double* const src = col0 ? (cc == 0 ? col0 : V + (int64_t)(cc - 1) * ldv) : V + (int64_t)cc * ldv;
+  double pm[kVParts / 4];
+#pragma unroll
+  for (int q = 0; q < kVParts / 4; ++q) pm[q] = part[(int64_t)cc * kVParts + g * (kVParts / 4) + q];
+  double v[8];
+  auto load = [&](int64_t ch) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int64_t b = ch * 32 + vperm(g, j);
+      v[j] = src[b < n ? b : n - 1];
+    }
+  };
+  load(ch0);
+  double mx = 0.0;
+#pragma unroll
+  for (int q = 0; q < kVParts / 4; ++q) mx = fmax(mx, pm[q]);
+  mx = fmax(mx, __shfl_xor(mx, 16, 64));
+  mx = fmax(mx, __shfl_xor(mx, 32, 64));
+  const int e = column_exponent(mx);
+  const double sc = ldexp(1.0, e);
+  if (ch0 == 0 && g == 0 && c < t) inv[c] = ldexp(1.0, -e - 15);
+  for (int64_t ch = ch0; ch < ch1; ++ch) {
+    f16x8 hi, lo;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int64_t b = ch * 32 + vperm(g, j);
+      const double x = b < n && c < t ? sc * v[j] : 0.0;
+      const double h = f16_round(x);
+      hi[j] = (_Float16)(float)h;
+      lo[j] = (_Float16)(float)(x - h);
+    }
+    if (ch + 1 < ch1) load(ch + 1);
+    const int64_t rest = ch * ntb + cb;
+    vf[(rest * 2 + 0) * 64 + lane] = __builtin_bit_cast(bf16x8, hi);
+    vf[(rest * 2 + 1) * 64 + lane] = __builtin_bit_cast(bf16x8, lo);
   }
-  vf[(rest * 2 + 0) * 64 + lane] = __builtin_bit_cast(bf16x8, hi);
-  vf[(rest * 2 + 1) * 64 + lane] = __builtin_bit_cast(bf16x8, lo);
 }
 
 // FP32 V fragments: (chunk, cb, tile, lane) -> float4 of V[b = 32 chunk + 16 tile + 4g + i]
@@ -892,7 +1001,24 @@ __global__ void kmm_epilogue_kernel(const double* __restrict__ part, int64_t nsp
   if (idx >= m * t) return;
   const int64_t c = idx / m, r = idx - c * m;
   double s = 0.0;
-  for (int64_t sp = 0; sp < nsplit; ++sp) s += part[(sp * tpad + c) * mpad + r];
+  const double* src = part + c * mpad + r;
+  const int64_t step = (int64_t)tpad * mpad;
+  int64_t sp = 0;
+  for (; sp + 16 <= nsplit; sp += 16, src += 16 * step) {  // in split order, 16 loads in flight
+    double v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = src[j * step];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s += v[j];
+  }
+  for (; sp + 4 <= nsplit; sp += 4, src += 4 * step) {
+    double v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = src[j * step];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s += v[j];
+  }
+  for (; sp < nsplit; ++sp, src += step) s += src[0];
   if (inv) s *= inv[c];
   double o = sf * s;
   if (V) o += diag * V[c * ldv + r];
@@ -1060,7 +1186,7 @@ static size_t part_bytes_max(int64_t npad, int64_t mpad, int ntb, bool row_indep
   return best;
 }
 
-// V region: [fragments | scale (tpad) | inv (tpad) | column-max partials (kVParts tpad)].
+// V region: [fragments | inv (tpad) | column-max partials (kVParts tpad)].
 static size_t vfrag_core_bytes(int64_t n, int ntb_alloc) {
   return align256((size_t)round_up(n, 32) * ntb_alloc * 64 + 64);
 }
@@ -1068,7 +1194,7 @@ static size_t vfrag_core_bytes(int64_t n, int ntb_alloc) {
 size_t kmm_vfrag_bytes(int64_t n, int t) {
   const int ntb0 = (t + 15) / 16;
   const int ntb = (ntb0 + nt_launch(ntb0) - 1) / nt_launch(ntb0) * nt_launch(ntb0);
-  return vfrag_core_bytes(n, ntb) + 2 * align256((size_t)ntb * 16 * 8) + align256((size_t)kVParts * ntb * 16 * 8);
+  return vfrag_core_bytes(n, ntb) + align256((size_t)ntb * 16 * 8) + align256((size_t)kVParts * ntb * 16 * 8);
 }
 
 static void carve_vfrag(KmmPlan& p, char* c) {
@@ -1076,8 +1202,7 @@ static void carve_vfrag(KmmPlan& p, char* c) {
   const int tpad = ntb_alloc * 16;
   p.vf = c;
   c += vfrag_core_bytes(p.n, ntb_alloc);
-  p.vscale = (double*)c;  c += align256((size_t)tpad * 8);
-  p.vinv = (double*)c;    c += align256((size_t)tpad * 8);
+  p.vinv = (double*)c;  c += align256((size_t)tpad * 8);
   p.vpart = (double*)c;
 }
 
@@ -1234,18 +1359,13 @@ static hipError_t prep_points(const KmmPlan& p, const Scale& sc, const double* P
     const hipError_t e = column_means(P, rows, p.d, p.cpart, p.ctr, st);
     if (e != hipSuccess) return e;
   }
+  if (mixed) return launch_prep_points(P, p.ctr, rows, rows_pad, p.d, p.ks, sc, xr, xc, nullptr, st);
   const int thr = 256;
-  prep_norm_kernel<<<(unsigned)((rows_pad + thr - 1) / thr), thr, 0, st>>>(P, rows, rows_pad, p.d, sc, mixed,
-                                                                           mixed ? p.ctr : nullptr, p.nrm64);
+  prep_norm_fp32_kernel<<<(unsigned)((rows_pad + thr - 1) / thr), thr, 0, st>>>(P, rows, rows_pad, p.d, sc, p.nrm64);
   const int64_t nblk = rows_pad / 16;
   const int64_t total = nblk * p.ks * 64;
-  if (mixed) {
-    prep_frag_f16x3_kernel<<<(unsigned)((total + thr - 1) / thr), thr, 0, st>>>(
-        P, p.nrm64, p.ctr, rows, nblk, p.d, p.ks, sc, (bf16x8*)xr, (bf16x8*)xc);
-  } else {
-    prep_frag_fp32_kernel<<<(unsigned)((total + thr - 1) / thr), thr, 0, st>>>(
-        P, p.nrm64, rows, nblk, p.d, p.ks, sc, (f32x4*)xr, (f32x4*)xc, nr, nc);
-  }
+  prep_frag_fp32_kernel<<<(unsigned)((total + thr - 1) / thr), thr, 0, st>>>(P, p.nrm64, rows, nblk, p.d, p.ks, sc,
+                                                                             (f32x4*)xr, (f32x4*)xc, nr, nc);
   return hipGetLastError();
 }
 
@@ -1277,17 +1397,8 @@ hipError_t prep_dist(const gp_kernel* kern, const double* X, int64_t n, int64_t 
                      void* xr, void* xc, double* nrm64, hipStream_t st) {
   if (!X || !ctr || !nrm64 || (!xr && !xc) || ks * 32 < 3 * kern->d + 6 || rows_pad % 64 != 0)
     return hipErrorInvalidValue;
-  const Scale sc = make_scale(kern);
-  const int thr = 256;
-  prep_norm_kernel<<<(unsigned)((rows_pad + thr - 1) / thr), thr, 0, st>>>(X, n, rows_pad, kern->d, sc, 1, ctr,
-                                                                           nrm64);
-  const int64_t nblk = rows_pad / 16;
-  const int64_t total = nblk * ks * 64;
-  prep_frag_f16x3_kernel<<<(unsigned)((total + thr - 1) / thr), thr, 0, st>>>(X, nrm64, ctr, n, nblk, kern->d, ks,
-                                                                             sc, (bf16x8*)xr, (bf16x8*)xc);
-  return hipGetLastError();
+  return launch_prep_points(X, ctr, n, rows_pad, kern->d, ks, make_scale(kern), xr, xc, nrm64, st);
 }
-
 
 template <int KS>
 static void launch_one(bool mixed, int nt, int kind, dim3 grid, const SweepArgs& a, hipStream_t st);
@@ -1347,12 +1458,14 @@ hipError_t kmm_prepare_v(const KmmPlan& p, const double* V, int64_t ldv, int t, 
   const int ntb_alloc = sc.groups * sc.nt;  // vf holds whole launch groups (zero padded)
   const int thr = 256;
   if (p.precision == GP_PREC_BF16X3) {
-    if (!p.vscale || !p.vinv || !p.vpart) return hipErrorInvalidValue;
+    if (!p.vinv || !p.vpart) return hipErrorInvalidValue;
     vmax_partial_kernel<<<dim3(kVParts, (unsigned)t), 256, 0, st>>>(V, ldv, col0, p.n, p.vpart);
-    vscale_kernel<<<(unsigned)((t + 63) / 64), 64, 0, st>>>(p.vpart, t, p.vscale, p.vinv);
-    const int64_t total = p.nchunks * ntb_alloc * 64;
-    prep_v_f16x3_kernel<<<(unsigned)((total + thr - 1) / thr), thr, 0, st>>>(V, ldv, col0, p.vscale, p.n, t,
-                                                                              p.nchunks, ntb_alloc, (bf16x8*)p.vf);
+    // one chunk per wave until the chip is full (four waves per SIMD), then up to eight
+    const int64_t units = p.nchunks * ntb_alloc;
+    const int per = (int)std::max<int64_t>(1, std::min<int64_t>(8, units / 4096));
+    const int64_t total = (p.nchunks + per - 1) / per * ntb_alloc * 64;
+    prep_v_f16x3_kernel<<<(unsigned)((total + thr - 1) / thr), thr, 0, st>>>(
+        V, ldv, col0, p.vpart, p.vinv, p.n, t, p.nchunks, ntb_alloc, per, (bf16x8*)p.vf);
   } else {
     const int64_t total = p.nchunks * ntb_alloc * 2 * 64;
     prep_v_fp32_kernel<<<(unsigned)((total + thr - 1) / thr), thr, 0, st>>>(V, ldv, col0, p.n, t, p.nchunks,

@@ -151,3 +151,17 @@ def test_woodbury_solve_at_the_edges_of_the_in_lds_factor(k):
     L = host(pc.L)
     ref = np.linalg.solve(L.T @ L + 1e-2 * np.eye(n), B.T).T
     assert np.linalg.norm(host(r.Z0) - ref) <= 1e-10 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("n,d", [(31, 3), (33, 16), (300, 17), (257, 49), (1000, 64), (513, 65), (300, 128)])
+def test_mixed_product_at_every_slice_count_of_the_point_preparation(n, d):
+    """Points are prepared 32 at a time in 16-feature slices (1 to 8 of them) and the centre is added over blocks of
+    rows.  Bar: the mixed form's 5e-5 on the off-diagonal part (a correlated kernel, data shifted by 100 lengthscales)."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n + d)
+    X, V = rng.standard_normal((n, d)) + 100.0, rng.standard_normal((3, n))
+    th = ok.Theta(rng.uniform(0.8, 1.2, d) * np.sqrt(d), 1.1, 1e-2, ok.MATERN52)
+    got = host(gp.kmm(_gk(th), dev(X), dev(V), precision="bf16x3"))
+    ref = ok.khat_matmul(X, th, V.T).T
+    off = ref - (1.1 + 1e-2) * V
+    assert np.linalg.norm(got - ref) <= 5e-5 * np.linalg.norm(off)
