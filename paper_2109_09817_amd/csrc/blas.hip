@@ -7,30 +7,12 @@
 //
 // Layout: every block of vectors is column-major with leading dimension n
 // (column c of an n x s block starts at c*n).
+#include "reduce.h"
 #include "solver.h"
 
 namespace gpk {
 
 constexpr int kThreads = 256;
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  return v;
-}
-
-// Block-wide sum in a fixed order; the result is valid in thread 0.
-__device__ __forceinline__ double block_sum(double v, double* sh) {
-  v = wave_sum(v);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 0) sh[w] = v;
-  __syncthreads();
-  double r = 0.0;
-  if (threadIdx.x == 0)
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) r += sh[i];
-  __syncthreads();
-  return r;
-}
 
 // partial[blk * s + c] = sum over this block's rows of A[c*n+i] * B[c*n+i].
 // grid = (nblk, s).  Rows are split in contiguous ranges per block.
@@ -61,31 +43,52 @@ __global__ void reduce_partials_kernel(const double* __restrict__ partial, int64
 
 // ------------------------------------------------------------------ mBCG steps
 
-// alpha = gamma / (d.w) for active columns (0 for frozen ones); flags breakdown.
-__global__ void mbcg_alpha_kernel(MbcgState st) {
-  const int c = threadIdx.x;
-  if (c >= st.s) return;
-  double a = 0.0;
-  if (st.active[c]) {
-    const double dl = st.delta[c];
-    if (!isfinite(dl) || !isfinite(st.gamma[c])) {
-      atomicOr(st.status, kStatusNonFinite);
-    } else if (!(dl > 0.0)) {
-      atomicOr(st.status, kStatusNotPD);
-    } else {
-      a = st.gamma[c] / dl;
-    }
-  }
-  st.alpha[c] = a;
+//
+// An iteration's scalars are formed where they are used: every workgroup of a
+// column adds that column's partial sums itself, all in the same order, so the
+// step sizes need no launches of their own.  An iteration at n = 2,048 is bound by
+// its launches: 10 now and one copy to the host, 15 and two before (a likelihood
+// with 9 iterations and 20 pivots: 2.00 -> 1.54 ms; n = 65,536 with 37: 54.4 ->
+// 53.4 ms).  gamma and active have two copies, read
+// from one and written to the other, since workgroups of a column do not run in
+// step; the column's first workgroup stores them and the host's records.
+
+// sum_b partial[b * s + c] for every thread of the block, added as by reduce_partials_kernel.
+__device__ __forceinline__ double column_sum(const double* __restrict__ partial, int64_t nblk, int s, int c, double* sh,
+                                             double* bc) {
+  double acc = 0.0;
+  for (int64_t b = threadIdx.x; b < nblk; b += blockDim.x) acc += partial[b * s + c];
+  const double r = block_sum(acc, sh);
+  if (threadIdx.x == 0) *bc = r;
+  __syncthreads();
+  return *bc;
 }
 
-// U += alpha D ; R -= alpha W ; partial ||R||^2.  grid = (nblk, s).
-__global__ void mbcg_update_ur_kernel(MbcgState st, const double* __restrict__ D, const double* __restrict__ W,
-                                      double* __restrict__ U, double* __restrict__ R, int64_t n,
-                                      int64_t rows_per_blk, double* __restrict__ partial) {
-  __shared__ double sh[kThreads / 64];
+// alpha = gamma / (d.w) for active columns (0 for frozen ones), flagging breakdown;
+// U += alpha D ; R -= alpha W ; rpart ||R||^2.  grid = (nblk, s).
+__global__ __launch_bounds__(kThreads) void mbcg_update_ur_kernel(MbcgState st, int cur, int64_t nblk,
+                                                                  const double* __restrict__ D,
+                                                                  const double* __restrict__ W, double* __restrict__ U,
+                                                                  double* __restrict__ R, int64_t n,
+                                                                  int64_t rows_per_blk) {
+  __shared__ double sh[kThreads / 64], bc;
   const int c = blockIdx.y;
-  const double a = st.alpha[c];
+  const double dl = column_sum(st.dpart, nblk, st.s, c, sh, &bc);
+  const double gamma = st.gamma[cur][c];
+  double a = 0.0;
+  unsigned flag = 0;
+  if (st.active[cur][c]) {
+    if (!isfinite(dl) || !isfinite(gamma))
+      flag = kStatusNonFinite;
+    else if (!(dl > 0.0))
+      flag = kStatusNotPD;
+    else
+      a = gamma / dl;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (flag) atomicOr(st.status, flag);
+    st.alpha[c] = a;
+  }
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_blk;
   const int64_t r1 = r0 + rows_per_blk < n ? r0 + rows_per_blk : n;
   const int64_t off = (int64_t)c * n;
@@ -97,47 +100,42 @@ __global__ void mbcg_update_ur_kernel(MbcgState st, const double* __restrict__ D
     acc += r * r;
   }
   const double s = block_sum(acc, sh);
-  if (threadIdx.x == 0) partial[(int64_t)blockIdx.x * st.s + c] = s;
+  if (threadIdx.x == 0) st.rpart[(int64_t)blockIdx.x * st.s + c] = s;
 }
 
-// Convergence bookkeeping after the residual update of iteration j.
-__global__ void mbcg_freeze_kernel(MbcgState st, int j, double tol) {
-  const int c = threadIdx.x;
-  if (c < st.s && st.active[c]) {
-    const double rn = sqrt(st.rnorm2[c]);
-    st.iters[c] = j + 1;
-    st.relres[c] = st.bnorm[c] > 0.0 ? rn / st.bnorm[c] : 0.0;
-    if (!isfinite(rn)) atomicOr(st.status, kStatusNonFinite);
-    if (rn <= tol * st.bnorm[c]) st.active[c] = 0;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int na = 0;
-    for (int i = 0; i < st.s; ++i) na += st.active[i];
-    *st.num_active = na;
-  }
-}
-
-// beta = gamma'/gamma for active columns (0 for frozen ones); gamma <- gamma'.
-__global__ void mbcg_beta_kernel(MbcgState st) {
-  const int c = threadIdx.x;
-  if (c >= st.s) return;
-  double b = 0.0;
-  if (st.active[c]) {
-    const double gn = st.gamma_new[c];
-    if (!isfinite(gn)) atomicOr(st.status, kStatusNonFinite);
-    b = gn / st.gamma[c];
-    st.gamma[c] = gn;
-  }
-  st.beta[c] = b;
-}
-
-// D = Z + beta D for active columns, 0 for frozen ones.  grid = (nblk, s).
-__global__ void mbcg_update_d_kernel(MbcgState st, const double* __restrict__ Z, double* __restrict__ D,
-                                     int64_t n, int64_t rows_per_blk) {
+// Convergence bookkeeping of iteration j (from rpart), beta = gamma'/gamma (from
+// gpart) for columns still active (0 for frozen ones), and D = Z + beta D for
+// active columns, 0 for frozen ones.  grid = (nblk, s).
+__global__ __launch_bounds__(kThreads) void mbcg_update_d_kernel(MbcgState st, int cur, int64_t nblk, int j, double tol,
+                                                                 const double* __restrict__ Z, double* __restrict__ D,
+                                                                 int64_t n, int64_t rows_per_blk) {
+  __shared__ double sh[kThreads / 64], bc;
   const int c = blockIdx.y;
-  const bool act = st.active[c] != 0;
-  const double b = st.beta[c];
+  const bool was = st.active[cur][c] != 0;
+  double b = 0.0, gamma = st.gamma[cur][c], rn = 0.0;
+  bool act = was;
+  if (was) {  // the same for the whole block
+    const double bnorm = st.bnorm[c];
+    rn = sqrt(column_sum(st.rpart, nblk, st.s, c, sh, &bc));
+    act = !(rn <= tol * bnorm);
+    __syncthreads();  // bc is written again
+    if (act) {
+      const double gn = column_sum(st.gpart, nblk, st.s, c, sh, &bc);
+      b = gn / gamma;
+      gamma = gn;
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (was) {
+      st.iters[c] = j + 1;
+      st.relres[c] = st.bnorm[c] > 0.0 ? rn / st.bnorm[c] : 0.0;
+      if (!isfinite(rn) || (act && !isfinite(gamma))) atomicOr(st.status, kStatusNonFinite);
+      if (!act) atomicSub(st.num_active, 1);
+    }
+    st.active[cur ^ 1][c] = act ? 1 : 0;
+    st.gamma[cur ^ 1][c] = gamma;
+    st.beta[c] = b;
+  }
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_blk;
   const int64_t r1 = r0 + rows_per_blk < n ? r0 + rows_per_blk : n;
   const int64_t off = (int64_t)c * n;
@@ -148,17 +146,17 @@ __global__ void mbcg_update_d_kernel(MbcgState st, const double* __restrict__ Z,
 __global__ void mbcg_init_kernel(MbcgState st) {
   const int c = threadIdx.x;
   if (c < st.s) {
-    st.gamma0[c] = st.gamma[c];
+    st.gamma0[c] = st.gamma[0][c];
     st.bnorm[c] = sqrt(st.bnorm[c]);
-    st.active[c] = st.bnorm[c] > 0.0 ? 1 : 0;
+    st.active[0][c] = st.bnorm[c] > 0.0 ? 1 : 0;
     st.iters[c] = 0;
     st.relres[c] = st.bnorm[c] > 0.0 ? 1.0 : 0.0;
-    if (!isfinite(st.gamma[c]) || !isfinite(st.bnorm[c])) atomicOr(st.status, kStatusNonFinite);
+    if (!isfinite(st.gamma[0][c]) || !isfinite(st.bnorm[c])) atomicOr(st.status, kStatusNonFinite);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     int na = 0;
-    for (int i = 0; i < st.s; ++i) na += st.active[i];
+    for (int i = 0; i < st.s; ++i) na += st.active[0][i];
     *st.num_active = na;
   }
 }
@@ -681,121 +679,112 @@ __global__ void probe_kernel(const double* __restrict__ y, int64_t n, const doub
 
 // ------------------------------------------------------------ pivoted Cholesky
 
-// Per-block argmax of delta (largest value, lowest index on ties) -> partial.
-__global__ void argmax_partial_kernel(const double* __restrict__ delta, int64_t n, int64_t rows_per_blk,
-                                      double* __restrict__ pval, int64_t* __restrict__ pidx) {
-  __shared__ double sv[kThreads];
-  __shared__ int64_t si[kThreads];
+// The better of two (value, index) pairs: the larger value, the lower index on a
+// tie; index -1 stands for none.  The order in which pairs meet does not matter.
+__device__ __forceinline__ void keep_max(double& bv, int64_t& bi, double v, int64_t i) {
+  if (i >= 0 && (bi < 0 || v > bv || (v == bv && i < bi))) {
+    bv = v;
+    bi = i;
+  }
+}
+
+template <int THREADS>
+__device__ __forceinline__ void block_max(double& bv, int64_t& bi, double* sv, int64_t* si) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double ov = __shfl_xor(bv, off, 64);
+    const int64_t oi = __shfl_xor(bi, off, 64);
+    keep_max(bv, bi, ov, oi);
+  }
+  if constexpr (THREADS > 64) {
+    if ((threadIdx.x & 63) == 0) {
+      sv[threadIdx.x >> 6] = bv;
+      si[threadIdx.x >> 6] = bi;
+    }
+    __syncthreads();
+    for (int w = 0; w < THREADS / 64; ++w) keep_max(bv, bi, sv[w], si[w]);
+    __syncthreads();
+  }
+}
+
+// Step m of the pivoted Cholesky: the pivot p, column m of L for all rows,
+// l_a = (K(x_a, x_p) - L[a, :m] L[p, :m]^T) / sqrt(delta_p), delta_a -= l_a^2,
+// delta_p = 0.  Kernel values in FP64 by direct differences.
+//
+// One launch per step (a step at n = 2,048 or 65,536 is bound by its launches and
+// their latency): each workgroup finds the pivot itself from the block maxima of
+// step m - 1 (delta is s_f everywhere before step 0, so its pivot is row 0), and
+// leaves the maximum of its rows' new delta for step m + 1 in the other of two
+// buffers.  Once the largest delta falls to stop_below, ps.rank stays behind m and
+// every later step returns.  n = 65,536, d = 48, rank 100: 21 us a step with the two
+// argmax launches, 15.2 now (X and half of L: 50 MB, 10.5 us at the copy rate); n =
+// 2,048, d = 32, rank 20: 7.4 us.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void pivchol_step_kernel(const double* __restrict__ X, int64_t n, int d,
+                                                               Scale inv_ell, int kind, double sf,
+                                                               double* __restrict__ L, double* __restrict__ delta,
+                                                               PivState ps, int m, double stop_below,
+                                                               int64_t rows_per_blk) {
+  __shared__ double xp[GP_MAX_D];
+  __shared__ double lp[1024];
+  __shared__ double sv[THREADS / 64 + 1];
+  __shared__ int64_t si[THREADS / 64 + 1];
+  const int nblk = gridDim.x;
+  double pv = sf;
+  int64_t p = 0;
+  if (m > 0) {
+    if (*ps.rank < m) return;  // stopped before step m (block 0 may already store m + 1)
+    const double* const bv = ps.bval + (m & 1) * nblk;
+    const int64_t* const bi = ps.bidx + (m & 1) * nblk;
+    pv = -1.0;
+    p = -1;
+    for (int b = threadIdx.x; b < nblk; b += THREADS) keep_max(pv, p, bv[b], bi[b]);
+    block_max<THREADS>(pv, p, sv, si);
+    if (!(pv > stop_below) || p < 0) return;  // rank stays m
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ps.piv[m] = p;
+    ps.pivval[m] = pv;
+    *ps.rank = m + 1;
+  }
+  for (int j = threadIdx.x; j < d; j += THREADS) xp[j] = X[p * d + j];
+  for (int j = threadIdx.x; j < m; j += THREADS) lp[j] = L[(int64_t)j * n + p];
+  __syncthreads();
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_blk;
   const int64_t r1 = r0 + rows_per_blk < n ? r0 + rows_per_blk : n;
   double bv = -1.0;
   int64_t bi = -1;
-  for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
-    const double v = delta[i];
-    if (v > bv) {  // strictly greater: the first (lowest) index of a tie wins within a thread
-      bv = v;
-      bi = i;
+  for (int64_t a = r0 + threadIdx.x; a < r1; a += THREADS) {
+    double r2 = 0.0;
+#pragma unroll 8
+    for (int j = 0; j < d; ++j) {
+      const double df = (X[a * d + j] - xp[j]) * inv_ell.s[j];
+      r2 += df * df;
+    }
+    double kv;
+    if (kind == GP_MATERN52) {
+      const double s = sqrt(5.0 * r2);
+      kv = sf * (1.0 + s + s * s / 3.0) * exp(-s);
+    } else {
+      kv = sf * exp(-0.5 * r2);
+    }
+    double acc = 0.0;
+#pragma unroll 8
+    for (int j = 0; j < m; ++j) acc += L[(int64_t)j * n + a] * lp[j];
+    const double l = (kv - acc) / sqrt(pv);
+    L[(int64_t)m * n + a] = l;
+    const double dn = (a == p) ? 0.0 : (m > 0 ? delta[a] : sf) - l * l;
+    delta[a] = dn;
+    if (dn > bv) {  // strictly greater: the first (lowest) index of a tie wins within a thread
+      bv = dn;
+      bi = a;
     }
   }
-  sv[threadIdx.x] = bv;
-  si[threadIdx.x] = bi;
-  __syncthreads();
-  for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      const double ov = sv[threadIdx.x + off];
-      const int64_t oi = si[threadIdx.x + off];
-      const double mv = sv[threadIdx.x];
-      const int64_t mi = si[threadIdx.x];
-      if (ov > mv || (ov == mv && oi >= 0 && (mi < 0 || oi < mi))) {
-        sv[threadIdx.x] = ov;
-        si[threadIdx.x] = oi;
-      }
-    }
-    __syncthreads();
-  }
+  block_max<THREADS>(bv, bi, sv, si);
   if (threadIdx.x == 0) {
-    pval[blockIdx.x] = sv[0];
-    pidx[blockIdx.x] = si[0];
+    ps.bval[((m + 1) & 1) * nblk + blockIdx.x] = bv;
+    ps.bidx[((m + 1) & 1) * nblk + blockIdx.x] = bi;
   }
-}
-
-// Final argmax over block partials; records the pivot of step m or stops.
-// Largest value, lowest index on ties: the answer does not depend on the order
-// in which partials are combined, so one block reduces them as a tree.
-__global__ __launch_bounds__(kThreads) void argmax_final_kernel(const double* __restrict__ pval,
-                                                                const int64_t* __restrict__ pidx, int64_t nblk,
-                                                                PivState ps, int m, double stop_below) {
-  __shared__ double sv[kThreads];
-  __shared__ int64_t si[kThreads];
-  if (*ps.rank < m) return;  // already stopped (the same for every thread)
-  double bv = -1.0;
-  int64_t bi = -1;
-  for (int64_t b = threadIdx.x; b < nblk; b += kThreads) {
-    const double v = pval[b];
-    const int64_t i = pidx[b];
-    if (i >= 0 && (bi < 0 || v > bv || (v == bv && i < bi))) {
-      bv = v;
-      bi = i;
-    }
-  }
-  sv[threadIdx.x] = bv;
-  si[threadIdx.x] = bi;
-  __syncthreads();
-  for (int off = kThreads / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      const double ov = sv[threadIdx.x + off];
-      const int64_t oi = si[threadIdx.x + off];
-      const double mv = sv[threadIdx.x];
-      const int64_t mi = si[threadIdx.x];
-      if (oi >= 0 && (mi < 0 || ov > mv || (ov == mv && oi < mi))) {
-        sv[threadIdx.x] = ov;
-        si[threadIdx.x] = oi;
-      }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x != 0) return;
-  bv = sv[0];
-  bi = si[0];
-  if (!(bv > stop_below) || bi < 0) {
-    return;  // rank stays m
-  }
-  ps.piv[m] = bi;
-  ps.pivval[m] = bv;
-  *ps.rank = m + 1;
-}
-
-// Column m of L for all rows: l_a = (K(x_a, x_p) - L[a, :m] L[p, :m]^T) / sqrt(delta_p),
-// delta_a -= l_a^2, delta_p = 0.  Kernel values in FP64 by direct differences.
-__global__ void pivchol_column_kernel(const double* __restrict__ X, int64_t n, int d, Scale inv_ell, int kind,
-                                      double sf, double* __restrict__ L, double* __restrict__ delta, PivState ps,
-                                      int m) {
-  __shared__ double xp[GP_MAX_D];
-  __shared__ double lp[1024];
-  if (*ps.rank <= m) return;  // stopped before step m
-  const int64_t p = ps.piv[m];
-  for (int j = threadIdx.x; j < d; j += blockDim.x) xp[j] = X[p * d + j];
-  for (int j = threadIdx.x; j < m; j += blockDim.x) lp[j] = L[(int64_t)j * n + p];
-  __syncthreads();
-  const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (a >= n) return;
-  double r2 = 0.0;
-  for (int j = 0; j < d; ++j) {
-    const double df = (X[a * d + j] - xp[j]) * inv_ell.s[j];
-    r2 += df * df;
-  }
-  double kv;
-  if (kind == GP_MATERN52) {
-    const double s = sqrt(5.0 * r2);
-    kv = sf * (1.0 + s + s * s / 3.0) * exp(-s);
-  } else {
-    kv = sf * exp(-0.5 * r2);
-  }
-  double acc = 0.0;
-  for (int j = 0; j < m; ++j) acc += L[(int64_t)j * n + a] * lp[j];
-  const double l = (kv - acc) / sqrt(ps.pivval[m]);
-  L[(int64_t)m * n + a] = l;
-  delta[a] = (a == p) ? 0.0 : delta[a] - l * l;
 }
 
 // --------------------------------------------------------------- host helpers
@@ -959,46 +948,50 @@ hipError_t mbcg_launch_init(const MbcgState& s, hipStream_t st) {
   mbcg_init_kernel<<<1, 256, 0, st>>>(s);
   return hipGetLastError();
 }
-hipError_t mbcg_launch_alpha(const MbcgState& s, hipStream_t st) {
-  mbcg_alpha_kernel<<<1, 256, 0, st>>>(s);
-  return hipGetLastError();
-}
-hipError_t mbcg_launch_update_ur(const MbcgState& s, const double* D, const double* W, double* U, double* R,
-                                 int64_t n, double* partial, hipStream_t st) {
+hipError_t coldot_partials(const double* A, const double* B, int64_t n, int s, double* partial, hipStream_t st) {
   const RowSplit rs = row_split(n, kDotBlocks);
-  mbcg_update_ur_kernel<<<dim3((unsigned)rs.nblk, (unsigned)s.s), kThreads, 0, st>>>(s, D, W, U, R, n,
-                                                                                      rs.rows_per_blk, partial);
-  reduce_partials_kernel<<<s.s, kThreads, 0, st>>>(partial, rs.nblk, s.s, s.rnorm2);
+  coldot_partial_kernel<<<dim3((unsigned)rs.nblk, (unsigned)s), kThreads, 0, st>>>(A, B, n, rs.rows_per_blk, s,
+                                                                                   partial);
   return hipGetLastError();
 }
-hipError_t mbcg_launch_freeze(const MbcgState& s, int j, double tol, hipStream_t st) {
-  mbcg_freeze_kernel<<<1, 256, 0, st>>>(s, j, tol);
-  return hipGetLastError();
-}
-hipError_t mbcg_launch_beta(const MbcgState& s, hipStream_t st) {
-  mbcg_beta_kernel<<<1, 256, 0, st>>>(s);
-  return hipGetLastError();
-}
-hipError_t mbcg_launch_update_d(const MbcgState& s, const double* Z, double* D, int64_t n, hipStream_t st) {
+hipError_t mbcg_launch_update_ur(const MbcgState& s, int cur, const double* D, const double* W, double* U, double* R,
+                                 int64_t n, hipStream_t st) {
   const RowSplit rs = row_split(n, kDotBlocks);
-  mbcg_update_d_kernel<<<dim3((unsigned)rs.nblk, (unsigned)s.s), kThreads, 0, st>>>(s, Z, D, n, rs.rows_per_blk);
+  mbcg_update_ur_kernel<<<dim3((unsigned)rs.nblk, (unsigned)s.s), kThreads, 0, st>>>(s, cur, rs.nblk, D, W, U, R, n,
+                                                                                      rs.rows_per_blk);
+  return hipGetLastError();
+}
+hipError_t mbcg_launch_update_d(const MbcgState& s, int cur, int j, double tol, const double* Z, double* D, int64_t n,
+                                hipStream_t st) {
+  const RowSplit rs = row_split(n, kDotBlocks);
+  mbcg_update_d_kernel<<<dim3((unsigned)rs.nblk, (unsigned)s.s), kThreads, 0, st>>>(s, cur, rs.nblk, j, tol, Z, D, n,
+                                                                                     rs.rows_per_blk);
   return hipGetLastError();
 }
 
-hipError_t pivchol_launch_argmax(const double* delta, int64_t n, double* pval, int64_t* pidx, const PivState& ps,
-                                 int m, double stop_below, hipStream_t st) {
-  const RowSplit rs = row_split(n, kDotBlocks);
-  argmax_partial_kernel<<<(unsigned)rs.nblk, kThreads, 0, st>>>(delta, n, rs.rows_per_blk, pval, pidx);
-  argmax_final_kernel<<<1, kThreads, 0, st>>>(pval, pidx, rs.nblk, ps, m, stop_below);
-  return hipGetLastError();
+// One wave per workgroup up to this many rows, so that few rows still reach many CUs (n = 2,048: 32 workgroups
+// instead of 8); four beyond, so that a step has at most 1,024 block maxima to compare.
+constexpr int64_t kPivWaveRows = 32768;
+
+static RowSplit pivchol_split(int64_t n) {
+  if (n > kPivWaveRows) return row_split(n, kDotBlocks);
+  return RowSplit{64, (n + 63) / 64};
 }
 
-hipError_t pivchol_launch_column(const double* X, int64_t n, const gp_kernel* kern, double* L, double* delta,
-                                 const PivState& ps, int m, hipStream_t st) {
+int64_t pivchol_blocks(int64_t n) { return pivchol_split(n).nblk; }
+
+hipError_t pivchol_launch_step(const double* X, int64_t n, const gp_kernel* kern, double* L, double* delta,
+                               const PivState& ps, int m, double stop_below, hipStream_t st) {
   Scale inv{};
   for (int j = 0; j < kern->d; ++j) inv.s[j] = 1.0 / kern->lengthscale[j];
-  pivchol_column_kernel<<<blocks_for(n), kThreads, 0, st>>>(X, n, kern->d, inv, kern->kind, kern->outputscale, L,
-                                                            delta, ps, m);
+  const RowSplit rs = pivchol_split(n);
+  const unsigned grid = (unsigned)rs.nblk;
+  if (n > kPivWaveRows)
+    pivchol_step_kernel<kThreads><<<grid, kThreads, 0, st>>>(X, n, kern->d, inv, kern->kind, kern->outputscale, L,
+                                                             delta, ps, m, stop_below, rs.rows_per_blk);
+  else
+    pivchol_step_kernel<64><<<grid, 64, 0, st>>>(X, n, kern->d, inv, kern->kind, kern->outputscale, L, delta, ps, m,
+                                                 stop_below, rs.rows_per_blk);
   return hipGetLastError();
 }
 

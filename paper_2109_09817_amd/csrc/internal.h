@@ -86,10 +86,17 @@ hipError_t kmm_prepare_cols(KmmPlan& p, const gp_kernel* kern, const double* Z, 
 // col0 (optional): column 0 taken from col0, columns c >= 1 from V column c - 1.
 hipError_t kmm_prepare_v(const KmmPlan& p, const double* V, int64_t ldv, int t, bool row_independent,
                          hipStream_t st, const double* col0 = nullptr);
+// Optional by-product of a square product's epilogue (mixed and FP32 forms): part[b t
+// + c] = sum of V[., c] out[., c] over rows [b rows, (b + 1) rows), rows a multiple of
+// 256, with the bits of coldot's partial sums.
+struct DotPartials {
+  double* part = nullptr;
+  int64_t rows = 256;
+};
 // The sweep and epilogue on already-prepared operands (Vdiag: V for the exact
 // diagonal term of the square product, ignored for cross products).
 hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, double* out, int64_t ldo,
-                     hipStream_t st, bool row_independent);
+                     hipStream_t st, bool row_independent, const DotPartials& dot = DotPartials());
 // The factor c of the prescaled coordinates x' = c (x - centre) / l, chosen so that the
 // profile reads r^2 through exp2: sqrt(5) log2(e) for Matern-5/2, sqrt(log2(e) / 2) for RBF.
 double profile_coordinate_scale(int kind);
@@ -120,7 +127,8 @@ bool kmm_plan_model(KmmPlan& p, const gp_kernel* kern, int precision, int64_t n,
 // Splits of the b range are chosen from n only when `row_independent` is set,
 // so that each output row's arithmetic does not depend on m.
 hipError_t kmm_apply(const KmmPlan& p, const double* V, int64_t ldv, int t, double* out,
-                     int64_t ldo, hipStream_t st, bool row_independent = false);
+                     int64_t ldo, hipStream_t st, bool row_independent = false,
+                     const DotPartials& dot = DotPartials());
 
 // The FP64 form (kmm_fp64.hip).
 F64Split f64_split(int64_t n, int64_t m, bool square, int t);

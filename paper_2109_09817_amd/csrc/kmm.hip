@@ -40,6 +40,7 @@
 // kmm_fp64.hip.
 #include "internal.h"
 #include "mfma_bf16.h"
+#include "reduce.h"
 
 #include <algorithm>
 #include <mutex>
@@ -992,37 +993,50 @@ __global__ __launch_bounds__(256, 2) void sweep_fp32_kernel(SweepArgs a) {
 }
 
 // out[c*ldo + r] = s_f * inv[c] * sum_split part + (square ? (s_f + sigma^2) V[c*ldv + r] : 0)
-// (inv: the mixed form's column factors, a power of two; null for the FP32 form)
-__global__ void kmm_epilogue_kernel(const double* __restrict__ part, int64_t nsplit, int tpad,
-                                    int64_t mpad, int64_t m, int t, double sf, double diag,
-                                    const double* __restrict__ inv, const double* __restrict__ V, int64_t ldv,
-                                    double* __restrict__ out, int64_t ldo) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= m * t) return;
-  const int64_t c = idx / m, r = idx - c * m;
-  double s = 0.0;
-  const double* src = part + c * mpad + r;
-  const int64_t step = (int64_t)tpad * mpad;
-  int64_t sp = 0;
-  for (; sp + 16 <= nsplit; sp += 16, src += 16 * step) {  // in split order, 16 loads in flight
-    double v[16];
+// (inv: the mixed form's column factors, a power of two; null for the FP32 form).
+// grid = (row blocks, columns); dot (nullable): dot[b t + c] = sum over the block's
+// rows of V out, added as in coldot_partial_kernel.
+__global__ __launch_bounds__(256) void kmm_epilogue_kernel(const double* __restrict__ part, int64_t nsplit, int tpad,
+                                                           int64_t mpad, int64_t m, int t, double sf, double diag,
+                                                           const double* __restrict__ inv, const double* __restrict__ V,
+                                                           int64_t ldv, double* __restrict__ out, int64_t ldo,
+                                                           int64_t rows_per_blk, double* __restrict__ dot) {
+  __shared__ double sh[4];
+  const int64_t c = blockIdx.y;
+  const int64_t r0 = (int64_t)blockIdx.x * rows_per_blk;
+  const int64_t r1 = r0 + rows_per_blk < m ? r0 + rows_per_blk : m;
+  double acc = 0.0;
+  for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
+    double s = 0.0;
+    const double* src = part + c * mpad + r;
+    const int64_t step = (int64_t)tpad * mpad;
+    int64_t sp = 0;
+    for (; sp + 16 <= nsplit; sp += 16, src += 16 * step) {  // in split order, 16 loads in flight
+      double v[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = src[j * step];
+      for (int j = 0; j < 16; ++j) v[j] = src[j * step];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) s += v[j];
+      for (int j = 0; j < 16; ++j) s += v[j];
+    }
+    for (; sp + 4 <= nsplit; sp += 4, src += 4 * step) {
+      double v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = src[j * step];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s += v[j];
+    }
+    for (; sp < nsplit; ++sp, src += step) s += src[0];
+    if (inv) s *= inv[c];
+    double o = sf * s;
+    const double vr = V ? V[c * ldv + r] : 0.0;
+    if (V) o += diag * vr;
+    out[c * ldo + r] = o;
+    acc += vr * o;
   }
-  for (; sp + 4 <= nsplit; sp += 4, src += 4 * step) {
-    double v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = src[j * step];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s += v[j];
+  if (dot) {
+    const double b = block_sum(acc, sh);
+    if (threadIdx.x == 0) dot[(int64_t)blockIdx.x * t + c] = b;
   }
-  for (; sp < nsplit; ++sp, src += step) s += src[0];
-  if (inv) s *= inv[c];
-  double o = sf * s;
-  if (V) o += diag * V[c * ldv + r];
-  out[c * ldo + r] = o;
 }
 
 // The split sum of the wide sweep: a workgroup takes one column and 64 rows,
@@ -1542,8 +1556,8 @@ static hipError_t kmm_sweep_wide(const KmmPlan& p, int t, const SplitChoice& sc,
 }
 
 hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, double* out, int64_t ldo,
-                     hipStream_t st, bool row_independent) {
-  if (t < 1 || t > p.tmax) return hipErrorInvalidValue;
+                     hipStream_t st, bool row_independent, const DotPartials& dot) {
+  if (t < 1 || t > p.tmax || (dot.part && !p.square)) return hipErrorInvalidValue;
   if (!p.xr || !p.xc || !p.nrm_b || !p.nrm_a || !p.vf || !p.part || !out) return hipErrorInvalidValue;
   const bool mixed = p.precision == GP_PREC_BF16X3;
   const int ntb = (t + 15) / 16;
@@ -1588,20 +1602,19 @@ hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, 
     std::lock_guard<std::mutex> g(timing().mu);
     timing().recs.push_back(rec);
   }
-  const int thr = 256;
-  const int64_t total = p.m * t;
-  kmm_epilogue_kernel<<<(unsigned)((total + thr - 1) / thr), thr, 0, st>>>(
-      p.part, sc.nsplit, sc.tpad, p.mpad, p.m, t, p.sf, p.square ? p.sf + p.noise : 0.0, mixed ? p.vinv : nullptr,
-      p.square ? Vdiag : nullptr, ldv, out, ldo);
+  const dim3 egrid((unsigned)((p.m + dot.rows - 1) / dot.rows), (unsigned)t);
+  kmm_epilogue_kernel<<<egrid, 256, 0, st>>>(p.part, sc.nsplit, sc.tpad, p.mpad, p.m, t, p.sf,
+                                             p.square ? p.sf + p.noise : 0.0, mixed ? p.vinv : nullptr,
+                                             p.square ? Vdiag : nullptr, ldv, out, ldo, dot.rows, dot.part);
   return hipGetLastError();
 }
 
 hipError_t kmm_apply(const KmmPlan& p, const double* V, int64_t ldv, int t, double* out, int64_t ldo,
-                     hipStream_t st, bool row_independent) {
-  if (p.precision == GP_PREC_FP64) return fp64_sweep(p, V, ldv, t, out, ldo, st);
+                     hipStream_t st, bool row_independent, const DotPartials& dot) {
+  if (p.precision == GP_PREC_FP64) return dot.part ? hipErrorInvalidValue : fp64_sweep(p, V, ldv, t, out, ldo, st);
   hipError_t e = kmm_prepare_v(p, V, ldv, t, row_independent, st);
   if (e != hipSuccess) return e;
-  return kmm_sweep(p, t, V, ldv, out, ldo, st, row_independent);
+  return kmm_sweep(p, t, V, ldv, out, ldo, st, row_independent, dot);
 }
 
 }  // namespace gpk

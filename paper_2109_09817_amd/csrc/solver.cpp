@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "api_common.h"
@@ -24,10 +25,10 @@ static double now_ms() {
 static size_t dot_partial_doubles(int64_t n, int s) { return (size_t)row_split(n, kDotBlocks).nblk * s; }
 
 size_t pivchol_ws_bytes(int64_t n, int k) {
-  const size_t nb = (size_t)row_split(n, kDotBlocks).nblk;
+  const size_t nb = 2 * (size_t)pivchol_blocks(n);
   size_t b = 0;
   b += align256(n * 8);                                   // delta
-  b += align256(nb * 8) + align256(nb * 8);               // argmax partials
+  b += align256(nb * 8) + align256(nb * 8);               // block maxima
   b += align256((size_t)k * 8) * 2 + align256(8);         // piv, pivval, rank
   b += align256((size_t)k * k * 8);                       // C
   b += align256(atb_partial_doubles(n, k, k) * 8);        // atb partial
@@ -39,6 +40,7 @@ size_t mbcg_ws_bytes(int precision, int d, int64_t n, int s, int rank) {
   b += 4 * align256((size_t)n * s * 8);  // R, Z, D, W
   b += 16 * align256((size_t)s * 8);     // per-column state
   b += align256((size_t)(2 * s + 2) * 8);
+  b += 3 * align256(dot_partial_doubles(n, s) * 8);  // d.w, ||r||^2, r.z
   const size_t part = std::max(dot_partial_doubles(n, s), rank > 0 ? atb_partial_doubles(n, rank, s) : 0);
   b += align256(part * 8);
   b += align256((size_t)std::max(rank, 1) * s * 8);  // Woodbury Y
@@ -68,7 +70,7 @@ bool host_cholesky(std::vector<double>& A, int k) {
 int run_pivchol(const gp_kernel* kern, const double* X, int64_t n, int k, double* L, double* Cchol,
                 int64_t* piv_host, int* rank_host, double* logdet_host, void* ws, size_t ws_bytes, hipStream_t st) {
   Carve cv(ws, ws_bytes);
-  const int64_t nb = row_split(n, kDotBlocks).nblk;
+  const int64_t nb = 2 * pivchol_blocks(n);
   double* delta = cv.take<double>(n);
   double* pval = cv.take<double>(nb);
   int64_t* pidx = cv.take<int64_t>(nb);
@@ -78,15 +80,12 @@ int run_pivchol(const gp_kernel* kern, const double* X, int64_t n, int k, double
   double* C = cv.take<double>((size_t)k * k);
   double* part = cv.take<double>(atb_partial_doubles(n, k, k));
   if (!part) return fail(GP_EWORKSPACE, "gp_pivchol_precond: workspace layout failed");
-  PivState ps{piv, pivval, rank};
+  PivState ps{piv, pivval, rank, pval, pidx};
   GPK_HIP(launch_fill(L, 0.0, n * (int64_t)k, st));
-  GPK_HIP(launch_fill(delta, kern->outputscale, n, st));
   GPK_HIP(launch_zero_words(rank, 1, st));
   GPK_HIP(launch_zero_words(piv, 2 * (int64_t)k, st));
-  for (int m = 0; m < k; ++m) {
-    GPK_HIP(pivchol_launch_argmax(delta, n, pval, pidx, ps, m, kPivStopRel * kern->outputscale, st));
-    GPK_HIP(pivchol_launch_column(X, n, kern, L, delta, ps, m, st));
-  }
+  for (int m = 0; m < k; ++m)
+    GPK_HIP(pivchol_launch_step(X, n, kern, L, delta, ps, m, kPivStopRel * kern->outputscale, st));
   GPK_HIP(atb(L, k, L, k, n, C, part, st));
   std::vector<double> Ch((size_t)k * k);
   int r = 0;
@@ -126,6 +125,17 @@ struct MbcgHost {
   int total_iters = 0;
 };
 
+// W = K_hat D and the partial sums of the columns' d.w: the mixed and FP32 forms add
+// them where they write W.
+static hipError_t kmm_apply_dot(const KmmPlan& plan, const double* D, int s, double* W, double* dpart,
+                                hipStream_t st) {
+  const int64_t n = plan.n;
+  if (plan.precision != GP_PREC_FP64)
+    return kmm_apply(plan, D, n, s, W, n, st, false, DotPartials{dpart, row_split(n, kDotBlocks).rows_per_blk});
+  const hipError_t e = kmm_apply(plan, D, n, s, W, n, st);
+  return e != hipSuccess ? e : coldot_partials(D, W, n, s, dpart, st);
+}
+
 int run_mbcg(const gp_kernel* kern, int precision, const double* X, int64_t n, const Precond& pc, const double* B,
              int s, int max_iter, double tol, double* U, double* Z0, MbcgHost& out, void* ws, size_t ws_bytes,
              hipStream_t st) {
@@ -141,15 +151,17 @@ int run_mbcg(const gp_kernel* kern, int precision, const double* X, int64_t n, c
   double* W = cv.take<double>(ns);
   MbcgState S;
   S.s = s;
-  S.gamma = cv.take<double>(s);
-  S.gamma_new = cv.take<double>(s);
+  S.gamma[0] = cv.take<double>(s);
+  S.gamma[1] = cv.take<double>(s);
   S.gamma0 = cv.take<double>(s);
-  S.delta = cv.take<double>(s);
-  S.rnorm2 = cv.take<double>(s);
   S.bnorm = cv.take<double>(s);
   S.relres = cv.take<double>(s);
-  S.active = cv.take<int>(s);
+  S.active[0] = cv.take<int>(s);
+  S.active[1] = cv.take<int>(s);
   S.iters = cv.take<int>(s);
+  S.dpart = cv.take<double>(dot_partial_doubles(n, s));
+  S.rpart = cv.take<double>(dot_partial_doubles(n, s));
+  S.gpart = cv.take<double>(dot_partial_doubles(n, s));
   double* xfer = cv.take<double>(2 * s + 2);  // [alpha | beta | num_active, status]
   const size_t part_n = std::max(dot_partial_doubles(n, s), pc.rank > 0 ? atb_partial_doubles(n, pc.rank, s) : 0);
   double* part = cv.take<double>(part_n);
@@ -168,14 +180,15 @@ int run_mbcg(const gp_kernel* kern, int precision, const double* X, int64_t n, c
   GPK_HIP(precond_apply(pc, R, Z, n, s, Y, part, st));
   if (Z0) GPK_HIP(launch_copy(Z, Z0, (int64_t)ns, st));
   GPK_HIP(launch_copy(Z, D, (int64_t)ns, st));
-  GPK_HIP(coldot(R, Z, n, s, S.gamma, part, st));
+  GPK_HIP(coldot(R, Z, n, s, S.gamma[0], part, st));
   GPK_HIP(coldot(B, B, n, s, S.bnorm, part, st));
   GPK_HIP(mbcg_launch_init(S, st));
   struct {
     int num_active;
     unsigned status;
   } flags{0, 0};
-  std::vector<double> ab(2 * s);
+  std::vector<double> ab(2 * s + 1);  // [alpha | beta | flags], as on the device
+  static_assert(sizeof flags == sizeof(double), "one double of flags");
   GPK_HIP(hipMemcpyAsync(&flags, S.num_active, sizeof flags, hipMemcpyDeviceToHost, st));
   GPK_HIP(hipStreamSynchronize(st));
   if (flags.status & kStatusNonFinite) return fail(GP_ENONFINITE, "gp_mbcg: non-finite right-hand side or P^{-1}B");
@@ -184,20 +197,17 @@ int run_mbcg(const gp_kernel* kern, int precision, const double* X, int64_t n, c
   out.beta.clear();
   out.total_iters = 0;
   for (int j = 0; j < max_iter && flags.num_active > 0; ++j) {
-    GPK_HIP(kmm_apply(plan, D, n, s, W, n, st));
-    GPK_HIP(coldot(D, W, n, s, S.delta, part, st));
-    GPK_HIP(mbcg_launch_alpha(S, st));
-    GPK_HIP(mbcg_launch_update_ur(S, D, W, U, R, n, part, st));
-    GPK_HIP(mbcg_launch_freeze(S, j, ftol, st));
+    const int cur = j & 1;
+    GPK_HIP(kmm_apply_dot(plan, D, s, W, S.dpart, st));
+    GPK_HIP(mbcg_launch_update_ur(S, cur, D, W, U, R, n, st));
     GPK_HIP(precond_apply(pc, R, Z, n, s, Y, part, st));
-    GPK_HIP(coldot(R, Z, n, s, S.gamma_new, part, st));
-    GPK_HIP(mbcg_launch_beta(S, st));
-    GPK_HIP(mbcg_launch_update_d(S, Z, D, n, st));
-    GPK_HIP(hipMemcpyAsync(ab.data(), xfer, sizeof(double) * 2 * s, hipMemcpyDeviceToHost, st));
-    GPK_HIP(hipMemcpyAsync(&flags, S.num_active, sizeof flags, hipMemcpyDeviceToHost, st));
+    GPK_HIP(coldot_partials(R, Z, n, s, S.gpart, st));
+    GPK_HIP(mbcg_launch_update_d(S, cur, j, ftol, Z, D, n, st));
+    GPK_HIP(hipMemcpyAsync(ab.data(), xfer, sizeof(double) * (2 * s + 1), hipMemcpyDeviceToHost, st));
     GPK_HIP(hipStreamSynchronize(st));
+    std::memcpy(&flags, &ab[2 * s], sizeof flags);
     out.alpha.insert(out.alpha.end(), ab.begin(), ab.begin() + s);
-    out.beta.insert(out.beta.end(), ab.begin() + s, ab.end());
+    out.beta.insert(out.beta.end(), ab.begin() + s, ab.begin() + 2 * s);
     out.total_iters = j + 1;
     if (flags.status & kStatusNonFinite) return fail(GP_ENONFINITE, "gp_mbcg: non-finite value at iteration %d", j);
     if (flags.status & kStatusNotPD) return fail(GP_ENOTPD, "gp_mbcg: d^T K_hat d <= 0 at iteration %d", j);

@@ -29,16 +29,16 @@ RowSplit row_split(int64_t n, int64_t target_blocks);
 // Device-resident per-column state of an mBCG run (arrays of s entries).
 struct MbcgState {
   int s;
-  double* gamma;      // r.z of the current residual
-  double* gamma_new;  // r.z after the preconditioner step
+  double* gamma[2];   // r.z of the current residual (iterations alternate between the copies)
   double* gamma0;     // b^T P^{-1} b
-  double* delta;      // d.w
+  double* dpart;      // partial sums [block][column] (row_split(n, kDotBlocks)) of d.w,
+  double* rpart;      // of ||r||^2 after the residual update
+  double* gpart;      // and of r.z after the preconditioner step
   double* alpha;      // current step sizes (copied to the host every iteration)
   double* beta;
-  double* rnorm2;
   double* bnorm;      // ||b|| (holds ||b||^2 until init)
   double* relres;
-  int* active;
+  int* active[2];     // likewise alternating
   int* iters;
   int* num_active;
   unsigned* status;
@@ -55,9 +55,13 @@ struct PivState {
   int64_t* piv;     // k pivots
   double* pivval;   // residual diagonal at each pivot
   int* rank;        // steps completed
+  double* bval;     // block maxima of the residual diagonal, two buffers of pivchol_blocks(n)
+  int64_t* bidx;    // and their rows
 };
 
 hipError_t coldot(const double* A, const double* B, int64_t n, int s, double* out, double* partial, hipStream_t st);
+// The first pass of coldot: partial[block * s + c] over row_split(n, kDotBlocks).
+hipError_t coldot_partials(const double* A, const double* B, int64_t n, int s, double* partial, hipStream_t st);
 size_t atb_partial_doubles(int64_t n, int pa, int qb);
 hipError_t atb(const double* A, int pa, const double* B, int qb, int64_t n, double* out, double* partial,
                hipStream_t st);
@@ -87,17 +91,16 @@ hipError_t launch_predict_finish(const double* P, int64_t m, int kc, double sf, 
 hipError_t launch_fill(double* dst, double v, int64_t count, hipStream_t st);
 
 hipError_t mbcg_launch_init(const MbcgState& s, hipStream_t st);
-hipError_t mbcg_launch_alpha(const MbcgState& s, hipStream_t st);
-hipError_t mbcg_launch_update_ur(const MbcgState& s, const double* D, const double* W, double* U, double* R,
-                                 int64_t n, double* partial, hipStream_t st);
-hipError_t mbcg_launch_freeze(const MbcgState& s, int j, double tol, hipStream_t st);
-hipError_t mbcg_launch_beta(const MbcgState& s, hipStream_t st);
-hipError_t mbcg_launch_update_d(const MbcgState& s, const double* Z, double* D, int64_t n, hipStream_t st);
+// Step cur of an iteration reads gamma[cur], active[cur] and writes the other copies
+// (update_d).  dpart, rpart and gpart must hold their partial sums.
+hipError_t mbcg_launch_update_ur(const MbcgState& s, int cur, const double* D, const double* W, double* U, double* R,
+                                 int64_t n, hipStream_t st);
+hipError_t mbcg_launch_update_d(const MbcgState& s, int cur, int j, double tol, const double* Z, double* D, int64_t n,
+                                hipStream_t st);
 
-hipError_t pivchol_launch_argmax(const double* delta, int64_t n, double* pval, int64_t* pidx, const PivState& ps,
-                                 int m, double stop_below, hipStream_t st);
-hipError_t pivchol_launch_column(const double* X, int64_t n, const gp_kernel* kern, double* L, double* delta,
-                                 const PivState& ps, int m, hipStream_t st);
+int64_t pivchol_blocks(int64_t n);
+hipError_t pivchol_launch_step(const double* X, int64_t n, const gp_kernel* kern, double* L, double* delta,
+                               const PivState& ps, int m, double stop_below, hipStream_t st);
 
 // Dense FP64 pieces on the matrix cores (exact.hip).  Row-major matrices.
 // C (m x nn) = L B, L m x m lower triangular as dense_lower_inverse leaves it.

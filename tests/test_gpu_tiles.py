@@ -165,3 +165,45 @@ def test_mixed_product_at_every_slice_count_of_the_point_preparation(n, d):
     ref = ok.khat_matmul(X, th, V.T).T
     off = ref - (1.1 + 1e-2) * V
     assert np.linalg.norm(got - ref) <= 5e-5 * np.linalg.norm(off)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 4097, 32768, 32769, 270000])
+def test_pivoted_cholesky_at_the_edges_of_its_row_blocks(n):
+    """64 rows to a workgroup up to n = 32,768, 256 beyond, 512 at n = 270,000.  The columns against the oracle's on the
+    same pivots, each of which attains the largest residual diagonal; bars as for the pivoted Cholesky elsewhere."""
+    from oracle.pivchol import pivoted_cholesky
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, 4))
+    th = ok.Theta(np.full(4, 1.5), 1.3, 1e-2, ok.MATERN52)
+    k = min(n, 6)
+    pc = gp.pivchol(_gk(th), dev(X), k)
+    assert pc.rank == k
+    piv = [int(p) for p in pc.pivots[:k]]
+    Lo, _, _ = pivoted_cholesky(X, th, k, pivots=piv)
+    np.testing.assert_allclose(host(pc.L).T, Lo, rtol=0, atol=1e-10)
+    delta = np.full(n, th.sf)
+    for m in range(k):
+        assert delta[piv[m]] >= delta.max() - 1e-12 * th.sf
+        delta -= Lo[:, m] ** 2
+
+
+@pytest.mark.parametrize("n,prec", [(1, "bf16x3"), (255, "fp32"), (257, "bf16x3"), (257, "fp64"), (1500, "fp64"),
+                                    (270000, "bf16x3")])
+def test_first_step_size_from_the_products_own_dot(n, prec):
+    """One iteration without a preconditioner: U = alpha B with alpha = B.B / B.(K B) per column, the dot added where the
+    product is written (512 rows to a workgroup at n = 270,000).  Against gp.kmm and numpy: sums of n positive and
+    negative terms in FP64, cancelling little here (K is diagonally dominated): bar 1e-11."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n)
+    X, B = rng.standard_normal((n, 6)), rng.standard_normal((3, n))
+    B[2] = 0.0  # never active
+    th = ok.Theta(np.full(6, 0.5), 1.0, 1.0, ok.MATERN52)
+    kern = _gk(th)
+    r = gp.mbcg(kern, dev(X), dev(B), 1, 0.0, precision=prec)
+    KB = host(gp.kmm(kern, dev(X), dev(B), precision=prec))
+    U = host(r.U)
+    for c in range(2):
+        alpha = (B[c] @ B[c]) / (B[c] @ KB[c])
+        assert np.linalg.norm(U[c] - alpha * B[c]) <= 1e-11 * np.linalg.norm(alpha * B[c])
+    assert not U[2].any()
