@@ -43,7 +43,6 @@ __global__ void reduce_partials_kernel(const double* __restrict__ partial, int64
 
 // ------------------------------------------------------------------ mBCG steps
 
-//
 // An iteration's scalars are formed where they are used: every workgroup of a
 // column adds that column's partial sums itself, all in the same order, so the
 // step sizes need no launches of their own.  An iteration at n = 2,048 is bound by

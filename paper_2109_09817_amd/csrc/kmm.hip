@@ -537,16 +537,39 @@ struct SweepArgs {
   int64_t cps;   // chunks per split
   int ntb;       // 16-column blocks in vf
   int tpad;      // columns of the partial buffer
+  int t;         // columns that hold a result; the others are not stored
+  int f32part;   // cps <= kFlush: each split is one FP32 window, stored exactly as FP32
   int square;    // mask the diagonal (square product)
 };
 
 // 16-row blocks per wave: each staged b-stream fragment serves NA tiles and
-// each V fragment NA row blocks, as far as the registers allow (two blocks
-// with three or four column blocks fit only up to KS = 5).
+// each V fragment NA row blocks, as far as 256 registers (two waves per SIMD)
+// allow.  n = 65,536 (KS = 13: 40,000), ms, this NA and the next smaller or larger one:
+// KS 5 NT 1: 1.82 (2: 1.98); KS 7 NT 1: 2.10 (2: 2.28), NT 4: 3.07 (1: 3.79);
+// KS 13 NT 1: 1.36 (4, spilling: 5.66; 1: 1.66), NT 2: 1.74 (2, spilling: 3.59),
+// NT 3: 1.85 (2, spilling: 6.41).  With two column blocks and KS <= 5 the kernel fits three
+// waves per SIMD (RBF KS 5 NT 2: 1.95 -> 1.84 ms).
 template <int KS, int NT>
 struct NAOf {
-  static constexpr int value = NT == 1 ? 4 : (NT == 2 || KS <= 5 ? 2 : 1);
+  static constexpr int value = NT == 1 ? (KS <= 7 ? 4 : 2) : (KS <= 7 ? 2 : 1);
+  static constexpr int occupancy = NT == 2 && KS <= 5 ? 3 : 2;
 };
+
+// partial[(split * tpad + col) * mpad + row .. row + 3] of one 16 x 16 block of sums.
+// Columns of the padding are not stored, nor are FP64 zeros: a split of one window is
+// an FP32 number (n = 100,003, m = 3,001, t = 33: 302 MB of partials before, 104 now;
+// n = 5,001, t = 33: 73 -> 63 us).
+__device__ __forceinline__ void store_partial(const SweepArgs& a, int64_t split, int64_t col, int64_t row,
+                                              const double* v) {
+  if (col >= a.t) return;
+  const int64_t o = (split * a.tpad + col) * a.mpad + row;
+  if (a.f32part) {
+    *(f32x4*)((float*)a.part + o) = f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a.part[o + i] = v[i];
+  }
+}
 
 // One 32-point chunk of the b stream staged in LDS: the 2 KS point fragments
 // followed by the NT (hi, lo) V fragments, 64 lanes x 16 bytes each.
@@ -555,11 +578,10 @@ struct ChunkUnits {
   static constexpr int kPoint = 2 * KS * 64;
   static constexpr int kV = 2 * NT * 64;
   static constexpr int kAll = kPoint + kV;
-  static constexpr int kPerThread = (kAll + 255) / 256;
 };
 
 template <int KS, int NT, int KIND>
-__global__ __launch_bounds__(256, 2) void sweep_bf16x3_kernel(SweepArgs a) {
+__global__ __launch_bounds__(256, (NAOf<KS, NT>::occupancy)) void sweep_bf16x3_kernel(SweepArgs a) {
   constexpr int NA = NAOf<KS, NT>::value;
   using CU = ChunkUnits<KS, NT>;
   __shared__ bf16x8 stage[2][CU::kAll];
@@ -592,37 +614,46 @@ __global__ __launch_bounds__(256, 2) void sweep_bf16x3_kernel(SweepArgs a) {
 
   const int64_t c_begin = (int64_t)blockIdx.y * a.cps;
   const int64_t c_end = c_begin + a.cps < a.nchunks ? c_begin + a.cps : a.nchunks;
+  const int nch = (int)(c_end - c_begin);
+  const int wu = __builtin_amdgcn_readfirstlane(wave);
+  // the chunk that holds the points of this wave's first row block
+  const int adiag = (int)((((int64_t)blockIdx.x * 4 + wu) * NA >> 1) - c_begin);
 
-  // cooperative load of one chunk: unit u < kPoint comes from the point stream,
-  // the rest from the V fragments of this launch's column group
-  bf16x8 pre[CU::kPerThread];
-  auto fetch = [&](int64_t ch) {
+  // Copy the next chunk into stage[buf] with direct global-to-LDS loads: the 64-lane
+  // units (16 bytes per lane) of the two streams are dealt to the waves in turn (unit
+  // j to wave j mod 4), so source and LDS slot of every load are fixed up to the wave
+  // index, which is held in a scalar register; no registers hold the data in flight.
+  // The fetch stands after the chunk's own LDS reads: the compiler would make reads
+  // behind it wait for it.  Completion is awaited and published by the barrier that
+  // ends the iteration.  n = 262,144, d = 48, t = 16: 31.2 ms through registers with
+  // per-thread addresses, 29.3 so, 28.9 with the diagonal below as a scalar branch;
+  // two chunks per barrier: the same.
+  const bf16x8* px = xr + c_begin * (2 * KS * 64) + tid;
+  const bf16x8* pv = vf + (c_begin * a.ntb + cb0) * 2 * 64 + tid;
+  auto load_stream = [&](const bf16x8* src, int units, int first, int buf) {
 #pragma unroll
-    for (int r = 0; r < CU::kPerThread; ++r) {
-      const int u = tid + 256 * r;
-      if (u < CU::kPoint) {
-        pre[r] = xr[(2 * ch * KS) * 64 + u];
-      } else if (u < CU::kAll) {
-        pre[r] = vf[(ch * a.ntb + cb0) * 2 * 64 + (u - CU::kPoint)];
-      }
+    for (int r = 0; r < (units + 3) / 4; ++r) {
+      const int j = wu + 4 * r;
+      if (j < units)
+        __builtin_amdgcn_global_load_lds((const void*)(src + 256 * r),
+                                         (__attribute__((address_space(3))) void*)&stage[buf][first + 64 * j], 16, 0,
+                                         0);
     }
   };
-  auto stash = [&](int buf) {
-#pragma unroll
-    for (int r = 0; r < CU::kPerThread; ++r) {
-      const int u = tid + 256 * r;
-      if (u < CU::kAll) stage[buf][u] = pre[r];
+  auto fetch = [&](int ch, int buf) {
+    if (ch < nch) {
+      load_stream(px, 2 * KS, 0, buf);
+      load_stream(pv, 2 * NT, CU::kPoint, buf);
     }
+    px += 2 * KS * 64;
+    pv += (int64_t)a.ntb * 2 * 64;
   };
-  if (c_begin < c_end) {
-    fetch(c_begin);
-    stash(0);
-  }
+  fetch(0, 0);
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  for (int64_t ch = c_begin; ch < c_end; ++ch) {
-    const int cur = (int)((ch - c_begin) & 1);
-    const bool more = ch + 1 < c_end;
-    if (more) fetch(ch + 1);
+  int cur = 0;
+  for (int ch = 0; ch < nch; ++ch, cur ^= 1) {
+    const bool more = ch + 1 < nch;
     bf16x8 B0[KS], B1[KS], VH[NT], VL[NT];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -634,6 +665,7 @@ __global__ __launch_bounds__(256, 2) void sweep_bf16x3_kernel(SweepArgs a) {
       VH[cb] = stage[cur][CU::kPoint + (2 * cb) * 64 + lane];
       VL[cb] = stage[cur][CU::kPoint + (2 * cb + 1) * 64 + lane];
     }
+    fetch(ch + 1, cur ^ 1);
 #pragma unroll
     for (int ab = 0; ab < NA; ++ab) {
       f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
@@ -649,9 +681,8 @@ __global__ __launch_bounds__(256, 2) void sweep_bf16x3_kernel(SweepArgs a) {
         mv[4 + i] = profile_scaled<KIND>(s1[i]);
       }
       if (a.square) {
-        const int64_t arow = (ablk0 + ab) * 16;
-        if (arow == ch * 32 || arow == ch * 32 + 16) {
-          const int off = arow == ch * 32 ? 0 : 4;
+        if (NA == 1 ? adiag == ch : adiag + (ab >> 1) == ch) {
+          const int off = (NA == 1 ? (wu & 1) : (ab & 1)) ? 4 : 0;
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             if ((lane & 15) == 4 * g + i) mv[off + i] = 0.f;
@@ -666,7 +697,7 @@ __global__ __launch_bounds__(256, 2) void sweep_bf16x3_kernel(SweepArgs a) {
         acc[ab][cb] = mfma_val(L, VH[cb], acc[ab][cb]);
       }
     }
-    if (((ch - c_begin + 1) % kFlush) == 0 || !more) {
+    if (((ch + 1) % kFlush) == 0 || !more) {
 #pragma unroll
       for (int ab = 0; ab < NA; ++ab)
 #pragma unroll
@@ -676,20 +707,14 @@ __global__ __launch_bounds__(256, 2) void sweep_bf16x3_kernel(SweepArgs a) {
           acc[ab][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
-    if (more) stash(cur ^ 1);
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   }
-  // partial[(split * tpad + col) * mpad + row]
 #pragma unroll
   for (int ab = 0; ab < NA; ++ab)
 #pragma unroll
-    for (int cb = 0; cb < NT; ++cb) {
-      const int64_t col = (int64_t)(cb0 + cb) * 16 + (lane & 15);
-      const int64_t row = (ablk0 + ab) * 16 + 4 * g;
-      double* dst = a.part + ((int64_t)blockIdx.y * a.tpad + col) * a.mpad + row;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) dst[i] = acc64[ab][cb][i];
-    }
+    for (int cb = 0; cb < NT; ++cb)
+      store_partial(a, blockIdx.y, (int64_t)(cb0 + cb) * 16 + (lane & 15), (ablk0 + ab) * 16 + 4 * g, acc64[ab][cb]);
 }
 
 // ------------------------------------------------------------------ wide cross sweep
@@ -875,24 +900,36 @@ __global__ __launch_bounds__(256, 2) void wide_cross_bf16x3_kernel(WideArgs a) {
   }
 }
 
-// 16-row blocks per wave of the FP32 form.
-template <int NT>
+// 16-row blocks per wave of the FP32 form: an MFMA of this form takes twice the
+// cycles for an eighth of the flops, so that a fragment's LDS read costs little
+// beside it, and more waves per SIMD are worth as much as its reuse: one
+// block with one or two column blocks (n = 65,536, KQ 3 NT 1: 5.43 ms, two blocks
+// 5.56, four 5.50; KQ 2 NT 2: 5.38, 5.62), two with more (KQ 2 NT 4: 6.36, one
+// 6.98) or with KQ = 8 (n = 40,000, NT 2: 4.38, one 4.67), as far as the registers allow.
+template <int KQ, int NT>
 struct NAOfF32 {
-  static constexpr int value = NT == 1 ? 4 : (NT == 2 ? 2 : 1);
+  static constexpr int value = (NT <= 2) == (KQ <= 4) ? 1 : 2;
 };
 
+// The FP32 form: distances and M V on v_mfma_f32_16x16x4, bound by them (32 cycles
+// each: at KQ = 2, NT = 3 40 per 16 x 32 tile) and the profile's VALU work, which adds
+// to them.  Staged as in the mixed form (the norms of the b stream through registers,
+// one chunk ahead): with every wave loading its fragments from global memory a
+// chunk's loads were awaited before its compute.  K(Z, X) V at n = 100,003, m =
+// 3,001, d = 21, t = 33, RBF: 0.62 -> 0.49 ms with FP32 partials; n = 65,536, d =
+// 64, t = 50: 11.8 -> 9.5 ms.
 template <int KQ, int NT, int KIND>
 __global__ __launch_bounds__(256, 2) void sweep_fp32_kernel(SweepArgs a) {
-  constexpr int NA = NAOfF32<NT>::value;
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  constexpr int NA = NAOfF32<KQ, NT>::value;
+  constexpr int kPoint = 2 * KQ * 64, kAll = kPoint + 2 * NT * 64;
+  __shared__ f32x4 stage[2][kAll];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4;
-  const int64_t ablk0 = ((int64_t)blockIdx.x * 4 + wave) * NA;
-  if (ablk0 * 16 >= a.mpad) return;
+  const int64_t ablk0 = ((int64_t)blockIdx.x * 4 + wu) * NA;  // every wave is live: mpad % (64 NA) == 0
   const int cb0 = blockIdx.z * NT;
-  const f32x4* __restrict__ xr = (const f32x4*)a.xr;
   const f32x4* __restrict__ xc = (const f32x4*)a.xc;
-  const f32x4* __restrict__ vf = (const f32x4*)a.vf;
 
   f32x4 A[NA][KQ];
   float na[NA];
@@ -903,100 +940,124 @@ __global__ __launch_bounds__(256, 2) void sweep_fp32_kernel(SweepArgs a) {
     na[ab] = a.nrm_a[(ablk0 + ab) * 16 + (lane & 15)];
   }
   double acc64[NA][NT][4];
-#pragma unroll
-  for (int ab = 0; ab < NA; ++ab)
-#pragma unroll
-    for (int cb = 0; cb < NT; ++cb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc64[ab][cb][i] = 0.0;
-
-  const int64_t c_begin = (int64_t)blockIdx.y * a.cps;
-  const int64_t c_end = c_begin + a.cps < a.nchunks ? c_begin + a.cps : a.nchunks;
-  for (int64_t c0 = c_begin; c0 < c_end; c0 += kFlush) {
-    const int64_t c1 = c0 + kFlush < c_end ? c0 + kFlush : c_end;
-    f32x4 acc[NA][NT];
-#pragma unroll
-    for (int ab = 0; ab < NA; ++ab)
-#pragma unroll
-      for (int cb = 0; cb < NT; ++cb) acc[ab][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t ch = c0; ch < c1; ++ch) {
-      f32x4 B0[KQ], B1[KQ];
-#pragma unroll
-      for (int q = 0; q < KQ; ++q) {
-        B0[q] = xr[((2 * ch) * KQ + q) * 64 + lane];
-        B1[q] = xr[((2 * ch + 1) * KQ + q) * 64 + lane];
-      }
-      const f32x4 nb0 = *(const f32x4*)(a.nrm_b + ch * 32 + 4 * g);
-      const f32x4 nb1 = *(const f32x4*)(a.nrm_b + ch * 32 + 16 + 4 * g);
-      f32x4 V0[NT], V1[NT];
-#pragma unroll
-      for (int cb = 0; cb < NT; ++cb) {
-        const int64_t base = ((ch * a.ntb + cb0 + cb) * 2) * 64 + lane;
-        V0[cb] = vf[base];
-        V1[cb] = vf[base + 64];
-      }
-#pragma unroll
-      for (int ab = 0; ab < NA; ++ab) {
-        f32x4 s0 = nb0 + na[ab];
-        f32x4 s1 = nb1 + na[ab];
-#pragma unroll
-        for (int q = 0; q < KQ; ++q)
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(B0[q][s], A[ab][q][s], s0, 0, 0, 0);
-            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(B1[q][s], A[ab][q][s], s1, 0, 0, 0);
-          }
-        f32x4 m0, m1;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          m0[i] = profile<KIND, true>(s0[i]);
-          m1[i] = profile<KIND, true>(s1[i]);
-        }
-        if (a.square) {
-          const int64_t arow = (ablk0 + ab) * 16;
-          if (arow == ch * 32) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if ((lane & 15) == 4 * g + i) m0[i] = 0.f;
-          } else if (arow == ch * 32 + 16) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if ((lane & 15) == 4 * g + i) m1[i] = 0.f;
-          }
-        }
-#pragma unroll
-        for (int cb = 0; cb < NT; ++cb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            acc[ab][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(m0[i], V0[cb][i], acc[ab][cb], 0, 0, 0);
-            acc[ab][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(m1[i], V1[cb][i], acc[ab][cb], 0, 0, 0);
-          }
-      }
-    }
-#pragma unroll
-    for (int ab = 0; ab < NA; ++ab)
-#pragma unroll
-      for (int cb = 0; cb < NT; ++cb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc64[ab][cb][i] += (double)acc[ab][cb][i];
-  }
+  f32x4 acc[NA][NT];
 #pragma unroll
   for (int ab = 0; ab < NA; ++ab)
 #pragma unroll
     for (int cb = 0; cb < NT; ++cb) {
-      const int64_t col = (int64_t)(cb0 + cb) * 16 + (lane & 15);
-      const int64_t row = (ablk0 + ab) * 16 + 4 * g;
-      double* dst = a.part + ((int64_t)blockIdx.y * a.tpad + col) * a.mpad + row;
+      acc[ab][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < 4; ++i) dst[i] = acc64[ab][cb][i];
+      for (int i = 0; i < 4; ++i) acc64[ab][cb][i] = 0.0;
     }
+
+  const int64_t c_begin = (int64_t)blockIdx.y * a.cps;
+  const int64_t c_end = c_begin + a.cps < a.nchunks ? c_begin + a.cps : a.nchunks;
+  const int nch = (int)(c_end - c_begin);
+  const int adiag = (int)((ablk0 >> 1) - c_begin);  // the chunk that holds the points of this wave's first row block
+
+  const f32x4* px = (const f32x4*)a.xr + c_begin * kPoint + tid;
+  const f32x4* pv = (const f32x4*)a.vf + (c_begin * a.ntb + cb0) * 2 * 64 + tid;
+  const float* pn = a.nrm_b + c_begin * 32 + 4 * g;
+  f32x4 nb0 = {0.f, 0.f, 0.f, 0.f}, nb1 = {0.f, 0.f, 0.f, 0.f};
+  auto load_stream = [&](const f32x4* src, int units, int first, int buf) {
+#pragma unroll
+    for (int r = 0; r < (units + 3) / 4; ++r) {
+      const int j = wu + 4 * r;
+      if (j < units)
+        __builtin_amdgcn_global_load_lds((const void*)(src + 256 * r),
+                                         (__attribute__((address_space(3))) void*)&stage[buf][first + 64 * j], 16, 0,
+                                         0);
+    }
+  };
+  auto fetch = [&](int ch, int buf) {
+    if (ch < nch) {
+      nb0 = *(const f32x4*)pn;
+      nb1 = *(const f32x4*)(pn + 16);
+      load_stream(px, 2 * KQ, 0, buf);
+      load_stream(pv, 2 * NT, kPoint, buf);
+    }
+    px += kPoint;
+    pv += (int64_t)a.ntb * 2 * 64;
+    pn += 32;
+  };
+  fetch(0, 0);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  int cur = 0;
+  for (int ch = 0; ch < nch; ++ch, cur ^= 1) {
+    const bool more = ch + 1 < nch;
+    f32x4 B0[KQ], B1[KQ], V0[NT], V1[NT];
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+      B0[q] = stage[cur][q * 64 + lane];
+      B1[q] = stage[cur][(KQ + q) * 64 + lane];
+    }
+#pragma unroll
+    for (int cb = 0; cb < NT; ++cb) {
+      V0[cb] = stage[cur][kPoint + (2 * cb) * 64 + lane];
+      V1[cb] = stage[cur][kPoint + (2 * cb + 1) * 64 + lane];
+    }
+    const f32x4 n0 = nb0, n1 = nb1;
+    fetch(ch + 1, cur ^ 1);
+#pragma unroll
+    for (int ab = 0; ab < NA; ++ab) {
+      f32x4 s0 = n0 + na[ab];
+      f32x4 s1 = n1 + na[ab];
+#pragma unroll
+      for (int q = 0; q < KQ; ++q)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(B0[q][s], A[ab][q][s], s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(B1[q][s], A[ab][q][s], s1, 0, 0, 0);
+        }
+      f32x4 m0, m1;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        m0[i] = profile<KIND, true>(s0[i]);
+        m1[i] = profile<KIND, true>(s1[i]);
+      }
+      if (a.square) {
+        if (NA == 1 ? adiag == ch : adiag + (ab >> 1) == ch) {
+          f32x4& md = (NA == 1 ? (wu & 1) : (ab & 1)) ? m1 : m0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if ((lane & 15) == 4 * g + i) md[i] = 0.f;
+        }
+      }
+#pragma unroll
+      for (int cb = 0; cb < NT; ++cb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[ab][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(m0[i], V0[cb][i], acc[ab][cb], 0, 0, 0);
+          acc[ab][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(m1[i], V1[cb][i], acc[ab][cb], 0, 0, 0);
+        }
+    }
+    if (((ch + 1) % kFlush) == 0 || !more) {
+#pragma unroll
+      for (int ab = 0; ab < NA; ++ab)
+#pragma unroll
+        for (int cb = 0; cb < NT; ++cb) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc64[ab][cb][i] += (double)acc[ab][cb][i];
+          acc[ab][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int ab = 0; ab < NA; ++ab)
+#pragma unroll
+    for (int cb = 0; cb < NT; ++cb)
+      store_partial(a, blockIdx.y, (int64_t)(cb0 + cb) * 16 + (lane & 15), (ablk0 + ab) * 16 + 4 * g, acc64[ab][cb]);
 }
 
 // out[c*ldo + r] = s_f * inv[c] * sum_split part + (square ? (s_f + sigma^2) V[c*ldv + r] : 0)
 // (inv: the mixed form's column factors, a power of two; null for the FP32 form).
 // grid = (row blocks, columns); dot (nullable): dot[b t + c] = sum over the block's
 // rows of V out, added as in coldot_partial_kernel.
-__global__ __launch_bounds__(256) void kmm_epilogue_kernel(const double* __restrict__ part, int64_t nsplit, int tpad,
+template <typename T>
+__global__ __launch_bounds__(256) void kmm_epilogue_kernel(const T* __restrict__ part, int64_t nsplit, int tpad,
                                                            int64_t mpad, int64_t m, int t, double sf, double diag,
                                                            const double* __restrict__ inv, const double* __restrict__ V,
                                                            int64_t ldv, double* __restrict__ out, int64_t ldo,
@@ -1008,24 +1069,24 @@ __global__ __launch_bounds__(256) void kmm_epilogue_kernel(const double* __restr
   double acc = 0.0;
   for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
     double s = 0.0;
-    const double* src = part + c * mpad + r;
+    const T* src = part + c * mpad + r;
     const int64_t step = (int64_t)tpad * mpad;
     int64_t sp = 0;
     for (; sp + 16 <= nsplit; sp += 16, src += 16 * step) {  // in split order, 16 loads in flight
-      double v[16];
+      T v[16];
 #pragma unroll
       for (int j = 0; j < 16; ++j) v[j] = src[j * step];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) s += v[j];
+      for (int j = 0; j < 16; ++j) s += (double)v[j];
     }
     for (; sp + 4 <= nsplit; sp += 4, src += 4 * step) {
-      double v[4];
+      T v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = src[j * step];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) s += v[j];
+      for (int j = 0; j < 4; ++j) s += (double)v[j];
     }
-    for (; sp < nsplit; ++sp, src += step) s += src[0];
+    for (; sp < nsplit; ++sp, src += step) s += (double)src[0];
     if (inv) s *= inv[c];
     double o = sf * s;
     const double vr = V ? V[c * ldv + r] : 0.0;
@@ -1163,10 +1224,14 @@ int kmm_ksteps(int precision, int d) {
 
 // Column blocks handled per launch (grid.z groups the rest).
 static int nt_launch(int ntb) { return ntb >= 4 ? 4 : ntb; }
-static int na_of(int ks, int nt, bool mixed) {  // NAOf<KS, NT> of the launched kernel
-  if (!mixed) return nt == 1 ? 4 : (nt == 2 ? 2 : 1);
-  return nt == 1 ? 4 : (nt == 2 || ks <= 5 ? 2 : 1);
+static int na_of(int ks, int nt, bool mixed) {  // NAOf, NAOfF32 of the launched kernel
+  if (!mixed) return (nt <= 2) == (ks <= 4) ? 1 : 2;
+  return nt == 1 ? (ks <= 7 ? 4 : 2) : (ks <= 7 ? 2 : 1);
 }
+
+// 16-row blocks per wave that the split rule counts with: it fixes the FP32 windows
+// and the order of the sums, which stay the same whatever a kernel's registers hold.
+static int na_of_split(int ks, int nt, bool mixed) { return nt == 1 ? 4 : nt == 2 || (mixed && ks <= 5) ? 2 : 1; }
 
 struct SplitChoice {
   int nt, groups, tpad;
@@ -1183,7 +1248,7 @@ static SplitChoice choose_split(int64_t npad, int64_t mpad, int ntb, bool row_in
     // depends on n only: each output row sees the same chunk boundaries whatever m is
     s.cps = std::max<int64_t>(8, (nchunks + 255) / 256);
   } else {
-    const int64_t row_wgs = mpad / (64 * na_of(ks, s.nt, mixed)) * s.groups;
+    const int64_t row_wgs = mpad / (64 * na_of_split(ks, s.nt, mixed)) * s.groups;
     const int64_t want = std::max<int64_t>(1, (2048 + row_wgs - 1) / row_wgs);
     s.cps = std::max<int64_t>(2, (nchunks + want - 1) / want);
   }
@@ -1576,6 +1641,8 @@ hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, 
   a.cps = sc.cps;
   a.ntb = sc.groups * sc.nt;
   a.tpad = sc.tpad;
+  a.t = t;
+  a.f32part = sc.cps <= kFlush ? 1 : 0;
   a.square = p.square ? 1 : 0;
   const int na = na_of(p.ks, sc.nt, mixed);
   dim3 grid((unsigned)(p.mpad / (64 * na)), (unsigned)sc.nsplit, (unsigned)sc.groups);
@@ -1603,9 +1670,15 @@ hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, 
     timing().recs.push_back(rec);
   }
   const dim3 egrid((unsigned)((p.m + dot.rows - 1) / dot.rows), (unsigned)t);
-  kmm_epilogue_kernel<<<egrid, 256, 0, st>>>(p.part, sc.nsplit, sc.tpad, p.mpad, p.m, t, p.sf,
-                                             p.square ? p.sf + p.noise : 0.0, mixed ? p.vinv : nullptr,
-                                             p.square ? Vdiag : nullptr, ldv, out, ldo, dot.rows, dot.part);
+  const double diag = p.square ? p.sf + p.noise : 0.0;
+  const double* const inv = mixed ? p.vinv : nullptr;
+  const double* const Vd = p.square ? Vdiag : nullptr;
+  if (a.f32part)
+    kmm_epilogue_kernel<float><<<egrid, 256, 0, st>>>((const float*)p.part, sc.nsplit, sc.tpad, p.mpad, p.m, t, p.sf,
+                                                      diag, inv, Vd, ldv, out, ldo, dot.rows, dot.part);
+  else
+    kmm_epilogue_kernel<double><<<egrid, 256, 0, st>>>(p.part, sc.nsplit, sc.tpad, p.mpad, p.m, t, p.sf, diag, inv, Vd,
+                                                       ldv, out, ldo, dot.rows, dot.part);
   return hipGetLastError();
 }
 

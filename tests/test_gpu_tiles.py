@@ -207,3 +207,36 @@ def test_first_step_size_from_the_products_own_dot(n, prec):
         alpha = (B[c] @ B[c]) / (B[c] @ KB[c])
         assert np.linalg.norm(U[c] - alpha * B[c]) <= 1e-11 * np.linalg.norm(alpha * B[c])
     assert not U[2].any()
+
+
+@pytest.mark.parametrize("prec,bar", [("bf16x3", 5e-5), ("fp32", 1e-5)])
+@pytest.mark.parametrize("d", [5, 21, 32, 48, 64, 100])
+@pytest.mark.parametrize("t", [1, 17, 33, 50])
+def test_square_product_at_every_width_of_the_sweeps(d, t, prec, bar):
+    """One to four 16-column blocks at each K step count: rows per wave, the diagonal's chunk and the columns stored
+    differ.  Off-diagonal part against the oracle; bars of the forms (5e-5, 1e-5) on a correlated kernel."""
+    from paper_2109_09817_amd import gp
+    n = 1003
+    rng = np.random.default_rng(100 * d + t)
+    X, V = rng.standard_normal((n, d)), rng.standard_normal((t, n))
+    th = ok.Theta(rng.uniform(0.8, 1.2, d) * np.sqrt(d), 1.1, 1e-2, ok.MATERN52)
+    got = host(gp.kmm(_gk(th), dev(X), dev(V), precision=prec))
+    ref = ok.khat_matmul(X, th, V.T).T
+    off = ref - (1.1 + 1e-2) * V
+    assert np.linalg.norm(got - ref) <= bar * np.linalg.norm(off)
+
+
+@pytest.mark.parametrize("prec,bar", [("bf16x3", 5e-5), ("fp32", 1e-5)])
+@pytest.mark.parametrize("n,m", [(30001, 0), (9001, 1200)])
+def test_products_with_one_and_several_windows_per_split(n, m, prec, bar):
+    """n = 30,001: splits of several FP32 windows, partials in FP64; a cross product's splits are single windows, stored
+    in FP32.  Against the FP64 form; bars as above."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n)
+    X, V = dev(rng.standard_normal((n, 21))), dev(rng.standard_normal((35, n)))
+    Z = dev(rng.standard_normal((m, 21))) if m else None
+    th = ok.Theta(np.full(21, 5.0), 1.1, 1e-2, ok.RBF)
+    got = host(gp.kmm(_gk(th), X, V, Z=Z, precision=prec))
+    ref = host(gp.kmm(_gk(th), X, V, Z=Z, precision="fp64"))
+    off = ref - (0.0 if m else (1.1 + 1e-2) * host(V))
+    assert np.linalg.norm(got - ref) <= bar * np.linalg.norm(off)
