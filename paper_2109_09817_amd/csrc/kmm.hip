@@ -623,9 +623,7 @@ __global__ __launch_bounds__(256, (NAOf<KS, NT>::occupancy)) void sweep_bf16x3_k
   // units (16 bytes per lane) of the two streams are dealt to the waves in turn (unit
   // j to wave j mod 4), so source and LDS slot of every load are fixed up to the wave
   // index, which is held in a scalar register; no registers hold the data in flight.
-  // The fetch stands after the chunk's own LDS reads: the compiler would make reads
-  // behind it wait for it.  Completion is awaited and published by the barrier that
-  // ends the iteration.  n = 262,144, d = 48, t = 16: 31.2 ms through registers with
+  // Completion is awaited and published by the barrier that ends the iteration.  n = 262,144, d = 48, t = 16: 31.2 ms through registers with
   // per-thread addresses, 29.3 so, 28.9 with the diagonal below as a scalar branch;
   // two chunks per barrier: the same.
   const bf16x8* px = xr + c_begin * (2 * KS * 64) + tid;
@@ -726,31 +724,41 @@ __global__ __launch_bounds__(256, (NAOf<KS, NT>::occupancy)) void sweep_bf16x3_k
 // distances and the profile of row block w (16 rows) into an LDS tile (FP16
 // hi / lo, two buffers so that one barrier per chunk suffices); then every
 // wave multiplies the four row blocks' tiles by its own column blocks (cb = w,
-// w + 4, ...).  Both operand streams run one chunk ahead in registers: the
-// point fragments of chunk c + 1 are loaded during chunk c - 1 and written to
-// LDS at the top of chunk c, and each wave's V fragments of chunk c + 1 are
-// loaded during chunk c.  FP32 windows of kFlush chunks are added into the
-// split's FP64 partials (this workgroup owns those slots) in the same order
-// as the sweep above, so each output row's sums depend on n only, not on the
-// batch; a split of one window stores it as FP32, which is exact and halves
+// w + 4, ...), and of the column blocks left over (257 columns: one) its own row
+// block's tile, so that the waves do the same work: 51 instead of 60 MFMA in the
+// busiest one.  Both operand streams run ahead in registers: the point fragments
+// of chunk c + 1 are loaded during chunk c - 1 and written to LDS at the top of
+// chunk c, and each wave's V fragments of chunk c + 1 are loaded during chunk c
+// into the other of two register sets.  FP32 windows of kFlush chunks are
+// added into the split's FP64 partials (this workgroup owns those slots) in the
+// same order as the sweep above, so each output row's sums depend on n only, not
+// on the batch; a split of one window stores it as FP32, which is exact and halves
 // the partials' traffic.  Workgroups are numbered so that the row groups of
 // one split run back to back on one XCD and share the chunk data in its L2.
-constexpr int kWideNB = 5;  // column blocks per wave: 4 waves x 5 x 16 = 320 >= 1 + 256 columns
+//
+// A batch of 1,200 rows (n = 262,144, d = 48, 257 columns) is bound by the matrix
+// cores (busy 48%, about what a mix of MFMA and VALU work reaches here) and the
+// 2 x 313 MB of its partials: mean and variance 696 -> 648 us; 24 rows are bound by
+// the streams: 89 -> 86 us (354 MB: 74 us at the copy rate); with few columns
+// the leftover rule spreads them over the waves: 41 columns 429 -> 244 us, one
+// column 423 -> 189 us.  Tried: direct global-to-LDS loads for the points (the
+// compiler then waits for every load in flight at each LDS read and barrier: 718 us
+// with two register sets, 654 with one and three workgroups per CU, but 100 us at 24 rows).
+constexpr int kWideBlocks = 20;  // column blocks: 320 columns >= 1 + 256
 
 struct WideArgs {
   const void* xr;  // b stream (training points)
   const void* xc;  // query-row fragments
   const void* vf;  // V fragments, vstride 16-column blocks per chunk
   double* part;    // [split][tpad][mpad], FP64, or FP32 when f32part
-  int64_t mpad, nchunks, cps, nsplit;
-  int ntb, vstride, tpad, rgroups;
+  int64_t m, mpad, nchunks, cps, nsplit;
+  int t, ntb, vstride, tpad, rgroups;  // columns, column blocks
   int f32part;  // cps <= kFlush: each split is one FP32 window, stored exactly as FP32
 };
 
-template <int KS, int KIND>
+template <int KS, int FULL, int REST, int KIND>
 __global__ __launch_bounds__(256, 2) void wide_cross_bf16x3_kernel(WideArgs a) {
-  constexpr int kPoint = 2 * KS * 64;         // 16-byte units of one chunk's point fragments
-  constexpr int kPer = (kPoint + 255) / 256;  // units per thread
+  constexpr int kPoint = 2 * KS * 64;  // 16-byte units of one chunk's point fragments
   __shared__ bf16x8 stage[2][kPoint];
   __shared__ bf16x8 tile[2][4][2][64];  // [parity][row block][hi / lo][lane]
   // hardware workgroup i runs on XCD i % 8; the j-th workgroup an XCD receives
@@ -762,100 +770,98 @@ __global__ __launch_bounds__(256, 2) void wide_cross_bf16x3_kernel(WideArgs a) {
   if (split >= a.nsplit) return;  // whole workgroup, before any barrier
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int64_t ablk = (int64_t)rg * 4 + wave;  // this wave's row block (16 rows)
-  const bf16x8* __restrict__ xr = (const bf16x8*)a.xr;
+  const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t ablk = (int64_t)rg * 4 + wu;  // this wave's row block (16 rows)
+  const bool live = ablk * 16 < a.m;          // it holds a query row
+  const bool live2 = (int64_t)rg * 64 + 32 < a.m;  // so does one of the last two row blocks
   const bf16x8* __restrict__ xc = (const bf16x8*)a.xc;
-  const bf16x8* __restrict__ vf = (const bf16x8*)a.vf;
   bf16x8 A[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) A[ks] = xc[(ablk * KS + ks) * 64 + lane];
-  f32x4 acc[4][kWideNB];
+  f32x4 acc[4][FULL > 0 ? FULL : 1], accr[REST > 0 ? REST : 1];
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-    for (int jb = 0; jb < kWideNB; ++jb) acc[rb][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int jb = 0; jb < FULL; ++jb) acc[rb][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < REST; ++j) accr[j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int64_t c_begin = split * a.cps;
   const int64_t c_end = c_begin + a.cps < a.nchunks ? c_begin + a.cps : a.nchunks;
+  const int nch = (int)(c_end - c_begin);  // >= 1
 
-  // Loads are unconditional (indexes clamped into the chunk and to the last
-  // column block) so that the number in flight is the same on every path and
-  // the waits before each use cover only what that use needs.
+  // Loads are unconditional (units, blocks and chunks beyond the last repeat the last
+  // one), so that the number in flight is the same on every path and a wait covers
+  // only what its use needs.
+  constexpr int kPer = (2 * KS + 3) / 4;
+  const bf16x8* const xr = (const bf16x8*)a.xr + c_begin * kPoint + lane;
   bf16x8 pre[kPer];
-  auto fetch = [&](int64_t ch) {
+  auto fetch = [&](int ch) {  // the points of chunk ch, 64-lane unit j by wave j mod 4
+    const bf16x8* const src = xr + (int64_t)(ch < nch ? ch : nch - 1) * kPoint;
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-      const int u = tid + 256 * r < kPoint ? tid + 256 * r : kPoint - 1;
-      pre[r] = xr[(2 * ch * KS) * 64 + u];
-    }
+    for (int r = 0; r < kPer; ++r) pre[r] = src[64 * (wu + 4 * r < 2 * KS ? wu + 4 * r : 2 * KS - 1)];
   };
   auto stash = [&](int buf) {
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-      const int u = tid + 256 * r;
-      if (u < kPoint) stage[buf][u] = pre[r];
-    }
+    for (int r = 0; r < kPer; ++r)
+      if (wu + 4 * r < 2 * KS) stage[buf][64 * (wu + 4 * r) + lane] = pre[r];
   };
-  bf16x8 Vc[kWideNB][2], Vn[kWideNB][2];
-  auto vload = [&](int64_t ch, bf16x8(&Vx)[kWideNB][2]) {
+  const int64_t vstep = (int64_t)a.vstride * 2 * 64;
+  const bf16x8* const vf = (const bf16x8*)a.vf + c_begin * vstep;
+  struct VFrag {
+    bf16x8 f[FULL + REST][2];
+  };
+  auto vload = [&](int ch, VFrag& v) {
+    const bf16x8* const src = vf + (int64_t)(ch < nch ? ch : nch - 1) * vstep;
 #pragma unroll
-    for (int jb = 0; jb < kWideNB; ++jb) {
-      const int cb = wave + 4 * jb < a.ntb ? wave + 4 * jb : a.ntb - 1;
-      Vx[jb][0] = vf[((ch * a.vstride + cb) * 2 + 0) * 64 + lane];
-      Vx[jb][1] = vf[((ch * a.vstride + cb) * 2 + 1) * 64 + lane];
+    for (int j = 0; j < FULL + REST; ++j) {
+      int cb = j < FULL ? wu + 4 * j : 3 * FULL + j;
+      cb = cb < a.ntb ? cb : a.ntb - 1;
+      v.f[j][0] = (src + (int64_t)cb * 128)[lane];
+      v.f[j][1] = (src + (int64_t)cb * 128 + 64)[lane];
     }
   };
-  // the FP32 window into the split's FP64 partials (written by the first
-  // window); later windows read a column block's 16 partials at once, then add
+  // one column block's sums of row block rb into the partials
   bool first_window = true;
+  auto put = [&](int cb, int rb, const f32x4& v) {
+    const int64_t col = (int64_t)cb * 16 + (lane & 15);
+    if (col >= a.t) return;
+    const int64_t o = (split * a.tpad + col) * a.mpad + (int64_t)rg * 64 + 16 * rb + 4 * (lane >> 4);
+    if (a.f32part) {
+      *(f32x4*)((float*)a.part + o) = v;
+    } else {
+      double* dst = a.part + o;
+      double old[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) old[i] = first_window ? 0.0 : dst[i];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) dst[i] = old[i] + (double)v[i];
+    }
+  };
   auto flush = [&]() {
-    const int64_t row0 = (int64_t)rg * 64 + 4 * (lane >> 4);
 #pragma unroll
-    for (int jb = 0; jb < kWideNB; ++jb) {
-      const int cb = wave + 4 * jb;
-      if (cb < a.ntb && a.f32part) {
-        const int64_t col = (int64_t)cb * 16 + (lane & 15);
-        float* dst = (float*)a.part + (split * a.tpad + col) * a.mpad + row0;
+    for (int jb = 0; jb < FULL; ++jb)
 #pragma unroll
-        for (int rb = 0; rb < 4; ++rb) *(f32x4*)(dst + 16 * rb) = acc[rb][jb];
-      } else if (cb < a.ntb) {
-        const int64_t col = (int64_t)cb * 16 + (lane & 15);
-        double* dst = a.part + (split * a.tpad + col) * a.mpad + row0;
-        double old[4][4];
-#pragma unroll
-        for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) old[rb][i] = first_window ? 0.0 : dst[16 * rb + i];
-#pragma unroll
-        for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) dst[16 * rb + i] = old[rb][i] + (double)acc[rb][jb][i];
+      for (int rb = 0; rb < 4; ++rb) {
+        put(wu + 4 * jb, rb, acc[rb][jb]);
+        acc[rb][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) acc[rb][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < REST; ++j) {
+      put(4 * FULL + j, wu, accr[j]);
+      accr[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     first_window = false;
   };
 
-  fetch(c_begin);
-  stash(0);
-  if (c_begin + 1 < c_end) fetch(c_begin + 1);
-  vload(c_begin, Vc);
-  // drain the prologue's loads: the loop then starts with nothing in flight,
-  // as it does after every iteration (the V copy below waits for the loads
-  // issued at its top), so no wait inside the loop covers a newer load
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  for (int64_t ch = c_begin; ch < c_end; ++ch) {
-    const int cur = (int)((ch - c_begin) & 1);
-    const bool more = ch + 1 < c_end;
-    // stage[cur ^ 1] was last read by every wave's phase A of the previous
-    // chunk, which the previous barrier closed
-    if (more) stash(cur ^ 1);
-    if (ch + 2 < c_end) fetch(ch + 2);
-    if (more) vload(ch + 1, Vn);
+  auto chunk = [&](int ch, const VFrag& V, VFrag& Vn) {
+    const int cur = ch & 1;
+    // stage[cur ^ 1] was last read in phase A of the previous chunk
+    stash(cur ^ 1);
+    fetch(ch + 2);
+    vload(ch + 1, Vn);
     // phase A: this wave's row block against the chunk
-    {
+    bf16x8 H, L;
+    if (live) {
       f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
@@ -868,35 +874,54 @@ __global__ __launch_bounds__(256, 2) void wide_cross_bf16x3_kernel(WideArgs a) {
         mv[i] = profile_scaled<KIND>(s0[i]);
         mv[4 + i] = profile_scaled<KIND>(s1[i]);
       }
-      bf16x8 H, L;
       split_f16x8(mv, H, L);
-      tile[cur][wave][0][lane] = H;
-      tile[cur][wave][1][lane] = L;
+      tile[cur][wu][0][lane] = H;
+      tile[cur][wu][1][lane] = L;
     }
     // the four tiles of this chunk, and the next chunk's points, are in LDS
     __syncthreads();
-    // phase B: the four row blocks against this wave's column blocks
+    // phase B: the four row blocks against this wave's column blocks, two at a time
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-      const bf16x8 TH = tile[cur][rb][0][lane];
-      const bf16x8 TL = tile[cur][rb][1][lane];
+    for (int rp = 0; rp < 4; rp += 2) {
+      if (rp == 0 || live2) {
+        bf16x8 T[2][2];
+        if (FULL > 0) {
 #pragma unroll
-      for (int jb = 0; jb < kWideNB; ++jb) {
-        if (wave + 4 * jb < a.ntb) {
-          acc[rb][jb] = mfma_val(TH, Vc[jb][0], acc[rb][jb]);
-          acc[rb][jb] = mfma_val(TH, Vc[jb][1], acc[rb][jb]);
-          acc[rb][jb] = mfma_val(TL, Vc[jb][0], acc[rb][jb]);
+          for (int i = 0; i < 2; ++i) {
+            T[i][0] = tile[cur][rp + i][0][lane];
+            T[i][1] = tile[cur][rp + i][1][lane];
+          }
+        }
+#pragma unroll
+        for (int jb = 0; jb < FULL; ++jb) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            acc[rp + i][jb] = mfma_val(T[i][0], V.f[jb][0], acc[rp + i][jb]);
+            acc[rp + i][jb] = mfma_val(T[i][0], V.f[jb][1], acc[rp + i][jb]);
+            acc[rp + i][jb] = mfma_val(T[i][1], V.f[jb][0], acc[rp + i][jb]);
+          }
         }
       }
     }
-    if (((ch - c_begin + 1) % kFlush) == 0 || !more) flush();
-    if (more) {
+    if (live) {
 #pragma unroll
-      for (int jb = 0; jb < kWideNB; ++jb) {
-        Vc[jb][0] = Vn[jb][0];
-        Vc[jb][1] = Vn[jb][1];
+      for (int j = 0; j < REST; ++j) {
+        accr[j] = mfma_val(H, V.f[FULL + j][0], accr[j]);
+        accr[j] = mfma_val(H, V.f[FULL + j][1], accr[j]);
+        accr[j] = mfma_val(L, V.f[FULL + j][0], accr[j]);
       }
     }
+    if (((ch + 1) % kFlush) == 0 || ch + 1 == nch) flush();
+  };
+  VFrag V0, V1;
+  fetch(0);
+  stash(0);
+  fetch(1);
+  vload(0, V0);
+  __syncthreads();
+  for (int ch = 0; ch < nch; ch += 2) {
+    chunk(ch, V0, V1);
+    if (ch + 1 < nch) chunk(ch + 1, V1, V0);
   }
 }
 
@@ -1553,12 +1578,25 @@ hipError_t kmm_prepare_v(const KmmPlan& p, const double* V, int64_t ldv, int t, 
   return hipGetLastError();
 }
 
+template <int KS, int FULL, int REST>
+static void launch_wide_form(int kind, dim3 grid, const WideArgs& a, hipStream_t st) {
+  if (kind == GP_MATERN52)
+    wide_cross_bf16x3_kernel<KS, FULL, REST, GP_MATERN52><<<grid, 256, 0, st>>>(a);
+  else
+    wide_cross_bf16x3_kernel<KS, FULL, REST, GP_RBF><<<grid, 256, 0, st>>>(a);
+}
+
 template <int KS>
 static void launch_wide(int kind, dim3 grid, const WideArgs& a, hipStream_t st) {
-  if (kind == GP_MATERN52)
-    wide_cross_bf16x3_kernel<KS, GP_MATERN52><<<grid, 256, 0, st>>>(a);
-  else
-    wide_cross_bf16x3_kernel<KS, GP_RBF><<<grid, 256, 0, st>>>(a);
+  // 4 FULL + REST >= ntb column blocks; up to two of a form's are beyond the last
+  const int ntb = a.ntb;
+  if (ntb == 1) return launch_wide_form<KS, 0, 1>(kind, grid, a, st);
+  if (ntb <= 3) return launch_wide_form<KS, 0, 3>(kind, grid, a, st);
+  if (ntb <= 5) return launch_wide_form<KS, 1, 1>(kind, grid, a, st);
+  if (ntb <= 9) return launch_wide_form<KS, 2, 1>(kind, grid, a, st);
+  if (ntb <= 13) return launch_wide_form<KS, 3, 1>(kind, grid, a, st);
+  if (ntb <= 17) return launch_wide_form<KS, 4, 1>(kind, grid, a, st);
+  launch_wide_form<KS, 5, 0>(kind, grid, a, st);
 }
 
 // Row-independent BF16X3 cross products (prediction): the wide sweep, same splits and partials.
@@ -1573,6 +1611,8 @@ static hipError_t kmm_sweep_wide(const KmmPlan& p, int t, const SplitChoice& sc,
   a.nchunks = p.nchunks;
   a.cps = sc.cps;
   a.nsplit = sc.nsplit;
+  a.t = t;
+  a.m = p.m;
   a.ntb = (t + 15) / 16;
   a.vstride = sc.groups * sc.nt;  // the V fragments hold whole launch groups
   a.tpad = a.ntb * 16;
@@ -1627,7 +1667,7 @@ hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, 
   const bool mixed = p.precision == GP_PREC_BF16X3;
   const int ntb = (t + 15) / 16;
   const SplitChoice sc = choose_split(p.npad, p.mpad, ntb, row_independent, p.ks, p.precision == GP_PREC_BF16X3);
-  if (row_independent && mixed && !p.square && ntb <= 4 * kWideNB && p.ks <= 7)
+  if (row_independent && mixed && !p.square && ntb <= kWideBlocks && p.ks <= 7)
     return kmm_sweep_wide(p, t, sc, out, ldo, st);
   SweepArgs a;
   a.xr = p.xr;

@@ -240,3 +240,21 @@ def test_products_with_one_and_several_windows_per_split(n, m, prec, bar):
     ref = host(gp.kmm(_gk(th), X, V, Z=Z, precision="fp64"))
     off = ref - (0.0 if m else (1.1 + 1e-2) * host(V))
     assert np.linalg.norm(got - ref) <= bar * np.linalg.norm(off)
+
+
+@pytest.mark.parametrize("n,m,t", [(3000, 1, 1), (3000, 17, 16), (2999, 33, 17), (3000, 64, 48), (3000, 65, 49),
+                                   (3000, 130, 80), (3000, 40, 81), (3000, 97, 144), (3000, 16, 145), (3000, 66, 208),
+                                   (3000, 50, 209), (3000, 80, 257), (3000, 31, 272), (3000, 100, 273),
+                                   (2001, 48, 320), (300001, 40, 20)])
+def test_wide_cross_product_at_its_column_forms(n, m, t):
+    """Column blocks per wave and left over, query rows that leave row blocks empty, and splits of several windows
+    (n = 300,001).  Against the FP64 form; the mixed form's bar, 5e-5."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n + t)
+    d = (5, 32, 48, 64)[t % 4]
+    X, V = dev(rng.standard_normal((n, d))), dev(rng.standard_normal((t, n)))
+    Z = dev(rng.standard_normal((m, d)))
+    kern = _gk(ok.Theta(np.full(d, 3.0), 1.1, 1e-2, ok.MATERN52 if t % 2 else ok.RBF))
+    got = host(gp.kmm(kern, X, V, Z=Z, precision="bf16x3"))
+    ref = host(gp.kmm(kern, X, V, Z=Z, precision="fp64"))
+    assert np.linalg.norm(got - ref) <= 5e-5 * np.linalg.norm(ref)
