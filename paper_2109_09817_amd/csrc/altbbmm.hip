@@ -485,7 +485,7 @@ int run_nystrom_chol(const gp_kernel* kern, const double* X, int64_t n, const in
   // F^T = L_M^{-1} K_MX (r x n row-major, i.e. F column-major)
   GPK_HIP(dense_lower_times(r, n, A, r, E, n, T, n, st));
   // G = F^T F + sigma^2 I (lower tiles), L_G, L_G^{-1}
-  GPK_HIP(dense_gram(r, n, T, n, G, r, st));
+  GPK_HIP(dense_gram(r, n, T, n, G, r, E, n * (int64_t)r, st));  // E is free until the last product
   add_diag_kernel<<<(unsigned)((r + thr - 1) / thr), thr, 0, st>>>(G, r, kern->noise);
   GPK_HIP(hipGetLastError());
   GPK_HIP(dense_cholesky(G, r, info + 1, Dinv, st));

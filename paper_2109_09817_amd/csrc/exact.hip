@@ -534,13 +534,14 @@ __global__ __launch_bounds__(256) void gemm64_f64_kernel(GemmArgs g) {
 // doubles, or x-major [x][k], pitch 18, both with 16-byte rows and distinct
 // banks for the 32 lanes of a half-wave.  Interior chunks load 16 bytes per
 // lane (rows need 8-byte alignment only), edges element by element.
-// n = 32,768, r = 4,096: L F takes 9.4 ms (59 TF/s of useful flops) against 24 ms
-// in 64-wide tiles over the full square; trailing updates of the exact GP (k = 256)
+// n = 32,768, r = 4,096: L F takes 9.2 ms (61 TF/s of useful flops; 9.6 with vector
+// address arithmetic) against 24 ms in 64-wide tiles over the full square; trailing updates of the exact GP (k = 256)
 // reach 39 TF/s against 28.
 constexpr int kGt = 128;       // tile edge
 constexpr int kGk = 16;        // k per chunk
 constexpr int kGKLd = kGt + 16;
 constexpr int kGXLd = kGk + 2;
+constexpr int64_t kGemmMaxLd = 1 << 22;  // 127 rows within 2^32 bytes
 constexpr int kGBuf = kGt * kGXLd > kGk * kGKLd ? kGt * kGXLd : kGk * kGKLd;
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
@@ -550,45 +551,58 @@ __device__ __forceinline__ int gemm_at(int k, int x) {
   return KMAJOR ? k * kGKLd + x : x * kGXLd + k;
 }
 
-// This thread's four 16-byte pieces of a 128 x 16 operand chunk at (x0, k0).
+// This thread's four 16-byte pieces of the 128 x 16 operand chunks of a tile at x0.
 // KMAJOR: element (x, k) at P[k ld + x], otherwise P[x ld + k]; x >= xn reads
-// some valid row (its outputs are not stored), k >= kn reads as zero.
+// some valid row (its outputs are not stored), k >= kn reads as zero.  A piece's
+// address is a scalar pointer to the chunk plus a byte offset within 32 bits (ld <=
+// kGemmMaxLd) that the tile fixes, so that a load costs no vector instruction:
+// these add to the time of the MFMAs.
 template <bool KMAJOR>
-__device__ __forceinline__ void gemm_load(const double* __restrict__ P, int64_t ld, int64_t x0, int64_t xn, int64_t k0,
-                                          int64_t kn, f64x2 (&v)[4]) {
-  const int tid = threadIdx.x;
-  if constexpr (KMAJOR) {
-    const int x = 2 * (tid & 63), k = tid >> 6;
-    if (x0 + kGt <= xn && k0 + kGk <= kn) {
-      const double* src = P + (k0 + k) * ld + x0 + x;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = *(const f64x2u*)(src + 4 * u * ld);
+struct GemmOperand {
+  const double* P;
+  int64_t ld, x0, xn, kn;
+  uint32_t off[KMAJOR ? 1 : 4];
+  __device__ __forceinline__ GemmOperand(const double* P_, int64_t ld_, int64_t x0_, int64_t xn_, int64_t kn_)
+      : P(P_), ld(ld_), x0(x0_), xn(xn_), kn(kn_) {
+    const int tid = threadIdx.x;
+    if constexpr (KMAJOR) {
+      off[0] = 8u * ((uint32_t)(tid >> 6) * (uint32_t)ld + 2u * (tid & 63));
     } else {
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int64_t xx = x0 + x + e < xn ? x0 + x + e : xn - 1;
-          const int64_t kk = k0 + k + 4 * u;
-          v[u][e] = kk < kn ? P[kk * ld + xx] : 0.0;
-        }
-    }
-  } else {
-    const int x = tid >> 3, k = 2 * (tid & 7);
-    const bool inner = k0 + kGk <= kn;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t xx = x0 + x + 32 * u < xn ? x0 + x + 32 * u : xn - 1;
-      const double* src = P + xx * ld + k0 + k;
-      if (inner) {
-        v[u] = *(const f64x2u*)src;
-      } else {
-        v[u][0] = k0 + k < kn ? src[0] : 0.0;
-        v[u][1] = k0 + k + 1 < kn ? src[1] : 0.0;
+      for (int u = 0; u < 4; ++u) {
+        const int64_t x = (tid >> 3) + 32 * u;
+        off[u] = 8u * ((uint32_t)(x0 + x < xn ? x : xn - 1 - x0) * (uint32_t)ld + 2u * (tid & 7));
       }
     }
   }
-}
+  __device__ __forceinline__ void load(int64_t k0, f64x2 (&v)[4]) const {
+    if (KMAJOR ? x0 + kGt <= xn && k0 + kGk <= kn : k0 + kGk <= kn) {
+      const char* src = (const char*)(KMAJOR ? P + k0 * ld + x0 : P + x0 * ld + k0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if constexpr (KMAJOR)
+          v[u] = *(const f64x2u*)(src + (int64_t)32 * u * ld + off[0]);
+        else
+          v[u] = *(const f64x2u*)(src + off[u]);
+      }
+      return;
+    }
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        if constexpr (KMAJOR) {
+          const int64_t x = x0 + 2 * (tid & 63) + e < xn ? x0 + 2 * (tid & 63) + e : xn - 1;
+          const int64_t k = k0 + (tid >> 6) + 4 * u;
+          v[u][e] = k < kn ? P[k * ld + x] : 0.0;
+        } else {
+          const double* src = (const double*)((const char*)(P + x0 * ld + k0) + off[u]);
+          v[u][e] = k0 + 2 * (tid & 7) + e < kn ? src[e] : 0.0;
+        }
+      }
+  }
+};
 
 template <bool KMAJOR>
 __device__ __forceinline__ void gemm_store(double* buf, const f64x2 (&v)[4]) {
@@ -601,41 +615,28 @@ __device__ __forceinline__ void gemm_store(double* buf, const f64x2 (&v)[4]) {
   }
 }
 
-template <bool TA, bool TB, bool LOWER, int MODE>
-__global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) double As[2][kGBuf], Bs[2][kGBuf];
-  const int64_t p = blockIdx.y;
-  const double* __restrict__ A = g.A + p * g.sA;
-  const double* __restrict__ B = g.B + p * g.sB;
-  double* C = g.C + p * g.sC;
-  const int64_t m = g.mstep > 0 ? (g.m - p * g.mstep < g.mmax ? g.m - p * g.mstep : g.mmax) : g.m;
-  const int64_t kall = g.mstep > 0 && g.tri == kTriA ? m : g.kk;
-  const int64_t lda = g.lda, ldb = g.ldb, ldc = g.ldc, nn = g.nn;
-  int64_t R, Cc, kbeg, kn;
-  if (!gemm_tile<LOWER, kGt>(g, m, kall, R, Cc, kbeg, kn)) return;  // whole workgroup
+// A(R.., kbeg..kn) B(kbeg..kn, Cc..) of one tile by one workgroup: acc[i][j] is the 16 x 16
+// block (i, j) of this wave's quadrant.  nch >= 1 chunks from kfirst in steps of kstep.
+template <bool TA, bool TB>
+__device__ __forceinline__ void gemm128_mac(const GemmOperand<TA>& opa, const GemmOperand<!TB>& opb, int64_t kfirst,
+                                            int64_t kstep, int nch, double (*As)[kGBuf], double (*Bs)[kGBuf],
+                                            f64x4 (&acc)[4][4]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r0 = 64 * (wave >> 1), c0 = 64 * (wave & 1);
   const int lr = lane & 15, lk = lane >> 4;
-  f64x4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
   f64x2 av[4], bv[4];
-  const int64_t nch = (kn - kbeg + kGk - 1) / kGk;
-  const int64_t kfirst = gemm_descends(g.tri) ? kbeg + (nch - 1) * kGk : kbeg;
-  const int64_t kstep = gemm_descends(g.tri) ? -kGk : kGk;
-  gemm_load<TA>(A, lda, R, m, kfirst, kn, av);
-  gemm_load<!TB>(B, ldb, Cc, nn, kfirst, kn, bv);
+  opa.load(kfirst, av);
+  opb.load(kfirst, bv);
   gemm_store<TA>(As[0], av);
   gemm_store<!TB>(Bs[0], bv);
   __syncthreads();
-  int cur = 0;
-  for (int64_t c = 0, kc = kfirst; c < nch; ++c, kc += kstep, cur ^= 1) {
+  int64_t kc = kfirst;
+  auto chunk = [&](int c, int cur) {
     const bool more = c + 1 < nch;
     if (more) {
-      gemm_load<TA>(A, lda, R, m, kc + kstep, kn, av);
-      gemm_load<!TB>(B, ldb, Cc, nn, kc + kstep, kn, bv);
+      kc += kstep;
+      opa.load(kc, av);
+      opb.load(kc, bv);
     }
 #pragma unroll
     for (int k = 0; k < kGk; k += 4) {
@@ -655,7 +656,37 @@ __global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(GemmArgs g) {
       gemm_store<!TB>(Bs[cur ^ 1], bv);
     }
     __syncthreads();
+  };
+  for (int c = 0; c < nch; c += 2) {  // the buffers' addresses are constants
+    chunk(c, 0);
+    if (c + 1 < nch) chunk(c + 1, 1);
   }
+}
+
+template <bool TA, bool TB, bool LOWER, int MODE>
+__global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) double As[2][kGBuf], Bs[2][kGBuf];
+  const int64_t p = blockIdx.y;
+  const double* __restrict__ A = g.A + p * g.sA;
+  const double* __restrict__ B = g.B + p * g.sB;
+  double* C = g.C + p * g.sC;
+  const int64_t m = g.mstep > 0 ? (g.m - p * g.mstep < g.mmax ? g.m - p * g.mstep : g.mmax) : g.m;
+  const int64_t kall = g.mstep > 0 && g.tri == kTriA ? m : g.kk;
+  const int64_t ldc = g.ldc, nn = g.nn;
+  int64_t R, Cc, kbeg, kn;
+  if (!gemm_tile<LOWER, kGt>(g, m, kall, R, Cc, kbeg, kn)) return;  // whole workgroup
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r0 = 64 * (wave >> 1), c0 = 64 * (wave & 1);
+  const int lr = lane & 15, lk = lane >> 4;
+  f64x4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const int nch = (int)((kn - kbeg + kGk - 1) / kGk);
+  const bool desc = gemm_descends(g.tri);
+  gemm128_mac<TA, TB>(GemmOperand<TA>(A, g.lda, R, m, kn), GemmOperand<!TB>(B, g.ldb, Cc, nn, kn),
+                      desc ? kbeg + (int64_t)(nch - 1) * kGk : kbeg, desc ? -kGk : kGk, nch, As, Bs, acc);
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb) {
     double old[4][4];
@@ -678,6 +709,83 @@ __global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(GemmArgs g) {
   }
 }
 
+// C = A A^T over the lower 128-wide tiles (A m x kk), its k range split where the
+// tiles alone leave CUs idle: the tiles beyond a multiple of 512 (two workgroups
+// per CU) are cut into `parts` runs of k each, whose products go to slabs
+// [tile][part][128][128] and are added in the order of k.  m = 4,096, kk = 32,768:
+// 528 tiles, of which the last 16 took half as long again as the first 512:
+// 13.6 -> 9.4 ms.  m = 1,024, kk = 8,192: 0.45 ms in 64-wide
+// tiles, 0.22 so.
+struct GramSplit {
+  int64_t full;  // tiles computed whole
+  int rest, parts;
+};
+
+__global__ __launch_bounds__(256, 2) void gram128_f64_kernel(GemmArgs g, GramSplit gs, double* slab) {
+  __shared__ __attribute__((aligned(16))) double As[2][kGBuf], Bs[2][kGBuf];
+  const int64_t h = blockIdx.x;
+  int64_t b, slot = -1;
+  int c0 = 0, c1 = (int)((g.kk + kGk - 1) / kGk);
+  if (h < gs.full) {  // as in gemm_tile, each XCD a contiguous run
+    const int64_t xcd = h & 7, q8 = gs.full >> 3, rem8 = gs.full & 7;
+    b = xcd * q8 + (xcd < rem8 ? xcd : rem8) + (h >> 3);
+  } else {
+    slot = h - gs.full;
+    b = gs.full + slot / gs.parts;
+    const int part = (int)(slot % gs.parts), n = c1;
+    c0 = (int)((int64_t)n * part / gs.parts);
+    c1 = (int)((int64_t)n * (part + 1) / gs.parts);
+  }
+  int64_t ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+  while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
+  while (ti * (ti + 1) / 2 > b) --ti;
+  const int64_t R = kGt * ti, Cc = kGt * (b - ti * (ti + 1) / 2);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  f64x4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  gemm128_mac<false, true>(GemmOperand<false>(g.A, g.lda, R, g.m, g.kk), GemmOperand<false>(g.A, g.lda, Cc, g.m, g.kk),
+                           (int64_t)c0 * kGk, kGk, c1 - c0, As, Bs, acc);
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 64 * (wave >> 1) + 16 * rb + lk + 4 * i, c = 64 * (wave & 1) + 16 * cb + lr;
+        if (slot >= 0)
+          slab[slot * (kGt * kGt) + r * kGt + c] = acc[rb][cb][i];
+        else if (R + r < g.m && Cc + c < g.m)
+          g.C[(R + r) * g.ldc + Cc + c] = acc[rb][cb][i];
+      }
+}
+
+// The split tiles' sums.  grid = (64, rest).
+__global__ __launch_bounds__(256) void gram_slab_sum_kernel(GemmArgs g, GramSplit gs, const double* __restrict__ slab) {
+  const int64_t b = gs.full + blockIdx.y;
+  int64_t ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+  while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
+  while (ti * (ti + 1) / 2 > b) --ti;
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int64_t row = kGt * ti + e / kGt, col = kGt * (b - ti * (ti + 1) / 2) + e % kGt;
+  if (row >= g.m || col >= g.m) return;
+  const double* src = slab + (int64_t)blockIdx.y * gs.parts * (kGt * kGt) + e;
+  double s = 0.0;
+  int p = 0;
+  for (; p + 8 <= gs.parts; p += 8) {
+    double v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = src[(int64_t)(p + j) * (kGt * kGt)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) s += v[j];
+  }
+  for (; p < gs.parts; ++p) s += src[(int64_t)p * (kGt * kGt)];
+  g.C[row * g.ldc + col] = s;
+}
+
 static int64_t tile_count(bool lower, int64_t m, int64_t nn, int64_t edge) {
   const int64_t nrt = (m + edge - 1) / edge, nct = (nn + edge - 1) / edge;
   return lower ? nrt * (nrt + 1) / 2 : nrt * nct;
@@ -697,6 +805,8 @@ static hipError_t gemm_launch(GemmArgs g, int64_t batch, hipStream_t st) {
   const int64_t tiles = tile_count(LOWER, rows, g.nn, edge);
   if (tiles <= 0 || batch <= 0) return hipSuccess;
   if (tiles > 0x7fffffff || batch > 65535 || g.kk < 1) return hipErrorInvalidValue;
+  if constexpr (WIDE)
+    if (g.lda > kGemmMaxLd || g.ldb > kGemmMaxLd) return gemm_launch<TA, TB, LOWER, MODE, false>(g, batch, st);
   g.nrt = (int)((rows + edge - 1) / edge);
   g.nct = (int)((g.nn + edge - 1) / edge);
   const dim3 grid((unsigned)tiles, (unsigned)batch);
@@ -1062,10 +1172,41 @@ hipError_t dense_lower_times(int64_t m, int64_t nn, const double* L, int64_t ldl
                                    : gemm_launch<false, false, false, kAssign, false>(g, 1, st);
 }
 
-hipError_t dense_gram(int64_t m, int64_t kk, const double* A, int64_t lda, double* C, int64_t ldc, hipStream_t st) {
+// The split that ends soonest: 512 workgroups run at a time, up to 256 of a last
+// round at twice the speed; a part has at least 16 chunks of k, and the slabs
+// fit the scratch memory.
+static GramSplit gram_split(int64_t tiles, int64_t kk, int64_t scratch_doubles) {
+  GramSplit gs{tiles, 0, 1};
+  const int64_t rest = tiles % 512;
+  if (rest == 0) return gs;
+  const int64_t cap = std::min((kk + kGk - 1) / kGk / 16, scratch_doubles / (rest * kGt * kGt));
+  double best = 1e300;
+  int parts = 1;
+  for (int64_t p = 1; p <= std::max<int64_t>(1, std::min<int64_t>(cap, 512)); ++p) {
+    const int64_t items = rest * p, last = items % 512;
+    const double t = ((double)(items / 512) + (last == 0 ? 0.0 : last <= 256 ? 0.5 : 1.0)) / (double)p;
+    if (t < 0.98 * best) {
+      best = t;
+      parts = (int)p;
+    }
+  }
+  if (parts > 1) gs = GramSplit{tiles - rest, (int)rest, parts};
+  return gs;
+}
+
+hipError_t dense_gram(int64_t m, int64_t kk, const double* A, int64_t lda, double* C, int64_t ldc, double* scratch,
+                      int64_t scratch_doubles, hipStream_t st) {
+  if (m < 1 || kk < 1) return hipErrorInvalidValue;
   const GemmArgs g{A, lda, 0, A, lda, 0, C, ldc, 0, m, m, kk, 0, 0, 0, 0, kTriNone};
-  return use_gemm128(true, m, m) ? gemm_launch<false, true, true, kAssign, true>(g, 1, st)
-                                 : gemm_launch<false, true, true, kAssign, false>(g, 1, st);
+  const int64_t tiles = tile_count(true, m, m, kGt);
+  const GramSplit gs = gram_split(tiles, kk, scratch_doubles);
+  if (lda > kGemmMaxLd || (gs.rest == 0 && !use_gemm128(true, m, m)))
+    return gemm_launch<false, true, true, kAssign, false>(g, 1, st);
+  const int64_t items = gs.full + (int64_t)gs.rest * gs.parts;
+  if (items > 0x7fffffff) return hipErrorInvalidValue;
+  gram128_f64_kernel<<<(unsigned)items, 256, 0, st>>>(g, gs, scratch);
+  if (gs.rest > 0) gram_slab_sum_kernel<<<dim3(kGt * kGt / 256, (unsigned)gs.rest), 256, 0, st>>>(g, gs, scratch);
+  return hipGetLastError();
 }
 
 size_t dense_dinv_doubles(int64_t n) { return (size_t)((n + kEb - 1) / kEb) * kEb * kEb; }

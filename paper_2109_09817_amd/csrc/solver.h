@@ -107,7 +107,8 @@ hipError_t pivchol_launch_step(const double* X, int64_t n, const gp_kernel* kern
 hipError_t dense_lower_times(int64_t m, int64_t nn, const double* L, int64_t ldl, const double* B, int64_t ldb,
                              double* C, int64_t ldc, hipStream_t st);
 // C (m x m) = A A^T for A m x kk: the tiles on and below the diagonal.
-hipError_t dense_gram(int64_t m, int64_t kk, const double* A, int64_t lda, double* C, int64_t ldc, hipStream_t st);
+hipError_t dense_gram(int64_t m, int64_t kk, const double* A, int64_t lda, double* C, int64_t ldc, double* scratch,
+                      int64_t scratch_doubles, hipStream_t st);
 // Doubles of the diagonal-block scratch of the two routines below.
 size_t dense_dinv_doubles(int64_t n);
 // In-place lower Cholesky factor of the symmetric n x n A (lower triangle read);

@@ -258,3 +258,22 @@ def test_wide_cross_product_at_its_column_forms(n, m, t):
     got = host(gp.kmm(kern, X, V, Z=Z, precision="bf16x3"))
     ref = host(gp.kmm(kern, X, V, Z=Z, precision="fp64"))
     assert np.linalg.norm(got - ref) <= 5e-5 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("n,r", [(700, 1), (5001, 127), (9000, 128), (5000, 129), (20011, 300), (1600, 1500)])
+def test_large_rank_factor_with_its_gram_split(n, r):
+    """F F^T with k split over workgroups (one to 78 tiles, ragged runs of k).  E against numpy; rounding is amplified
+    by cond(K_MM + delta I), below 1e4 on this data: bar 1e-11."""
+    import scipy.linalg as sl
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n + r)
+    X = rng.standard_normal((n, 6))
+    th = ok.Theta(rng.uniform(0.3, 0.6, 6), 1.0, 1e-2, ok.MATERN52)
+    M = np.sort(rng.choice(n, r, replace=False))
+    E = host(gp.nystrom_chol_precond(_gk(th), dev(X), M).E)
+    KMX = ok.kernel(X[M], X, th)
+    KMM = KMX[:, M] + 1e-10 * r * np.eye(r)
+    assert np.linalg.cond(KMM) < 1e4
+    F = sl.solve_triangular(np.linalg.cholesky(KMM), KMX, lower=True)
+    ref = sl.solve_triangular(np.linalg.cholesky(F @ F.T + 1e-2 * np.eye(r)), F, lower=True)
+    assert np.linalg.norm(E - ref) <= 1e-11 * np.linalg.norm(ref)
