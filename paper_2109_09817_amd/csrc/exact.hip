@@ -137,10 +137,8 @@ __device__ __forceinline__ void chol_inverse_16(double (&a)[kDb], double (&x)[kD
 // follow block diagonal by block diagonal, X_ij = -X_ii sum_k L_ik X_kj.
 // Column by column over all 64 (128 barriers, then 64 dependent rows of the
 // inverse) it took 74 us; this form: 29 us (n = 7,503: 118 of them, 30.1 -> 24.8 ms).
-__global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A, int64_t n, int64_t j0, int jb,
-                                                         int* __restrict__ info, double* __restrict__ Dinv) {
-  __shared__ double Ls[kEb * kDbLd];
-  __shared__ double Xs[kEb * kDbLd];
+__device__ __forceinline__ void potrf_diag(double* __restrict__ A, int64_t n, int64_t j0, int jb, int* __restrict__ info,
+                                           double* __restrict__ Dinv, double* Ls, double* Xs) {
   constexpr int kPer = kEb * kEb / 256;
   const int tid = threadIdx.x;
   {
@@ -236,8 +234,8 @@ __global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A,
 //   P(r, k) = PT ? Pm[(p0 + k) ldp + pr + r] : Pm[(pr + r) ldp + p0 + k]
 //   Q(k, c) = QT ? Qm[(qc + c) ldq + q0 + k] : Qm[(q0 + k) ldq + qc + c]
 // where pr = R (pfix < 0) or pfix, and qc = Cc (qfix < 0) or qfix.  Tile (ti,
-// tj) has R = rbase + 64 ti, Cc = cbase + 64 tj; LOWER enumerates tj <= ti <
-// nrt, otherwise the nrt x nct rectangle.  Output rows and columns at or beyond
+// tj) has R = rbase + 64 ti, Cc = cbase + 64 tj; LOWER enumerates tj <= ti of the
+// nrt x nct (nct <= nrt) rectangle, otherwise all of it.  Output rows and columns at or beyond
 // n are skipped (their operands read as 0).  Every operand is read before
 // the tile is written, so C's tile may be one of the operand tiles (never
 // another workgroup's).  The products run on the FP64 matrix cores
@@ -256,6 +254,14 @@ __device__ __forceinline__ int lds_at(int k, int x) {
   return KMAJOR ? k * kKMajorLd + x : x * kXMajorLd + k;
 }
 
+// Tile b of a lower triangle counted row by row: (0, 0), (1, 0), (1, 1), ...
+__device__ __forceinline__ void lower_tile(int64_t b, int64_t& ti, int64_t& tj) {
+  ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+  while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
+  while (ti * (ti + 1) / 2 > b) --ti;
+  tj = b - ti * (ti + 1) / 2;
+}
+
 template <bool PT, bool QT, bool LOWER, bool ASSIGN>
 __global__ __launch_bounds__(256) void tile_update_kernel(const double* Pm, int64_t ldp, int64_t pfix, int64_t p0,
                                                           const double* Qm, int64_t ldq, int64_t qfix, int64_t q0,
@@ -266,17 +272,16 @@ __global__ __launch_bounds__(256) void tile_update_kernel(const double* Pm, int6
   int64_t ti, tj;
   // Workgroup h runs on XCD h % 8; each XCD takes a contiguous run of tiles
   // (consecutive tiles of a tile row share their P panel in that XCD's L2).
-  const int64_t T = LOWER ? (int64_t)nrt * (nrt + 1) / 2 : (int64_t)nrt * nct;
+  const int64_t tri = LOWER ? (int64_t)nct * (nct + 1) / 2 : 0;  // the nct x nct part
+  const int64_t T = LOWER ? tri + (int64_t)(nrt - nct) * nct : (int64_t)nrt * nct;
   const int64_t h = blockIdx.x, xcd = h & 7, q8 = T >> 3, rem8 = T & 7;
   const int64_t b = xcd * q8 + (xcd < rem8 ? xcd : rem8) + (h >> 3);
-  if (LOWER) {
-    ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
-    while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
-    while (ti * (ti + 1) / 2 > b) --ti;
-    tj = b - ti * (ti + 1) / 2;
+  if (LOWER && b < tri) {
+    lower_tile(b, ti, tj);
   } else {
-    ti = b / nct;
-    tj = b - ti * nct;
+    ti = (b - tri) / nct;
+    tj = b - tri - ti * nct;
+    if (LOWER) ti += nct;
   }
   const int64_t R = rbase + kEb * ti, Cc = cbase + kEb * tj;
   const int64_t pr = pfix < 0 ? R : pfix, qc = qfix < 0 ? Cc : qfix;
@@ -362,7 +367,8 @@ template <bool PT, bool QT, bool LOWER, bool ASSIGN>
 static hipError_t tile_update(const double* Pm, int64_t ldp, int64_t pfix, int64_t p0, const double* Qm, int64_t ldq,
                               int64_t qfix, int64_t q0, double* Cm, int64_t n, int kb, int64_t rbase, int64_t cbase,
                               int nrt, int nct, hipStream_t st) {
-  const int64_t tiles = LOWER ? (int64_t)nrt * (nrt + 1) / 2 : (int64_t)nrt * nct;
+  const int64_t tiles =
+      LOWER ? (int64_t)nct * (nct + 1) / 2 + (int64_t)(nrt - nct) * nct : (int64_t)nrt * nct;
   if (tiles <= 0) return hipSuccess;
   tile_update_kernel<PT, QT, LOWER, ASSIGN><<<(unsigned)tiles, 256, 0, st>>>(Pm, ldp, pfix, p0, Qm, ldq, qfix, q0, Cm,
                                                                              n, kb, rbase, cbase, nrt, nct);
@@ -419,10 +425,7 @@ __device__ __forceinline__ bool gemm_tile(const GemmArgs& g, int64_t m, int64_t 
   const int64_t b = LOWER && g.tri == kTriAt ? h : xcd * q8 + (xcd < rem8 ? xcd : rem8) + (h >> 3);
   int64_t ti, tj;
   if (LOWER) {
-    ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
-    while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
-    while (ti * (ti + 1) / 2 > b) --ti;
-    tj = b - ti * (ti + 1) / 2;
+    lower_tile(b, ti, tj);
   } else if (g.tri == kTriB) {
     const int64_t grp = b / (8 * (int64_t)g.nct), rest = b - grp * 8 * g.nct;
     const int64_t width = g.nrt - 8 * grp < 8 ? g.nrt - 8 * grp : 8;
@@ -663,30 +666,12 @@ __device__ __forceinline__ void gemm128_mac(const GemmOperand<TA>& opa, const Ge
   }
 }
 
-template <bool TA, bool TB, bool LOWER, int MODE>
-__global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) double As[2][kGBuf], Bs[2][kGBuf];
-  const int64_t p = blockIdx.y;
-  const double* __restrict__ A = g.A + p * g.sA;
-  const double* __restrict__ B = g.B + p * g.sB;
-  double* C = g.C + p * g.sC;
-  const int64_t m = g.mstep > 0 ? (g.m - p * g.mstep < g.mmax ? g.m - p * g.mstep : g.mmax) : g.m;
-  const int64_t kall = g.mstep > 0 && g.tri == kTriA ? m : g.kk;
-  const int64_t ldc = g.ldc, nn = g.nn;
-  int64_t R, Cc, kbeg, kn;
-  if (!gemm_tile<LOWER, kGt>(g, m, kall, R, Cc, kbeg, kn)) return;  // whole workgroup
+template <int MODE>
+__device__ __forceinline__ void gemm128_store(double* C, int64_t ldc, int64_t m, int64_t nn, int64_t R, int64_t Cc,
+                                              const f64x4 (&acc)[4][4]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r0 = 64 * (wave >> 1), c0 = 64 * (wave & 1);
   const int lr = lane & 15, lk = lane >> 4;
-  f64x4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
-  const int nch = (int)((kn - kbeg + kGk - 1) / kGk);
-  const bool desc = gemm_descends(g.tri);
-  gemm128_mac<TA, TB>(GemmOperand<TA>(A, g.lda, R, m, kn), GemmOperand<!TB>(B, g.ldb, Cc, nn, kn),
-                      desc ? kbeg + (int64_t)(nch - 1) * kGk : kbeg, desc ? -kGk : kGk, nch, As, Bs, acc);
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb) {
     double old[4][4];
@@ -707,6 +692,30 @@ __global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(GemmArgs g) {
                                                  : (MODE == kNegate ? -acc[rb][cb][i] : acc[rb][cb][i]);
       }
   }
+}
+
+template <bool TA, bool TB, bool LOWER, int MODE>
+__global__ __launch_bounds__(256, 2) void gemm128_f64_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) double As[2][kGBuf], Bs[2][kGBuf];
+  const int64_t p = blockIdx.y;
+  const double* __restrict__ A = g.A + p * g.sA;
+  const double* __restrict__ B = g.B + p * g.sB;
+  double* C = g.C + p * g.sC;
+  const int64_t m = g.mstep > 0 ? (g.m - p * g.mstep < g.mmax ? g.m - p * g.mstep : g.mmax) : g.m;
+  const int64_t kall = g.mstep > 0 && g.tri == kTriA ? m : g.kk;
+  const int64_t ldc = g.ldc, nn = g.nn;
+  int64_t R, Cc, kbeg, kn;
+  if (!gemm_tile<LOWER, kGt>(g, m, kall, R, Cc, kbeg, kn)) return;  // whole workgroup
+  f64x4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const int nch = (int)((kn - kbeg + kGk - 1) / kGk);
+  const bool desc = gemm_descends(g.tri);
+  gemm128_mac<TA, TB>(GemmOperand<TA>(A, g.lda, R, m, kn), GemmOperand<!TB>(B, g.ldb, Cc, nn, kn),
+                      desc ? kbeg + (int64_t)(nch - 1) * kGk : kbeg, desc ? -kGk : kGk, nch, As, Bs, acc);
+  gemm128_store<MODE>(C, ldc, m, nn, R, Cc, acc);
 }
 
 // C = A A^T over the lower 128-wide tiles (A m x kk), its k range split where the
@@ -736,10 +745,9 @@ __global__ __launch_bounds__(256, 2) void gram128_f64_kernel(GemmArgs g, GramSpl
     c0 = (int)((int64_t)n * part / gs.parts);
     c1 = (int)((int64_t)n * (part + 1) / gs.parts);
   }
-  int64_t ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
-  while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
-  while (ti * (ti + 1) / 2 > b) --ti;
-  const int64_t R = kGt * ti, Cc = kGt * (b - ti * (ti + 1) / 2);
+  int64_t ti, tj;
+  lower_tile(b, ti, tj);
+  const int64_t R = kGt * ti, Cc = kGt * tj;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lk = lane >> 4;
   f64x4 acc[4][4];
@@ -766,11 +774,10 @@ __global__ __launch_bounds__(256, 2) void gram128_f64_kernel(GemmArgs g, GramSpl
 // The split tiles' sums.  grid = (64, rest).
 __global__ __launch_bounds__(256) void gram_slab_sum_kernel(GemmArgs g, GramSplit gs, const double* __restrict__ slab) {
   const int64_t b = gs.full + blockIdx.y;
-  int64_t ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
-  while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
-  while (ti * (ti + 1) / 2 > b) --ti;
+  int64_t ti, tj;
+  lower_tile(b, ti, tj);
   const int e = blockIdx.x * 256 + threadIdx.x;
-  const int64_t row = kGt * ti + e / kGt, col = kGt * (b - ti * (ti + 1) / 2) + e % kGt;
+  const int64_t row = kGt * ti + e / kGt, col = kGt * tj + e % kGt;
   if (row >= g.m || col >= g.m) return;
   const double* src = slab + (int64_t)blockIdx.y * gs.parts * (kGt * kGt) + e;
   double s = 0.0;
@@ -819,54 +826,82 @@ static hipError_t gemm_launch(GemmArgs g, int64_t batch, hipStream_t st) {
 
 static int ntiles(int64_t len) { return (int)((len + kEb - 1) / kEb); }
 
+// Workgroup 0 factors the 64-wide diagonal block at j0; the others take tiles
+// [t0, t0 + gridDim.x - 1) of the lower 128-wide tiles of A[j2.., j2..] -= P P^T, P =
+// A[j2.., p0 .. p0 + kb): the trailing update left by the super-panel before.  The
+// two touch different parts of A (j0 + 64 <= j2, p0 + kb <= j0).
+__global__ __launch_bounds__(256, 2) void potrf_update_kernel(double* A, int64_t n, int64_t j0, int jb, int* info,
+                                                              double* Dinv, int64_t j2, int64_t p0, int kb,
+                                                              int64_t t0) {
+  constexpr int kPotrf = 2 * kEb * kDbLd, kGemm = 4 * kGBuf;
+  __shared__ __attribute__((aligned(16))) double sh[kPotrf > kGemm ? kPotrf : kGemm];
+  if (blockIdx.x == 0) {
+    potrf_diag(A, n, j0, jb, info, Dinv, sh, sh + kEb * kDbLd);
+    return;
+  }
+  // each XCD takes a contiguous run of the tiles
+  const int64_t T = gridDim.x - 1, h = blockIdx.x - 1, xcd = h & 7, q8 = T >> 3, rem8 = T & 7;
+  int64_t ti, tj;
+  lower_tile(t0 + xcd * q8 + (xcd < rem8 ? xcd : rem8) + (h >> 3), ti, tj);
+  const int64_t m = n - j2, R = kGt * ti, Cc = kGt * tj;
+  const double* P = A + j2 * n + p0;
+  f64x4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  gemm128_mac<false, true>(GemmOperand<false>(P, n, R, m, kb), GemmOperand<false>(P, n, Cc, m, kb), 0, kGk,
+                           (kb + kGk - 1) / kGk, (double(*)[kGBuf])sh, (double(*)[kGBuf])(sh + 2 * kGBuf), acc);
+  gemm128_store<kSubtract>(A + j2 * n + j2, n, m, m, R, Cc, acc);
+}
+
 // A = L L^T in place (lower triangle; the diagonal blocks' upper parts are
 // zeroed, the rest of the upper triangle holds no result); the inverses of the
 // diagonal blocks stay in Dinv (block bi at 64 * 64 * bi).  Two levels of
 // blocking: 64-wide panels inside 256-wide super-panels.  A panel updates only
-// the columns of its own super-panel; the trailing matrix beyond it takes the
-// whole super-panel at once (k = 256), so that it is read and written once per
-// 256 columns instead of once per 64.
+// the columns of its own super-panel; what lies beyond takes the whole super-panel
+// at once (k = 256), so that it is read and written once per 256 columns instead
+// of once per 64: first the next super-panel's columns, and the rest beside the next
+// four diagonal blocks, each of which is 33 us of one workgroup: up to 255 tiles, one per
+// CU (50 us), beside each block, in as few launches as that allows; more per launch only
+// where four launches do not hold them.  n = 7,503: 10.3 ms with the trailing update in
+// launches of its own and the panel's own updates in two, 8.9 ms so (17.5 instead of
+// 19.1 ms for value, gradient and inverse); four equal shares, each with
+// a tile's 50 us: 9.8 ms.
 constexpr int kSp = 4 * kEb;
 
 static hipError_t cholesky(double* A, int64_t n, int* info, double* Dinv, hipStream_t st) {
+  if (n > kGemmMaxLd) return hipErrorInvalidValue;  // 2^47 bytes
   hipError_t e = hipSuccess;
   for (int64_t J0 = 0; J0 < n; J0 += kSp) {
     const int64_t Jend = std::min<int64_t>(n, J0 + kSp);
+    // the trailing update by the super-panel before this one, columns from Jend on
+    const int64_t shared = J0 > 0 ? tile_count(true, n - Jend, n - Jend, kGt) : 0;
+    const int64_t per = std::max<int64_t>(255, (shared + 3) / 4);
     for (int64_t j0 = J0; j0 < Jend; j0 += kEb) {
       const int jb = (int)std::min<int64_t>(kEb, n - j0);
-      const int64_t rest = n - j0 - jb;
+      const int64_t rest = n - j0 - jb, q = (j0 - J0) / kEb;
       double* Di = Dinv + j0 / kEb * kEb * kEb;
-      potrf_diag_kernel<<<1, 256, 0, st>>>(A, n, j0, jb, info, Di);
+      const int64_t t0 = std::min(shared, q * per), t1 = std::min(shared, (q + 1) * per);
+      potrf_update_kernel<<<(unsigned)(1 + t1 - t0), 256, 0, st>>>(A, n, j0, jb, info, Di, Jend, J0 - kSp, kSp, t0);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       if (rest <= 0) return hipSuccess;
       // L21 = A21 L11^{-T} for every row below (jb = 64 here)
       e = tile_update<false, true, false, true>(A, n, -1, j0, Di, kEb, 0, 0, A, n, jb, j0 + jb, j0, ntiles(rest),
                                                 1, st);
       if (e != hipSuccess) return e;
-      // the rest of this super-panel's columns, [j0 + 64, Jend): the lower
-      // triangle of its diagonal part, then the rows below the super-panel
+      // the rest of this super-panel's columns, [j0 + 64, Jend), on and below the diagonal
       const int64_t wcols = Jend - j0 - jb;
       if (wcols > 0) {
         e = tile_update<false, true, true, false>(A, n, -1, j0, A, n, -1, j0, A, n, jb, j0 + jb, j0 + jb,
-                                                  ntiles(wcols), 0, st);
+                                                  ntiles(rest), ntiles(wcols), st);
         if (e != hipSuccess) return e;
-        if (n > Jend) {
-          e = tile_update<false, true, false, false>(A, n, -1, j0, A, n, -1, j0, A, n, jb, Jend, j0 + jb,
-                                                     ntiles(n - Jend), ntiles(wcols), st);
-          if (e != hipSuccess) return e;
-        }
       }
     }
-    // A22 -= L21 L21^T over the lower tiles beyond the super-panel, k = Jend - J0
+    // the next super-panel's columns, k = 256
     if (n > Jend) {
-      const int64_t rest = n - Jend;
-      const double* P = A + Jend * n + J0;
-      if (use_gemm128(true, rest, rest))
-        e = gemm_launch<false, true, true, kSubtract, true>(
-            GemmArgs{P, n, 0, P, n, 0, A + Jend * n + Jend, n, 0, rest, rest, Jend - J0, 0, 0, 0, 0, kTriNone}, 1, st);
-      else
-        e = tile_update<false, true, true, false>(A, n, -1, J0, A, n, -1, J0, A, n, (int)(Jend - J0), Jend, Jend,
-                                                  ntiles(rest), 0, st);
+      e = tile_update<false, true, true, false>(A, n, -1, J0, A, n, -1, J0, A, n, kSp, Jend, Jend, ntiles(n - Jend),
+                                                ntiles(std::min<int64_t>(kSp, n - Jend)), st);
       if (e != hipSuccess) return e;
     }
   }

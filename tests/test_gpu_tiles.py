@@ -277,3 +277,16 @@ def test_large_rank_factor_with_its_gram_split(n, r):
     F = sl.solve_triangular(np.linalg.cholesky(KMM), KMX, lower=True)
     ref = sl.solve_triangular(np.linalg.cholesky(F @ F.T + 1e-2 * np.eye(r)), F, lower=True)
     assert np.linalg.norm(E - ref) <= 1e-11 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("n", [256, 257, 320, 511, 513, 769, 1100, 3000])
+def test_cholesky_with_its_trailing_update_beside_the_diagonal_blocks(n):
+    """K_hat^{-1} y around the 256-wide super-panels (no, one and several shares of tiles, ragged last panels; n = 3,000:
+    more than one launch of them).  Residual of K_hat omega = y in FP64: relative bar 1e-11 at cond(K_hat) below 1e4."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n)
+    X, y = rng.standard_normal((n, 5)), rng.standard_normal(n)
+    th = ok.Theta(rng.uniform(0.5, 1.0, 5), 1.2, 0.1, ok.MATERN52)
+    r = gp.exact_mll_and_grad(_gk(th), dev(X), dev(y), with_grad=False, with_omega=True)
+    back = ok.khat_matmul(X, th, host(r.omega)[:, None])[:, 0]
+    assert np.linalg.norm(back - y) <= 1e-11 * np.linalg.norm(y)
