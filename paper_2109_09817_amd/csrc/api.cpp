@@ -93,8 +93,7 @@ int kmm_run(const gp_kernel* kern, int32_t precision, const double* X, int64_t n
   if (!kmm_plan_init(p, kern, precision, n, square ? n : m, square, t, ws, ws_bytes))
     return fail(GP_EWORKSPACE, "gp_kmm: workspace layout failed");
   p.no_timing = no_timing;
-  GPK_HIP(kmm_prepare(p, kern, X, Z, st));
-  GPK_HIP(kmm_apply(p, V, ldv, t, out, ldo, st, /*row_independent=*/!square));
+  GPK_HIP(kmm_product(p, kern, X, Z, V, ldv, t, out, ldo, st));
   return GP_OK;
 }
 

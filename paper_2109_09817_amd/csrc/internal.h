@@ -130,6 +130,11 @@ hipError_t kmm_apply(const KmmPlan& p, const double* V, int64_t ldv, int t, doub
                      int64_t ldo, hipStream_t st, bool row_independent = false,
                      const DotPartials& dot = DotPartials());
 
+// kmm_prepare and kmm_apply of one product (row-independent if it is a cross product),
+// in fewer launches.
+hipError_t kmm_product(KmmPlan& p, const gp_kernel* kern, const double* X, const double* Z, const double* V,
+                       int64_t ldv, int t, double* out, int64_t ldo, hipStream_t st);
+
 // The FP64 form (kmm_fp64.hip).
 F64Split f64_split(int64_t n, int64_t m, bool square, int t);
 hipError_t fp64_prepare(KmmPlan& p, const gp_kernel* kern, const double* X, const double* Z, hipStream_t st);

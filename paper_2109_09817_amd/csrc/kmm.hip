@@ -127,11 +127,11 @@ size_t colmean_scratch_doubles(int64_t n, int d) { return (size_t)colmean_blocks
 
 // Both passes add in order; their loads are issued 32 rows (or all blocks) ahead,
 // since one load at a time made the second pass 244 us at n = 262,144 (10 us now).
-__global__ __launch_bounds__(128) void colmean_partial_kernel(const double* __restrict__ X, int64_t n, int d,
-                                                              int64_t rows_per_blk, double* __restrict__ part) {
+__device__ __forceinline__ void colmean_partial(const double* __restrict__ X, int64_t n, int d, int64_t rows_per_blk,
+                                                int64_t blk, double* __restrict__ part) {
   const int j = threadIdx.x;
   if (j >= d) return;
-  const int64_t r0 = (int64_t)blockIdx.x * rows_per_blk;
+  const int64_t r0 = blk * rows_per_blk;
   const int64_t r1 = r0 + rows_per_blk < n ? r0 + rows_per_blk : n;
   double s = 0.0;
   int64_t i = r0;
@@ -143,7 +143,12 @@ __global__ __launch_bounds__(128) void colmean_partial_kernel(const double* __re
     for (int u = 0; u < 32; ++u) s += v[u];
   }
   for (; i < r1; ++i) s += X[i * d + j];
-  part[(int64_t)blockIdx.x * d + j] = s;
+  part[blk * d + j] = s;
+}
+
+__global__ __launch_bounds__(128) void colmean_partial_kernel(const double* __restrict__ X, int64_t n, int d,
+                                                              int64_t rows_per_blk, double* __restrict__ part) {
+  colmean_partial(X, n, d, rows_per_blk, blockIdx.x, part);
 }
 
 constexpr int kMeanCols = 8;  // columns per workgroup of the second pass
@@ -247,19 +252,40 @@ __global__ __launch_bounds__(256) void prep_norm_fp32_kernel(const double* __res
 // 55 us here.
 constexpr int kPrepPts = 32;
 
+// The centre: given, or (part) the column sums of nblk <= kMeanFold blocks, added and
+// divided as in colmean_final_kernel and stored to ctr by the first workgroup.
+constexpr int kMeanFold = 16;
+
+struct PointSet {
+  const double* X;
+  int64_t n;          // points; rows beyond them are padding
+  bf16x8 *xr, *xc;    // row and column side (nullable)
+  double* nrm;        // nullable
+};
+
+struct Centre {
+  double* ctr;
+  const double* part;  // null: ctr holds the centre
+  int nblk;
+  int64_t n;
+};
+
 template <int NS>  // 16-feature slices
-__global__ __launch_bounds__(256) void prep_points_f16x3_kernel(const double* __restrict__ X,
-                                                                const double* __restrict__ ctr, int64_t n,
-                                                                int64_t npad, int d, int KS, Scale sc,
-                                                                bf16x8* __restrict__ xr, bf16x8* __restrict__ xc,
-                                                                double* __restrict__ nrm) {
+__device__ __forceinline__ void prep_points_block(const PointSet& ps, const Centre& ce, int64_t blk, int d, int KS,
+                                                  const Scale& sc) {
   extern __shared__ __attribute__((aligned(16))) _Float16 rows[];  // [side][point][pitch]
   __shared__ int bad[kPrepPts];
+  __shared__ double cm[GP_MAX_D];
+  const double* __restrict__ X = ps.X;
+  const int64_t n = ps.n;
+  bf16x8* __restrict__ xr = ps.xr;
+  bf16x8* __restrict__ xc = ps.xc;
+  double* __restrict__ nrm = ps.nrm;
   const int pitch = 32 * KS + 8;  // halves
   _Float16* const Rr = rows;
   _Float16* const Rc = rows + kPrepPts * pitch;
   const int tid = threadIdx.x;
-  const int64_t p0 = (int64_t)blockIdx.x * kPrepPts;
+  const int64_t p0 = blk * kPrepPts;
   const int fl = tid & 15, rl = tid >> 4;
   double x[NS][2];
 #pragma unroll
@@ -271,12 +297,29 @@ __global__ __launch_bounds__(256) void prep_points_f16x3_kernel(const double* __
       x[j][q] = X[p * d + f];
     }
   if (tid < kPrepPts) bad[tid] = 0;
+  if (tid < d) {
+    double c;
+    if (ce.part) {
+      double w[kMeanFold];
+#pragma unroll
+      for (int u = 0; u < kMeanFold; ++u) w[u] = ce.part[(int64_t)(u < ce.nblk ? u : ce.nblk - 1) * d + tid];
+      c = 0.0;
+#pragma unroll
+      for (int u = 0; u < kMeanFold; ++u)
+        if (u < ce.nblk) c += w[u];
+      c /= (double)ce.n;
+      if (blockIdx.x == 0) ce.ctr[tid] = c;
+    } else {
+      c = ce.ctr[tid];
+    }
+    cm[tid] = c;
+  }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < NS; ++j) {
     const int f = 16 * j + fl;
     if (f < d) {
-      const double s = sc.s[f], c = ctr[f];
+      const double s = sc.s[f], c = cm[f];
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         const int r = rl + 16 * q;
@@ -326,7 +369,7 @@ __global__ __launch_bounds__(256) void prep_points_f16x3_kernel(const double* __
   }
   __syncthreads();
   // unit u of the workgroup: point block u / (64 KS), K step, lane
-  const int64_t u0 = (int64_t)blockIdx.x * (kPrepPts / 16) * KS * 64;
+  const int64_t u0 = blk * (kPrepPts / 16) * KS * 64;
   for (int u = tid; u < (kPrepPts / 16) * KS * 64; u += 256) {
     const int lane = u & 63, bk = u >> 6;
     const int blk = bk >= KS ? 1 : 0, ks = bk - blk * KS;
@@ -336,14 +379,22 @@ __global__ __launch_bounds__(256) void prep_points_f16x3_kernel(const double* __
   }
 }
 
+template <int NS>
+__global__ __launch_bounds__(256) void prep_points_f16x3_kernel(PointSet ps, Centre ce, int d, int KS, Scale sc) {
+  prep_points_block<NS>(ps, ce, blockIdx.x, d, KS, sc);
+}
+
+static size_t prep_points_lds(int KS) { return 2 * (size_t)kPrepPts * (32 * KS + 8) * sizeof(_Float16); }
+
 static hipError_t launch_prep_points(const double* X, const double* ctr, int64_t n, int64_t npad, int d, int KS,
                                      const Scale& sc, void* xr, void* xc, double* nrm, hipStream_t st) {
   static_assert(kPrepPts == 32, "two point blocks per workgroup");
   if (npad % kPrepPts != 0) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)(npad / kPrepPts);
-  const size_t lds = 2 * (size_t)kPrepPts * (32 * KS + 8) * sizeof(_Float16);
-#define GPK_PREP(NS) \
-  prep_points_f16x3_kernel<NS><<<grid, 256, lds, st>>>(X, ctr, n, npad, d, KS, sc, (bf16x8*)xr, (bf16x8*)xc, nrm)
+  const size_t lds = prep_points_lds(KS);
+  const PointSet ps{X, n, (bf16x8*)xr, (bf16x8*)xc, nrm};
+  const Centre ce{const_cast<double*>(ctr), nullptr, 0, 0};
+#define GPK_PREP(NS) prep_points_f16x3_kernel<NS><<<grid, 256, lds, st>>>(ps, ce, d, KS, sc)
   switch ((d + 15) / 16) {
     case 1: GPK_PREP(1); break;
     case 2: GPK_PREP(2); break;
@@ -397,13 +448,11 @@ __global__ void prep_frag_fp32_kernel(const double* __restrict__ X, const double
 // below 2^15 and, down to 2^-1046 relative to that, in FP16's normal range).
 constexpr int kVParts = 64;
 
-__global__ __launch_bounds__(256) void vmax_partial_kernel(const double* __restrict__ V, int64_t ldv,
-                                                           const double* __restrict__ col0, int64_t n,
-                                                           double* __restrict__ part) {
+__device__ __forceinline__ void vmax_partial(const double* __restrict__ V, int64_t ldv, const double* __restrict__ col0,
+                                             int64_t n, int c, int q, double* __restrict__ part) {
   __shared__ double red[256];
-  const int c = blockIdx.y;
   const int64_t per = (n + kVParts - 1) / kVParts;
-  const int64_t r0 = (int64_t)blockIdx.x * per;
+  const int64_t r0 = q * per;
   const int64_t r1 = r0 + per < n ? r0 + per : n;
   const double* src = col0 ? (c == 0 ? col0 : V + (int64_t)(c - 1) * ldv) : V + (int64_t)c * ldv;
   double mx = 0.0;
@@ -414,7 +463,13 @@ __global__ __launch_bounds__(256) void vmax_partial_kernel(const double* __restr
     if ((int)threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[(int64_t)c * kVParts + blockIdx.x] = red[0];
+  if (threadIdx.x == 0) part[(int64_t)c * kVParts + q] = red[0];
+}
+
+__global__ __launch_bounds__(256) void vmax_partial_kernel(const double* __restrict__ V, int64_t ldv,
+                                                           const double* __restrict__ col0, int64_t n,
+                                                           double* __restrict__ part) {
+  vmax_partial(V, ldv, col0, n, blockIdx.y, blockIdx.x, part);
 }
 
 __device__ __forceinline__ int column_exponent(double mx) {
@@ -447,12 +502,26 @@ hipError_t column_absmax(const double* V, int64_t ldv, int64_t n, int t, double*
 // hl = 1: lo = RNE16(v' - hi).  Columns c >= t are zero.  Every wave derives its
 // columns' scales from the kVParts maxima (a quarter per lane group), once for the
 // `per` chunks it converts; the first chunk's waves store inv.
-__global__ __launch_bounds__(256) void prep_v_f16x3_kernel(const double* __restrict__ V, int64_t ldv,
-                                                           const double* __restrict__ col0,
-                                                           const double* __restrict__ part, double* __restrict__ inv,
-                                                           int64_t n, int t, int64_t nchunks, int ntb, int per,
-                                                           bf16x8* __restrict__ vf) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+struct VSet {
+  const double* V;
+  int64_t ldv;
+  const double* col0;
+  const double* part;  // column maxima
+  double* inv;
+  int64_t n, nchunks;
+  int t, ntb, per;
+  bf16x8* vf;
+};
+
+__device__ __forceinline__ void prep_v_block(const VSet& vs, int64_t blk) {
+  const double* __restrict__ V = vs.V;
+  const double* __restrict__ col0 = vs.col0;
+  const double* __restrict__ part = vs.part;
+  double* __restrict__ inv = vs.inv;
+  bf16x8* __restrict__ vf = vs.vf;
+  const int64_t n = vs.n, nchunks = vs.nchunks, ldv = vs.ldv;
+  const int t = vs.t, ntb = vs.ntb, per = vs.per;
+  const int64_t idx = blk * 256 + threadIdx.x;
   const int lane = (int)(idx & 63);
   const int cb = (int)((idx >> 6) % ntb);
   const int64_t ch0 = (idx >> 6) / ntb * per;  // this wave: chunks ch0 .. ch0 + per - 1 of column block cb
@@ -497,6 +566,37 @@ __global__ __launch_bounds__(256) void prep_v_f16x3_kernel(const double* __restr
     vf[(rest * 2 + 0) * 64 + lane] = __builtin_bit_cast(bf16x8, hi);
     vf[(rest * 2 + 1) * 64 + lane] = __builtin_bit_cast(bf16x8, lo);
   }
+}
+
+__global__ __launch_bounds__(256) void prep_v_f16x3_kernel(VSet vs) { prep_v_block(vs, blockIdx.x); }
+
+// One product's operands in two launches (three beyond kMeanFold blocks of rows): the
+// sums and maxima of X and V, then the fragments of X, of Z (a cross product's rows)
+// and of V.  A small product is bound by its launches: n = 2,048, d = 32, t = 9: 33 us
+// with one launch per operand and pass (7), 23 so (4).
+__global__ __launch_bounds__(256) void prep_reduce_f16x3_kernel(const double* __restrict__ X, int64_t n, int d,
+                                                                int64_t rows_per_blk, int nmean,
+                                                                double* __restrict__ mpart,
+                                                                const double* __restrict__ V, int64_t ldv,
+                                                                double* __restrict__ vpart) {
+  if ((int)blockIdx.x < nmean) {
+    colmean_partial(X, n, d, rows_per_blk, blockIdx.x, mpart);
+    return;
+  }
+  const int b = blockIdx.x - nmean;
+  vmax_partial(V, ldv, nullptr, n, b / kVParts, b % kVParts, vpart);
+}
+
+template <int NS>
+__global__ __launch_bounds__(256) void prep_operands_f16x3_kernel(PointSet px, PointSet pz, int64_t nbx, int64_t nbz,
+                                                                  Centre ce, int d, int KS, Scale sc, VSet vs) {
+  const int64_t b = blockIdx.x;
+  if (b < nbx)
+    prep_points_block<NS>(px, ce, b, d, KS, sc);
+  else if (b < nbx + nbz)
+    prep_points_block<NS>(pz, ce, b - nbx, d, KS, sc);
+  else
+    prep_v_block(vs, b - nbx - nbz);
 }
 
 // FP32 V fragments: (chunk, cb, tile, lane) -> float4 of V[b = 32 chunk + 16 tile + 4g + i]
@@ -1554,23 +1654,30 @@ static void launch_one(bool mixed, int nt, int kind, dim3 grid, const SweepArgs&
   }
 }
 
+// The mixed form's V operand for one launch, and its workgroups.
+static VSet v_set(const KmmPlan& p, const double* V, int64_t ldv, int t, bool row_independent, const double* col0,
+                  int64_t* blocks) {
+  const SplitChoice sc = choose_split(p.npad, p.mpad, (t + 15) / 16, row_independent, p.ks, true);
+  const int ntb = sc.groups * sc.nt;  // vf holds whole launch groups (zero padded)
+  // one chunk per wave until the chip is full (four waves per SIMD), then up to eight
+  const int per = (int)std::max<int64_t>(1, std::min<int64_t>(8, p.nchunks * ntb / 4096));
+  *blocks = ((p.nchunks + per - 1) / per * ntb * 64 + 255) / 256;
+  return VSet{V, ldv, col0, p.vpart, p.vinv, p.n, p.nchunks, t, ntb, per, (bf16x8*)p.vf};
+}
+
 hipError_t kmm_prepare_v(const KmmPlan& p, const double* V, int64_t ldv, int t, bool row_independent,
                          hipStream_t st, const double* col0) {
   if (t < 1 || t > p.tmax || !p.vf || !V) return hipErrorInvalidValue;
-  const int ntb = (t + 15) / 16;
-  const SplitChoice sc = choose_split(p.npad, p.mpad, ntb, row_independent, p.ks, p.precision == GP_PREC_BF16X3);
-  const int ntb_alloc = sc.groups * sc.nt;  // vf holds whole launch groups (zero padded)
-  const int thr = 256;
   if (p.precision == GP_PREC_BF16X3) {
     if (!p.vinv || !p.vpart) return hipErrorInvalidValue;
+    int64_t blocks;
+    const VSet vs = v_set(p, V, ldv, t, row_independent, col0, &blocks);
     vmax_partial_kernel<<<dim3(kVParts, (unsigned)t), 256, 0, st>>>(V, ldv, col0, p.n, p.vpart);
-    // one chunk per wave until the chip is full (four waves per SIMD), then up to eight
-    const int64_t units = p.nchunks * ntb_alloc;
-    const int per = (int)std::max<int64_t>(1, std::min<int64_t>(8, units / 4096));
-    const int64_t total = (p.nchunks + per - 1) / per * ntb_alloc * 64;
-    prep_v_f16x3_kernel<<<(unsigned)((total + thr - 1) / thr), thr, 0, st>>>(
-        V, ldv, col0, p.vpart, p.vinv, p.n, t, p.nchunks, ntb_alloc, per, (bf16x8*)p.vf);
+    prep_v_f16x3_kernel<<<(unsigned)blocks, 256, 0, st>>>(vs);
   } else {
+    const int ntb = (t + 15) / 16;
+    const SplitChoice sc = choose_split(p.npad, p.mpad, ntb, row_independent, p.ks, false);
+    const int ntb_alloc = sc.groups * sc.nt, thr = 256;
     const int64_t total = p.nchunks * ntb_alloc * 2 * 64;
     prep_v_fp32_kernel<<<(unsigned)((total + thr - 1) / thr), thr, 0, st>>>(V, ldv, col0, p.n, t, p.nchunks,
                                                                              ntb_alloc, (f32x4*)p.vf);
@@ -1720,6 +1827,49 @@ hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, 
     kmm_epilogue_kernel<double><<<egrid, 256, 0, st>>>(p.part, sc.nsplit, sc.tpad, p.mpad, p.m, t, p.sf, diag, inv, Vd,
                                                        ldv, out, ldo, dot.rows, dot.part);
   return hipGetLastError();
+}
+
+hipError_t kmm_product(KmmPlan& p, const gp_kernel* kern, const double* X, const double* Z, const double* V,
+                       int64_t ldv, int t, double* out, int64_t ldo, hipStream_t st) {
+  const bool row_independent = !p.square;
+  if (p.precision != GP_PREC_BF16X3) {
+    const hipError_t e = kmm_prepare(p, kern, X, Z, st);
+    return e != hipSuccess ? e : kmm_apply(p, V, ldv, t, out, ldo, st, row_independent);
+  }
+  if (t < 1 || t > p.tmax || !p.vf || !V || !X || (!p.square && !Z) || !p.ctr || !p.cpart || !p.vinv || !p.vpart ||
+      !p.xr || !p.xc)
+    return hipErrorInvalidValue;
+  const Scale sc = make_scale(kern);
+  const int64_t nblk = colmean_blocks(p.n), rpb = (p.n + nblk - 1) / nblk;
+  prep_reduce_f16x3_kernel<<<(unsigned)(nblk + (int64_t)kVParts * t), 256, 0, st>>>(X, p.n, p.d, rpb, (int)nblk,
+                                                                                   p.cpart, V, ldv, p.vpart);
+  Centre ce{p.ctr, p.cpart, (int)nblk, p.n};
+  if (nblk > kMeanFold) {
+    colmean_final_kernel<<<(unsigned)((p.d + kMeanCols - 1) / kMeanCols), 256, 0, st>>>(p.cpart, (int)nblk, p.d, p.n,
+                                                                                      p.ctr);
+    ce.part = nullptr;
+  }
+  // the square case prepares both sides at once; rows up to max(npad, mpad) so xc covers mpad
+  const int64_t xrows = p.square ? std::max(p.npad, p.mpad) : p.npad, zrows = p.square ? 0 : p.mpad;
+  if (xrows % kPrepPts != 0 || zrows % kPrepPts != 0) return hipErrorInvalidValue;
+  const PointSet px{X, p.n, (bf16x8*)p.xr, p.square ? (bf16x8*)p.xc : nullptr, nullptr};
+  const PointSet pz{Z, p.m, nullptr, (bf16x8*)p.xc, nullptr};
+  int64_t vblocks;
+  const VSet vs = v_set(p, V, ldv, t, row_independent, nullptr, &vblocks);
+  const int64_t nbx = xrows / kPrepPts, nbz = zrows / kPrepPts;
+  const unsigned grid = (unsigned)(nbx + nbz + vblocks);
+  const size_t lds = prep_points_lds(p.ks);
+#define GPK_PREP(NS) prep_operands_f16x3_kernel<NS><<<grid, 256, lds, st>>>(px, pz, nbx, nbz, ce, p.d, p.ks, sc, vs)
+  switch ((p.d + 15) / 16) {
+    case 1: GPK_PREP(1); break;
+    case 2: GPK_PREP(2); break;
+    case 3: GPK_PREP(3); break;
+    case 4: GPK_PREP(4); break;
+    default: GPK_PREP(8); break;
+  }
+#undef GPK_PREP
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : kmm_sweep(p, t, V, ldv, out, ldo, st, row_independent);
 }
 
 hipError_t kmm_apply(const KmmPlan& p, const double* V, int64_t ldv, int t, double* out, int64_t ldo,

@@ -290,3 +290,19 @@ def test_cholesky_with_its_trailing_update_beside_the_diagonal_blocks(n):
     r = gp.exact_mll_and_grad(_gk(th), dev(X), dev(y), with_grad=False, with_omega=True)
     back = ok.khat_matmul(X, th, host(r.omega)[:, None])[:, 0]
     assert np.linalg.norm(back - y) <= 1e-11 * np.linalg.norm(y)
+
+
+@pytest.mark.parametrize("n,m,d,t", [(1, 3, 5, 2), (4096, 0, 32, 9), (4097, 0, 33, 3), (4096, 33, 17, 20),
+                                     (4353, 300, 64, 1), (4000, 31, 100, 65)])
+def test_mixed_product_with_its_operands_prepared_together(n, m, d, t):
+    """The centre from up to 16 blocks of 256 rows is added where the points are prepared, from more before; X, Z and V
+    in one launch.  Data shifted by 100 lengthscales: a wrong centre loses all digits.  Against the oracle; 5e-5."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n + t)
+    X, V = rng.standard_normal((n, d)) + 100.0, rng.standard_normal((t, n))
+    Z = rng.standard_normal((m, d)) + 100.0 if m else None
+    th = ok.Theta(rng.uniform(0.8, 1.2, d) * np.sqrt(d), 1.1, 1e-2, ok.MATERN52)
+    got = host(gp.kmm(_gk(th), dev(X), dev(V), Z=dev(Z) if m else None, precision="bf16x3"))
+    ref = ok.cross_matmul(Z, X, th, V.T).T if m else ok.khat_matmul(X, th, V.T).T
+    off = ref - (0.0 if m else (1.1 + 1e-2) * V)
+    assert np.linalg.norm(got - ref) <= 5e-5 * np.linalg.norm(off)
