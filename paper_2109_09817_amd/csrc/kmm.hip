@@ -1193,6 +1193,7 @@ __global__ __launch_bounds__(256) void kmm_epilogue_kernel(const T* __restrict__
   const int64_t r1 = r0 + rows_per_blk < m ? r0 + rows_per_blk : m;
   double acc = 0.0;
   for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
+    const double vr = V ? V[c * ldv + r] : 0.0;
     double s = 0.0;
     const T* src = part + c * mpad + r;
     const int64_t step = (int64_t)tpad * mpad;
@@ -1214,7 +1215,6 @@ __global__ __launch_bounds__(256) void kmm_epilogue_kernel(const T* __restrict__
     for (; sp < nsplit; ++sp, src += step) s += (double)src[0];
     if (inv) s *= inv[c];
     double o = sf * s;
-    const double vr = V ? V[c * ldv + r] : 0.0;
     if (V) o += diag * vr;
     out[c * ldo + r] = o;
     acc += vr * o;

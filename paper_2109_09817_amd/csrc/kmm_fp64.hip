@@ -34,7 +34,7 @@ constexpr int kF64Rows = 64;   // output rows per workgroup
 // beyond a multiple of 16 (a block of 50 or 17, a single vector) cost four FMAs
 // per entry on the VALU instead of a 16-column MFMA block that is mostly padding.
 // n = 24,576, t = 50, d = 48: 5.0 ms with predicated loads, one entry at a time
-// through sqrt and exp and one or two workgroups per CU; 2.8 ms now (31 TFLOP/s of
+// through sqrt and exp and one or two workgroups per CU; 2.69 ms now (33 TFLOP/s of
 // n^2 (d + 2 t)).  Error against a long double product on sampled rows 3.0e-15
 // (5.1e-15 before: one long sum per row).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -174,29 +174,50 @@ __global__ __launch_bounds__(256, 2) void sweep_fp64_kernel(F64Args a, int first
   // consecutive values; thread tid takes every 256th (offsets clamped into X),
   // and 32 values of every eighth column of V.
   const int nd = kF64Chunk * d;
-  int bpos[kBPer], bf[kBPer];  // LDS position and feature of each point value
+  int bpos[kBPer];        // LDS position of each point value,
+  uint32_t boff[kBPer];   // its byte offset from the chunk's first
+  // and its feature's scale, from LDS where the registers would cost a wave per SIMD
+  // or spill (t = 16, d = 48: 1.86 ms, 1.98 from registers; t = 50: 2.76, 2.70)
+  constexpr bool kRegScale = DP <= 48 && (NCB != 1 || REM > 0);
+  double bsc[kRegScale ? kBPer : 1];
+  int bf[kRegScale ? 1 : kBPer];
 #pragma unroll
   for (int it = 0; it < kBPer; ++it) {
     const int e = tid + 256 * it < nd ? tid + 256 * it : nd - 1;
-    bf[it] = e % d;
-    bpos[it] = e / d * kBLd + bf[it];
+    bpos[it] = e / d * kBLd + e % d;
+    boff[it] = 8u * e;
+    if constexpr (kRegScale)
+      bsc[it] = a.sc[e % d];
+    else
+      bf[it] = e % d;
   }
   for (int e = tid; e < kF64Chunk * kBLd; e += 256) Bs[e] = 0.0;  // the features beyond d stay zero
   if (tid < DP) Sc[tid] = tid < d ? a.sc[tid] : 0.0;
   const int vcol = tid >> 5, vj = tid & 31;
+  const double* vp[kVPer];  // V of point vj in this thread's columns
+#pragma unroll
+  for (int it = 0; it < kVPer; ++it)
+    vp[it] = a.V + (int64_t)(c0 + (8 * it + vcol < live ? 8 * it + vcol : live - 1)) * a.ldv + vj;
   double bv[kBPer], vv[kVPer], nv;
+  // Full chunks add a scalar to offsets and pointers that stay: vector address
+  // arithmetic adds to the time of the MFMAs.
   auto load = [&](int64_t c0b) {
-    const double* const Xc = a.Xb + c0b * d;
-    const int blim = (int)(n - c0b < kF64Chunk ? (n - c0b) * d : nd) - 1;
-    const int jv = n - c0b < kF64Chunk && vj >= (int)(n - c0b) ? (int)(n - c0b) - 1 : vj;
+    const char* const Xc = (const char*)(a.Xb + c0b * d);
+    if (n - c0b >= kF64Chunk) {
 #pragma unroll
-    for (int it = 0; it < kBPer; ++it) bv[it] = Xc[tid + 256 * it < blim ? tid + 256 * it : blim];
+      for (int it = 0; it < kBPer; ++it) bv[it] = *(const double*)(Xc + boff[it]);
 #pragma unroll
-    for (int it = 0; it < kVPer; ++it) {
-      const int c = 8 * it + vcol < live ? 8 * it + vcol : live - 1;
-      vv[it] = a.V[(int64_t)(c0 + c) * a.ldv + c0b + jv];
+      for (int it = 0; it < kVPer; ++it) vv[it] = vp[it][c0b];
+      nv = a.nb[c0b + vj];
+      return;
     }
-    nv = a.nb[c0b + jv];
+    const uint32_t blim = 8u * (uint32_t)((n - c0b) * d - 1);
+    const int back = vj >= (int)(n - c0b) ? vj - (int)(n - c0b) + 1 : 0;  // points beyond n repeat the last one
+#pragma unroll
+    for (int it = 0; it < kBPer; ++it) bv[it] = *(const double*)(Xc + (boff[it] < blim ? boff[it] : blim));
+#pragma unroll
+    for (int it = 0; it < kVPer; ++it) vv[it] = vp[it][c0b - back];
+    nv = a.nb[c0b + vj - back];
   };
   const int64_t b_begin = (int64_t)blockIdx.z * a.cps * kF64Chunk;
   const int64_t b_end = b_begin + a.cps * kF64Chunk < n ? b_begin + a.cps * kF64Chunk : n;
@@ -210,7 +231,7 @@ __global__ __launch_bounds__(256, 2) void sweep_fp64_kernel(F64Args a, int first
     }
 #pragma unroll
     for (int it = 0; it < kBPer; ++it)
-      if (tid + 256 * it < nd) Bs[bpos[it]] = bv[it] * Sc[bf[it]];
+      if (tid + 256 * it < nd) Bs[bpos[it]] = bv[it] * (kRegScale ? bsc[kRegScale ? it : 0] : Sc[bf[kRegScale ? 0 : it]]);
 #pragma unroll
     for (int it = 0; it < kVPer; ++it) Vs[(8 * it + vcol) * kVLd + vj] = vv[it];
     if (tid < kF64Chunk) Ns[tid] = nv;
@@ -311,7 +332,7 @@ __global__ __launch_bounds__(256) void fp64_splitsum_kernel(F64Args a, int64_t n
 // that a plan that needs no partials within GP_KMM_NOALLOC_MAX_BYTES stays within
 // it with them; points beyond kF64SplitMaxN leave no room and take one split
 // (their rows alone fill the chip).
-// n = 8,192, t = 50: 128 workgroups on 256 CUs took 1.08 ms, 1,536 take 0.39 ms.
+// n = 8,192, t = 50: 128 workgroups on 256 CUs took 1.08 ms, 1,536 take 0.36 ms.
 constexpr int64_t kF64Groups = 1536;
 constexpr int64_t kF64MinChunks = 12;
 constexpr int64_t kF64CrossSplits = 64;
