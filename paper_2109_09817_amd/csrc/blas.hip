@@ -415,24 +415,27 @@ __device__ __forceinline__ double div_by(double v, double d, double r) {
 // l holds entries l and l + 64 and each solved entry is subtracted from all others
 // at once, which is the scalar order.  Backward, the scalar order subtracts the
 // newest entry first, a chain of k^2 / 2 FMAs: one lane per right-hand side, factor
-// and solution read from LDS a batch ahead (both padded with zeros, so that no
-// batch has a remainder).  k = 100, s = 16: 350 us with one thread per column and
-// everything in L2, 99 us here.
-constexpr int kCholLdsK = 128;  // (k + 24 | 1) (k + 4) + k doubles of the 160 KB of LDS
+// and solution read from LDS 8 terms ahead, also across rows.  A batch reads past
+// the last entry: the solution is zero there, so that the factor's
+// entries only have to be finite.  k = 100, s = 16: 350 us with one thread per column
+// and everything in L2, 99 us with the reads where the compiler moved them, next to their
+// use, 80 us so (16 terms ahead 84).
+constexpr int kCholLdsK = 128;  // LDS: chol_lds_bytes
 constexpr int kCholCols = 4;    // right-hand sides per workgroup
-constexpr int kCholPad = 24;
+constexpr int kCholB = 8;       // terms of a batch
+constexpr int kCholPad = 4 * kCholB;
 
 static size_t chol_lds_bytes(int k) {
-  return sizeof(double) * ((size_t)((k + kCholPad) | 1) * (k + kCholCols) + k);
+  return sizeof(double) * ((size_t)(k | 1) * k + kCholPad + (size_t)kCholCols * ((k + kCholPad) | 1) + k);
 }
 
 __global__ __launch_bounds__(256) void chol_solve_lds_kernel(const double* __restrict__ Lc, int k,
                                                              double* __restrict__ Y, int s) {
   extern __shared__ double lds[];
-  const int pitch = (k + kCholPad) | 1;
-  double* const Ls = lds;               // entry (row i, column j) at j pitch + i
-  double* const Ys = Ls + k * pitch;    // entry i of column c at c pitch + i
-  double* const Rd = Ys + kCholCols * pitch;  // 1 / L_jj
+  const int pitch = k | 1, ypitch = (k + kCholPad) | 1;
+  double* const Ls = lds;                          // entry (row i, column j) at j pitch + i
+  double* const Ys = Ls + k * pitch + kCholPad;    // entry i of column c at c ypitch + i
+  double* const Rd = Ys + kCholCols * ypitch;      // 1 / L_jj
   const int tid = threadIdx.x;
   const int lane = tid & 63, hi = lane + 64, wave = tid >> 6;
   const int c = blockIdx.x * kCholCols + wave;  // this wave's right-hand side
@@ -450,14 +453,16 @@ __global__ __launch_bounds__(256) void chol_solve_lds_kernel(const double* __res
     for (int u = 0; u < 8; ++u) {
       const int j = j0 + 4 * u;
       if (j < k) {
-        if (lane < pitch) Ls[j * pitch + lane] = lane < k ? v0[u] : 0.0;
-        if (hi < pitch) Ls[j * pitch + hi] = hi < k ? v1[u] : 0.0;
+        // zeros above the diagonal: whatever the factor's array holds there is never used
+        if (lane < pitch) Ls[j * pitch + lane] = lane >= j && lane < k ? v0[u] : 0.0;
+        if (hi < pitch) Ls[j * pitch + hi] = hi >= j && hi < k ? v1[u] : 0.0;
         if (lane + 128 < pitch) Ls[j * pitch + lane + 128] = 0.0;
         if (j == lane) Rd[j] = 1.0 / v0[u];
         if (j == hi) Rd[j] = 1.0 / v1[u];
       }
     }
   }
+  if (tid < kCholPad) Ls[k * pitch + tid] = 0.0;
   __syncthreads();
   double y0 = y0in, y1 = y1in;
   {
@@ -483,44 +488,54 @@ __global__ __launch_bounds__(256) void chol_solve_lds_kernel(const double* __res
       l1 = l1n;
     }
   }
-  if (lane < pitch) Ys[wave * pitch + lane] = lane < k ? y0 : 0.0;
-  if (hi < pitch) Ys[wave * pitch + hi] = hi < k ? y1 : 0.0;
-  if (lane + 128 < pitch) Ys[wave * pitch + lane + 128] = 0.0;
+  for (int i = k + lane; i < ypitch; i += 64) Ys[wave * ypitch + i] = 0.0;
+  if (lane < k) Ys[wave * ypitch + lane] = y0;
+  if (hi < k) Ys[wave * ypitch + hi] = y1;
   __syncthreads();
   const int cb = blockIdx.x * kCholCols + tid;
   if (tid >= kCholCols || cb >= s) return;
   // backward, L^T x = z: x_j = (z_j - L_{j+1,j} x_{j+1} - L_{j+2,j} x_{j+2} - ...) / L_jj
-  double* const Yc = Ys + tid * pitch;
-  constexpr int kB = 8;
-  double x = 0.0;
-  for (int j = k - 1; j >= 0; --j) {
-    const double* const col = Ls + j * pitch;
-    const double* lp = col + j + 2;
-    const double* yp = Yc + j + 2;
-    double la[kB], ya[kB], lb[kB], yb[kB];
-    auto read = [&](double(&l)[kB], double(&y)[kB], int at) {
+  double* const Yc = Ys + tid * ypitch;
+  double la[kCholB], ya[kCholB], lb[kCholB], yb[kCholB];
+  auto read = [&](double(&l)[kCholB], double(&y)[kCholB], int j, int at) {
+    const double* const lp = Ls + j * pitch + j + 2 + at;
+    const double* const yp = Yc + j + 2 + at;
 #pragma unroll
-      for (int u = 0; u < kB; ++u) {
-        l[u] = lp[at + u];
-        y[u] = yp[at + u];
-      }
-    };
-    read(la, ya, 0);
-    double v = fma(-col[j + 1], x, Yc[j]);  // j = k - 1: a zero of the padding
-    const double d = col[j], r = Rd[j];
-    for (int left = k - j - 2; left > 0; left -= 2 * kB, lp += 2 * kB, yp += 2 * kB) {
-      read(lb, yb, kB);
-#pragma unroll
-      for (int u = 0; u < kB; ++u) v = fma(-la[u], ya[u], v);
-      read(la, ya, 2 * kB);
-      if (left > kB) {
-#pragma unroll
-        for (int u = 0; u < kB; ++u) v = fma(-lb[u], yb[u], v);
-      }
+    for (int u = 0; u < kCholB; ++u) {
+      l[u] = lp[u];
+      y[u] = yp[u];
     }
+  };
+  double x = 0.0;  // x_{j+1}; the entry of the factor beside it is in the padding at j = k - 1
+  double c1 = 0.0, z = Yc[k - 1], d = Ls[(k - 1) * pitch + k - 1], r = Rd[k - 1];
+  read(la, ya, k - 1, 0);
+  for (int j = k - 1; j >= 0; --j) {
+    const int jn = j > 0 ? j - 1 : 0;  // the next row
+    const double c1n = Ls[jn * pitch + jn + 1], zn = Yc[jn], dn = Ls[jn * pitch + jn], rn = Rd[jn];
+    double v = fma(-c1, x, z);
+    const int terms = k - j - 2;
+    int at = 0;
+    do {
+      const bool last = at + 2 * kCholB >= terms;
+      read(lb, yb, j, at + kCholB);
+      __builtin_amdgcn_sched_barrier(0);  // the compiler would move the reads down to their use
+#pragma unroll
+      for (int u = 0; u < kCholB; ++u) v = fma(-la[u], ya[u], v);
+      __builtin_amdgcn_sched_barrier(0);
+      read(la, ya, last ? jn : j, last ? 0 : at + 2 * kCholB);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < kCholB; ++u) v = fma(-lb[u], yb[u], v);
+      __builtin_amdgcn_sched_barrier(0);
+      at += 2 * kCholB;
+    } while (at < terms);
     x = div_by(v, d, r);
     Yc[j] = x;
     Y[(int64_t)j * s + cb] = x;
+    c1 = c1n;
+    z = zn;
+    d = dn;
+    r = rn;
   }
 }
 
