@@ -72,7 +72,10 @@ extern "C" {
  * makes every product involving it NaN (gp_mbcg then fails with GP_ENONFINITE);
  * GP_PREC_FP32 has no such bound. */
 #define GP_PREC_BF16X3 1
-#define GP_PREC_FP64 2   /* FP64 throughout (low-noise regime); gp_kmm, gp_mbcg and gp_bcg only, d <= 64 */
+/* FP64 throughout (low-noise regime); gp_kmm, gp_mbcg, gp_bcg and gp_bpcg only, d <= 64.  A
+ * point with a NaN or infinite coordinate, or one some 1e153 lengthscales from the origin
+ * (the square of its distance overflows), makes every product involving it NaN. */
+#define GP_PREC_FP64 2
 
 #define GP_MAX_D 128 /* largest feature count d */
 

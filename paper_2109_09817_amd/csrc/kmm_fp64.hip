@@ -93,18 +93,38 @@ __device__ __forceinline__ void profile64x4(const f64x4& h, double (&m)[4]) {
   }
 }
 
+// Squared scaled norms below this keep S finite; the profile's clamps would turn a NaN
+// S into m = 1 and an infinite one into m = 0.  A point at or beyond it (a NaN or
+// infinite coordinate, or one some 1e153 lengthscales from the origin) makes every
+// product involving it NaN, as in the mixed form never silently wrong.  The preparation
+// leaves NaN in the first norm of a block of kF64Block that holds such a point; the
+// sweep looks there once, at its end (a test per chunk took up to 4% of it).
+constexpr double kF64FarNorm = 0x1p1021;
+constexpr int kF64Block = 256;
+
 // sc64[f] = feature scale (thread f < d); nrm[p] = |x_p (.) sc|^2 for p < rows.
-__global__ void prep_fp64_kernel(const double* __restrict__ X, int64_t rows, int d, Scale sc,
+__global__ __launch_bounds__(kF64Block) void prep_fp64_kernel(const double* __restrict__ X, int64_t rows, int d, Scale sc,
                                  double* __restrict__ sc64, double* __restrict__ nrm) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p < d) sc64[p] = sc.s[p];
-  if (p >= rows) return;
   double s = 0.0;
-  for (int f = 0; f < d; ++f) {
-    const double v = X[p * d + f] * sc.s[f];
-    s = fma(v, v, s);
+  if (p < rows) {
+    for (int f = 0; f < d; ++f) {
+      const double v = X[p * d + f] * sc.s[f];
+      s = fma(v, v, s);
+    }
   }
-  nrm[p] = s;
+  __shared__ int far[kF64Block / 64];
+  const int wave_far = __any(!(s < kF64FarNorm));
+  if ((threadIdx.x & 63) == 0) far[threadIdx.x >> 6] = wave_far;
+  if (threadIdx.x != 0 && p < rows) nrm[p] = s;
+  __syncthreads();
+  if (threadIdx.x == 0 && p < rows) {
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < kF64Block / 64; ++w) any |= far[w];
+    nrm[p] = any ? __builtin_nan("") : s;
+  }
 }
 
 struct F64Args {
@@ -273,8 +293,11 @@ __global__ __launch_bounds__(256, 2) void sweep_fp64_kernel(F64Args a, int first
     }
   }
   // acc[cb][i]: row 16 wave + lk + 4 i, column 16 cb + lr -> LDS tile [column][row]
+  const double mark = a.nb[kF64Block * lane < n ? kF64Block * lane : 0];  // in flight across the barriers
   __syncthreads();
   double* const Os = buf;
+  int* const row_far = (int*)Ns;
+  if (lk == 0) row_far[16 * wave + lr] = !(naa < kF64FarNorm);
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
@@ -285,17 +308,21 @@ __global__ __launch_bounds__(256, 2) void sweep_fp64_kernel(F64Args a, int first
     accr[c] += __shfl_xor(accr[c], 32);
     if (lk == 0) Os[(16 * NCB + c) * kOLd + 16 * wave + lr] = accr[c];
   }
+  bool far = !(mark < kF64FarNorm);
+  for (int64_t p = kF64Block * (64 + lane); p < n; p += 64 * kF64Block) far |= !(a.nb[p] < kF64FarNorm);
   __syncthreads();
+  // lane's row (a square product of one point has the exact diagonal only)
+  const bool nan = (__any(far) || row_far[lane]) && !(a.square && n == 1);
+  auto sum = [&](int c) { return nan ? __builtin_nan("") : Os[c * kOLd + lane]; };
   if (a.part) {
     const int64_t r = (int64_t)blockIdx.x * kF64Rows + lane;
-    for (int c = wave; c < live; c += 4)
-      a.part[((int64_t)blockIdx.z * a.t + c0 + c) * a.slab + r] = Os[c * kOLd + lane];
+    for (int c = wave; c < live; c += 4) a.part[((int64_t)blockIdx.z * a.t + c0 + c) * a.slab + r] = sum(c);
     return;
   }
   const int64_t ar = a0 + lane;
   if (ar >= a.m) return;
   for (int c = wave; c < live; c += 4) {
-    double y = a.sf * Os[c * kOLd + lane];
+    double y = a.sf * sum(c);
     if (a.square) y = fma(a.noise, a.V[(int64_t)(c0 + c) * a.ldv + ar], y);
     a.out[(int64_t)(c0 + c) * a.ldo + ar] = y;
   }
@@ -406,10 +433,8 @@ hipError_t fp64_prepare(KmmPlan& p, const gp_kernel* kern, const double* X, cons
   if (!X || (!p.square && !Z) || !p.sc64) return hipErrorInvalidValue;
   p.x64 = X;
   p.z64 = p.square ? X : Z;
-  const int thr = 256;
-  prep_fp64_kernel<<<(unsigned)((std::max<int64_t>(p.n, p.d) + thr - 1) / thr), thr, 0, st>>>(X, p.n, p.d,
-                                                                                            make_scale64(kern), p.sc64,
-                                                                                            p.nb64);
+  prep_fp64_kernel<<<(unsigned)((std::max<int64_t>(p.n, p.d) + kF64Block - 1) / kF64Block), kF64Block, 0, st>>>(
+      X, p.n, p.d, make_scale64(kern), p.sc64, p.nb64);
   return hipGetLastError();
 }
 
