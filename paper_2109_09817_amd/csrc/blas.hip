@@ -343,7 +343,19 @@ __global__ __launch_bounds__(256) void tall_product_kernel(const double* A, int6
 #pragma unroll
   for (int h = 0; h < NCB; ++h) acc[h] = f64x4{0.0, 0.0, 0.0, 0.0};
   double av[4], cv[4][NCB];
-  auto load = [&](int k) {  // 16 k values: MFMA u takes k + 4 u + lg; beyond kend A is zero
+  // 16 k values: MFMA u takes k + 4 u + lg.  Beyond kend both operands are zero (an
+  // infinity of C times a zero of A would be NaN).
+  auto load = [&](int k) {
+    if (k + 16 <= kend) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t kx = k + 4 * u + lg;
+        av[u] = Ar[kx * lda];
+#pragma unroll
+        for (int h = 0; h < NCB; ++h) cv[u][h] = Cc[h][kx * ldc];
+      }
+      return;
+    }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int kx = k + 4 * u + lg;
@@ -351,7 +363,10 @@ __global__ __launch_bounds__(256) void tall_product_kernel(const double* A, int6
       const double v = Ar[kc * lda];
       av[u] = kx < kend ? v : 0.0;
 #pragma unroll
-      for (int h = 0; h < NCB; ++h) cv[u][h] = Cc[h][kc * ldc];
+      for (int h = 0; h < NCB; ++h) {
+        const double w = Cc[h][kc * ldc];
+        cv[u][h] = kx < kend ? w : 0.0;
+      }
     }
   };
   if (kbeg < kend) {

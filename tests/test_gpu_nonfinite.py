@@ -65,3 +65,20 @@ def test_square_product_of_one_point_is_its_exact_diagonal(prec):
     for x in (1.0, 1e200):
         got = host(gp.kmm(k, dev(np.array([[x, 2.0]])), dev(V), precision=prec))
         np.testing.assert_array_equal(got, 1.75 * V)
+
+
+@pytest.mark.parametrize("r", [1, 5, 16, 63, 100])
+@pytest.mark.parametrize("s", [1, 20, 64])
+def test_tall_product_keeps_infinities(r, s):
+    """sigma^{-1} V + Z^T diag(g) Z V with Z > 0 > g and one entry of V infinite: that column is -inf, NaN where +inf meets
+    -inf, and the other columns keep their bits, however the r terms are padded."""
+    from paper_2109_09817_amd import gp
+    n, i0 = 150, 77
+    rng = np.random.default_rng(r + s)
+    Z, g, V = rng.uniform(0.5, 1.0, (r, n)), -rng.uniform(0.5, 1.0, r), rng.standard_normal((s, n))
+    pc = gp.Nystrom(dev(Z), dev(g), np.arange(r), 0.25)
+    ref = host(gp.nystrom_apply(pc, dev(V)))
+    V[s // 2, i0] = np.inf
+    ref[s // 2] = -np.inf
+    ref[s // 2, i0] = np.nan
+    np.testing.assert_array_equal(host(gp.nystrom_apply(pc, dev(V))), ref)
