@@ -1,0 +1,28 @@
+"""Branches of the tiled kernels that only large sizes and wide blocks reach, and the sums whose order is fixed to the bit."""
+import numpy as np
+import pytest
+
+import oracle.kernel as ok
+from _helpers import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+def _gk(th):
+    from paper_2109_09817_amd import gp
+    return gp.Kernel(th.ell, th.sf, th.noise, "matern52" if th.kind == ok.MATERN52 else "rbf")
+
+
+@pytest.mark.parametrize("n", [3400, 6209, 7201])
+def test_cholesky_and_inverse_beyond_one_launch_of_trailing_tiles(n):
+    """A diagonal block carries up to 255 of the 128-wide trailing tiles beside it: 276 tiles take two launches (n = 3,400),
+    more than 1,020 take larger shares (n = 6,209: 1,035).  The doubled inverse takes 128-wide batches from four pairs of
+    1,024 rows (n = 7,201) or two of 2,048 on, the last one ragged.  Residual of K_hat omega = y: about 1e-16 times
+    cond(K_hat) < 1e4 and the square root of n; bar 1e-10 (a tile left out or taken twice: above 1e-3)."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n)
+    X, y = rng.standard_normal((n, 5)), rng.standard_normal(n)
+    th = ok.Theta(rng.uniform(0.3, 0.6, 5), 1.2, 0.1, ok.MATERN52)
+    r = gp.exact_mll_and_grad(_gk(th), dev(X), dev(y), with_grad=False, with_omega=True)
+    back = ok.khat_matmul(X, th, host(r.omega)[:, None])[:, 0]
+    assert np.linalg.norm(back - y) <= 1e-10 * np.linalg.norm(y)
