@@ -26,3 +26,21 @@ def test_cholesky_and_inverse_beyond_one_launch_of_trailing_tiles(n):
     r = gp.exact_mll_and_grad(_gk(th), dev(X), dev(y), with_grad=False, with_omega=True)
     back = ok.khat_matmul(X, th, host(r.omega)[:, None])[:, 0]
     assert np.linalg.norm(back - y) <= 1e-10 * np.linalg.norm(y)
+
+
+def test_large_rank_factor_with_whole_and_split_gram_tiles():
+    """r = 4,001: 528 lower 128-wide tiles, 512 of them whole and 16 split in k, their products in slabs.  P^{-1} P v = v with
+    P^{-1} = sigma^{-2} (I - E E^T) and P v by a dense solve: rounding is amplified by cond(K_MM) and cond(P), both below 1e4
+    here, at most 1e-8; bar 1e-8 (a tile left out: above 1e-3)."""
+    from paper_2109_09817_amd import gp
+    n, r, s2 = 4600, 4001, 0.1
+    rng = np.random.default_rng(r)
+    X = rng.standard_normal((n, 6))
+    th = ok.Theta(rng.uniform(0.3, 0.6, 6), 1.0, s2, ok.MATERN52)
+    M = np.sort(rng.choice(n, r, replace=False))
+    E = host(gp.nystrom_chol_precond(_gk(th), dev(X), M).E)
+    KMX = ok.kernel(X[M], X, th)
+    v = rng.standard_normal((n, 3))
+    Pv = KMX.T @ np.linalg.solve(KMX[:, M] + 1e-10 * r * np.eye(r), KMX @ v) + s2 * v
+    back = (Pv - E.T @ (E @ Pv)) / s2
+    assert np.linalg.norm(back - v) <= 1e-8 * np.linalg.norm(v)
