@@ -1,4 +1,6 @@
 """Branches of the tiled kernels that only large sizes and wide blocks reach, and the sums whose order is fixed to the bit."""
+from fractions import Fraction
+
 import numpy as np
 import pytest
 
@@ -87,3 +89,76 @@ def test_woodbury_solve_in_groups_of_columns(s):
     L = host(pc.L)
     ref = np.linalg.solve(L.T @ L + 1e-2 * np.eye(n), B.T).T
     assert np.linalg.norm(host(r.Z0) - ref) <= 1e-10 * np.linalg.norm(ref)
+
+
+def _fma(a, b, c):
+    return float(Fraction(a) * Fraction(b) + Fraction(c))
+
+
+@pytest.mark.parametrize("k", [3, 70, 128, 130])
+def test_woodbury_solve_has_the_bits_of_its_scalar_loops(k):
+    """Z0 = (B - L C^{-1} L^T B) / sigma^2, every sum a chain of FMAs in ascending order of its index: the matrix cores and
+    the in-LDS solve (k <= 128) keep these bits, on which mBCG's results rest."""
+    from paper_2109_09817_amd import gp
+    n, d, s, noise = 150, 5, 2, 1e-2
+    rng = np.random.default_rng(k)
+    X, B = rng.standard_normal((n, d)), rng.standard_normal((s, n))
+    kern = gp.Kernel(rng.uniform(1.0, 2.0, d), 1.0, noise)
+    pc = gp.pivchol(kern, dev(X), k)
+    Z0 = host(gp.mbcg(kern, dev(X), dev(B), 1, 0.0, pc=pc, precision="fp32").Z0)
+    L, Cc = host(pc.L), host(pc.Cchol)  # L[j] = column j; Cc[j, i] = entry (i, j) of the factor
+    for c in range(s):
+        y = []
+        for j in range(k):
+            v = 0.0
+            for i in range(n):
+                v = _fma(L[j, i], B[c, i], v)
+            y.append(v)
+        for j in range(k):
+            for i in range(j):
+                y[j] = _fma(-Cc[i, j], y[i], y[j])
+            y[j] = y[j] / Cc[j, j]
+        for j in reversed(range(k)):
+            for i in range(j + 1, k):
+                y[j] = _fma(-Cc[j, i], y[i], y[j])
+            y[j] = y[j] / Cc[j, j]
+        ref = np.empty(n)
+        for i in range(n):
+            v = 0.0
+            for j in range(k):
+                v = _fma(L[j, i], y[j], v)
+            ref[i] = (1.0 / noise) * (B[c, i] - v)
+        np.testing.assert_array_equal(Z0[c], ref)
+
+
+def _block_dot(a, b):
+    """Sum of a b as the column reductions add it, up to 256 blocks of 256 rows: products, a tree over the lanes of each wave,
+    the waves of a block in order, and the block sums once more in the same way."""
+    def block_sum(v):
+        w = np.zeros(256)
+        w[:len(v)] = v
+        w = w.reshape(4, 64)
+        while w.shape[1] > 1:
+            h = w.shape[1] // 2
+            w = w[:, :h] + w[:, h:]
+        r = 0.0
+        for x in w[:, 0]:
+            r = r + x
+        return r
+    p = a * b
+    return block_sum([block_sum(p[i:i + 256]) for i in range(0, len(p), 256)])
+
+
+@pytest.mark.parametrize("prec", ["bf16x3", "fp32", "fp64"])
+@pytest.mark.parametrize("n", [1, 300, 1031])
+def test_first_step_size_to_the_bit(n, prec):
+    """alpha = (B . B) / (B . K_hat B), the product's dot added in its epilogue (mixed and FP32 forms) or by the column
+    reduction (FP64): the same additions, on the values that gp_kmm returns for the same product."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n)
+    X, B = rng.standard_normal((n, 6)), rng.standard_normal((3, n))
+    kern = gp.Kernel(np.full(6, 1.5), 1.1, 0.5)
+    r = gp.mbcg(kern, dev(X), dev(B), 1, 0.0, precision=prec)
+    KB = host(gp.kmm(kern, dev(X), dev(B), precision=prec))
+    ref = [_block_dot(B[c], B[c]) / _block_dot(B[c], KB[c]) for c in range(3)]
+    np.testing.assert_array_equal(r.alpha[0], ref)
