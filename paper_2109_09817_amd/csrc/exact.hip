@@ -229,23 +229,22 @@ __device__ __forceinline__ void potrf_diag(double* __restrict__ A, int64_t n, in
 
 // ---------------------------------------------------------------- tile updates
 
-// C[R + r][Cc + c] -= sum_{k < kb} P(r, k) Q(k, c) (ASSIGN: =) over a set of
+// C[R + r][Cc + c] -= sum_{k < kb} P(r, k) Q(c, k) (ASSIGN: =) over a set of
 // 64 x 64 tiles (k in chunks of 64 staged in LDS in turn), with
-//   P(r, k) = PT ? Pm[(p0 + k) ldp + pr + r] : Pm[(pr + r) ldp + p0 + k]
-//   Q(k, c) = QT ? Qm[(qc + c) ldq + q0 + k] : Qm[(q0 + k) ldq + qc + c]
-// where pr = R (pfix < 0) or pfix, and qc = Cc (qfix < 0) or qfix.  Tile (ti,
-// tj) has R = rbase + 64 ti, Cc = cbase + 64 tj; LOWER enumerates tj <= ti of the
-// nrt x nct (nct <= nrt) rectangle, otherwise all of it.  Output rows and columns at or beyond
+//   P(r, k) = Pm[(R + r) ldp + p0 + k],  Q(c, k) = Qm[(qc + c) ldq + q0 + k]
+// where qc = Cc (qfix < 0) or qfix.  Tile (ti, tj) has R = rbase + 64 ti, Cc =
+// cbase + 64 tj; LOWER enumerates tj <= ti of the nrt x nct (nct <= nrt)
+// rectangle, otherwise all of it.  Output rows and columns at or beyond
 // n are skipped (their operands read as 0).  Every operand is read before
 // the tile is written, so C's tile may be one of the operand tiles (never
 // another workgroup's).  The products run on the FP64 matrix cores
 // (v_mfma_f64_16x16x4: lane l supplies P(row l % 16, k l / 16) and Q(k l / 16,
 // column l % 16) and receives rows l / 16 + 4 i of column l % 16); wave w
-// owns the 32 x 32 quadrant (w / 2, w % 2).  Each operand keeps in LDS the
-// orientation of its source rows, so that a wave's staging writes are
+// owns the 32 x 32 quadrant (w / 2, w % 2).  Operands in LDS keep the
+// orientation of their source rows, so that a wave's staging writes are
 // contiguous: k-major [k][x] (pitch 80 doubles) when the source runs along x,
-// x-major [x][k] (pitch 66) when it runs along k.  Both pitches put the 32
-// lanes of a half-wave on distinct banks for the operand reads.
+// x-major [x][k] (pitch 66) when it runs along k, as both operands do here.  Both
+// pitches put the 32 lanes of a half-wave on distinct banks for the operand reads.
 constexpr int kKMajorLd = kEb + 16;
 constexpr int kXMajorLd = kEb + 2;
 
@@ -262,13 +261,11 @@ __device__ __forceinline__ void lower_tile(int64_t b, int64_t& ti, int64_t& tj) 
   tj = b - ti * (ti + 1) / 2;
 }
 
-template <bool PT, bool QT, bool LOWER, bool ASSIGN>
-__global__ __launch_bounds__(256) void tile_update_kernel(const double* Pm, int64_t ldp, int64_t pfix, int64_t p0,
-                                                          const double* Qm, int64_t ldq, int64_t qfix, int64_t q0,
-                                                          double* Cm, int64_t n, int kb, int64_t rbase, int64_t cbase,
-                                                          int nrt, int nct) {
-  __shared__ double Ps[kEb * kKMajorLd];  // P(r, k) at lds_at<PT>(k, r)
-  __shared__ double Qs[kEb * kKMajorLd];  // Q(k, c) at lds_at<!QT>(k, c)
+template <bool LOWER, bool ASSIGN>
+__global__ __launch_bounds__(256) void tile_update_kernel(const double* Pm, int64_t ldp, int64_t p0, const double* Qm,
+                                                          int64_t ldq, int64_t qfix, int64_t q0, double* Cm, int64_t n,
+                                                          int kb, int64_t rbase, int64_t cbase, int nrt, int nct) {
+  __shared__ double Ps[kEb * kXMajorLd], Qs[kEb * kXMajorLd];  // P(r, k) and Q(c, k) at lds_at<false>(k, r or c)
   int64_t ti, tj;
   // Workgroup h runs on XCD h % 8; each XCD takes a contiguous run of tiles
   // (consecutive tiles of a tile row share their P panel in that XCD's L2).
@@ -284,7 +281,7 @@ __global__ __launch_bounds__(256) void tile_update_kernel(const double* Pm, int6
     if (LOWER) ti += nct;
   }
   const int64_t R = rbase + kEb * ti, Cc = cbase + kEb * tj;
-  const int64_t pr = pfix < 0 ? R : pfix, qc = qfix < 0 ? Cc : qfix;
+  const int64_t qc = qfix < 0 ? Cc : qfix;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r0 = 32 * (wave >> 1), c0 = 32 * (wave & 1);
   const int lr = lane & 15, lk = lane >> 4;
@@ -301,28 +298,17 @@ __global__ __launch_bounds__(256) void tile_update_kernel(const double* Pm, int6
 #pragma unroll
     for (int it = 0; it < kPer; ++it) {
       const int e = (int)threadIdx.x + 256 * it;
-      const int x = e / kEb, y = e % kEb;  // consecutive threads: consecutive y
-      {
-        const int r = PT ? y : x, k = PT ? x : y;
-        const bool ok = kc + k < kb && R + r < n;
-        const int64_t kk = p0 + kc + k;
-        pv[it] = ok ? (PT ? Pm[kk * ldp + pr + r] : Pm[(pr + r) * ldp + kk]) : 0.0;
-      }
-      {
-        const int c = QT ? x : y, k = QT ? y : x;
-        const bool ok = kc + k < kb && Cc + c < n;
-        const int64_t kk = q0 + kc + k;
-        qv[it] = ok ? (QT ? Qm[(qc + c) * ldq + kk] : Qm[kk * ldq + qc + c]) : 0.0;
-      }
+      const int x = e / kEb, k = e % kEb;  // consecutive threads: consecutive k
+      pv[it] = kc + k < kb && R + x < n ? Pm[(R + x) * ldp + p0 + kc + k] : 0.0;
+      qv[it] = kc + k < kb && Cc + x < n ? Qm[(qc + x) * ldq + q0 + kc + k] : 0.0;
     }
   };
   auto store = [&]() {
 #pragma unroll
     for (int it = 0; it < kPer; ++it) {
       const int e = (int)threadIdx.x + 256 * it;
-      const int x = e / kEb, y = e % kEb;
-      Ps[PT ? lds_at<true>(x, y) : lds_at<false>(y, x)] = pv[it];
-      Qs[QT ? lds_at<false>(y, x) : lds_at<true>(x, y)] = qv[it];
+      Ps[lds_at<false>(e % kEb, e / kEb)] = pv[it];
+      Qs[lds_at<false>(e % kEb, e / kEb)] = qv[it];
     }
   };
   load(0);
@@ -333,8 +319,8 @@ __global__ __launch_bounds__(256) void tile_update_kernel(const double* Pm, int6
     if (kc + kEb < kb) load(kc + kEb);
 #pragma unroll 4
     for (int k = 0; k < kEb; k += 4) {
-      const double a0 = Ps[lds_at<PT>(k + lk, r0 + lr)], a1 = Ps[lds_at<PT>(k + lk, r0 + 16 + lr)];
-      const double q0v = Qs[lds_at<!QT>(k + lk, c0 + lr)], q1v = Qs[lds_at<!QT>(k + lk, c0 + 16 + lr)];
+      const double a0 = Ps[lds_at<false>(k + lk, r0 + lr)], a1 = Ps[lds_at<false>(k + lk, r0 + 16 + lr)];
+      const double q0v = Qs[lds_at<false>(k + lk, c0 + lr)], q1v = Qs[lds_at<false>(k + lk, c0 + 16 + lr)];
       acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, q0v, acc[0][0], 0, 0, 0);
       acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, q1v, acc[0][1], 0, 0, 0);
       acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, q0v, acc[1][0], 0, 0, 0);
@@ -363,20 +349,20 @@ __global__ __launch_bounds__(256) void tile_update_kernel(const double* Pm, int6
       }
 }
 
-template <bool PT, bool QT, bool LOWER, bool ASSIGN>
-static hipError_t tile_update(const double* Pm, int64_t ldp, int64_t pfix, int64_t p0, const double* Qm, int64_t ldq,
-                              int64_t qfix, int64_t q0, double* Cm, int64_t n, int kb, int64_t rbase, int64_t cbase,
-                              int nrt, int nct, hipStream_t st) {
+template <bool LOWER, bool ASSIGN>
+static hipError_t tile_update(const double* Pm, int64_t ldp, int64_t p0, const double* Qm, int64_t ldq, int64_t qfix,
+                              int64_t q0, double* Cm, int64_t n, int kb, int64_t rbase, int64_t cbase, int nrt, int nct,
+                              hipStream_t st) {
   const int64_t tiles =
       LOWER ? (int64_t)nct * (nct + 1) / 2 + (int64_t)(nrt - nct) * nct : (int64_t)nrt * nct;
   if (tiles <= 0) return hipSuccess;
-  tile_update_kernel<PT, QT, LOWER, ASSIGN><<<(unsigned)tiles, 256, 0, st>>>(Pm, ldp, pfix, p0, Qm, ldq, qfix, q0, Cm,
-                                                                             n, kb, rbase, cbase, nrt, nct);
+  tile_update_kernel<LOWER, ASSIGN><<<(unsigned)tiles, 256, 0, st>>>(Pm, ldp, p0, Qm, ldq, qfix, q0, Cm, n, kb, rbase,
+                                                                     cbase, nrt, nct);
   return hipGetLastError();
 }
 
 // General FP64 products on the matrix cores.  C (m x nn, row-major with ldc)
-// = A B, = -A B or -= A B:
+// = A B or = -A B (-= A B only where potrf_update_kernel stores a tile):
 //   A(i, k) = TA ? A[k lda + i] : A[i lda + k], B(k, j) = TB ? B[j ldb + k] : B[k ldb + j].
 // LOWER computes only the tiles with tj <= ti (m = nn).  Rows and columns
 // beyond the matrices read as zero or as some valid row; nothing outside C's
@@ -448,6 +434,7 @@ __device__ __forceinline__ bool gemm_tile(const GemmArgs& g, int64_t m, int64_t 
 // 64 x 64 output tiles, k in chunks of 64 staged in LDS as in the tile kernel above.
 template <bool TA, bool TB, bool LOWER, int MODE>
 __global__ __launch_bounds__(256) void gemm64_f64_kernel(GemmArgs g) {
+  static_assert(MODE != kSubtract, "the tile is stored, not added to");
   __shared__ double As[kEb * kKMajorLd];  // A(r, k) at lds_at<TA>(k, r)
   __shared__ double Bs[kEb * kKMajorLd];  // B(k, c) at lds_at<!TB>(k, c)
   const int64_t p = blockIdx.y;
@@ -887,21 +874,19 @@ static hipError_t cholesky(double* A, int64_t n, int* info, double* Dinv, hipStr
       if ((e = hipGetLastError()) != hipSuccess) return e;
       if (rest <= 0) return hipSuccess;
       // L21 = A21 L11^{-T} for every row below (jb = 64 here)
-      e = tile_update<false, true, false, true>(A, n, -1, j0, Di, kEb, 0, 0, A, n, jb, j0 + jb, j0, ntiles(rest),
-                                                1, st);
+      e = tile_update<false, true>(A, n, j0, Di, kEb, 0, 0, A, n, jb, j0 + jb, j0, ntiles(rest), 1, st);
       if (e != hipSuccess) return e;
       // the rest of this super-panel's columns, [j0 + 64, Jend), on and below the diagonal
       const int64_t wcols = Jend - j0 - jb;
       if (wcols > 0) {
-        e = tile_update<false, true, true, false>(A, n, -1, j0, A, n, -1, j0, A, n, jb, j0 + jb, j0 + jb,
-                                                  ntiles(rest), ntiles(wcols), st);
+        e = tile_update<true, false>(A, n, j0, A, n, -1, j0, A, n, jb, j0 + jb, j0 + jb, ntiles(rest), ntiles(wcols), st);
         if (e != hipSuccess) return e;
       }
     }
     // the next super-panel's columns, k = 256
     if (n > Jend) {
-      e = tile_update<false, true, true, false>(A, n, -1, J0, A, n, -1, J0, A, n, kSp, Jend, Jend, ntiles(n - Jend),
-                                                ntiles(std::min<int64_t>(kSp, n - Jend)), st);
+      e = tile_update<true, false>(A, n, J0, A, n, -1, J0, A, n, kSp, Jend, Jend, ntiles(n - Jend),
+                                   ntiles(std::min<int64_t>(kSp, n - Jend)), st);
       if (e != hipSuccess) return e;
     }
   }

@@ -60,7 +60,6 @@ struct KmmPlan {
   double* vinv = nullptr;    // mixed form: 2^-15 / (column scale of V's fragments), applied to the partial sums
   double* vpart = nullptr;   // mixed form: column-max partials (scratch of kmm_prepare_v)
   double* part = nullptr;
-  int64_t part_splits = 0;  // splits the partial buffer can hold
   // FP64 form: the points themselves (caller memory), prescaled features and norms
   const double* x64 = nullptr;  // b stream (training points), n x d
   const double* z64 = nullptr;  // output rows, m x d
