@@ -983,17 +983,35 @@ hipError_t coldot_partials(const double* A, const double* B, int64_t n, int s, d
                                                                                    partial);
   return hipGetLastError();
 }
-hipError_t mbcg_launch_update_ur(const MbcgState& s, int cur, const double* D, const double* W, double* U, double* R,
+
+// Every workgroup of a column adds that column's partial sums, so that this work grows with the
+// square of their number.  Up to kSumInPlace (n = 131,072) it costs less than the three launches that
+// it saves (an iteration at n = 65,536, d = 5, 16 columns: 1,448 us, 1,459 with the sums first; n =
+// 131,072: 5,509 and 5,496); beyond, the sums are formed first (n = 262,144, 33 columns: 28.97 ->
+// 28.75 ms).  One partial sum is left then, which is its own sum: the same bits.
+constexpr int64_t kSumInPlace = 512;
+
+static int64_t sum_partials(double*& part, double* sum, int64_t nblk, int s, hipStream_t st) {
+  if (nblk <= kSumInPlace) return nblk;
+  reduce_partials_kernel<<<s, kThreads, 0, st>>>(part, nblk, s, sum);
+  part = sum;
+  return 1;
+}
+
+hipError_t mbcg_launch_update_ur(MbcgState s, int cur, const double* D, const double* W, double* U, double* R,
                                  int64_t n, hipStream_t st) {
   const RowSplit rs = row_split(n, kDotBlocks);
-  mbcg_update_ur_kernel<<<dim3((unsigned)rs.nblk, (unsigned)s.s), kThreads, 0, st>>>(s, cur, rs.nblk, D, W, U, R, n,
+  const int64_t np = sum_partials(s.dpart, s.dsum, rs.nblk, s.s, st);
+  mbcg_update_ur_kernel<<<dim3((unsigned)rs.nblk, (unsigned)s.s), kThreads, 0, st>>>(s, cur, np, D, W, U, R, n,
                                                                                       rs.rows_per_blk);
   return hipGetLastError();
 }
-hipError_t mbcg_launch_update_d(const MbcgState& s, int cur, int j, double tol, const double* Z, double* D, int64_t n,
+hipError_t mbcg_launch_update_d(MbcgState s, int cur, int j, double tol, const double* Z, double* D, int64_t n,
                                 hipStream_t st) {
   const RowSplit rs = row_split(n, kDotBlocks);
-  mbcg_update_d_kernel<<<dim3((unsigned)rs.nblk, (unsigned)s.s), kThreads, 0, st>>>(s, cur, rs.nblk, j, tol, Z, D, n,
+  sum_partials(s.rpart, s.rsum, rs.nblk, s.s, st);
+  const int64_t np = sum_partials(s.gpart, s.gsum, rs.nblk, s.s, st);
+  mbcg_update_d_kernel<<<dim3((unsigned)rs.nblk, (unsigned)s.s), kThreads, 0, st>>>(s, cur, np, j, tol, Z, D, n,
                                                                                      rs.rows_per_blk);
   return hipGetLastError();
 }

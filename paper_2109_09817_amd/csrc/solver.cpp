@@ -159,6 +159,9 @@ int run_mbcg(const gp_kernel* kern, int precision, const double* X, int64_t n, c
   S.active[0] = cv.take<int>(s);
   S.active[1] = cv.take<int>(s);
   S.iters = cv.take<int>(s);
+  S.dsum = cv.take<double>(s);
+  S.rsum = cv.take<double>(s);
+  S.gsum = cv.take<double>(s);
   S.dpart = cv.take<double>(dot_partial_doubles(n, s));
   S.rpart = cv.take<double>(dot_partial_doubles(n, s));
   S.gpart = cv.take<double>(dot_partial_doubles(n, s));

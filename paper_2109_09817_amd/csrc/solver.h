@@ -34,6 +34,7 @@ struct MbcgState {
   double* dpart;      // partial sums [block][column] (row_split(n, kDotBlocks)) of d.w,
   double* rpart;      // of ||r||^2 after the residual update
   double* gpart;      // and of r.z after the preconditioner step
+  double *dsum, *rsum, *gsum;  // the sums themselves, where there are many partial sums
   double* alpha;      // current step sizes (copied to the host every iteration)
   double* beta;
   double* bnorm;      // ||b|| (holds ||b||^2 until init)
@@ -93,9 +94,9 @@ hipError_t launch_fill(double* dst, double v, int64_t count, hipStream_t st);
 hipError_t mbcg_launch_init(const MbcgState& s, hipStream_t st);
 // Step cur of an iteration reads gamma[cur], active[cur] and writes the other copies
 // (update_d).  dpart, rpart and gpart must hold their partial sums.
-hipError_t mbcg_launch_update_ur(const MbcgState& s, int cur, const double* D, const double* W, double* U, double* R,
+hipError_t mbcg_launch_update_ur(MbcgState s, int cur, const double* D, const double* W, double* U, double* R,
                                  int64_t n, hipStream_t st);
-hipError_t mbcg_launch_update_d(const MbcgState& s, int cur, int j, double tol, const double* Z, double* D, int64_t n,
+hipError_t mbcg_launch_update_d(MbcgState s, int cur, int j, double tol, const double* Z, double* D, int64_t n,
                                 hipStream_t st);
 
 int64_t pivchol_blocks(int64_t n);

@@ -162,3 +162,30 @@ def test_first_step_size_to_the_bit(n, prec):
     KB = host(gp.kmm(kern, dev(X), dev(B), precision=prec))
     ref = [_block_dot(B[c], B[c]) / _block_dot(B[c], KB[c]) for c in range(3)]
     np.testing.assert_array_equal(r.alpha[0], ref)
+
+
+@pytest.mark.parametrize("n", [131072, 131073, 262145])
+def test_first_step_size_to_the_bit_with_many_partial_sums(n):
+    """512 blocks' sums are added by every workgroup, more of them once before; 512 rows to a block at n = 262,145.  B holds
+    signs, so that every product is exact and the FMAs are plain additions."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n)
+    X, B = rng.standard_normal((n, 4)), rng.choice([-1.0, 1.0], (2, n))
+    kern = gp.Kernel(np.full(4, 0.5), 1.1, 0.5)
+    r = gp.mbcg(kern, dev(X), dev(B), 1, 0.0, precision="bf16x3")
+    KB = host(gp.kmm(kern, dev(X), dev(B), precision="bf16x3"))
+
+    def block_sum(v):
+        w = np.zeros(256)
+        for i in range(0, len(v), 256):
+            w[:len(v[i:i + 256])] += v[i:i + 256]
+        w = w.reshape(4, 64)
+        while w.shape[1] > 1:
+            h = w.shape[1] // 2
+            w = w[:, :h] + w[:, h:]
+        return ((w[0, 0] + w[1, 0]) + w[2, 0]) + w[3, 0]
+    rows = 256 if n <= 262144 else 512
+
+    def dot(a, b):
+        return block_sum(np.array([block_sum((a * b)[i:i + rows]) for i in range(0, n, rows)]))
+    np.testing.assert_array_equal(r.alpha[0], [dot(B[c], B[c]) / dot(B[c], KB[c]) for c in range(2)])
