@@ -163,6 +163,13 @@ typedef struct gp_mll_info {
  * X: device n x d; Z: device m x d or NULL; V: device n x t (ldv >= n);
  * out: device (n or m) x t (ldo >= rows), must not overlap V.
  * n >= 1, 1 <= t <= 4096.  Asynchronous on stream.
+ * Repeated calls give the same bits.  How the sum over the training points is split
+ * depends on n and, in every form, on t: a column of a block and the same column alone
+ * may differ in the last bits.  Each row of a cross product (Z != NULL) is bitwise
+ * independent of the other rows of Z.
+ * The workspace holds the partial sums of such a split (in GP_PREC_FP64 up to 48 MiB:
+ * 39 MB at n = 8,192, t = 50, where X has 3 MB), so that its size follows from
+ * gp_workspace_bytes alone.
  */
 int gp_kmm(const gp_kernel* kern, int32_t precision,
            const double* X, int64_t n, const double* Z, int64_t m,
@@ -231,6 +238,8 @@ int gp_pivchol_precond(const gp_kernel* kern, const double* X, int64_t n, int32_
  * (K_hat^{-1} B); Z0: device n x s output P^{-1} B (nullable).  s <= 256.
  * Synchronises once per iteration.  Returns GP_WNOCONV if some column had
  * not converged after max_iter iterations (tol > 0).
+ * Workspace: gp_workspace_bytes(GP_OP_MBCG, n, 0, d, s, rank, precision): the
+ * product's, four n x s blocks and the column reductions' partial sums.
  */
 int gp_mbcg(const gp_kernel* kern, int32_t precision,
             const double* X, int64_t n, const gp_precond* pc,

@@ -47,8 +47,8 @@ __global__ void reduce_partials_kernel(const double* __restrict__ partial, int64
 // column adds that column's partial sums itself, all in the same order, so the
 // step sizes need no launches of their own.  An iteration at n = 2,048 is bound by
 // its launches: 10 now and one copy to the host, 15 and two before (a likelihood
-// with 9 iterations and 20 pivots: 2.00 -> 1.54 ms; n = 65,536 with 37: 54.4 ->
-// 53.4 ms).  gamma and active have two copies, read
+// with 9 iterations and 20 pivots: 2.00 -> 1.54 ms).  Where there are many partial
+// sums they are added once before (kSumInPlace).  gamma and active have two copies, read
 // from one and written to the other, since workgroups of a column do not run in
 // step; the column's first workgroup stores them and the host's records.
 
@@ -416,7 +416,8 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 }
 
 // v / d from the correctly rounded r = 1 / d: one residual correction of v r gives
-// the correctly rounded quotient (Markstein 1990), the bits of the division.
+// the correctly rounded quotient (Markstein 1990), the bits of the division where
+// nothing over- or underflows.
 __device__ __forceinline__ double div_by(double v, double d, double r) {
   const double q = v * r;
   return fma(fma(-q, d, v), r, q);

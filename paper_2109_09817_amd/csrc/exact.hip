@@ -11,11 +11,14 @@
 //
 // with dK/dlog l_j = psi(r) (dx_j / l_j)^2, psi(r) = (5/3) s_f (1 + sqrt5 r)
 // e^{-sqrt5 r} (Matern-5/2; RBF: k), dK/dlog s_f = K and dK_hat/dlog sigma^2
-// = sigma^2 I.  Every O(n^3) step is a sequence of 64 x 64 FP64 tile
-// products C -= P Q (or C = P Q) over k <= 256 on the FP64 matrix cores, the
-// panels staged in LDS; triangular solves against a 64 x 64 diagonal block
-// multiply by its inverse (formed in LDS by one workgroup), so that they are
-// tile products too.
+// = sigma^2 I.  Every O(n^3) step is a sequence of FP64 tile products on the
+// matrix cores, the operands staged in LDS: the panels of the Cholesky
+// factorisation in 64 x 64 tiles (k = 64 inside a super-panel of 256 columns, 256
+// for the next one), its trailing updates in 128 x 128 tiles beside the next
+// diagonal blocks, the inverse and the large-rank products in 128 x 128 tiles where
+// these fill the chip and 64 x 64 below.  Triangular solves against a 64 x 64
+// diagonal block multiply by its inverse (formed in LDS by one workgroup), so
+// that they are tile products too.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -136,7 +139,8 @@ __device__ __forceinline__ void chol_inverse_16(double (&a)[kDb], double (&x)[kD
 // l / 16 + 4 i); 3 barriers a step.  The inverse's blocks below the diagonal
 // follow block diagonal by block diagonal, X_ij = -X_ii sum_k L_ik X_kj.
 // Column by column over all 64 (128 barriers, then 64 dependent rows of the
-// inverse) it took 74 us; this form: 29 us (n = 7,503: 118 of them, 30.1 -> 24.8 ms).
+// inverse) it took 74 us; this form: 29 us in a launch of its own (n = 7,503: 118 of
+// them, 30.1 -> 24.8 ms), 31 to 35 us in the fused launch below.
 __device__ __forceinline__ void potrf_diag(double* __restrict__ A, int64_t n, int64_t j0, int jb, int* __restrict__ info,
                                            double* __restrict__ Dinv, double* Ls, double* Xs) {
   constexpr int kPer = kEb * kEb / 256;
@@ -522,7 +526,9 @@ __global__ __launch_bounds__(256) void gemm64_f64_kernel(GemmArgs g) {
 // (74 KB of LDS each), so one multiplies while the other waits at its barrier.
 // Each operand keeps its source orientation in LDS: k-major [k][x], pitch 144
 // doubles, or x-major [x][k], pitch 18, both with 16-byte rows and distinct
-// banks for the 32 lanes of a half-wave.  Interior chunks load 16 bytes per
+// banks for the operand reads of a half-wave.  The 16-byte x-major stores do
+// conflict (a row spans 32 of 64 banks and the next starts 36 on): 0.5 conflict cycles per
+// LDS instruction in L F, 0.9 in the Gram, 1 to 3% of the cycles.  Interior chunks load 16 bytes per
 // lane (rows need 8-byte alignment only), edges element by element.
 // n = 32,768, r = 4,096: L F takes 9.2 ms (61 TF/s of useful flops; 9.6 with vector
 // address arithmetic) against 24 ms in 64-wide tiles over the full square; trailing updates of the exact GP (k = 256)
@@ -849,7 +855,7 @@ __global__ __launch_bounds__(256, 2) void potrf_update_kernel(double* A, int64_t
 // the columns of its own super-panel; what lies beyond takes the whole super-panel
 // at once (k = 256), so that it is read and written once per 256 columns instead
 // of once per 64: first the next super-panel's columns, and the rest beside the next
-// four diagonal blocks, each of which is 33 us of one workgroup: up to 255 tiles, one per
+// four diagonal blocks, each of which is 31 to 35 us of one workgroup: up to 255 tiles, one per
 // CU (50 us), beside each block, in as few launches as that allows; more per launch only
 // where four launches do not hold them.  n = 7,503: 10.3 ms with the trailing update in
 // launches of its own and the panel's own updates in two, 8.9 ms so (17.5 instead of

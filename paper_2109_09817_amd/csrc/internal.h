@@ -51,9 +51,10 @@ struct KmmPlan {
   // workspace carve-out
   void* xr = nullptr;
   void* xc = nullptr;
+  // laid out in the mixed form too, which carries its norms in the fragments and uses none of the three
   float* nrm_b = nullptr;   // FP32 form: norms of the b stream
   float* nrm_a = nullptr;   // FP32 form: norms of the output rows
-  double* nrm64 = nullptr;  // FP64 norms scratch (n or m entries)
+  double* nrm64 = nullptr;  // FP32 form: FP64 norms scratch (n or m entries)
   double* ctr = nullptr;    // mixed form: the centre of the coordinates (the b stream's column means, d values)
   double* cpart = nullptr;  // scratch of the column means (colmean_scratch_doubles(n, d))
   void* vf = nullptr;

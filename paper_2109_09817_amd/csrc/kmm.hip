@@ -1181,6 +1181,9 @@ __global__ __launch_bounds__(256, 2) void sweep_fp32_kernel(SweepArgs a) {
 // (inv: the mixed form's column factors, a power of two; null for the FP32 form).
 // grid = (row blocks, columns); dot (nullable): dot[b t + c] = sum over the block's
 // rows of V out, added as in coldot_partial_kernel.
+// Bound by HBM where there is one split (n = 917,504, t = 16: 352 MB in 117 us; 75 us with
+// one value in flight per thread and more waves, which many splits are slower with), by the
+// partials' reads where there are many.
 template <typename T>
 __global__ __launch_bounds__(256) void kmm_epilogue_kernel(const T* __restrict__ part, int64_t nsplit, int tpad,
                                                            int64_t mpad, int64_t m, int t, double sf, double diag,
@@ -1695,7 +1698,7 @@ static void launch_wide_form(int kind, dim3 grid, const WideArgs& a, hipStream_t
 
 template <int KS>
 static void launch_wide(int kind, dim3 grid, const WideArgs& a, hipStream_t st) {
-  // 4 FULL + REST >= ntb column blocks; up to two of a form's are beyond the last
+  // 4 FULL + REST >= ntb column blocks; up to three of a form's are beyond the last
   const int ntb = a.ntb;
   if (ntb == 1) return launch_wide_form<KS, 0, 1>(kind, grid, a, st);
   if (ntb <= 3) return launch_wide_form<KS, 0, 3>(kind, grid, a, st);

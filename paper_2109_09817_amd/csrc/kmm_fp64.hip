@@ -35,8 +35,9 @@ constexpr int kF64Rows = 64;   // output rows per workgroup
 // per entry on the VALU instead of a 16-column MFMA block that is mostly padding.
 // n = 24,576, t = 50, d = 48: 5.0 ms with predicated loads, one entry at a time
 // through sqrt and exp and one or two workgroups per CU; 2.69 ms now (33 TFLOP/s of
-// n^2 (d + 2 t)).  Error against a long double product on sampled rows 3.0e-15
-// (5.1e-15 before: one long sum per row).
+// n^2 (d + 2 t)).  Counters there: matrix pipe busy 54% at 2.07 GHz, waves waiting on 19%
+// of their cycles, 3.3 LDS conflict cycles per LDS instruction.  Error against a long
+// double product on sampled rows 3.0e-15 (5.1e-15 before: one long sum per row).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // m(r) for four entries at once from h = -S / 2, S = r^2 scaled as for the mixed
@@ -44,8 +45,8 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // (RBF: 2^-S).  S is kept above 1e-300, where m is 1 to rounding, and the exponent
 // below 1100, where 2^-u is 0.
 //   sqrt: the hardware's reciprocal square root (about 2^-23), one coupled Newton
-//   step for sqrt and half its reciprocal (2^-46), one residual correction, which
-//   leaves the rounding of the last operation.
+//   step for sqrt and half its reciprocal (Goldschmidt 1964; 2^-46), one residual
+//   correction, which leaves the rounding of the last operation.
 //   2^-u: -u = k + f, f in [-1/2, 1/2] (exact), and the degree-11 interpolant of 2^f
 //   at the Chebyshev nodes (relative error 1e-17).
 // Four chains run in step: a single chain waits on every result (FP64 latency is
@@ -148,7 +149,7 @@ struct F64Args {
 // last one and are not stored).
 template <int DP, int KIND, int NCB, int REM>
 __global__ __launch_bounds__(256, 2) void sweep_fp64_kernel(F64Args a, int first_col, int live) {
-  constexpr int kBLd = DP + 2;           // point rows: the MFMA's 16-lane reads hit distinct banks
+  constexpr int kBLd = DP + 2;           // point rows: a half-wave's operand reads hit distinct banks
   constexpr int kVLd = kF64Chunk + 2;    // V columns, likewise
   constexpr int kOLd = kF64Rows + 1;     // output tile columns
   constexpr int kKs = DP / 4;            // K steps of the distance MFMA
@@ -360,6 +361,12 @@ __global__ __launch_bounds__(256) void fp64_splitsum_kernel(F64Args a, int64_t n
 // it with them; points beyond kF64SplitMaxN leave no room and take one split
 // (their rows alone fill the chip).
 // n = 8,192, t = 50: 128 workgroups on 256 CUs took 1.08 ms, 1,536 take 0.36 ms.
+//
+// kF64MinChunks matters below n = 6,000 only (d = 48, us, at least 4 / 8 / 12 / 16 / 24
+// chunks): n = 1,200, t = 16: 32 / 44 / 50 / 63 / 101; n = 2,000, t = 50: 60 / 52 / 62 / 84 /
+// 114; n = 4,096, t = 50: 145 / 123 / 134 / 109 / 148; n = 6,000, t = 50: 223 / 224 / 235 / 231 /
+// 234.  No one value is best; 12 is within 1.3 of the best from n = 2,000 on.  The error is 2e-16
+// to 6e-16 (rms) with all of 4 to 16.
 constexpr int64_t kF64Groups = 1536;
 constexpr int64_t kF64MinChunks = 12;
 constexpr int64_t kF64CrossSplits = 64;
