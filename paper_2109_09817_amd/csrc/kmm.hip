@@ -1025,16 +1025,31 @@ __global__ __launch_bounds__(256, 2) void wide_cross_bf16x3_kernel(WideArgs a) {
   }
 }
 
-// 16-row blocks per wave of the FP32 form: an MFMA of this form takes twice the
-// cycles for an eighth of the flops, so that a fragment's LDS read costs little
-// beside it, and more waves per SIMD are worth as much as its reuse: one
-// block with one or two column blocks (n = 65,536, KQ 3 NT 1: 5.43 ms, two blocks
-// 5.56, four 5.50; KQ 2 NT 2: 5.38, 5.62), two with more (KQ 2 NT 4: 6.36, one
-// 6.98) or with KQ = 8 (n = 40,000, NT 2: 4.38, one 4.67), as far as the registers allow.
-template <int KQ, int NT>
-struct NAOfF32 {
-  static constexpr int value = (NT <= 2) == (KQ <= 4) ? 1 : 2;
-};
+// 16-row blocks per wave of the FP32 form, one or two.  An MFMA of this form takes twice
+// the cycles for an eighth of the flops, so that a fragment's LDS read costs little
+// beside it: with two blocks the work itself gets pair_gain_f32 (per mille) faster, more
+// under RBF, whose shorter profile leaves the reads exposed; -1: not at all (n = 65,536,
+// Matern: KQ 3 NT 1 5.43 ms with one, 5.56 with two) or two blocks spill.  Measured
+// where both fill the CUs, one / two blocks, ms: RBF n = 110,000, d = 48, t = 1 14.9 / 12.3, t
+// = 17 17.7 / 16.4; n = 30,000, d = 48, t = 40 1.68 / 1.50, d = 100, t = 20 2.72 / 2.35; Matern n =
+// 30,000, d = 48, t = 64 2.02 / 1.97, d = 21, t = 40 1.55 / 1.54, d = 100, t = 1 2.35 / 2.22.
+//
+// But half as many workgroups of twice the work may leave CUs idle: with w of them the
+// busiest CU does 2 ceil(w / 256) halves against ceil(2 w / 256).  That ratio, where it is above
+// one, is what two blocks cost (Matern, d = 5, t = 40: n = 20,000, w = 1,106, 10 against 9: 0.578 /
+// 0.644 ms; RBF, d = 21, t = 17: n = 2,500, w = 800, 8 against 7: 28.7 / 30.3 us), so two
+// are taken where the gain makes up for it.  A row's sums are the same with either.
+constexpr int pair_gain_f32(int kq, int nt, int kind) {
+  if (kq > 4) return nt > 2 ? -1 : (kind == GP_RBF ? 112 : 60);
+  if (kind == GP_RBF) return nt > 2 ? 112 : 67;
+  return nt > 2 ? 10 : -1;
+}
+
+static int na_f32(int kq, int nt, int kind, int64_t mpad, int64_t nsplit, int64_t groups) {
+  const int gain = pair_gain_f32(kq, nt, kind);
+  const int64_t w = mpad / 128 * nsplit * groups;
+  return gain >= 0 && 2 * ((w + 255) / 256) * 1000 <= (2 * w + 255) / 256 * (1000 + gain) ? 2 : 1;
+}
 
 // The FP32 form: distances and M V on v_mfma_f32_16x16x4, bound by them (32 cycles
 // each: at KQ = 2, NT = 3 40 per 16 x 32 tile) and the profile's VALU work, which adds
@@ -1043,9 +1058,8 @@ struct NAOfF32 {
 // chunk's loads were awaited before its compute.  K(Z, X) V at n = 100,003, m =
 // 3,001, d = 21, t = 33, RBF: 0.62 -> 0.49 ms with FP32 partials; n = 65,536, d =
 // 64, t = 50: 11.8 -> 9.5 ms.
-template <int KQ, int NT, int KIND>
+template <int KQ, int NT, int KIND, int NA>
 __global__ __launch_bounds__(256, 2) void sweep_fp32_kernel(SweepArgs a) {
-  constexpr int NA = NAOfF32<KQ, NT>::value;
   constexpr int kPoint = 2 * KQ * 64, kAll = kPoint + 2 * NT * 64;
   __shared__ f32x4 stage[2][kAll];
   const int tid = threadIdx.x;
@@ -1352,8 +1366,7 @@ int kmm_ksteps(int precision, int d) {
 
 // Column blocks handled per launch (grid.z groups the rest).
 static int nt_launch(int ntb) { return ntb >= 4 ? 4 : ntb; }
-static int na_of(int ks, int nt, bool mixed) {  // NAOf, NAOfF32 of the launched kernel
-  if (!mixed) return (nt <= 2) == (ks <= 4) ? 1 : 2;
+static int na_of(int ks, int nt) {  // NAOf of the launched kernel
   return nt == 1 ? (ks <= 7 ? 4 : 2) : (ks <= 7 ? 2 : 1);
 }
 
@@ -1608,33 +1621,33 @@ hipError_t prep_dist(const gp_kernel* kern, const double* X, int64_t n, int64_t 
 }
 
 template <int KS>
-static void launch_one(bool mixed, int nt, int kind, dim3 grid, const SweepArgs& a, hipStream_t st);
+static void launch_one(bool mixed, int nt, int kind, int na, dim3 grid, const SweepArgs& a, hipStream_t st);
 
 // BF16X3 K steps (32 wide) and FP32 K groups (16 wide) that are instantiated.
-static bool dispatch_ks(int ks, int nt, int kind, bool mixed, dim3 grid, const SweepArgs& a,
+static bool dispatch_ks(int ks, int nt, int kind, bool mixed, int na, dim3 grid, const SweepArgs& a,
                         hipStream_t st) {
   if (mixed) {
     switch (ks) {
-      case 2: launch_one<2>(true, nt, kind, grid, a, st); return true;
-      case 4: launch_one<4>(true, nt, kind, grid, a, st); return true;
-      case 5: launch_one<5>(true, nt, kind, grid, a, st); return true;
-      case 7: launch_one<7>(true, nt, kind, grid, a, st); return true;
-      case 13: launch_one<13>(true, nt, kind, grid, a, st); return true;
+      case 2: launch_one<2>(true, nt, kind, na, grid, a, st); return true;
+      case 4: launch_one<4>(true, nt, kind, na, grid, a, st); return true;
+      case 5: launch_one<5>(true, nt, kind, na, grid, a, st); return true;
+      case 7: launch_one<7>(true, nt, kind, na, grid, a, st); return true;
+      case 13: launch_one<13>(true, nt, kind, na, grid, a, st); return true;
       default: return false;
     }
   }
   switch (ks) {
-    case 1: launch_one<1>(false, nt, kind, grid, a, st); return true;
-    case 2: launch_one<2>(false, nt, kind, grid, a, st); return true;
-    case 3: launch_one<3>(false, nt, kind, grid, a, st); return true;
-    case 4: launch_one<4>(false, nt, kind, grid, a, st); return true;
-    case 8: launch_one<8>(false, nt, kind, grid, a, st); return true;
+    case 1: launch_one<1>(false, nt, kind, na, grid, a, st); return true;
+    case 2: launch_one<2>(false, nt, kind, na, grid, a, st); return true;
+    case 3: launch_one<3>(false, nt, kind, na, grid, a, st); return true;
+    case 4: launch_one<4>(false, nt, kind, na, grid, a, st); return true;
+    case 8: launch_one<8>(false, nt, kind, na, grid, a, st); return true;
     default: return false;
   }
 }
 
 template <int KS, int NT, int KIND>
-static void launch_form(bool mixed, dim3 grid, const SweepArgs& a, hipStream_t st) {
+static void launch_form(bool mixed, int na, dim3 grid, const SweepArgs& a, hipStream_t st) {
   if constexpr (KS == 2 || KS == 4 || KS == 5 || KS == 7 || KS == 13) {
     if (mixed) {
       sweep_bf16x3_kernel<KS, NT, KIND><<<grid, 256, 0, st>>>(a);
@@ -1642,18 +1655,28 @@ static void launch_form(bool mixed, dim3 grid, const SweepArgs& a, hipStream_t s
     }
   }
   if constexpr (KS == 1 || KS == 2 || KS == 3 || KS == 4 || KS == 8) {
-    if (!mixed) sweep_fp32_kernel<KS, NT, KIND><<<grid, 256, 0, st>>>(a);
+    if constexpr (pair_gain_f32(KS, NT, KIND) >= 0) {
+      if (!mixed && na == 2) {
+        sweep_fp32_kernel<KS, NT, KIND, 2><<<grid, 256, 0, st>>>(a);
+        return;
+      }
+    }
+    if (!mixed) sweep_fp32_kernel<KS, NT, KIND, 1><<<grid, 256, 0, st>>>(a);
   }
 }
 
 template <int KS>
-static void launch_one(bool mixed, int nt, int kind, dim3 grid, const SweepArgs& a, hipStream_t st) {
+static void launch_one(bool mixed, int nt, int kind, int na, dim3 grid, const SweepArgs& a, hipStream_t st) {
   const bool m52 = kind == GP_MATERN52;
   switch (nt) {
-    case 1: m52 ? launch_form<KS, 1, GP_MATERN52>(mixed, grid, a, st) : launch_form<KS, 1, GP_RBF>(mixed, grid, a, st); break;
-    case 2: m52 ? launch_form<KS, 2, GP_MATERN52>(mixed, grid, a, st) : launch_form<KS, 2, GP_RBF>(mixed, grid, a, st); break;
-    case 3: m52 ? launch_form<KS, 3, GP_MATERN52>(mixed, grid, a, st) : launch_form<KS, 3, GP_RBF>(mixed, grid, a, st); break;
-    default: m52 ? launch_form<KS, 4, GP_MATERN52>(mixed, grid, a, st) : launch_form<KS, 4, GP_RBF>(mixed, grid, a, st); break;
+    case 1: m52 ? launch_form<KS, 1, GP_MATERN52>(mixed, na, grid, a, st)
+                : launch_form<KS, 1, GP_RBF>(mixed, na, grid, a, st); break;
+    case 2: m52 ? launch_form<KS, 2, GP_MATERN52>(mixed, na, grid, a, st)
+                : launch_form<KS, 2, GP_RBF>(mixed, na, grid, a, st); break;
+    case 3: m52 ? launch_form<KS, 3, GP_MATERN52>(mixed, na, grid, a, st)
+                : launch_form<KS, 3, GP_RBF>(mixed, na, grid, a, st); break;
+    default: m52 ? launch_form<KS, 4, GP_MATERN52>(mixed, na, grid, a, st)
+                : launch_form<KS, 4, GP_RBF>(mixed, na, grid, a, st); break;
   }
 }
 
@@ -1794,7 +1817,7 @@ hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, 
   a.t = t;
   a.f32part = sc.cps <= kFlush ? 1 : 0;
   a.square = p.square ? 1 : 0;
-  const int na = na_of(p.ks, sc.nt, mixed);
+  const int na = mixed ? na_of(p.ks, sc.nt) : na_f32(p.ks, sc.nt, p.kind, p.mpad, sc.nsplit, sc.groups);
   dim3 grid((unsigned)(p.mpad / (64 * na)), (unsigned)sc.nsplit, (unsigned)sc.groups);
   SweepTiming::Rec rec{};
   bool timed = false;
@@ -1808,7 +1831,7 @@ hipError_t kmm_sweep(const KmmPlan& p, int t, const double* Vdiag, int64_t ldv, 
     if (e == hipSuccess) e = hipEventRecord(rec.a, st);
     if (e != hipSuccess) return e;
   }
-  if (!dispatch_ks(p.ks, sc.nt, p.kind, mixed, grid, a, st)) return hipErrorInvalidValue;
+  if (!dispatch_ks(p.ks, sc.nt, p.kind, mixed, na, grid, a, st)) return hipErrorInvalidValue;
   if (timed) {
     hipError_t e = hipEventRecord(rec.b, st);
     if (e != hipSuccess) return e;

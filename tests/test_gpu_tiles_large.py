@@ -189,3 +189,28 @@ def test_first_step_size_to_the_bit_with_many_partial_sums(n):
     def dot(a, b):
         return block_sum(np.array([block_sum((a * b)[i:i + rows]) for i in range(0, n, rows)]))
     np.testing.assert_array_equal(r.alpha[0], [dot(B[c], B[c]) / dot(B[c], KB[c]) for c in range(2)])
+
+
+@pytest.mark.parametrize("kind", [ok.MATERN52, ok.RBF])
+@pytest.mark.parametrize("d", [5, 21, 48, 64, 100])
+@pytest.mark.parametrize("t", [3, 20, 40, 64, 130])
+def test_fp32_products_with_one_and_two_row_blocks_per_wave(t, d, kind):
+    """One or two 16-row blocks per wave, by the number of workgroups (m = 1,500 rows, single rows and 300 of them differ in
+    it): a row has the same bits either way.  Square product (n = 7,001) against the FP64 form or the
+    oracle, bar 1e-5 of the off-diagonal part as elsewhere."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(d + t)
+    n, m = 50000, 1500
+    X, V, Z = dev(rng.standard_normal((n, d))), dev(rng.standard_normal((t, n))), rng.standard_normal((m, d))
+    th = ok.Theta(rng.uniform(0.8, 1.2, d) * np.sqrt(d), 1.1, 1e-2, kind)
+    got = host(gp.kmm(_gk(th), X, V, Z=dev(Z), precision="fp32"))
+    for r in (0, 31, 700, 1499):
+        np.testing.assert_array_equal(host(gp.kmm(_gk(th), X, V, Z=dev(Z[r:r + 1]), precision="fp32"))[:, 0], got[:, r])
+    np.testing.assert_array_equal(host(gp.kmm(_gk(th), X, V, Z=dev(Z[900:1200]), precision="fp32")), got[:, 900:1200])
+    X, V = X[:7001].contiguous(), V[:, :7001].contiguous()
+    got = host(gp.kmm(_gk(th), X, V, precision="fp32"))
+    if d <= 64:
+        ref = host(gp.kmm(_gk(th), X, V, precision="fp64"))
+    else:
+        ref = ok.khat_matmul(host(X), th, host(V).T).T
+    assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref - 1.11 * host(V))
