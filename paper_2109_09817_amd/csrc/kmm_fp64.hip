@@ -141,14 +141,15 @@ struct F64Args {
   int64_t slab;        // rows of the partial buffer
   int64_t cps;         // chunks per split
   int d, t, square;
+  int columns;         // of the whole product
   double sf, noise;
 };
 
-// Columns c0 .. c0 + tc - 1 of the pass, tc <= 16 NCB + REM: NCB 16-column blocks
-// on the matrix cores, REM columns on the VALU (columns beyond tc repeat the
+// Columns c0 .. c0 + live - 1 of the pass, live <= 16 NCB + REM: NCB 16-column blocks
+// on the matrix cores, REM columns on the VALU (columns beyond live repeat the
 // last one and are not stored).
 template <int DP, int KIND, int NCB, int REM>
-__global__ __launch_bounds__(256, 2) void sweep_fp64_kernel(F64Args a, int first_col, int live) {
+__global__ __launch_bounds__(256, 2) void sweep_fp64_kernel(F64Args a, int first_col, int columns) {
   constexpr int kBLd = DP + 2;           // point rows: a half-wave's operand reads hit distinct banks
   constexpr int kVLd = kF64Chunk + 2;    // V columns, likewise
   constexpr int kOLd = kF64Rows + 1;     // output tile columns
@@ -171,6 +172,7 @@ __global__ __launch_bounds__(256, 2) void sweep_fp64_kernel(F64Args a, int first
   const int64_t n = a.n;
   const int64_t a0 = a.row0 + (int64_t)blockIdx.x * kF64Rows;
   const int c0 = first_col + blockIdx.y * kF64Cols;
+  const int live = a.t - c0 < columns ? a.t - c0 : columns;
   const int64_t arow = a0 + 16 * wave + lr;          // this lane's row in the products
   const int64_t crow = arow < a.m ? arow : a.m - 1;  // rows beyond m compute row m - 1, not stored
   double xa[kKs];
@@ -394,11 +396,28 @@ F64Split f64_split(int64_t n, int64_t m, bool square, int t) {
   return s;
 }
 
+// Whether one to four columns beyond whole blocks of 16 go to the VALU, whose sums have
+// another order: not in a cross product of more than 64 columns, which takes one
+// launch or two by the number of its rows, on which a row's bits must not depend.
+static bool on_valu(int live, bool square, int t) {
+  return live % 16 >= 1 && live % 16 <= 4 && (square || t <= kF64Cols);
+}
+
+// One launch of 64-column groups for all columns, the last group padded (true), or one
+// for the whole groups and one in a smaller form for the rest: by the rounds of the 512
+// workgroups that run at a time and a workgroup's time, in MFMAs per 16 x 32 tile.  The second
+// launch waits for the first: n = 60, d = 48, t = 100 21 us in one launch, 41 in two.
+static bool one_launch(int64_t gx, int64_t nsplit, int whole, int rest, int d, bool square, int t) {
+  const int base = (d + 15) / 16 * 8 + 15;  // distances and profile
+  const int64_t all = base + 32, part = base + (on_valu(rest, square, t) ? rest / 16 * 8 + 2 : (rest + 15) / 16 * 8);
+  auto rounds = [](int64_t w) { return (w + 511) / 512; };
+  return rounds(gx * nsplit * (whole + 1)) * all <= rounds(gx * nsplit * whole) * all + rounds(gx * nsplit) * part;
+}
+
 template <int DP, int KIND>
 static void launch_fp64(int live, int first_col, dim3 grid, const F64Args& a, hipStream_t st) {
 #define GPK_F64(NCB, REM) sweep_fp64_kernel<DP, KIND, NCB, REM><<<grid, 256, 0, st>>>(a, first_col, live)
-  const int rem = live % 16;
-  const bool valu = rem >= 1 && rem <= 4;
+  const bool valu = on_valu(live, a.square != 0, a.columns);
   switch (valu ? live / 16 : (live + 15) / 16) {
     case 0: GPK_F64(0, 4); break;
     case 1: valu ? GPK_F64(1, 4) : GPK_F64(1, 0); break;
@@ -462,6 +481,7 @@ hipError_t fp64_sweep(const KmmPlan& p, const double* V, int64_t ldv, int t, dou
   a.slab = sp.slab;
   a.d = p.d;
   a.square = p.square ? 1 : 0;
+  a.columns = t;
   a.sf = p.sf;
   a.noise = p.noise;
   a.part = sp.nsplit > 1 ? p.part : nullptr;
@@ -474,9 +494,10 @@ hipError_t fp64_sweep(const KmmPlan& p, const double* V, int64_t ldv, int t, dou
       const int64_t rows = std::min(sp.slab, p.m - a.row0);
       const unsigned gx = (unsigned)((rows + kF64Rows - 1) / kF64Rows);
       hipError_t e = hipSuccess;
+      const bool one = whole > 0 && rest > 0 && one_launch(gx, sp.nsplit, whole, rest, p.d, p.square, t);
       if (whole > 0)
-        e = launch_columns(p.kind, p.d, kF64Cols, 0, dim3(gx, (unsigned)whole, (unsigned)sp.nsplit), a, st);
-      if (e == hipSuccess && rest > 0)
+        e = launch_columns(p.kind, p.d, kF64Cols, 0, dim3(gx, (unsigned)(whole + one), (unsigned)sp.nsplit), a, st);
+      if (e == hipSuccess && rest > 0 && !one)
         e = launch_columns(p.kind, p.d, rest, whole * kF64Cols, dim3(gx, 1, (unsigned)sp.nsplit), a, st);
       if (e != hipSuccess) return e;
       if (a.part) {

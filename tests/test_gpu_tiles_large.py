@@ -214,3 +214,28 @@ def test_fp32_products_with_one_and_two_row_blocks_per_wave(t, d, kind):
     else:
         ref = ok.khat_matmul(host(X), th, host(V).T).T
     assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref - 1.11 * host(V))
+
+
+@pytest.mark.parametrize("kind", [ok.MATERN52, ok.RBF])
+@pytest.mark.parametrize("t", [65, 68, 69, 100, 130])
+def test_fp64_products_beyond_64_columns(t, kind):
+    """Columns beyond whole groups of 64 in the same launch (small n) or in one of their own (n = 9,000).  Bar as for the
+    other FP64 products: 1e-13 of |K| |V|.  A row of a cross product has the same bits alone and among others, which take
+    more launches."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(t)
+    for n, d in ((60, 48), (700, 20), (9000, 8)):
+        X, V = rng.standard_normal((n, d)), rng.standard_normal((t, n))
+        th = ok.Theta(rng.uniform(1.0, 2.0, d) * np.sqrt(d), 1.2, 1e-3, kind)
+        rows = np.arange(n) if n < 1000 else np.sort(rng.choice(n, 500, replace=False))
+        got = host(gp.kmm(_gk(th), dev(X), dev(V), precision="fp64"))[:, rows]
+        K = ok.kernel(X[rows], X, th)
+        K[np.arange(len(rows)), rows] += 1e-3
+        assert np.max(np.abs(got - V @ K.T) / (np.abs(V) @ np.abs(K).T)) <= 1e-13
+    Z = rng.standard_normal((40000, 8))
+    th = ok.Theta(rng.uniform(2.0, 4.0, 8), 1.0, 0.0, kind)
+    X, V = rng.standard_normal((900, 8)), rng.standard_normal((t, 900))
+    got = host(gp.kmm(_gk(th), dev(X), dev(V), Z=dev(Z), precision="fp64"))
+    for r in (0, 20001, 39999):
+        one = host(gp.kmm(_gk(th), dev(X), dev(V), Z=dev(Z[r:r + 1]), precision="fp64"))
+        np.testing.assert_array_equal(one[:, 0], got[:, r])
