@@ -145,11 +145,18 @@ struct F64Args {
   double sf, noise;
 };
 
+// Waves per SIMD asked of the compiler: one form fits four by a register or two and left to itself
+// takes one too many (n = 24,576, d = 32, t = 16, RBF: 1.34 ms with three, 1.32 with four).
+constexpr int f64_waves(int dp, int kind, int ncb, int rem) {
+  return dp == 32 && kind == GP_RBF && ncb == 1 && rem == 0 ? 4 : 2;
+}
+
 // Columns c0 .. c0 + live - 1 of the pass, live <= 16 NCB + REM: NCB 16-column blocks
 // on the matrix cores, REM columns on the VALU (columns beyond live repeat the
 // last one and are not stored).
 template <int DP, int KIND, int NCB, int REM>
-__global__ __launch_bounds__(256, 2) void sweep_fp64_kernel(F64Args a, int first_col, int columns) {
+__global__ __launch_bounds__(256, (f64_waves(DP, KIND, NCB, REM))) void sweep_fp64_kernel(F64Args a, int first_col,
+                                                                                          int columns) {
   constexpr int kBLd = DP + 2;           // point rows: a half-wave's operand reads hit distinct banks
   constexpr int kVLd = kF64Chunk + 2;    // V columns, likewise
   constexpr int kOLd = kF64Rows + 1;     // output tile columns
@@ -181,10 +188,14 @@ __global__ __launch_bounds__(256, 2) void sweep_fp64_kernel(F64Args a, int first
     const int f = 4 * s + lk;
     xa[s] = f < d ? a.Xa[crow * d + f] * a.sc[f] : 0.0;
   }
-  double naa = 0.0;  // the sequence of additions of prep_fp64_kernel
-  for (int f = 0; f < d; ++f) {
-    const double v = a.Xa[crow * d + f] * a.sc[f];
-    naa = fma(v, v, naa);
+  double naa = 0.0;
+  if (a.square) {
+    naa = a.nb[crow];
+  } else {  // the sequence of additions of prep_fp64_kernel
+    for (int f = 0; f < d; ++f) {
+      const double v = a.Xa[crow * d + f] * a.sc[f];
+      naa = fma(v, v, naa);
+    }
   }
   f64x4 acc[NCB > 0 ? NCB : 1];
 #pragma unroll

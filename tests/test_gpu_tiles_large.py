@@ -239,3 +239,22 @@ def test_fp64_products_beyond_64_columns(t, kind):
     for r in (0, 20001, 39999):
         one = host(gp.kmm(_gk(th), dev(X), dev(V), Z=dev(Z[r:r + 1]), precision="fp64"))
         np.testing.assert_array_equal(one[:, 0], got[:, r])
+
+
+@pytest.mark.parametrize("kind", [ok.MATERN52, ok.RBF])
+@pytest.mark.parametrize("n,d", [(31, 3), (64, 32), (65, 64), (700, 48)])
+def test_fp64_square_and_cross_products_agree(n, d, kind):
+    """A square product reads its row norms, a cross product computes them, by the same additions: without noise and with
+    the same rows both forms differ in the diagonal alone, which the square one sets to s_f and the cross one gets from
+    a squared distance that rounds to at most (d + 4) 2^-52 of the norms."""
+    from paper_2109_09817_amd import gp
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, d))
+    th = ok.Theta(rng.uniform(1.0, 2.0, d) * np.sqrt(d), 1.2, 0.0, kind)
+    V = np.eye(n)[: min(n, 16)]
+    square = host(gp.kmm(_gk(th), dev(X), dev(V), precision="fp64"))
+    cross = host(gp.kmm(_gk(th), dev(X), dev(V), Z=dev(X), precision="fp64"))
+    off = ~np.eye(len(V), n, dtype=bool)
+    np.testing.assert_array_equal(square[off], cross[off])
+    r2 = 2 * (d + 4) * 2.0**-52 * np.max(np.sum((X / th.ell) ** 2, axis=1))
+    assert np.max(np.abs(square[~off] - cross[~off])) <= 1.2 * (5 / 3 + 0.5) * r2 + 1e-15
