@@ -34,8 +34,8 @@ constexpr int kF64Rows = 64;   // output rows per workgroup
 // beyond a multiple of 16 (a block of 50 or 17, a single vector) cost four FMAs
 // per entry on the VALU instead of a 16-column MFMA block that is mostly padding.
 // n = 24,576, t = 50, d = 48: 5.0 ms with predicated loads, one entry at a time
-// through sqrt and exp and one or two workgroups per CU; 2.69 ms now (33 TFLOP/s of
-// n^2 (d + 2 t)).  Counters there: matrix pipe busy 54% at 2.07 GHz, waves waiting on 19%
+// through sqrt and exp and one or two workgroups per CU; 2.67 ms now (33 TFLOP/s of
+// n^2 (d + 2 t)).  Counters there: matrix pipe busy 55% at 2.06 GHz, waves waiting on 19%
 // of their cycles, 3.3 LDS conflict cycles per LDS instruction.  Error against a long
 // double product on sampled rows 3.0e-15 (5.1e-15 before: one long sum per row).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(256) void fp64_splitsum_kernel(F64Args a, int64_t n
 // that a plan that needs no partials within GP_KMM_NOALLOC_MAX_BYTES stays within
 // it with them; points beyond kF64SplitMaxN leave no room and take one split
 // (their rows alone fill the chip).
-// n = 8,192, t = 50: 128 workgroups on 256 CUs took 1.08 ms, 1,536 take 0.36 ms.
+// n = 8,192, t = 50: 128 workgroups on 256 CUs took 1.08 ms, 1,536 take 0.34 ms.
 //
 // kF64MinChunks matters below n = 6,000 only (d = 48, us, at least 4 / 8 / 12 / 16 / 24
 // chunks): n = 1,200, t = 16: 32 / 44 / 50 / 63 / 101; n = 2,000, t = 50: 60 / 52 / 62 / 84 /
